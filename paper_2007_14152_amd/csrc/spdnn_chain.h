@@ -138,13 +138,10 @@ __global__ __launch_bounds__(kBlk) void fused_chain_kernel(
             // out once, ahead of the layer loop, and kept -- spilled -- for all layers)
             int tl = tid;
             asm volatile("" : "+v"(tl));
-            const uint16_t* prel = w.rel + tl;
-            const float* pval = w.val + tl;
+            load_slots(off, w.rel, 0, tl);
+            load_weights(wv, w.val, 0, tl);
 #pragma unroll
-            for (int k = 0; k < kNnz; ++k) {
-                off[k] = lds_base + tile_offset((uint32_t)prel[k * kBlk] & (kCap - 1));
-                wv[k] = pval[k * kBlk];
-            }
+            for (int k = 0; k < kNnz; ++k) off[k] = lds_base + tile_offset(off[k] & (kCap - 1));
         }
 
         float acc[kRows] = {0.f, 0.f, 0.f, 0.f};

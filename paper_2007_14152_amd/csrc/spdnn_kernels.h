@@ -32,9 +32,11 @@ constexpr float kClip = 32.0f;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// A lane's connections are stored so that it fetches them with 16-byte loads, consecutive lanes from consecutive
+// addresses: eight slots or four weights per load.
 struct LayerWeights {
-    const uint16_t* rel;  // [nblk][32][kBlk] stage << 12 | LDS slot of (column - c_lo) within the stage
-    const float* val;     // [nblk][32][kBlk]
+    const uint16_t* rel;  // [nblk][4][kBlk][8] stage << 12 | LDS slot of (column - c_lo) within the stage
+    const float* val;     // [nblk][8][kBlk][4]
     const int2* win;      // [nblk] {c_lo, ncols}, both multiples of 4
     const uint32_t* qsel;  // [nblk][kBlk] balanced single-stage layers: see balance_kernel
 };
@@ -71,6 +73,42 @@ constexpr uint32_t kPadSlot = kCap;
 // Steps per stage of the wide format: 2 stages exist only for layers that run two neurons per
 // lane with all their steps in registers (2 x 32 = 4 x 16 = 64 steps per neuron).
 __host__ __device__ inline int wide_steps(int nstage) { return nstage > 8 ? 8 : nstage <= 2 ? 32 : 16; }
+
+// Where connection `step` of lane `lane` of output block b is kept in LayerWeights::rel and ::val.
+__device__ __forceinline__ size_t rel_entry(int b, int step, int lane) {
+    return (((size_t)b * (kNnz / 8) + (step >> 3)) * kBlk + lane) * 8 + (step & 7);
+}
+__device__ __forceinline__ size_t val_entry(int b, int step, int lane) {
+    return (((size_t)b * (kNnz / 4) + (step >> 2)) * kBlk + lane) * 4 + (step & 3);
+}
+// The 32 slots / weights of a lane.  A vector-memory instruction takes about 16 clocks of the CU's address path
+// whatever its width, and a launch cannot start computing before they are in: 12 loads per lane instead of 64.
+// Whole passes: 120 layers of 1024 neurons on 1000 rows 848 -> 798 us, 48 strided layers of 16384 neurons on 2000
+// rows 2131 -> 2058 us; large batches, whose launches are long, unchanged.
+__device__ __forceinline__ void load_slots(uint32_t (&r)[kNnz], const uint16_t* __restrict__ rel, int b, int lane) {
+    const uint4* p = reinterpret_cast<const uint4*>(rel + rel_entry(b, 0, lane));
+#pragma unroll
+    for (int c = 0; c < kNnz / 8; ++c) {
+        const uint4 q = p[c * kBlk];
+        const uint32_t d[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            r[8 * c + 2 * i] = d[i] & 0xffffu;
+            r[8 * c + 2 * i + 1] = d[i] >> 16;
+        }
+    }
+}
+__device__ __forceinline__ void load_weights(float (&w)[kNnz], const float* __restrict__ val, int b, int lane) {
+    const f32x4* p = reinterpret_cast<const f32x4*>(val + val_entry(b, 0, lane));
+#pragma unroll
+    for (int c = 0; c < kNnz / 4; ++c) {
+        const f32x4 q = p[c * kBlk];
+        w[4 * c] = q.x;
+        w[4 * c + 1] = q.y;
+        w[4 * c + 2] = q.z;
+        w[4 * c + 3] = q.w;
+    }
+}
 
 // Eight connections of one output neuron applied to the four rows of an LDS
 // tile: acc[r] = fma(tile[col_k][r], w_k, acc[r]) for k = 0..7 in that order.
@@ -766,14 +804,12 @@ __global__ __launch_bounds__(kBlk) void fused_layer_kernel(
     float wv[kNnz];
     uint32_t stg[MULTI ? kNnz / 8 : 1] = {};
     {
-        const uint16_t* prel = w.rel + (size_t)b * kNnz * kBlk + tid;
-        const float* pval = w.val + (size_t)b * kNnz * kBlk + tid;
+        load_slots(off, w.rel, b, tid);
+        load_weights(wv, w.val, b, tid);
 #pragma unroll
         for (int k = 0; k < kNnz; ++k) {
-            const uint32_t rel = prel[k * kBlk];
-            wv[k] = pval[k * kBlk];
-            off[k] = lds_base + tile_offset(rel & (kCap - 1));
-            if (MULTI) stg[k >> 3] |= (rel >> kCapLog2) << (4 * (k & 7));
+            if (MULTI) stg[k >> 3] |= (off[k] >> kCapLog2) << (4 * (k & 7));
+            off[k] = lds_base + tile_offset(off[k] & (kCap - 1));
         }
     }
     if (MULTI) {
@@ -1002,11 +1038,12 @@ __global__ __launch_bounds__(kBlk) void fused_pair_kernel(
 
     uint32_t offA[kNnz], offB[kNnz];
     {
-        const uint16_t* prel = w.rel + (size_t)b * kNnz * kBlk + tid;
+        load_slots(offA, w.rel, b, tid);
+        load_slots(offB, w.rel, b + 1, tid);
 #pragma unroll
         for (int k = 0; k < kNnz; ++k) {
-            offA[k] = lds_base + tile_offset(prel[k * kBlk]);
-            offB[k] = lds_base + tile_offset(prel[(kNnz + k) * kBlk]);
+            offA[k] = lds_base + tile_offset(offA[k]);
+            offB[k] = lds_base + tile_offset(offB[k]);
         }
     }
     const float bjA = bias[jA], bjB = bias[jB];
@@ -2360,7 +2397,7 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const int32_t*
 
 // One wave per set of 16 neurons whose lanes are served together: orders the set's
 // connections for conflict-free LDS reads and writes them lane-major: entry
-// (block b, step s, lane t) holds the LDS slot of the connection's column (plus
+// (block b, step s, lane t) -- rel_entry, val_entry -- holds the LDS slot of the connection's column (plus
 // the stage number in bits 12 and up) and its weight, for the connection lane t
 // uses at step s.
 //
@@ -2411,7 +2448,8 @@ __global__ __launch_bounds__(kOrderPackThreads) void order_pack_kernel(const int
     const bool balanced = *widest <= kCap;
     const uint16_t* tab = slot_tab + (size_t)(pair ? (b & ~1) : b) * kCap;
     auto slot_of = [&](uint32_t r) -> uint32_t { return balanced ? tab[r] : col_slot(r); };
-    auto entry = [&](int step) -> size_t { return ((size_t)b * kNnz + step) * kBlk + my_lane; };
+    auto entry = [&](int step) -> size_t { return rel_entry(b, step, my_lane); };
+    auto wentry = [&](int step) -> size_t { return val_entry(b, step, my_lane); };
     int nsteps = kNnz;
     const int my_len = !exists ? 0 : len ? (int)len[j] : kNnz;
     if (len) {  // steps this set needs; everything else is weight 0 on the window's first column
@@ -2426,7 +2464,7 @@ __global__ __launch_bounds__(kOrderPackThreads) void order_pack_kernel(const int
         const uint16_t zero_slot = (uint16_t)slot_of(0);
         for (int step = 0; step < kNnz; ++step) {
             rel[entry(step)] = zero_slot;
-            wval[entry(step)] = 0.0f;
+            wval[wentry(step)] = 0.0f;
         }
     }
     auto column = [&](int k) -> int {  // out-of-range columns were reported; keep them harmless
@@ -2535,7 +2573,7 @@ __global__ __launch_bounds__(kOrderPackThreads) void order_pack_kernel(const int
             const bool ok = c >= 0 && c < N;
             const uint32_t r = ok ? (uint32_t)win_rel(c, c_lo, N) : 0u;  // stage number | slot inside the stage
             rel[entry(step)] = (uint16_t)((r & ~(uint32_t)(kCap - 1)) | slot_of(r & (kCap - 1)));
-            wval[entry(step)] = ok ? val[src] : 0.0f;
+            wval[wentry(step)] = ok ? val[src] : 0.0f;
         }
         __syncthreads();
     }

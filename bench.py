@@ -286,12 +286,13 @@ def main():
         executed = float(sum(int(r) for r in rows_trace)) * N * 32
     ms_per_step = dt / a.steps * 1e3
     achieved = sum_bytes / (sum_ms * 1e-3) / 1e9 if sum_ms > 0 else 0.0
-    one_launch = model.one_launch(batch)   # small networks: every layer inside one launch of fused_chain_kernel
+    one_launch = model.one_launch(batch)   # small networks: every layer inside one launch of resident_kernel
+    resident = N <= 4096 and not a.out_of_core   # ... which runs several layers per launch at any batch
     kinds = {}
     for l in range(int(launches // a.steps)):
-        k = "fused_chain_kernel" if one_launch else sp.KERNEL_NAMES[model.layer_kernel(l)]
+        k = "resident_kernel" if resident else sp.KERNEL_NAMES[model.layer_kernel(l)]
         kinds[k] = kinds.get(k, 0) + 1
-    kernel0 = "fused_chain_kernel" if one_launch else sp.KERNEL_NAMES[model.layer_kernel(0)]
+    kernel0 = "resident_kernel" if resident else sp.KERNEL_NAMES[model.layer_kernel(0)]
     layers_run = int(launches // a.steps)
     if one_launch:   # the library shares the launch's duration out among the layers; the launch is the unit here
         launches = a.steps

@@ -220,8 +220,8 @@ int spdnn_destroy(spdnn_t h);
 const char* spdnn_last_error(void);
 
 /* Measurement aid (not part of the paper's method): with profiling on, spdnn_infer brackets
- * every layer's fused launches (one, or one per pass of a general layer) with HIP events on the
- * model's stream. */
+ * every layer's fused launches (one, or one per pass of a general layer; or the launch of several
+ * layers at once) with HIP events on the model's stream. */
 int spdnn_set_profiling(spdnn_t h, int32_t on);
 
 /* After an spdnn_infer with profiling on: *layers_run = number of layers that were launched
@@ -232,7 +232,8 @@ int spdnn_set_profiling(spdnn_t h, int32_t on);
 int spdnn_get_profile(spdnn_t h, int32_t cap, int32_t* layers_run, int32_t* rows_in,
                       float* fused_ms);
 
-/* Measurement and test aid: which of the library's fused kernels layer l runs on, chosen at
+/* Measurement and test aid: which of the library's per-layer fused kernels layer l is set up for (models of at most
+ * 4096 neurons whose weights are resident run their layers inside one kernel of their own instead), chosen at
  * spdnn_create from the layer's pattern (Section III-A-2's shared-memory stages) and weights:
  * SPDNN_KERNEL_SINGLE  every 1024-neuron block's column window fits one LDS stage;
  * SPDNN_KERNEL_STAGED  two stages (or a wider pattern that does not fit the wide format);
@@ -255,13 +256,12 @@ int spdnn_get_profile(spdnn_t h, int32_t cap, int32_t* layers_run, int32_t* rows
 #define SPDNN_KERNEL_ROW2 6
 int spdnn_layer_kernel(spdnn_t h, int32_t l, int32_t* kind);
 
-/* Whether spdnn_infer on `batch` rows runs all layers of the model in ONE launch (*yes = 1) or one launch
- * per layer (0).  One launch is taken for models of at most 1024 neurons per layer (one workgroup then
- * computes every neuron of its rows, so Listing 1's loop over the layers -- kernel, pruning, buffer swap
- * -- can run inside the workgroup) whose layers all fit one LDS stage, when a workgroup's share of the
- * rows is small (at most 128): the case in which the gaps between dependent kernels outweigh the
- * kernels.  With profiling on, such a launch's duration is shared out among the layers in proportion
- * to the rows they had (spdnn_get_profile). */
+/* Whether spdnn_infer on `batch` rows runs all layers of the model in ONE launch (*yes = 1).  Answered for models of
+ * at most 1024 neurons per layer (one workgroup then computes every neuron of its rows, so Listing 1's loop over the
+ * layers -- kernel, pruning, buffer swap -- can run inside the workgroup) whose layers all fit one LDS stage: 1 when a
+ * workgroup's share of the rows is small (at most 128).  Larger batches, and models of up to 4096 neurons (always
+ * reported as 0), keep their rows on the chip for several layers per launch.  With profiling on, a launch's duration is
+ * shared out among its layers in proportion to the rows they had (spdnn_get_profile). */
 int spdnn_one_launch(spdnn_t h, int32_t batch, int32_t* yes);
 
 /* Number of fused-kernel launches (passes) layer l takes: 1, or for a general layer whose

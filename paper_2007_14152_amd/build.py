@@ -11,7 +11,8 @@ CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(CSRC, "libspdnn.so")
 SOURCES = [os.path.join(CSRC, "spdnn.hip")]
 HEADERS = [os.path.join(CSRC, "spdnn_kernels.h"), os.path.join(CSRC, "spdnn_order.h"),
-           os.path.join(CSRC, "spdnn_layout.h"),
+           os.path.join(CSRC, "spdnn_layout.h"), os.path.join(CSRC, "spdnn_row2.h"),
+           os.path.join(CSRC, "spdnn_resident.h"), os.path.join(CSRC, "spdnn_cut.h"),
            os.path.join(os.path.dirname(_HERE), "include", "spdnn.h")]
 # host build of the connection-ordering routine, for tests of the set-up logic without a GPU
 ORDER_HOST_LIB = os.path.join(CSRC, "libspdnn_order_host.so")
@@ -61,7 +62,7 @@ def build(verbose: bool = False, extra=()) -> str:
                                    % (k, v["ScratchSize [bytes/lane]"]))
     if verbose:
         for k, v in sorted(usage.items()):
-            if "fused_" in k:
+            if "fused_" in k or "resident_" in k:
                 print("%s: VGPRs %s, scratch %s B/lane" % (k, v.get("VGPRs"), v.get("ScratchSize [bytes/lane]")))
     subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-o", ORDER_HOST_LIB, ORDER_HOST_SRC],
                    check=True)

@@ -93,10 +93,11 @@ struct spdnn_model {
     std::vector<LayerDesc> layers;     // one per pass (launch); a layer is one pass unless some neuron has more than 32 connections
     std::vector<int32_t> first_pass;   // L+1 entries: layer l is passes first_pass[l] .. first_pass[l+1]-1
     int* host_counts = nullptr;  // pinned, L+1 entries: rows active on entry to layer l
-    // all layers in one launch (fused_chain_kernel): possible if every layer is a single-stage layer of one output block
-    const spdnn::LayerWeights* chain_layers = nullptr;  // device copy of the layers' descriptors (NULL: not possible)
-    int* chain_rows = nullptr;                          // device, L + 1 counters
-    int chain_lds_cols = 0;
+    // rows that stay in LDS from layer to layer (resident_kernel): networks of at most 4096 neurons whose layers are one
+    // pass each
+    const spdnn::ResidentLayer* res_layers = nullptr;  // device copy of the layers' descriptors (NULL: not possible)
+    int* res_rows = nullptr;                           // device, L + 1 counters
+    bool res_uniform = false;                          // every layer has one weight for all its connections
     // out-of-core weights: pass p's block lives in host memory and is copied into device slot p & 1
     const char* ooc_host = nullptr;
     char* ooc_slot[2] = {nullptr, nullptr};
@@ -166,15 +167,15 @@ size_t block_bytes(int32_t N, int nstage_cap) {  // one pass's re-laid weights
     const int32_t nblk = (N + spdnn::kBlk - 1) / spdnn::kBlk;
     return layer_bytes(nblk) + wide_bytes(nblk, nstage_cap);
 }
-size_t chain_bytes(int32_t L) {  // all layers in one launch: the layers' descriptors and the rows-per-layer counters
-    return up((size_t)L * sizeof(spdnn::LayerWeights)) + up(((size_t)L + 1) * sizeof(int));
+size_t res_bytes(int32_t L) {  // resident_kernel: the layers' descriptors and the rows-per-layer counters
+    return up((size_t)L * sizeof(spdnn::ResidentLayer)) + up(((size_t)L + 1) * sizeof(int));
 }
 size_t arena_bytes_for(int32_t N, int32_t L, int nstage_cap) {
-    return up((size_t)N * sizeof(float)) + (size_t)L * block_bytes(N, nstage_cap) + staging_bytes(N, L) + chain_bytes(L);
+    return up((size_t)N * sizeof(float)) + (size_t)L * block_bytes(N, nstage_cap) + staging_bytes(N, L) + res_bytes(L);
 }
 // out-of-core: the device holds the bias, two blocks and the staging area; the host holds all blocks
 size_t ooc_device_bytes_for(int32_t N, int32_t L, int nstage_cap) {
-    return up((size_t)N * sizeof(float)) + 2 * block_bytes(N, nstage_cap) + staging_bytes(N, L) + chain_bytes(L);
+    return up((size_t)N * sizeof(float)) + 2 * block_bytes(N, nstage_cap) + staging_bytes(N, L);
 }
 
 struct WorkView {
@@ -220,7 +221,13 @@ hipError_t allow_big_lds() {
                                hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)spdnn::tile_pair_bytes(spdnn::kCap) + (VIRT ? kVirtLds : 0));
 }
-
+template <int NB, int PM>
+hipError_t allow_resident_lds(int bytes) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::resident_kernel<NB, PM, false>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    return e != hipSuccess ? e : hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::resident_kernel<NB, PM, true>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
 
 // The fused kernels and set-up kernels use more dynamic LDS than the default limit allows.
 int allow_large_lds() {
@@ -252,8 +259,12 @@ int allow_large_lds() {
                                 hipFuncAttributeMaxDynamicSharedMemorySize, tile_lds));
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::fused_wide_kernel<8>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, tile_lds));
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::fused_chain_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)spdnn::tile_pair_bytes(spdnn::kBlk)));
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::balance_kernel<4>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(spdnn::BalanceScratch<4>)));
+    const int res_lds = (int)spdnn::res_tile_bytes(spdnn::kCap, 2) + spdnn::kResMiscBytes;
+    HIP_TRY((allow_resident_lds<1, 4>(res_lds)));
+    HIP_TRY((allow_resident_lds<2, 4>(res_lds)));
+    HIP_TRY((allow_resident_lds<4, 2>(res_lds)));
     return SPDNN_OK;
 }
 
@@ -438,7 +449,7 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
         o += up((size_t)nblk * sizeof(int2));
         m->layers[l].virt.fin = reinterpret_cast<const uint32_t*>(base + o);
         o += up((size_t)nblk * spdnn::kBlk * sizeof(uint32_t));
-        m->layers[l].w = spdnn::LayerWeights{rel, wv, win, qsel};
+        m->layers[l].w = spdnn::LayerWeights{rel, wv, win, qsel, 0};
         win_dev[l] = win;
         spdnn::WideWeights ww{};
         ww.win = win;
@@ -491,9 +502,9 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
     int* err_dev = reinterpret_cast<int*>(base + o);
     HIP_TRY(hipMemsetAsync(err_dev, 0, sizeof(int) * (size_t)(5 * P + 1), stream));
     o += up(sizeof(int) * (size_t)(5 * P + 1));
-    spdnn::LayerWeights* chain_layers_dev = reinterpret_cast<spdnn::LayerWeights*>(base + o);
-    o += up((size_t)P * sizeof(spdnn::LayerWeights));
-    int* chain_rows_dev = reinterpret_cast<int*>(base + o);
+    spdnn::ResidentLayer* res_layers_dev = reinterpret_cast<spdnn::ResidentLayer*>(base + o);  // (not with out-of-core weights)
+    o += up((size_t)P * sizeof(spdnn::ResidentLayer));
+    int* res_rows_dev = reinterpret_cast<int*>(base + o);
 
     // Layers that are already on the device and need no staging are set up on several streams in turn.
     struct SetupStreams {
@@ -589,6 +600,13 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
         int* pair_dev = err_dev + 1 + 3 * P + 2 * l;
         spdnn::block_window_kernel<<<nblk, spdnn::kBlk, 0, stream>>>(di, N, win_dev[l], err_dev, widest_dev, dv,
                                                                        err_dev + 1 + 2 * P + l, nrows);
+        // A row that fits one LDS stage: the blocks share one tile layout, that of the whole row, which is what
+        // resident_kernel needs (out-of-core weights, which it does not take, are laid out the same: same sums).
+        const bool whole = N <= spdnn::kCap && !d.multi;
+        if (whole) {
+            spdnn::whole_row_window_kernel<<<1, 64, 0, stream>>>(win_dev[l], nblk, N, widest_dev);
+            d.w.planes_log2 = spdnn::res_planes_log2(nblk);
+        }
         // a layer of several passes runs the one-neuron-per-lane kernels, whose epilogue knows about passes
         if (!d.multi)
             spdnn::pair_merge_kernel<<<1, 64, 0, stream>>>(win_dev[l], nblk, N, dv, err_dev + 1 + 2 * P + l, widest_dev,
@@ -738,14 +756,18 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
             if (where == SPDNN_HOST) HIP_TRY(hipStreamSynchronize(stream));  // staging is reused
             continue;
         }
-        if (pair)
+        const int unit = whole ? nblk : pair ? 2 : 1;  // blocks that share a tile layout
+        if (unit > 2)
+            spdnn::balance_kernel<4><<<1, spdnn::kBalanceThreads, sizeof(spdnn::BalanceScratch<4>), stream>>>(
+                di, N, win_dev[l], widest_dev, slot_tab, const_cast<uint32_t*>(d.w.qsel));
+        else if (unit == 2)
             spdnn::balance_kernel<2><<<nblk / 2, spdnn::kBalanceThreads, sizeof(spdnn::BalanceScratch<2>), stream>>>(
                 di, N, win_dev[l], widest_dev, slot_tab, const_cast<uint32_t*>(d.w.qsel));
         else
             spdnn::balance_kernel<1><<<nblk, spdnn::kBalanceThreads, sizeof(spdnn::BalanceScratch<1>), stream>>>(
                 di, N, win_dev[l], widest_dev, slot_tab, const_cast<uint32_t*>(d.w.qsel), nrows);
         spdnn::order_pack_kernel<<<nblk * spdnn::kOrderThreads, spdnn::kOrderPackThreads, 0, stream>>>(
-            di, dv, N, win_dev[l], widest_dev, slot_tab, pair, const_cast<uint16_t*>(d.w.rel),
+            di, dv, N, win_dev[l], widest_dev, slot_tab, unit, d.w.planes_log2, const_cast<uint16_t*>(d.w.rel),
             const_cast<float*>(d.w.val), nrows, lens, lens ? const_cast<uint8_t*>(d.virt.nb8) : nullptr);
         HIP_TRY(hipGetLastError());
         int widest = 4;
@@ -788,20 +810,26 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
     if (herr[0]) return fail(SPDNN_EINVAL, "a column index is outside [0, N)");
     for (int32_t l = 0; l < P; ++l)
         if ((m->layers[l].mode == kWide || m->layers[l].mode == kWidePair) && herr[1 + l]) m->layers[l].mode = kStaged;
-    // One output block and nothing but single-stage layers of one launch each: the whole network can run in one
-    // launch (fused_chain_kernel), which takes the layers' descriptors from device memory.
-    bool chain = nblk == 1 && !ooc && P == L;
-    for (int32_t l = 0; chain && l < P; ++l) chain = m->layers[l].mode == kSingle && !m->layers[l].multi;
-    if (chain) {
-        std::vector<spdnn::LayerWeights> lw((size_t)L);
-        for (int32_t l = 0; l < L; ++l) {
-            lw[l] = m->layers[l].w;
-            m->chain_lds_cols = std::max(m->chain_lds_cols, m->layers[l].lds_cols);
-        }
-        HIP_TRY(hipMemcpyAsync(chain_layers_dev, lw.data(), sizeof(spdnn::LayerWeights) * (size_t)L, hipMemcpyHostToDevice, stream));
+    // Rows of at most one LDS stage and nothing but layers of one pass each: the rows can stay in LDS from layer to
+    // layer (resident_kernel, which takes the layers' descriptors from device memory).
+    if (N <= spdnn::kCap && !ooc && P == L) {
+        std::vector<int> differ((size_t)L);  // layers with more than one weight value
+        std::vector<int> info(2 * (size_t)L);
+        HIP_TRY(hipMemcpyAsync(differ.data(), err_dev + 1 + 2 * P, sizeof(int) * (size_t)L, hipMemcpyDeviceToHost, stream));
+        HIP_TRY(hipMemcpyAsync(info.data(), err_dev + 1 + 3 * P, sizeof(int) * 2 * (size_t)L, hipMemcpyDeviceToHost, stream));
         HIP_TRY(hipStreamSynchronize(stream));
-        m->chain_layers = chain_layers_dev;
-        m->chain_rows = chain_rows_dev;
+        std::vector<spdnn::ResidentLayer> rl((size_t)L);
+        m->res_uniform = true;
+        for (int32_t l = 0; l < L; ++l) {
+            const spdnn::LayerWeights& w = m->layers[l].w;
+            rl[l] = spdnn::ResidentLayer{w.rel, w.val, w.qsel, 0.0f};
+            m->res_uniform = m->res_uniform && !differ[l];
+            std::memcpy(&rl[l].wuni, &info[2 * (size_t)l + 1], sizeof(float));
+        }
+        HIP_TRY(hipMemcpyAsync(res_layers_dev, rl.data(), sizeof(spdnn::ResidentLayer) * (size_t)L, hipMemcpyHostToDevice, stream));
+        HIP_TRY(hipStreamSynchronize(stream));
+        m->res_layers = res_layers_dev;
+        m->res_rows = res_rows_dev;
     }
     guard.m = nullptr;
     *out = m;
@@ -859,19 +887,194 @@ int static_scratch(void** out) {
     return SPDNN_OK;
 }
 
-// All layers in one launch (fused_chain_kernel)?  Yes if the model allows it and a workgroup's share of the rows is
-// small enough; *q = the launch's row chunks.
-bool one_launch_shape(spdnn_t h, int32_t batch, int32_t* q) {
+// How resident_kernel runs a network: the most groups of 64 neurons a wave owns, the most planes of 4 rows a pass
+// holds, the workgroup's threads and LDS, and how many workgroups fit the GPU at once.
+struct ResidentShape {
+    int nb, planes, threads, lds, slots;
+};
+ResidentShape resident_shape(const spdnn_model* h, int32_t rows) {
+    ResidentShape r;
+    r.planes = 1 << spdnn::res_planes_log2(h->nblk);
+    r.nb = h->nblk > 2 ? 4 : h->nblk == 1 && rows <= spdnn::kRows * h->num_cu ? 1 : 2;
+    const int groups = (h->N + 63) / 64, waves = (groups + r.nb - 1) / r.nb;
+    r.threads = 64 * waves;
+    r.lds = (int)spdnn::res_tile_bytes(h->N, r.planes) + spdnn::kResMiscBytes;
+    r.slots = h->num_cu * std::max(1, std::min(16 / waves, 160 * 1024 / r.lds));
+    return r;
+}
+
+// All layers in one launch?  With rows in LDS from layer to layer, if a workgroup's share of the rows is small: they
+// stay with the workgroup they started in, and a share that is packed together again as rows die is all the
+// rebalancing there is.  One output block: up to kShareRows rows per CU; more blocks: what one pass holds.
+bool one_launch(spdnn_t h, int32_t batch) {
+    if (batch <= 0 || h->res_layers == nullptr) return false;
     const int32_t groups = (batch + spdnn::kRows - 1) / spdnn::kRows;
-    const int32_t chunks = std::max(1, std::min(h->num_cu, groups));
-    if (q) *q = chunks;
-    return batch > 0 && h->chain_layers != nullptr && (groups + chunks - 1) / chunks * spdnn::kRows <= spdnn::kChainRows;
+    const int32_t share = (groups + h->num_cu - 1) / h->num_cu * spdnn::kRows;
+    return share <= (h->nblk == 1 ? spdnn::kShareRows : spdnn::kRows * (1 << spdnn::res_planes_log2(h->nblk)));
+}
+
+hipError_t launch_resident(spdnn_t h, const ResidentShape& r, int32_t Q, const float* Yin, float* Ymid, float* Yout, uint8_t* flags,
+                           const spdnn::RowLists& rl, const spdnn::ResidentArgs& ra) {
+    const auto run = [&](auto nb, auto planes, auto uni) {
+        spdnn::resident_kernel<decltype(nb)::value, decltype(planes)::value, decltype(uni)::value>
+            <<<Q, r.threads, r.lds, h->stream>>>(Yin, Ymid, Yout, flags, rl, ra, h->bias_dev, h->N);
+    };
+    const auto run_uni = [&](auto nb, auto planes) {
+        if (h->res_uniform) run(nb, planes, std::true_type{});
+        else run(nb, planes, std::false_type{});
+    };
+    if (r.nb == 1) run_uni(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
+    else if (r.nb == 2) run_uni(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+    else run_uni(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{});
+    return hipGetLastError();
+}
+
+// Waits until a kernel has stored a count to its slot in pinned host memory.  The slot is polled; the stream is
+// asked now and then whether it has run dry, only so that a failed launch ends the wait.
+int wait_count(spdnn_t h, int32_t l, int32_t* count) {
+    volatile int* slot = h->host_counts + l;
+    int32_t c = *slot;
+    for (uint32_t spin = 1; c < 0; ++spin) {
+        if ((spin & 1023u) == 0) {
+            const hipError_t q = hipStreamQuery(h->stream);
+            if (q == hipSuccess) {  // everything launched is done: the count has been stored
+                c = *slot;
+                if (c < 0) return fail(SPDNN_EHIP, "layer %d finished without reporting its active rows", l);
+                break;
+            }
+            if (q != hipErrorNotReady) HIP_TRY(q);
+        }
+        c = *slot;
+    }
+    std::atomic_thread_fence(std::memory_order_acquire);
+    *count = c;
+    return SPDNN_OK;
+}
+
+// The result: the rows whose flag is set among those the last launch wrote (numbers gid_in, or without lists the whole
+// batch), their numbers ascending to active_rows_dev and their values, from Y_last, to Y_final_dev.  Nothing here waits
+// for the count but the host at the end: rows are numbered straight into the caller's array, and the gather takes the
+// count from device memory (at most `bound` rows).  Returns with the stream drained.
+int finish_infer(spdnn_t h, const uint8_t* flags, const int* count_in, const int* gid_in, int32_t batch, int32_t row_offset,
+                 int* count_out, int* cat_out, int32_t slot, const float* Y_last, int32_t bound, int32_t* n_active_host,
+                 int32_t* active_rows_dev, float* Y_final_dev) {
+    hipStream_t s = h->stream;
+    h->host_counts[slot] = -1;
+    spdnn::compact_kernel<<<spdnn::kCompactWGs, 1024, 0, s>>>(flags, nullptr, count_in, count_out, gid_in, active_rows_dev, cat_out,
+                                                              h->host_counts + slot, batch, row_offset);
+    HIP_TRY(hipGetLastError());
+    if (Y_final_dev && bound > 0) {
+        const int n4 = h->N / 4;
+        const size_t total = (size_t)bound * n4;
+        const int g = (int)std::min<size_t>((total + 255) / 256, 65536);
+        spdnn::gather_rows_kernel<<<g, 256, 0, s>>>(reinterpret_cast<const float4*>(Y_last), cat_out, count_out, n4,
+                                                   reinterpret_cast<float4*>(Y_final_dev));
+        HIP_TRY(hipGetLastError());
+    }
+    HIP_TRY(hipStreamSynchronize(s));
+    const int n = h->host_counts[slot];
+    if (n < 0) return fail(SPDNN_EHIP, "the last layer finished without reporting its active rows");
+    *n_active_host = n;
+    return SPDNN_OK;
+}
+
+// infer_impl for networks whose rows stay in LDS from layer to layer (resident_kernel).
+int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv, int32_t row_offset,
+                   int32_t* n_active_host, int32_t* active_rows_dev, float* Y_final_dev) {
+    const int32_t L = h->L;
+    hipStream_t s = h->stream;
+    struct DrainModel {  // nothing of this call is left running on return, whatever happens
+        hipStream_t s;
+        bool armed = true;
+        ~DrainModel() {
+            if (armed) (void)hipStreamSynchronize(s);
+        }
+    } drain_model{s};
+    const bool one = one_launch(h, batch);
+    int* layer_rows = nullptr;
+    if (h->profiling) {
+        layer_rows = h->res_rows;
+        spdnn::clear_counters_kernel<<<(L + 256) / 256, 256, 0, s>>>(layer_rows, L + 1);
+        HIP_TRY(hipGetLastError());
+    }
+    // Runs of layers.  In one launch the workgroups pack their shares together once, behind the first two layers, if
+    // they are of several passes.  Otherwise the batch is compacted and shared out anew after two layers, where most
+    // of the rows that die have died.  If fewer than a quarter died, all layers that are left are one launch; if
+    // not, the next run is four times as long, and so on.  (A launch costs the gap before it, 20 us, and the rows'
+    // way through memory; a share of rows that die unevenly costs the workgroups' waiting for the fullest one.)
+    struct Run {
+        int32_t l0, l1;
+    };
+    std::vector<Run> runs;
+    int32_t alive = batch, before = batch;
+    spdnn::RowLists rl{};
+    int32_t k = 0;     // launches so far
+    int32_t len = 2;   // layers of the next run
+    for (int32_t l0 = 0; l0 < L; ++k, len *= 4) {
+        const bool rest = one || (k > 0 && (int64_t)alive * 4 > (int64_t)before * 3) || len >= L - l0;
+        const int32_t l1 = rest ? L : l0 + len;
+        const ResidentShape shape = resident_shape(h, alive);
+        const int32_t groups = (alive + spdnn::kRows - 1) / spdnn::kRows;
+        const int32_t Q = std::min(groups, shape.slots);
+        const bool several = (groups + Q - 1) / Q > shape.planes;
+        const spdnn::ResidentArgs ra{h->res_layers, l0, one && several ? std::min(l0 + 2, l1) : l1, l1, L, batch, layer_rows};
+        if (h->profiling) HIP_TRY(hipEventRecord(h->t0[l0], s));
+        HIP_TRY(launch_resident(h, shape, Q, k == 0 ? Y0_dev : wv.Y[(k + 1) & 1], wv.Y[(k + 1) & 1], wv.Y[k & 1], wv.flags[0], rl, ra));
+        if (h->profiling) HIP_TRY(hipEventRecord(h->t1[l0], s));
+        runs.push_back(Run{l0, l1});
+        l0 = l1;
+        if (l1 == L) break;
+        h->host_counts[l1] = -1;
+        spdnn::compact_kernel<<<spdnn::kCompactWGs, 1024, 0, s>>>(wv.flags[0], nullptr, rl.count, wv.count[k & 1], rl.gid, wv.gid[k & 1],
+                                                                  wv.cat[k & 1], h->host_counts + l1, batch, row_offset);
+        HIP_TRY(hipGetLastError());
+        before = alive;
+        const int rc = wait_count(h, l1, &alive);
+        if (rc != SPDNN_OK) return rc;
+        rl.count = wv.count[k & 1];
+        rl.gid = wv.gid[k & 1];
+        rl.cat = wv.cat[k & 1];
+        if (alive == 0) break;
+    }
+    int32_t rc = SPDNN_OK;
+    if (alive > 0)
+        rc = finish_infer(h, wv.flags[0], rl.count, rl.gid, batch, row_offset, wv.count[k & 1], wv.cat[k & 1], L + 1,
+                          wv.Y[k & 1], alive, n_active_host, active_rows_dev, Y_final_dev);
+    else {
+        HIP_TRY(hipStreamSynchronize(s));
+        *n_active_host = 0;
+    }
+    if (rc != SPDNN_OK) return rc;
+    drain_model.armed = false;
+    if (h->profiling) {  // a launch's time is shared out among its layers by the rows they had
+        std::vector<int> rows((size_t)L + 1);
+        HIP_TRY(hipMemcpy(rows.data(), layer_rows, sizeof(int) * rows.size(), hipMemcpyDeviceToHost));
+        rows[0] = batch;
+        int32_t run = L;  // "launched": up to the first layer without rows
+        for (int32_t l = 1; l < L; ++l)
+            if (rows[l] == 0) {
+                run = l + 1;
+                break;
+            }
+        h->prof_layers = run;
+        h->prof_ms.assign(run, 0.0f);
+        h->prof_rows.assign(rows.begin(), rows.begin() + run);
+        for (const Run& r : runs) {
+            float ms = 0.0f;
+            HIP_TRY(hipEventElapsedTime(&ms, h->t0[r.l0], h->t1[r.l0]));
+            double sum = 0.0;
+            for (int32_t l = r.l0; l < std::min(r.l1, run); ++l) sum += rows[l];
+            for (int32_t l = r.l0; l < std::min(r.l1, run); ++l) h->prof_ms[l] = sum > 0 ? (float)(ms * rows[l] / sum) : 0.0f;
+        }
+    }
+    return SPDNN_OK;
 }
 
 // All L layers on `batch` rows whose first row has the original number row_offset; wv = the carved
 // work memory.  Returns with the model's stream drained, also when a HIP call fails half way.
 int infer_impl(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv, int32_t row_offset,
                int32_t* n_active_host, int32_t* active_rows_dev, float* Y_final_dev) {
+    if (h->res_layers) return infer_resident(h, Y0_dev, batch, wv, row_offset, n_active_host, active_rows_dev, Y_final_dev);
     const int32_t N = h->N, L = h->L;
     hipStream_t s = h->stream;
     // Kernels may be queued when a later HIP call fails: nothing of this call is left running on return.
@@ -885,39 +1088,11 @@ int infer_impl(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv
 
     for (int32_t l = 1; l <= L; ++l) h->host_counts[l] = -1;  // "not reported yet"
     h->host_counts[0] = batch;
-    int32_t chain_q = 1;
-    const bool chain = one_launch_shape(h, batch, &chain_q);
     // "layer -1": every row of the batch is flagged alive, under its own number
     spdnn::init_lists_kernel<<<(batch + 255) / 256, 256, 0, s>>>(wv.gid[1], wv.flags[2], wv.flags[0], wv.count[1], batch,
-                                                                 row_offset, chain ? h->chain_rows : nullptr, chain ? L + 1 : 0);
+                                                                 row_offset);
     int32_t bound = batch;  // upper bound of the rows active at the layer being launched
     int32_t run = 0;        // layers launched
-    int32_t rot = 0;        // how often the lists have rotated (= run, unless all layers ran in one launch)
-    int32_t final_buf = 0;  // work buffer that holds the last layer's output
-    std::vector<int> chain_rows_host;
-    // All layers in one launch, if the model allows it and a workgroup's share of the rows fits its lists.
-    if (chain) {
-        if (h->profiling) HIP_TRY(hipEventRecord(h->t0[0], s));
-        spdnn::RowLists rl;  // as "layer 0" of the lists' rotation
-        rl.flags_prev = wv.flags[2];
-        rl.count_prev = wv.count[1];
-        rl.gid_prev = wv.gid[1];
-        rl.cat = wv.cat[0];
-        rl.gid = wv.gid[0];
-        rl.count = wv.count[0];
-        rl.host_count = h->host_counts;
-        rl.flags_clear = wv.flags[1];
-        const spdnn::ChainArgs ca{h->chain_layers, L, h->chain_rows};
-        const size_t lds = spdnn::tile_pair_bytes((h->chain_lds_cols + 255) / 256 * 256);
-        spdnn::fused_chain_kernel<<<(chain_q + 7) / 8 * 8, spdnn::kBlk, lds, s>>>(Y0_dev, wv.Y[0], wv.Y[1], wv.flags[0], rl, ca,
-                                                                                  h->bias_dev, N, chain_q);
-        HIP_TRY(hipGetLastError());
-        if (h->profiling) HIP_TRY(hipEventRecord(h->t1[0], s));
-        chain_rows_host.resize((size_t)L + 1);
-        HIP_TRY(hipMemcpyAsync(chain_rows_host.data(), h->chain_rows, sizeof(int) * ((size_t)L + 1), hipMemcpyDeviceToHost, s));
-        rot = 1;
-        final_buf = (L - 1) & 1;
-    }
     // Out-of-core weights (Section III-B-1): pass p runs from device slot p & 1.  The copy stream fills
     // the two slots, and refills a slot with pass p + 2 as soon as the kernels of pass p are done with
     // it, so the transfer of the next layer runs under the current layer's kernel.
@@ -936,7 +1111,7 @@ int infer_impl(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv
     } drain{h->ooc_stream};
     if (h->ooc_host)
         for (int32_t p = 0; p < std::min(P, 2); ++p) HIP_TRY(ooc_fetch(p));
-    for (int32_t l = 0; l < L && !chain; ++l) {
+    for (int32_t l = 0; l < L; ++l) {
         const float* Yin = (l == 0) ? Y0_dev : wv.Y[(l - 1) & 1];
         float* Yout = wv.Y[l & 1];
         if (h->profiling) HIP_TRY(hipEventRecord(h->t0[l], s));
@@ -1043,81 +1218,26 @@ int infer_impl(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv
         // whether it has run dry, only so that a failed launch ends the wait.  Nothing else is put between two
         // layers' kernels: an event recorded after every layer made the gap between them longer.
         if (l + 2 >= kLag) {
-            const int32_t lr = l + 2 - kLag;
-            volatile int* slot = h->host_counts + lr;
-            int32_t c = *slot;
-            for (uint32_t spin = 1; c < 0; ++spin) {
-                if ((spin & 1023u) == 0) {
-                    const hipError_t q = hipStreamQuery(s);
-                    if (q == hipSuccess) {  // everything launched is done: the count has been stored
-                        c = *slot;
-                        if (c < 0) return fail(SPDNN_EHIP, "layer %d finished without reporting its active rows", lr);
-                        break;
-                    }
-                    if (q != hipErrorNotReady) HIP_TRY(q);
-                }
-                c = *slot;
-            }
-            std::atomic_thread_fence(std::memory_order_acquire);
+            int32_t c = 0;
+            const int rc = wait_count(h, l + 2 - kLag, &c);
+            if (rc != SPDNN_OK) return rc;
             bound = c;
             if (bound == 0) break;
         }
     }
-    if (!chain) {
-        rot = run;
-        final_buf = (run - 1) & 1;
-    }
-    // the rows that survive the last layer launched: the same compaction, as a kernel of its own.  Its count goes
-    // to host_counts[run] (rows on entry to the layer that would come next); after a one-launch run the entries
-    // 1 .. L are the launch's own counts, and the survivors' count goes to the spare entry L + 1.
-    const int32_t final_slot = chain ? L + 1 : run;
-    h->host_counts[L + 1] = -1;
-    spdnn::compact_kernel<<<spdnn::kCompactWGs, 1024, 0, s>>>(wv.flags[(rot + 2) % 3], wv.flags[(rot + 1) % 3],
-                                                              wv.count[(rot + 1) & 1], wv.count[rot & 1], wv.gid[(rot + 1) & 1],
-                                                              wv.gid[rot & 1], wv.cat[rot & 1], h->host_counts + final_slot);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(hipStreamSynchronize(s));
-    const int32_t n = h->host_counts[final_slot];
-    if (n < 0) return fail(SPDNN_EHIP, "layer %d finished without reporting its active rows", run - 1);
-    if (chain) {  // rows on entry to every layer, from the launch's counters; "launched" = up to the first layer without rows
-        run = L;
-        for (int32_t l = 1; l <= L; ++l) {
-            h->host_counts[l] = chain_rows_host[(size_t)l];
-            if (chain_rows_host[(size_t)l] == 0 && run == L && l < L) run = l + 1;
-        }
-    }
-    *n_active_host = n;
-    if (n > 0) {
-        const int* cat_f = wv.cat[rot & 1];
-        const int* gid_f = wv.gid[rot & 1];
-        HIP_TRY(hipMemcpyAsync(active_rows_dev, gid_f, sizeof(int) * (size_t)n, hipMemcpyDeviceToDevice, s));
-        if (Y_final_dev) {
-            const int n4 = N / 4;
-            const size_t total = (size_t)n * n4;
-            const int g = (int)std::min<size_t>((total + 255) / 256, 65536);
-            spdnn::gather_rows_kernel<<<g, 256, 0, s>>>(reinterpret_cast<const float4*>(wv.Y[final_buf]), cat_f, n, n4,
-                                                       reinterpret_cast<float4*>(Y_final_dev));
-            HIP_TRY(hipGetLastError());
-        }
-        HIP_TRY(hipStreamSynchronize(s));
-    }
+    // the rows that survive the last layer launched: the same compaction, as a kernel of its own; its count goes to
+    // host_counts[run] (rows on entry to the layer that would come next)
+    const int rc = finish_infer(h, wv.flags[(run + 2) % 3], wv.count[(run + 1) & 1], wv.gid[(run + 1) & 1], batch, row_offset, wv.count[run & 1],
+                                wv.cat[run & 1], run, wv.Y[(run - 1) & 1], bound, n_active_host, active_rows_dev, Y_final_dev);
+    if (rc != SPDNN_OK) return rc;
     drain_model.armed = false;
     if (h->profiling) {
         h->prof_layers = run;
         h->prof_ms.assign(run, 0.0f);
         h->prof_rows.assign(run, 0);
-        float chain_ms = 0.0f;
-        double chain_rows_sum = 0.0;
-        if (chain) {  // one launch: its time is shared out among the layers by the rows they had
-            HIP_TRY(hipEventElapsedTime(&chain_ms, h->t0[0], h->t1[0]));
-            for (int32_t l = 0; l < run; ++l) chain_rows_sum += (double)h->host_counts[l];
-        }
         for (int32_t l = 0; l < run; ++l) {
             h->prof_rows[l] = h->host_counts[l];
-            if (chain)
-                h->prof_ms[l] = chain_rows_sum > 0 ? (float)(chain_ms * (double)h->host_counts[l] / chain_rows_sum) : 0.0f;
-            else
-                HIP_TRY(hipEventElapsedTime(&h->prof_ms[l], h->t0[l], h->t1[l]));
+            HIP_TRY(hipEventElapsedTime(&h->prof_ms[l], h->t0[l], h->t1[l]));
         }
     }
     return SPDNN_OK;
@@ -1334,7 +1454,7 @@ int spdnn_layer_kernel(spdnn_t h, int32_t l, int32_t* kind) {
 int spdnn_one_launch(spdnn_t h, int32_t batch, int32_t* yes) {
     if (!h || !yes) return fail(SPDNN_EINVAL, "null argument");
     if (batch < 0) return fail(SPDNN_EINVAL, "batch < 0");
-    *yes = one_launch_shape(h, batch, nullptr) ? 1 : 0;
+    *yes = h->nblk == 1 && one_launch(h, batch) ? 1 : 0;
     return SPDNN_OK;
 }
 

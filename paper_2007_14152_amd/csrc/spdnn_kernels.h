@@ -39,6 +39,7 @@ struct LayerWeights {
     const float* val;     // [nblk][8][kBlk][4]
     const int2* win;      // [nblk] {c_lo, ncols}, both multiples of 4
     const uint32_t* qsel;  // [nblk][kBlk] balanced single-stage layers: see balance_kernel
+    int planes_log2;       // 0, or for layers whose slots are kept as entry codes (res_code): log2 of the planes
 };
 
 // Layout for layers whose column windows need 3 or more LDS stages ("wide" layers).
@@ -809,7 +810,7 @@ __global__ __launch_bounds__(kBlk) void fused_layer_kernel(
 #pragma unroll
         for (int k = 0; k < kNnz; ++k) {
             if (MULTI) stg[k >> 3] |= (off[k] >> kCapLog2) << (4 * (k & 7));
-            off[k] = lds_base + tile_offset(off[k] & (kCap - 1));
+            off[k] = lds_base + tile_offset(MULTI ? off[k] & (kCap - 1) : res_slot(off[k], w.planes_log2));
         }
     }
     if (MULTI) {
@@ -1042,8 +1043,8 @@ __global__ __launch_bounds__(kBlk) void fused_pair_kernel(
         load_slots(offB, w.rel, b + 1, tid);
 #pragma unroll
         for (int k = 0; k < kNnz; ++k) {
-            offA[k] = lds_base + tile_offset(offA[k]);
-            offB[k] = lds_base + tile_offset(offB[k]);
+            offA[k] = lds_base + tile_offset(res_slot(offA[k], w.planes_log2));
+            offB[k] = lds_base + tile_offset(res_slot(offB[k], w.planes_log2));
         }
     }
     const float bjA = bias[jA], bjB = bias[jB];
@@ -1762,7 +1763,7 @@ __global__ __launch_bounds__(kBlk) void fused_wide_pair4_kernel(
 
 }  // namespace spdnn
 #include "spdnn_row2.h"
-#include "spdnn_chain.h"
+#include "spdnn_resident.h"
 namespace spdnn {
 
 // Compact form of a wide layer's steps for the two-neurons-per-lane wide kernels: the 16-bit
@@ -1826,18 +1827,21 @@ constexpr int kCompactWGs = 16;
 constexpr int kCompactRounds = 4;
 static_assert(kCompactRounds * 16 == 64, "one wave scans the (round, wave) counts");
 
+// flags_clear may be NULL (nothing to clear); without count_in and gid_in the rows are the whole batch, row i under
+// the number row_offset + i.
 __global__ __launch_bounds__(1024) void compact_kernel(const uint8_t* __restrict__ flags_in,
                                                        uint8_t* __restrict__ flags_clear,
                                                        const int* __restrict__ count_in, int* __restrict__ count_out,
                                                        const int* __restrict__ gid_in, int* __restrict__ gid_out,
-                                                       int* __restrict__ cat_out, int* host_count) {
+                                                       int* __restrict__ cat_out, int* host_count, int batch,
+                                                       int row_offset) {
     __shared__ int tot[kCompactRounds * 16];  // [round][wave]: kept rows, then exclusive offsets
     __shared__ int wave_tot[16];
     __shared__ int red[17];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
-    const int A = *count_in;
+    const int A = count_in ? *count_in : batch;
     const int S = ((A + (int)gridDim.x - 1) / (int)gridDim.x + 1023) & ~1023;
     const int lo = min(A, (int)blockIdx.x * S);
     const int hi = min(A, lo + S);
@@ -1859,12 +1863,12 @@ __global__ __launch_bounds__(1024) void compact_kernel(const uint8_t* __restrict
             const int i = chunk0 + (r << 10) + tid;
             const bool ok = r < nr && i < hi;
             f[r] = ok ? flags_in[i] : 0;
-            g[r] = ok ? gid_in[i] : 0;
+            g[r] = !ok ? 0 : gid_in ? gid_in[i] : row_offset + i;
         }
 #pragma unroll
         for (int r = 0; r < kCompactRounds; ++r) {
             const int i = chunk0 + (r << 10) + tid;
-            if (r < nr && i < hi) flags_clear[i] = 0;
+            if (flags_clear && r < nr && i < hi) flags_clear[i] = 0;
             const unsigned long long m = __ballot(f[r] != 0);
             if (f[r] != 0) mine |= 1u << r;
             if (lane == 0) tot[r * 16 + wave] = __popcll(m);
@@ -1904,7 +1908,7 @@ __global__ __launch_bounds__(1024) void compact_kernel(const uint8_t* __restrict
 // numbered through).
 __global__ void init_lists_kernel(int* __restrict__ gid_prev, uint8_t* __restrict__ flags_prev,
                                   uint8_t* __restrict__ flags_first, int* __restrict__ count_prev, int batch,
-                                  int row_offset, int* __restrict__ counters = nullptr, int ncounters = 0) {
+                                  int row_offset) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < batch) {
         gid_prev[i] = row_offset + i;
@@ -1912,14 +1916,18 @@ __global__ void init_lists_kernel(int* __restrict__ gid_prev, uint8_t* __restric
         flags_first[i] = 0;
     }
     if (i == 0) *count_prev = batch;
-    // counters that the inference adds to (rows per layer of a one-launch run), cleared here
-    for (int k = i; k < ncounters; k += gridDim.x * blockDim.x) counters[k] = 0;
+}
+
+// Rows-per-layer counters that a resident_kernel run adds to.
+__global__ void clear_counters_kernel(int* __restrict__ counters, int n) {
+    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) counters[k] = 0;
 }
 
 // a4: surviving rows of Y_L, gathered into a dense [n][N] array (16-byte pieces).
-__global__ void gather_rows_kernel(const float4* __restrict__ src, const int* __restrict__ cat, int n,
-                                   int n4, float4* __restrict__ dst) {
-    const size_t total = (size_t)n * n4;
+// n: device memory -- the host need not know it to launch this.
+__global__ void gather_rows_kernel(const float4* __restrict__ src, const int* __restrict__ cat,
+                                   const int* __restrict__ n, int n4, float4* __restrict__ dst) {
+    const size_t total = (size_t)*n * n4;
     for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
          e += (size_t)gridDim.x * blockDim.x) {
         const size_t row = e / n4;
@@ -1991,6 +1999,14 @@ __global__ __launch_bounds__(kBlk) void block_window_kernel(const int32_t* __res
         win[blockIdx.x] = make_int2(c_lo, ncols);
         atomicMax(widest, ncols);  // the layer's widest window (zero before the launch)
     }
+}
+
+// Networks whose rows fit one LDS stage: every block's window is the whole row, whatever it reads of it, so that all
+// blocks share one tile layout.
+__global__ void whole_row_window_kernel(int2* __restrict__ win, int nblk, int N, int* __restrict__ widest) {
+    const int b = threadIdx.x;
+    if (b < nblk) win[b] = make_int2(0, N);
+    if (b == 0) *widest = N;
 }
 
 // ---------------------------------------------------------------------------
@@ -2245,14 +2261,14 @@ __global__ __launch_bounds__(64) void pair_merge_kernel(int2* __restrict__ win, 
 // One wave per output block.  Output: slot_tab[b][c] = LDS slot of stage-local column
 // c, qsel[b][t] = quads (times 16, one per byte) of staging lane t's four columns.
 // A layer with a wider window is left alone (order_pack_kernel then uses col_slot()).
-// UB = output blocks per unit: 1, or 2 for layers that run two neurons per lane (the
-// two blocks then share window, tile layout and staging quads, stored under the first).
+// UB = output blocks per unit: 1, or 2 for layers that run two neurons per lane, or all of
+// a network of at most 4096 neurons (up to 4): a unit's blocks share window, tile layout and
+// staging quads (written under each of them; the slot table under the first).
 template <int UB>
 struct BalanceScratch {
-    uint32_t cursor[kCap];                 // connections per column, then fill position
-    uint32_t ofs[kCap + 4];                // start of column c's entries in ent[]
+    uint32_t cursor[kCap];                 // connections per column, then fill position: in the end, where the next column starts
     uint8_t ent[UB * kNnz * kBlk];         // lane set (0..64*UB-1) of every connection, grouped by column
-    uint32_t load[UB * kBlk / kGroup][16];  // connections lane set S already has in quad q
+    uint32_t load[UB * kBlk / kGroup][8];  // connections lane set S already has in quad q, two quads to a word
     uint16_t cost[16][16];
 };
 constexpr int kBalanceThreads = 64;
@@ -2270,7 +2286,7 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const int32_t*
     const int lane = threadIdx.x;
     const int c_lo = win[b].x;
     for (int c = lane; c < kCap; c += kBalanceThreads) B.cursor[c] = 0;
-    for (int i = lane; i < UB * (kBlk / kGroup) * 16; i += kBalanceThreads) (&B.load[0][0])[i] = 0;
+    for (int i = lane; i < UB * (kBlk / kGroup) * 8; i += kBalanceThreads) (&B.load[0][0])[i] = 0;
     __syncthreads();
     // stage-local column of connection e = (neuron << 5 | k) of this unit, or -1
     auto rel_of = [&](int e) -> int {
@@ -2297,11 +2313,9 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const int32_t*
         uint32_t run = incl - sum;
         for (int i = 0; i < per; ++i) {
             const uint32_t n = B.cursor[lane * per + i];
-            B.ofs[lane * per + i] = run;
             B.cursor[lane * per + i] = run;
             run += n;
         }
-        if (lane == kBalanceThreads - 1) B.ofs[kCap] = run;
     }
     __syncthreads();
     for (int e = lane; e < UB * kNnz * kBlk; e += kBalanceThreads) {
@@ -2312,6 +2326,7 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const int32_t*
         B.ent[pos] = (uint8_t)(((n >> 6) << 2) | set_of_lane(n & 63u));
     }
     __syncthreads();
+    auto ofs = [&](int c) -> uint32_t { return c ? B.cursor[c - 1] : 0u; };  // where column c's entries start
 
     // Cost phase: lanes 4 i .. 4 i + 3 share column i of the group, each takes every fourth of its connections
     // and adds up, for all 16 quads, what the connections' lane sets already hold there.
@@ -2322,11 +2337,11 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const int32_t*
         const int a = g & 3, set = (g >> 2) & 3, wave = g >> 4;
         auto column_of = [&](int i) { return 4 * (wave * 64 + lane_of_group(set, i)) + a; };
         const int c_row = column_of(row);
-        const uint32_t e0 = B.ofs[c_row], e1 = B.ofs[c_row + 1];
+        const uint32_t e0 = ofs(c_row), e1 = ofs(c_row + 1);
         // The columns choose in the order of their connection counts, busiest first, lowest index among equals:
         // known before any cost is.  rank = my column's place in that order (every 16 lanes: column lane & 15).
         const int c_mine = column_of(lane & 15);
-        const int cnt = (int)B.ofs[c_mine + 1] - (int)B.ofs[c_mine];
+        const int cnt = (int)ofs(c_mine + 1) - (int)ofs(c_mine);
         int rank = 0;
         {
             const int key = (cnt << 4) | (15 - (lane & 15));
@@ -2344,12 +2359,16 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const int32_t*
             for (uint32_t e = e0 + sub; e < e1; e += 4) {
                 const uint4* ld = reinterpret_cast<const uint4*>(&B.load[B.ent[e]][0]);
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
+                for (int v = 0; v < 2; ++v) {
                     const uint4 x = ld[v];
-                    acc[4 * v + 0] += x.x;
-                    acc[4 * v + 1] += x.y;
-                    acc[4 * v + 2] += x.z;
-                    acc[4 * v + 3] += x.w;
+                    acc[8 * v + 0] += x.x & 0xffffu;
+                    acc[8 * v + 1] += x.x >> 16;
+                    acc[8 * v + 2] += x.y & 0xffffu;
+                    acc[8 * v + 3] += x.y >> 16;
+                    acc[8 * v + 4] += x.z & 0xffffu;
+                    acc[8 * v + 5] += x.z >> 16;
+                    acc[8 * v + 6] += x.w & 0xffffu;
+                    acc[8 * v + 7] += x.w >> 16;
                 }
             }
 #pragma unroll
@@ -2381,13 +2400,15 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const int32_t*
         // the chosen quads take the columns' connections on board (all 64 lanes: column `row`, every fourth entry)
         {
             const int ch = __shfl(chosen, row);
-            for (uint32_t e = e0 + sub; e < e1; e += 4) atomicAdd(&B.load[B.ent[e]][ch], 1u);
+            for (uint32_t e = e0 + sub; e < e1; e += 4) atomicAdd(&B.load[B.ent[e]][ch >> 1], 1u << (16 * (ch & 1)));
         }
         if (lane < 16) {
             slot_tab[(size_t)b * kCap + c_mine] = (uint16_t)((g << 4) | chosen);
             packed |= (uint32_t)(chosen << 4) << (8 * a);
             if (a == 3) {
-                qsel[(size_t)b * kBlk + wave * 64 + lane_of_group(set, lane)] = packed;
+                const int nblk = ((nrows < 0 ? N : nrows) + kBlk - 1) / kBlk;
+                for (int i = 0; i < UB && b + i < nblk; ++i)
+                    qsel[(size_t)(b + i) * kBlk + wave * 64 + lane_of_group(set, lane)] = packed;
                 packed = 0;
             }
         }
@@ -2420,7 +2441,8 @@ __global__ __launch_bounds__(kOrderPackThreads) void order_pack_kernel(const int
                                                                    const int2* __restrict__ win,
                                                                    const int* __restrict__ widest,
                                                                    const uint16_t* __restrict__ slot_tab,
-                                                                   int pair,  // the layer's tile layout is per two blocks
+                                                                   int unit,  // the layer's tile layout is per so many blocks
+                                                                   int planes_log2,  // slots are kept as entry codes (res_code)
                                                                    uint16_t* __restrict__ rel,
                                                                    float* __restrict__ wval,
                                                                    // VirtInfo layers: idx / val have nrows rows (all of them
@@ -2446,7 +2468,7 @@ __global__ __launch_bounds__(kOrderPackThreads) void order_pack_kernel(const int
     const bool exists = j < rows;
     // LDS slot of stage-local column r: from balance_kernel for single-stage layers
     const bool balanced = *widest <= kCap;
-    const uint16_t* tab = slot_tab + (size_t)(pair ? (b & ~1) : b) * kCap;
+    const uint16_t* tab = slot_tab + (size_t)(b - b % unit) * kCap;
     auto slot_of = [&](uint32_t r) -> uint32_t { return balanced ? tab[r] : col_slot(r); };
     auto entry = [&](int step) -> size_t { return rel_entry(b, step, my_lane); };
     auto wentry = [&](int step) -> size_t { return val_entry(b, step, my_lane); };
@@ -2461,7 +2483,7 @@ __global__ __launch_bounds__(kOrderPackThreads) void order_pack_kernel(const int
         if (set == 0 && lane == 0 && nb8) nb8[b * 16 + (t >> 2)] = (uint8_t)(((longest + 7) & ~7) / 8);
     }
     if (on && (len || !exists)) {  // lanes past the last neuron, and the steps a short lane leaves empty
-        const uint16_t zero_slot = (uint16_t)slot_of(0);
+        const uint16_t zero_slot = (uint16_t)res_code(slot_of(0), planes_log2);
         for (int step = 0; step < kNnz; ++step) {
             rel[entry(step)] = zero_slot;
             wval[wentry(step)] = 0.0f;
@@ -2572,7 +2594,7 @@ __global__ __launch_bounds__(kOrderPackThreads) void order_pack_kernel(const int
             const int c = idx[src];
             const bool ok = c >= 0 && c < N;
             const uint32_t r = ok ? (uint32_t)win_rel(c, c_lo, N) : 0u;  // stage number | slot inside the stage
-            rel[entry(step)] = (uint16_t)((r & ~(uint32_t)(kCap - 1)) | slot_of(r & (kCap - 1)));
+            rel[entry(step)] = (uint16_t)((r & ~(uint32_t)(kCap - 1)) | res_code(slot_of(r & (kCap - 1)), planes_log2));
             wval[wentry(step)] = ok ? val[src] : 0.0f;
         }
         __syncthreads();

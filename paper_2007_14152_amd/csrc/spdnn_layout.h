@@ -62,6 +62,14 @@ SPDNN_HD inline uint32_t store_group(uint32_t c) {  // of stage-local column c
     return (((t >> 6) << 2) | set_of_lane(t & 63u)) << 2 | (c & 3u);
 }
 
+// Networks of at most 4096 neurons keep their rows in LDS from layer to layer (resident_kernel): a pass holds up to
+// `planes` tiles of 4 rows, interleaved in chunks of 16 columns like the tile pair above, and a connection's slot is
+// kept as its entry code -- the LDS byte address of plane 0's entry, divided by 16 -- so that one shift makes it an
+// address.  Four planes of up to 2048 columns or two of up to 4096: 13 bits.
+SPDNN_HD inline int res_planes_log2(int nblk) { return nblk <= 2 ? 2 : 1; }
+SPDNN_HD inline uint32_t res_code(uint32_t slot, int planes_log2) { return ((slot >> 4) << (4 + planes_log2)) | (slot & 15u); }
+SPDNN_HD inline uint32_t res_slot(uint32_t code, int planes_log2) { return ((code >> (4 + planes_log2)) << 4) | (code & 15u); }
+
 // Column windows are cyclic: the window {c_lo, ncols} of a block of output neurons covers the columns
 // (c_lo + i) mod N, i < ncols (c_lo, ncols and N multiples of 4).  The strided, modular patterns that the
 // challenge networks are built from wrap around the row end; their footprint is narrow only on the circle.

@@ -1,0 +1,388 @@
+// a1 + a2 + a3 for networks of at most 4096 neurons per layer: feature rows stay in LDS from layer to layer.
+//
+// A workgroup that computes EVERY neuron of the rows it is given has the next layer's input in its own hands: rows
+// are independent (Eq. 1), so it can take a few rows through many layers without touching memory in between.  Up to
+// 4096 columns fit: a pass holds 4 * P feature rows as P planes of 4 rows (an entry = 4 rows of one column, 16
+// bytes), P <= 8, 4, 2 for 1, 2, 3-4 output blocks of 1024 neurons: at most 128 KB of LDS.  What moves instead are
+// the connections, which every workgroup reads once per layer and pass (64 KB per 1024 neurons where the layer has
+// one weight, 192 KB otherwise) straight into registers, a neuron-group ahead of their use.  A layer is
+//
+//   compute   lane = output neuron, for each of its NB blocks: 32 connections x P ds_read_b128 x 4 FMAs, summed in the
+//             order the set-up chose, bias last -- the same operations in the same order as the per-layer kernels;
+//             the clipped results stay in registers (NB * P * 4 <= 32)
+//   barrier   every wave is done reading the rows
+//   write     the results go over the input, each to the slot its column has in the NEXT layer's tile layout
+//   barrier
+//
+// The rows that still have a positive output are a bit mask; rows that died stay in place as zeros (bias <= 0 keeps
+// them zero) until so many are dead that the survivors need fewer planes: then the write packs them together
+// (Listing 1's pruning inside the pass).  A pass whose rows have all died is over.
+//
+// What bounds it.  One weight per layer: LDS reads (16 bytes per connection, plane and lane; 256 B per clock and CU) and
+// the FMAs behind them, which take nearly the same time (counters at 1024 neurons, 30 000 rows: LDS active 82 % of the
+// clocks, a fifth of that bank conflicts, vector instructions 72 %).  Weights of their own at 4096 neurons: the stream of
+// connections, 768 KB per layer and pass, which a CU pulls out of L2 at 25 bytes per clock.  One workgroup on its own:
+// latency.  The copies between LDS and memory happen once per launch instead of once per layer.
+// Whole passes, one launch per layer -> this kernel: 1000 rows x 120 layers of 1024 neurons 0.85 -> 0.28 ms, 60 000 rows
+// 7.40 -> 5.12; 4096 neurons, 24 layers, 60 000 rows 5.82 -> 5.19; 10 007 rows, 12 layers with weights of their own
+// 1.19 -> 0.95; one row, 12 layers of 1024 neurons 133 -> 67 us.
+//
+// Workgroups.  Networks of one block whose rows are more than a quad per CU run two workgroups per CU of eight waves
+// (two groups of 64 neurons per wave), so that one computes while the other writes or waits at a barrier (120 layers,
+// 60 000 rows: 5.19 -> 5.12 ms against one workgroup with eight planes); fewer rows, one of sixteen waves.
+#pragma once
+
+namespace spdnn {
+
+// Most rows a workgroup may own when networks of one output block run all their layers in one launch.
+constexpr int kShareRows = 128;
+
+struct ResidentLayer {   // one layer, in device memory
+    const uint16_t* rel;   // LayerWeights::rel, slots as entry codes (res_code)
+    const float* val;
+    const uint32_t* qsel;  // quads of the columns of this layer's input (LayerWeights::qsel, block 0: all blocks share it)
+    float wuni;            // the layer's weight, if all layers of the network have only one
+};
+struct ResidentArgs {
+    const ResidentLayer* layers;
+    int l0, lmid, l1;  // layers l0 .. l1-1; rows of a share of several passes are packed together again at lmid
+    int L;             // layers of the network
+    int A;             // rows on entry, if the lists are not there yet (rl.count == NULL): row i is in slot i
+    int* layer_rows;   // NULL, or [L + 1] counters: [l] += rows alive on entry to layer l
+};
+
+// Bytes of LDS: the planes, then the bookkeeping.
+constexpr int kResMiscBytes = 1024;
+SPDNN_HD inline uint32_t res_chunk_bytes(int planes) { return 256u * (uint32_t)planes; }
+SPDNN_HD inline uint32_t res_tile_bytes(int N, int planes) { return (uint32_t)((N + 255) / 256) * 16u * res_chunk_bytes(planes); }
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// Eight connections of one neuron on P planes: acc[p] += tile[plane p][column i] * w_i, i = 0..7 in that order.  codes =
+// the eight entry codes, two to a register; an SDWA shift makes a half an LDS address, which serves all planes through
+// the read's immediate offset.  The reads of all (connection, plane) pairs form one pipeline of four in flight.  The
+// accumulators and addresses sit in fixed registers so that the assembler's own loop can number them: plane p in
+// v[80+4p .. 83+4p], address i in v[72+i], reads in v[112:127].
+#define SPDNN_RES_ADDR(I, C, H) \
+    "v_lshlrev_b32_sdwa v[72+" I "], %[s4], %[" C "] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_" H "\n\t"
+#define SPDNN_RES_READ(K)                                                                                        \
+    "ds_read_b128 v[112+4*((" K ")%%4):115+4*((" K ")%%4)], v[72+(" K ")/%[P]] offset:256*((" K ")%%%[P])\n\t"
+#define SPDNN_RES_CONN(W)                                    \
+    ".set spdnn_p, 0\n\t"                                    \
+    ".rept %[P]\n\t"                                         \
+    ".if 8*%[P]-spdnn_k > 4\n\t"                             \
+    "s_waitcnt lgkmcnt(3)\n\t"                               \
+    ".else\n\t"                                              \
+    "s_waitcnt lgkmcnt(8*%[P]-spdnn_k-1)\n\t"                \
+    ".endif\n\t"                                             \
+    "v_fmac_f32 v[80+4*spdnn_p], " W ", v[112+4*(spdnn_k%%4)]\n\t" \
+    "v_fmac_f32 v[81+4*spdnn_p], " W ", v[113+4*(spdnn_k%%4)]\n\t" \
+    "v_fmac_f32 v[82+4*spdnn_p], " W ", v[114+4*(spdnn_k%%4)]\n\t" \
+    "v_fmac_f32 v[83+4*spdnn_p], " W ", v[115+4*(spdnn_k%%4)]\n\t" \
+    ".if spdnn_k+4 < 8*%[P]\n\t"                             \
+    SPDNN_RES_READ("spdnn_k+4")                              \
+    ".endif\n\t"                                             \
+    ".set spdnn_p, spdnn_p+1\n\t"                            \
+    ".set spdnn_k, spdnn_k+1\n\t"                            \
+    ".endr\n\t"
+#define SPDNN_RES_HEAD                                                                                                 \
+    SPDNN_RES_ADDR("0", "c0", "0") SPDNN_RES_ADDR("1", "c0", "1") SPDNN_RES_ADDR("2", "c1", "0") SPDNN_RES_ADDR("3", "c1", "1") \
+    ".set spdnn_k, 0\n\t" SPDNN_RES_READ("0") SPDNN_RES_READ("1") SPDNN_RES_READ("2") SPDNN_RES_READ("3")                 \
+    SPDNN_RES_ADDR("4", "c2", "0") SPDNN_RES_ADDR("5", "c2", "1") SPDNN_RES_ADDR("6", "c3", "0") SPDNN_RES_ADDR("7", "c3", "1")
+#define SPDNN_RES_ASM_U                                                                                                \
+    SPDNN_RES_HEAD SPDNN_RES_CONN("%[w]") SPDNN_RES_CONN("%[w]") SPDNN_RES_CONN("%[w]") SPDNN_RES_CONN("%[w]")           \
+    SPDNN_RES_CONN("%[w]") SPDNN_RES_CONN("%[w]") SPDNN_RES_CONN("%[w]") SPDNN_RES_CONN("%[w]")
+#define SPDNN_RES_ASM_W                                                                                                \
+    SPDNN_RES_HEAD SPDNN_RES_CONN("%[w0]") SPDNN_RES_CONN("%[w1]") SPDNN_RES_CONN("%[w2]") SPDNN_RES_CONN("%[w3]")       \
+    SPDNN_RES_CONN("%[w4]") SPDNN_RES_CONN("%[w5]") SPDNN_RES_CONN("%[w6]") SPDNN_RES_CONN("%[w7]")
+#define SPDNN_RES_ACC1 "+{v[80:83]}"(acc[0])
+#define SPDNN_RES_ACC2 SPDNN_RES_ACC1, "+{v[84:87]}"(acc[1])
+#define SPDNN_RES_ACC3 SPDNN_RES_ACC2, "+{v[88:91]}"(acc[2])
+#define SPDNN_RES_ACC4 SPDNN_RES_ACC3, "+{v[92:95]}"(acc[3])
+#define SPDNN_RES_IN [c0] "v"(codes.x), [c1] "v"(codes.y), [c2] "v"(codes.z), [c3] "v"(codes.w), [s4] "s"(4), [P] "n"(P)
+#define SPDNN_RES_CLOBBER                                                                                            \
+    "v72", "v73", "v74", "v75", "v76", "v77", "v78", "v79", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119",  \
+        "v120", "v121", "v122", "v123", "v124", "v125", "v126", "v127", "memory"
+#define SPDNN_RES_CASE(Q)                                                                                             \
+    if constexpr (P == Q) {                                                                                          \
+        if constexpr (UNI)                                                                                           \
+            asm volatile(SPDNN_RES_ASM_U : SPDNN_RES_ACC##Q : SPDNN_RES_IN, [w] "s"(wu) : SPDNN_RES_CLOBBER);          \
+        else                                                                                                         \
+            asm volatile(SPDNN_RES_ASM_W                                                                              \
+                         : SPDNN_RES_ACC##Q                                                                          \
+                         : SPDNN_RES_IN, [w0] "v"(wa.x), [w1] "v"(wa.y), [w2] "v"(wa.z), [w3] "v"(wa.w), [w4] "v"(wb.x), \
+                           [w5] "v"(wb.y), [w6] "v"(wb.z), [w7] "v"(wb.w)                                              \
+                         : SPDNN_RES_CLOBBER);                                                                       \
+    }
+template <int P, bool UNI>
+__device__ __forceinline__ void res_fma8(f32x4 (&acc)[P], u32x4 codes, float wu, f32x4 wa, f32x4 wb) {
+    SPDNN_RES_CASE(1)
+    SPDNN_RES_CASE(2)
+    SPDNN_RES_CASE(3)
+    SPDNN_RES_CASE(4)
+}
+
+// NB = most groups of 64 neurons a wave owns (output blocks), PM = most planes, UNI = every layer of the network has one
+// weight for all its connections (which then takes a scalar register, and half the bytes).  blockDim.x = 64 * W with W = ceil(U / NB),
+// U = ceil(N / 64) groups of 64 neurons; wave w owns the groups w, w + W, ...  Q = workgroups, each with a run of
+// neighbouring rows; gridDim.x = Q.
+template <int NB, int PM, bool UNI>
+__global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict__ Yin, float* Ymid, float* Yout,
+                                                        uint8_t* __restrict__ flags, RowLists rl, ResidentArgs ra,
+                                                        const float* __restrict__ bias, int N) {
+    // The entry codes are addresses from the start of the workgroup's LDS: everything is dynamic, nothing static.
+    extern __shared__ __align__(16) char res_lds[];
+    using lds_f4 = __attribute__((address_space(3))) f32x4;
+    constexpr uint32_t CH = 256u * PM;  // bytes of a chunk: 16 columns x PM planes
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int T = blockDim.x, W = T >> 6, U = (N + 63) >> 6;
+    const uint32_t misc = res_tile_bytes(N, PM);
+    uint32_t* live_word = reinterpret_cast<uint32_t*>(res_lds + misc);             // [2], raised by the layers in turn
+    int* row_at = reinterpret_cast<int*>(res_lds + misc + 16);                     // [4 * PM] row to copy to or from, per slot; -1: none
+    uint16_t* loc = reinterpret_cast<uint16_t*>(res_lds + misc + 16 + 4 * 4 * 4);  // [kShareRows] rows alive at lmid
+
+    // my rows: r0 .. r0 + nrows - 1 of the list on entry, and of the output
+    const int A = rl.count ? __builtin_amdgcn_readfirstlane(*rl.count) : ra.A;
+    const bool identity = !rl.count;
+    const int groups = (A + kRows - 1) / kRows;
+    const int per = groups / (int)gridDim.x, extra = groups - per * (int)gridDim.x;  // the first `extra` take one more
+    const int wg = blockIdx.x;
+    const int r0 = (wg * per + min(wg, extra)) * kRows;
+    const int nrows = min(A - r0, (per + (wg < extra ? 1 : 0)) * kRows);
+    if (nrows <= 0) return;
+
+    const int nb_w = (U - wave + W - 1) / W;  // my groups of 64 neurons (at least one: W <= U)
+    float bj[NB];  // lanes past the last neuron: minus infinity, which makes their outputs 0
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int j = 64 * (b * W + wave) + lane;
+        bj[b] = j < N ? bias[j] : -__builtin_inff();
+    }
+    {  // waves of one SIMD take turns rather than meet at the LDS all at once (see fused_layer_kernel)
+        const int pw = __builtin_amdgcn_readfirstlane(3 - ((threadIdx.x >> 8) & 3));
+        if (pw == 1) __builtin_amdgcn_s_setprio(1);
+        else if (pw == 2) __builtin_amdgcn_s_setprio(2);
+        else if (pw == 3) __builtin_amdgcn_s_setprio(3);
+    }
+
+    // Connections, fetched ahead: slots a whole group of 64 neurons (4 chunks of 8), weights two chunks.
+    // (Address spaces are spelled out: as generic pointers these loads would wait, and be waited for, with the LDS reads.)
+    u32x4 cbuf[4];
+    f32x4 wbuf[4] = {};
+    using gchar = const __attribute__((address_space(1))) char;
+    using gu32x4 = const __attribute__((address_space(1))) u32x4;
+    using gf32x4 = const __attribute__((address_space(1))) f32x4;
+    using gu32 = const __attribute__((address_space(1))) uint32_t;
+    struct Item {  // a layer's connections of one group of 64 neurons
+        gchar *c, *w;
+    };
+    auto item = [&](const ResidentLayer& d, int b) -> Item {
+        const int u = b * W + wave;
+        const uint32_t at = ((u >> 4) * (kNnz / 8) * kBlk + (u & 15) * 64) * 16;
+        const uint32_t wat = ((u >> 4) * (kNnz / 4) * kBlk + (u & 15) * 64) * 16;
+        return Item{(gchar*)(uintptr_t)d.rel + at, (gchar*)(uintptr_t)d.val + wat};
+    };
+    const uint32_t lane16 = 16u * lane;
+    auto fetch_codes = [&](const Item& it, int c) { cbuf[c] = *(gu32x4*)(it.c + (lane16 + (uint32_t)c * (16 * kBlk))); };
+    auto fetch_weights = [&](const Item& it, int c) {
+        if constexpr (UNI) return;
+        wbuf[2 * (c & 1)] = *(gf32x4*)(it.w + (lane16 + (uint32_t)(2 * c) * (16 * kBlk)));
+        wbuf[2 * (c & 1) + 1] = *(gf32x4*)(it.w + (lane16 + (uint32_t)(2 * c + 1) * (16 * kBlk)));
+    };
+    // The descriptors are constant while the kernel runs: scalar loads.
+    using clayer = const __attribute__((address_space(4))) ResidentLayer;
+    auto layer_at = [&](int l) -> ResidentLayer {
+        clayer* d = (clayer*)(uintptr_t)(ra.layers + l);
+        return ResidentLayer{d->rel, d->val, d->qsel, d->wuni};
+    };
+
+    int nalive = nrows;  // of my rows, on entry to the current run of layers
+    for (int seg = 0; seg < 2; ++seg) {
+        const int la = seg == 0 ? ra.l0 : ra.lmid, lb = seg == 0 ? ra.lmid : ra.l1;
+        if (la >= lb || nalive == 0) continue;
+        const bool last_seg = lb == ra.l1;
+        const float* src = seg == 0 ? Yin : Ymid;
+        float* dst = last_seg ? Yout : Ymid;
+        const ResidentLayer first = layer_at(la);
+        const uint32_t* q_in = first.qsel;
+        const uint32_t* q_out = layer_at(min(lb, ra.L - 1)).qsel;  // any layout does for the last layer's output
+        const int quads = (nalive + kRows - 1) / kRows;
+        const int npass = (quads + PM - 1) / PM;
+        int kept = 0;         // rows alive at the end of the passes so far
+        bool primed = false;  // cbuf / wbuf hold the first group's connections of layer la
+        int i1 = 0;
+        for (int pass = 0; pass < npass; ++pass) {
+            const int i0 = i1;  // this pass: rows i0 .. i1 - 1 of the share (seg 1: of the list of survivors)
+            i1 = min(nalive, (int)(((pass + 1) * quads) / npass) * kRows);
+            const int n0 = i1 - i0;
+            int P = (n0 + kRows - 1) / kRows;
+            uint32_t live = n0 >= 32 ? 0xffffffffu : (1u << n0) - 1u;
+            // lane s (of every wave): number, inside my share, of the row in slot s
+            int rid = lane < n0 ? i0 + lane : 0;
+            if (seg == 1 && lane < n0) rid = loc[i0 + lane];
+            if (tid < kRows * PM) row_at[tid] = tid >= n0 ? -1 : seg == 0 && !identity ? rl.cat[r0 + rid] : r0 + rid;
+            if (seg == 0 && tid < n0) flags[r0 + rid] = 0;  // wave 0, like every other store to the flags
+            if (tid < 2) live_word[tid] = 0u;
+            if (!primed) {
+                const Item it = item(first, 0);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) fetch_codes(it, c);
+                fetch_weights(it, 0);
+                fetch_weights(it, 1);
+            }
+            __syncthreads();  // also: the pass before has left the tile
+            const int n4 = N >> 2;
+            for (int e = tid; e < P * n4; e += T) {  // 4 rows x 4 columns per turn
+                const int p = e / n4, t = e - p * n4;
+                const int4 at = *reinterpret_cast<const int4*>(row_at + 4 * p);
+                const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+                const size_t col = (size_t)t * 4;
+                const f32x4 a0 = *reinterpret_cast<const f32x4*>(src + (size_t)at.x * N + col);
+                const f32x4 a1 = at.y < 0 ? zero : *reinterpret_cast<const f32x4*>(src + (size_t)at.y * N + col);
+                const f32x4 a2 = at.z < 0 ? zero : *reinterpret_cast<const f32x4*>(src + (size_t)at.z * N + col);
+                const f32x4 a3 = at.w < 0 ? zero : *reinterpret_cast<const f32x4*>(src + (size_t)at.w * N + col);
+                const uint32_t qp = q_in[t];
+                const uint32_t base = (store_group((uint32_t)t * 4u)) * CH + 256u * p;
+                *reinterpret_cast<lds_f4*>(base + (qp & 0xffu)) = f32x4{a0.x, a1.x, a2.x, a3.x};
+                *reinterpret_cast<lds_f4*>(base + CH + ((qp >> 8) & 0xffu)) = f32x4{a0.y, a1.y, a2.y, a3.y};
+                *reinterpret_cast<lds_f4*>(base + 2u * CH + ((qp >> 16) & 0xffu)) = f32x4{a0.z, a1.z, a2.z, a3.z};
+                *reinterpret_cast<lds_f4*>(base + 3u * CH + (qp >> 24)) = f32x4{a0.w, a1.w, a2.w, a3.w};
+            }
+            __syncthreads();
+
+            // Layers l .. as long as PP planes are needed: a loop of its own for every number of planes.
+            int l = la;
+            auto layers = [&](auto Ptag) {
+                constexpr int PP = decltype(Ptag)::value;
+                while (l < lb && P == PP) {
+                    const ResidentLayer cur = layer_at(l);
+                    // after the last layer comes, for the connections, the next pass's first
+                    const ResidentLayer nxt = layer_at(l + 1 < lb ? l + 1 : la);
+                    gu32* q_next = (gu32*)(uintptr_t)(l + 1 < lb ? nxt.qsel : q_out);
+                    uint32_t at[NB];  // where my neurons' outputs go
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) at[b] = q_next[min(64 * (b * W + wave) + lane, N - 1) >> 2];
+                    f32x4 res[NB][PP];
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+#pragma unroll
+                        for (int p = 0; p < PP; ++p) res[b][p] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        if (b < nb_w) {
+                            f32x4 acc[PP];
+#pragma unroll
+                            for (int p = 0; p < PP; ++p) acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+                            const Item mine = item(cur, b);
+                            const Item next = b + 1 < nb_w ? item(cur, b + 1) : item(nxt, 0);
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) {
+                                res_fma8<PP, UNI>(acc, cbuf[c], cur.wuni, wbuf[2 * (c & 1)], wbuf[2 * (c & 1) + 1]);
+                                fetch_codes(next, c);
+                                if (c < 2) fetch_weights(mine, c + 2);
+                                else fetch_weights(next, c - 2);
+                                if (b == 0 && c == 0) {
+#pragma unroll
+                                    for (int i = 0; i < NB; ++i) {
+                                        const int j = 64 * (i * W + wave) + lane;
+                                        at[i] = store_group((uint32_t)j) * CH + ((at[i] >> (8 * (j & 3))) & 0xffu);
+                                    }
+                                }
+                            }
+#pragma unroll
+                            for (int p = 0; p < PP; ++p)
+#pragma unroll
+                                for (int r = 0; r < kRows; ++r) res[b][p][r] = fminf(fmaxf(acc[p][r] + bj[b], 0.0f), kClip);
+                        }
+                    }
+                    // which rows have a positive output in my neurons
+                    uint32_t pos = 0;
+#pragma unroll
+                    for (int p = 0; p < PP; ++p)
+#pragma unroll
+                        for (int r = 0; r < kRows; ++r) {
+                            float m = res[0][p][r];
+#pragma unroll
+                            for (int b = 1; b < NB; ++b) m = fmaxf(m, res[b][p][r]);
+                            if (__builtin_amdgcn_ballot_w64(m > 0.0f) != 0ull) pos |= 1u << (kRows * p + r);
+                        }
+                    if (lane == 0 && pos) atomicOr(&live_word[l & 1], pos);
+                    __syncthreads();  // every wave has read what it needs of the rows
+                    live &= __builtin_amdgcn_readfirstlane(live_word[l & 1]);
+                    if (tid == 0) live_word[(l + 1) & 1] = 0u;
+                    const int n = __popc(live);
+                    P = (n + kRows - 1) / kRows;
+                    if (P == PP) {
+#pragma unroll
+                        for (int b = 0; b < NB; ++b) {
+                            const int j = 64 * (b * W + wave) + lane;
+                            if (j < N)
+#pragma unroll
+                                for (int p = 0; p < PP; ++p) *reinterpret_cast<lds_f4*>(at[b] + 256u * p) = res[b][p];
+                        }
+                    } else if (n > 0) {  // fewer planes will do: the survivors move together
+                        using lds_f = __attribute__((address_space(3))) float;
+#pragma unroll
+                        for (int b = 0; b < NB; ++b) {
+                            const int j = 64 * (b * W + wave) + lane;
+                            if (j < N) {
+#pragma unroll
+                                for (int s = 0; s < kRows * PP; ++s)
+                                    if ((live >> s) & 1u) {
+                                        const int to = __popc(live & ((1u << s) - 1u));
+                                        *reinterpret_cast<lds_f*>(at[b] + 256u * (to >> 2) + 4u * (to & 3)) = res[b][s >> 2][s & 3];
+                                    }
+                                for (int s = n; s < kRows * P; ++s) *reinterpret_cast<lds_f*>(at[b] + 256u * (s >> 2) + 4u * (s & 3)) = 0.0f;
+                            }
+                        }
+                        // slot s now holds what the s-th live slot held
+                        int from = 0;
+                        for (uint32_t rest = live, k = 0; rest; rest &= rest - 1u, ++k)
+                            if (lane == (int)k) from = __builtin_ctz(rest);
+                        rid = __shfl(rid, from, 64);
+                        live = n >= 32 ? 0xffffffffu : (1u << n) - 1u;
+                    }
+                    __syncthreads();
+                    if (tid == 0 && n > 0 && ra.layer_rows) atomicAdd(&ra.layer_rows[l + 1], n);
+                    ++l;
+                }
+            };
+            if constexpr (PM >= 4) {
+                layers(std::integral_constant<int, 4>{});
+                layers(std::integral_constant<int, 3>{});
+            }
+            layers(std::integral_constant<int, 2>{});
+            layers(std::integral_constant<int, 1>{});
+            primed = live != 0u;
+            if (!live) continue;
+
+            // the survivors' rows go to memory, under the slots they came with
+            if (tid < kRows * PM) row_at[tid] = (live >> tid) & 1u ? r0 + rid : -1;
+            if (wave == 0 && lane < 32 && ((live >> lane) & 1u)) {
+                if (last_seg) flags[r0 + rid] = 1;
+                else loc[kept + __popc(live & ((1u << lane) - 1u))] = (uint16_t)rid;
+            }
+            kept += __popc(live);
+            __syncthreads();
+            for (int e = tid; e < P * n4; e += T) {
+                const int p = e / n4, t = e - p * n4;
+                const int4 at = *reinterpret_cast<const int4*>(row_at + 4 * p);
+                const size_t col = (size_t)t * 4;
+                const uint32_t qp = q_out[t];
+                const uint32_t base = (store_group((uint32_t)t * 4u)) * CH + 256u * p;
+                const f32x4 c0 = *reinterpret_cast<const lds_f4*>(base + (qp & 0xffu));
+                const f32x4 c1 = *reinterpret_cast<const lds_f4*>(base + CH + ((qp >> 8) & 0xffu));
+                const f32x4 c2 = *reinterpret_cast<const lds_f4*>(base + 2u * CH + ((qp >> 16) & 0xffu));
+                const f32x4 c3 = *reinterpret_cast<const lds_f4*>(base + 3u * CH + (qp >> 24));
+                if (at.x >= 0) *reinterpret_cast<f32x4*>(dst + (size_t)at.x * N + col) = f32x4{c0.x, c1.x, c2.x, c3.x};
+                if (at.y >= 0) *reinterpret_cast<f32x4*>(dst + (size_t)at.y * N + col) = f32x4{c0.y, c1.y, c2.y, c3.y};
+                if (at.z >= 0) *reinterpret_cast<f32x4*>(dst + (size_t)at.z * N + col) = f32x4{c0.z, c1.z, c2.z, c3.z};
+                if (at.w >= 0) *reinterpret_cast<f32x4*>(dst + (size_t)at.w * N + col) = f32x4{c0.w, c1.w, c2.w, c3.w};
+            }
+            __syncthreads();  // row_at is free for the next pass
+        }
+        nalive = kept;
+        __syncthreads();
+    }
+}
+
+}  // namespace spdnn

@@ -1,0 +1,60 @@
+"""Networks of at most 4096 neurons: the rows stay in LDS from layer to layer (resident_kernel).  One case per shape the
+kernel takes -- one to four output blocks, ragged last blocks, one weight or many, a share of one quad of rows, of one
+pass, of several passes, batches that are compacted between launches -- with rows that die on the way, so that passes
+lose planes and rows move together.  Checked against the oracle: survivors, values, and rows alive on entry to every layer."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from parity_util import check_against_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N,batch,L,uniform", [
+    (32, 9000, 5, False),     # one group of 64 lanes, half of them without a neuron
+    (100, 36000, 4, True),    # small rows, several workgroups per CU; more rows than one launch takes
+    (1000, 4100, 6, False),   # last group ragged; two launches' worth of passes in one launch
+    (1024, 1021, 7, True),    # one quad of rows per workgroup, a wave per group of 64 neurons
+    (1024, 9001, 7, False),   # two groups per wave, several passes per share
+    (1028, 3000, 4, True),    # a second block of four neurons
+    (1500, 1100, 4, False),
+    (2048, 5000, 4, True),    # four planes
+    (2052, 1500, 3, False),   # three blocks: two planes
+    (3072, 2500, 3, True),
+    (4092, 700, 3, False),
+    (4096, 2100, 4, True),    # eight rows per pass, two launches
+    (4096, 2600, 11, False),  # ... and three
+])
+def test_rows_stay_on_chip_through_the_layers(N, batch, L, uniform):
+    import torch
+    import paper_2007_14152_amd as sp
+    rng = np.random.default_rng(N + batch + L)
+    idx = [np.sort(rng.integers(0, N, size=(N, 32)), axis=1).astype(np.int32) for _ in range(L)]
+    val = [np.full((N, 32), 0.0625, np.float32) if uniform else rng.uniform(0.02, 0.11, size=(N, 32)).astype(np.float32)
+           for _ in range(L)]
+    bias = -rng.uniform(0.0, 0.5, size=N).astype(np.float32)
+    Y0 = synth.gen_y0(batch, N, 23, density="mixed")
+    Y0[3] = 0
+    sample = batch if batch <= 3000 else 1500   # the oracle on the first rows and the last
+    ids = np.arange(batch) if sample == batch else np.r_[0:sample // 2, batch - sample // 2:batch]
+    ref = oracle.infer(idx, val, bias, Y0[ids])
+    m = sp.Model(idx, val, bias)
+    m.set_profiling(True)
+    n, rows, Y = m.infer(torch.from_numpy(Y0).to("cuda:0"))
+    run, rows_in, ms = m.profile()
+    m.close()
+    rows, Y = rows.cpu().numpy(), Y.cpu().numpy()
+    assert n == len(rows) and 0 < n < batch and np.all(np.diff(rows) > 0)
+    mine = np.isin(rows, ids)
+    common, _ = check_against_oracle(ref, int(mine.sum()), rows[mine], Y[mine], row_ids=ids, what="N=%d" % N)
+    assert common > 0
+    assert run == L and int(rows_in[0]) == batch and np.all(np.diff(rows_in[:L]) <= 0) and int(rows_in[L - 1]) >= n
+    if sample == batch and not (ref.fragile_layer >= 0).any():
+        assert [int(x) for x in rows_in[:L]] == [int(x) for x in ref.active_per_layer[:L]]
+    # the same call without the measurement: same bits
+    m = sp.Model(idx, val, bias)
+    n2, rows2, Y2 = m.infer(torch.from_numpy(Y0).to("cuda:0"))
+    m.close()
+    assert n2 == n and np.array_equal(rows2.cpu().numpy(), rows) and np.array_equal(Y2.cpu().numpy(), Y)

@@ -112,7 +112,9 @@ int spdnn_create(spdnn_t* out, int32_t N, int32_t L, const int32_t* const* idx,
  * III-A-3, per wave), and the lanes' sums are added inside the workgroup before bias and ReLU.
  * Such a layer runs as up to P launches, P = ceil(K/32) rounded up to a power of two, each of
  * which computes the outputs of a share of the neurons and takes one layer's room in the
- * weights arena; P is what is called the layer's passes here.
+ * weights arena; P is what is called the layer's passes here.  (Models of at most 4096 neurons do without the launches:
+ * the neurons are sorted by length and a lane keeps its neuron, 32 connections after 32; the passes then only say how
+ * much room a layer takes.)
  *
  * spdnn_csr_passes: passes[l] (host, may be NULL) = passes of layer l, *total = their sum,
  * which is the "L" to size the weights arena with (spdnn_weights_bytes(N, *total, ...)); if

@@ -97,7 +97,8 @@ struct spdnn_model {
     // pass each
     const spdnn::ResidentLayer* res_layers = nullptr;  // device copy of the layers' descriptors (NULL: not possible)
     int* res_rows = nullptr;                           // device, L + 1 counters
-    bool res_uniform = false;                          // every layer has one weight for all its connections
+    int res_mode = spdnn::kResWeights;
+    uint32_t res_part_stride = 0;                      // kResParts
     // out-of-core weights: pass p's block lives in host memory and is copied into device slot p & 1
     const char* ooc_host = nullptr;
     char* ooc_slot[2] = {nullptr, nullptr};
@@ -223,10 +224,13 @@ hipError_t allow_big_lds() {
 }
 template <int NB, int PM>
 hipError_t allow_resident_lds(int bytes) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::resident_kernel<NB, PM, false>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    return e != hipSuccess ? e : hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::resident_kernel<NB, PM, true>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    for (const void* f : {reinterpret_cast<const void*>(&spdnn::resident_kernel<NB, PM, spdnn::kResWeights>),
+                          reinterpret_cast<const void*>(&spdnn::resident_kernel<NB, PM, spdnn::kResUniform>),
+                          reinterpret_cast<const void*>(&spdnn::resident_kernel<NB, PM, spdnn::kResParts>)}) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // The fused kernels and set-up kernels use more dynamic LDS than the default limit allows.
@@ -261,7 +265,7 @@ int allow_large_lds() {
                                 hipFuncAttributeMaxDynamicSharedMemorySize, tile_lds));
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::balance_kernel<4>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(spdnn::BalanceScratch<4>)));
-    const int res_lds = (int)spdnn::res_tile_bytes(spdnn::kCap, 2) + spdnn::kResMiscBytes;
+    const int res_lds = (int)spdnn::res_tile_bytes(spdnn::kCap, 2) + spdnn::kResMiscBytes + 4 * spdnn::kCap;
     HIP_TRY((allow_resident_lds<1, 4>(res_lds)));
     HIP_TRY((allow_resident_lds<2, 4>(res_lds)));
     HIP_TRY((allow_resident_lds<4, 2>(res_lds)));
@@ -326,6 +330,11 @@ int scan_csr(int32_t N, int32_t L, const int32_t* const* ptr, void* scratch_dev,
     }
     return SPDNN_OK;
 }
+
+// resident_kernel: the most groups of 64 neurons a wave owns -- one if there is at most a quad of rows per CU and
+// sixteen waves can own all there are -- and the workgroup's waves.
+int resident_groups_per_wave(int32_t nblk, bool few_rows) { return nblk > 2 ? 4 : nblk == 1 && few_rows ? 1 : 2; }
+int resident_waves(int32_t N, int nb) { return ((N + 63) / 64 + nb - 1) / nb; }
 
 // Set-up shared by spdnn_create (ptr == NULL: every layer is [N][32]) and spdnn_create_csr
 // (device arrays; layer l is cut into passes_of[l] passes of 32 connections per neuron).
@@ -528,6 +537,17 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
         }
     }
 
+    // General layers of a network that resident_kernel takes, not all of them of exactly 32 connections per neuron:
+    // neurons by length (kResParts).
+    bool parts = false;
+    std::vector<int32_t> hp((size_t)N + 1);
+    if (ptr && N <= spdnn::kCap)
+        for (int32_t ll = 0; ll < L && !parts; ++ll) {
+            HIP_TRY(hipMemcpyAsync(hp.data(), ptr[ll], sizeof(int32_t) * hp.size(), hipMemcpyDeviceToHost, stream));
+            HIP_TRY(hipStreamSynchronize(stream));
+            for (int32_t j = 0; j < N && !parts; ++j) parts = hp[j + 1] - hp[j] != spdnn::kNnz;
+        }
+
     const size_t raw = (size_t)N * spdnn::kNnz;
     std::vector<int2> hw((size_t)P * nblk);
     std::vector<int2> virt_ranges;  // several lanes per neuron: {first neuron, neurons} of the current layer's workgroups
@@ -539,6 +559,56 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
         const float* dv = val[ll];
         LayerDesc& d = m->layers[l];
         d.multi = passes_of[ll] > 1;
+        if (parts) {
+            const int32_t r = round_of[l], first = l - r;  // the layer's tables are under its first pass
+            uint16_t* perm_dev = const_cast<uint16_t*>(m->layers[first].virt.slot);
+            const int nlanes = nblk * spdnn::kBlk;
+            if (r == 0) {
+                HIP_TRY(hipMemcpyAsync(hp.data(), ptr[ll], sizeof(int32_t) * hp.size(), hipMemcpyDeviceToHost, stream));
+                HIP_TRY(hipStreamSynchronize(stream));
+                std::vector<uint16_t> perm;
+                std::vector<uint32_t> nch;
+                spdnn::order_by_length(hp.data(), N, nlanes, resident_waves(N, resident_groups_per_wave(nblk, false)), perm, nch);
+                HIP_TRY(hipMemcpyAsync(perm_dev, perm.data(), sizeof(uint16_t) * perm.size(), hipMemcpyHostToDevice, stream));
+                HIP_TRY(hipMemcpyAsync(const_cast<uint32_t*>(d.virt.fin), nch.data(), sizeof(uint32_t) * nch.size(), hipMemcpyHostToDevice, stream));
+                HIP_TRY(hipStreamSynchronize(stream));  // both go out of scope
+            }
+            spdnn::csr_part_kernel<<<(unsigned)((size_t)nlanes * spdnn::kNnz / 256), 256, 0, stream>>>(ptr[ll], idx[ll], val[ll], perm_dev, nlanes, r,
+                                                                                                 st_idx, st_val, st_len);
+            int* widest_dev = err_dev + 1 + P + l;
+            int* pair_dev = err_dev + 1 + 3 * P + 2 * l;
+            spdnn::block_window_kernel<<<nblk, spdnn::kBlk, 0, stream>>>(st_idx, N, win_dev[l], err_dev, widest_dev, st_val,
+                                                                         err_dev + 1 + 2 * P + l, nlanes);
+            spdnn::whole_row_window_kernel<<<1, 64, 0, stream>>>(win_dev[l], nblk, N, widest_dev);
+            d.w.planes_log2 = spdnn::res_planes_log2(nblk);
+            int pair_info[2] = {0, 0};
+            if (r == 0) {
+                if (!d.multi) {  // what a layer of at most 32 connections reports as its kernel
+                    spdnn::pair_merge_kernel<<<1, 64, 0, stream>>>(win_dev[l], nblk, N, st_val, err_dev + 1 + 2 * P + l, widest_dev, pair_dev);
+                    HIP_TRY(hipMemcpyAsync(pair_info, pair_dev, sizeof(pair_info), hipMemcpyDeviceToHost, stream));
+                    HIP_TRY(hipStreamSynchronize(stream));
+                }
+                // the tile layout, balanced for every neuron's first 32 connections
+                uint32_t* qsel = const_cast<uint32_t*>(d.w.qsel);
+                if (nblk > 2)
+                    spdnn::balance_kernel<4><<<1, spdnn::kBalanceThreads, sizeof(spdnn::BalanceScratch<4>), stream>>>(
+                        st_idx, N, win_dev[l], widest_dev, slot_tab, qsel, nlanes, st_len);
+                else if (nblk == 2)
+                    spdnn::balance_kernel<2><<<1, spdnn::kBalanceThreads, sizeof(spdnn::BalanceScratch<2>), stream>>>(
+                        st_idx, N, win_dev[l], widest_dev, slot_tab, qsel, nlanes, st_len);
+                else
+                    spdnn::balance_kernel<1><<<1, spdnn::kBalanceThreads, sizeof(spdnn::BalanceScratch<1>), stream>>>(
+                        st_idx, N, win_dev[l], widest_dev, slot_tab, qsel, nlanes, st_len);
+            }
+            spdnn::order_pack_kernel<<<nblk * spdnn::kOrderThreads, spdnn::kOrderPackThreads, 0, stream>>>(
+                st_idx, st_val, N, win_dev[l], widest_dev, slot_tab, nblk, d.w.planes_log2, const_cast<uint16_t*>(d.w.rel),
+                const_cast<float*>(d.w.val), nlanes, st_len);
+            HIP_TRY(hipGetLastError());
+            d.mode = pair_info[0] == 1 ? kPair : kSingle;
+            d.lds_cols = N;
+            d.virt_lanes = passes_of[ll];
+            continue;
+        }
         int nrows = -1;                 // rows of di / dv if not N
         const uint8_t* lens = nullptr;  // connections per row if not 32
         if (ptr && d.multi) {
@@ -548,7 +618,6 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
             // are cut into launches of nblk; launch r is pass r.  Their lanes are set up like the neurons of a
             // fixed-32 layer.
             if (round_of[l] == 0) {
-                std::vector<int32_t> hp((size_t)N + 1);
                 std::vector<int2> qw((size_t)N / 4);  // columns of every four neurons (the staging area as scratch)
                 int2* qw_dev = reinterpret_cast<int2*>(st_idx);
                 spdnn::csr_quartet_window_kernel<<<(N / 4 + 255) / 256, 256, 0, stream>>>(ptr[ll], idx[ll], N, qw_dev);
@@ -810,26 +879,27 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
     if (herr[0]) return fail(SPDNN_EINVAL, "a column index is outside [0, N)");
     for (int32_t l = 0; l < P; ++l)
         if ((m->layers[l].mode == kWide || m->layers[l].mode == kWidePair) && herr[1 + l]) m->layers[l].mode = kStaged;
-    // Rows of at most one LDS stage and nothing but layers of one pass each: the rows can stay in LDS from layer to
-    // layer (resident_kernel, which takes the layers' descriptors from device memory).
-    if (N <= spdnn::kCap && !ooc && P == L) {
-        std::vector<int> differ((size_t)L);  // layers with more than one weight value
-        std::vector<int> info(2 * (size_t)L);
-        HIP_TRY(hipMemcpyAsync(differ.data(), err_dev + 1 + 2 * P, sizeof(int) * (size_t)L, hipMemcpyDeviceToHost, stream));
-        HIP_TRY(hipMemcpyAsync(info.data(), err_dev + 1 + 3 * P, sizeof(int) * 2 * (size_t)L, hipMemcpyDeviceToHost, stream));
+    // Rows of at most one LDS stage: they can stay in LDS from layer to layer (resident_kernel, which takes the layers'
+    // descriptors from device memory).
+    if (N <= spdnn::kCap && !ooc) {
+        std::vector<int> differ((size_t)P);  // passes with more than one weight value
+        std::vector<int> info(2 * (size_t)P);
+        HIP_TRY(hipMemcpyAsync(differ.data(), err_dev + 1 + 2 * P, sizeof(int) * (size_t)P, hipMemcpyDeviceToHost, stream));
+        HIP_TRY(hipMemcpyAsync(info.data(), err_dev + 1 + 3 * P, sizeof(int) * 2 * (size_t)P, hipMemcpyDeviceToHost, stream));
         HIP_TRY(hipStreamSynchronize(stream));
         std::vector<spdnn::ResidentLayer> rl((size_t)L);
-        m->res_uniform = true;
+        m->res_mode = parts ? spdnn::kResParts : spdnn::kResUniform;
         for (int32_t l = 0; l < L; ++l) {
-            const spdnn::LayerWeights& w = m->layers[l].w;
-            rl[l] = spdnn::ResidentLayer{w.rel, w.val, w.qsel, 0.0f};
-            m->res_uniform = m->res_uniform && !differ[l];
-            std::memcpy(&rl[l].wuni, &info[2 * (size_t)l + 1], sizeof(float));
+            const LayerDesc& d = m->layers[first_pass[l]];
+            rl[l] = spdnn::ResidentLayer{d.w.rel, d.w.val, d.w.qsel, 0.0f, d.virt.slot, d.virt.fin};
+            std::memcpy(&rl[l].wuni, &info[2 * (size_t)first_pass[l] + 1], sizeof(float));
+            if (!parts && differ[first_pass[l]]) m->res_mode = spdnn::kResWeights;
         }
         HIP_TRY(hipMemcpyAsync(res_layers_dev, rl.data(), sizeof(spdnn::ResidentLayer) * (size_t)L, hipMemcpyHostToDevice, stream));
         HIP_TRY(hipStreamSynchronize(stream));
         m->res_layers = res_layers_dev;
         m->res_rows = res_rows_dev;
+        m->res_part_stride = (uint32_t)blk_bytes;
     }
     guard.m = nullptr;
     *out = m;
@@ -895,10 +965,10 @@ struct ResidentShape {
 ResidentShape resident_shape(const spdnn_model* h, int32_t rows) {
     ResidentShape r;
     r.planes = 1 << spdnn::res_planes_log2(h->nblk);
-    r.nb = h->nblk > 2 ? 4 : h->nblk == 1 && rows <= spdnn::kRows * h->num_cu ? 1 : 2;
-    const int groups = (h->N + 63) / 64, waves = (groups + r.nb - 1) / r.nb;
+    r.nb = resident_groups_per_wave(h->nblk, rows <= spdnn::kRows * h->num_cu);
+    const int waves = resident_waves(h->N, r.nb);
     r.threads = 64 * waves;
-    r.lds = (int)spdnn::res_tile_bytes(h->N, r.planes) + spdnn::kResMiscBytes;
+    r.lds = (int)spdnn::res_tile_bytes(h->N, r.planes) + spdnn::kResMiscBytes + (h->res_mode == spdnn::kResParts ? 4 * h->N : 0);
     r.slots = h->num_cu * std::max(1, std::min(16 / waves, 160 * 1024 / r.lds));
     return r;
 }
@@ -915,17 +985,18 @@ bool one_launch(spdnn_t h, int32_t batch) {
 
 hipError_t launch_resident(spdnn_t h, const ResidentShape& r, int32_t Q, const float* Yin, float* Ymid, float* Yout, uint8_t* flags,
                            const spdnn::RowLists& rl, const spdnn::ResidentArgs& ra) {
-    const auto run = [&](auto nb, auto planes, auto uni) {
-        spdnn::resident_kernel<decltype(nb)::value, decltype(planes)::value, decltype(uni)::value>
+    const auto run = [&](auto nb, auto planes, auto mode) {
+        spdnn::resident_kernel<decltype(nb)::value, decltype(planes)::value, decltype(mode)::value>
             <<<Q, r.threads, r.lds, h->stream>>>(Yin, Ymid, Yout, flags, rl, ra, h->bias_dev, h->N);
     };
-    const auto run_uni = [&](auto nb, auto planes) {
-        if (h->res_uniform) run(nb, planes, std::true_type{});
-        else run(nb, planes, std::false_type{});
+    const auto run_mode = [&](auto nb, auto planes) {
+        if (h->res_mode == spdnn::kResUniform) run(nb, planes, std::integral_constant<int, spdnn::kResUniform>{});
+        else if (h->res_mode == spdnn::kResParts) run(nb, planes, std::integral_constant<int, spdnn::kResParts>{});
+        else run(nb, planes, std::integral_constant<int, spdnn::kResWeights>{});
     };
-    if (r.nb == 1) run_uni(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
-    else if (r.nb == 2) run_uni(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
-    else run_uni(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{});
+    if (r.nb == 1) run_mode(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
+    else if (r.nb == 2) run_mode(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+    else run_mode(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{});
     return hipGetLastError();
 }
 
@@ -1017,7 +1088,7 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
         const int32_t groups = (alive + spdnn::kRows - 1) / spdnn::kRows;
         const int32_t Q = std::min(groups, shape.slots);
         const bool several = (groups + Q - 1) / Q > shape.planes;
-        const spdnn::ResidentArgs ra{h->res_layers, l0, one && several ? std::min(l0 + 2, l1) : l1, l1, L, batch, layer_rows};
+        const spdnn::ResidentArgs ra{h->res_layers, l0, one && several ? std::min(l0 + 2, l1) : l1, l1, L, batch, h->res_part_stride, layer_rows};
         if (h->profiling) HIP_TRY(hipEventRecord(h->t0[l0], s));
         HIP_TRY(launch_resident(h, shape, Q, k == 0 ? Y0_dev : wv.Y[(k + 1) & 1], wv.Y[(k + 1) & 1], wv.Y[k & 1], wv.flags[0], rl, ra));
         if (h->profiling) HIP_TRY(hipEventRecord(h->t1[l0], s));

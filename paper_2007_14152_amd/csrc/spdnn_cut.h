@@ -102,4 +102,30 @@ inline std::vector<NeuronRange> cut_workgroups(const int32_t* hp, const int* qw,
     return out;
 }
 
+// The neurons of a general layer by length, for resident_kernel: perm[lane] = neuron, 0xFFFF past the last one; longest
+// first, neighbours first among equals; nch[g] = chunks of 8 connections of the longest neuron of lanes 64g .. 64g+63.
+// Wave w of `waves` takes the groups w, waves + w, 2 waves + w, ...: every second run of `waves` groups goes the other way
+// round, so that the wave with the longest neurons of one run has the shortest of the next.
+inline void order_by_length(const int32_t* hp, int32_t N, int32_t nlanes, int waves, std::vector<uint16_t>& perm,
+                            std::vector<uint32_t>& nch) {
+    std::vector<uint16_t> by(N);
+    for (int32_t j = 0; j < N; ++j) by[j] = (uint16_t)j;
+    std::stable_sort(by.begin(), by.end(), [&](uint16_t a, uint16_t b) { return hp[a + 1] - hp[a] > hp[b + 1] - hp[b]; });
+    const bool even = hp[by[0] + 1] - hp[by[0]] == hp[by[N - 1] + 1] - hp[by[N - 1]];  // all of one length: left in place
+    const int32_t groups = N / 64;  // full groups of 64 lanes; a ragged last one stays where it is
+    perm.assign((size_t)nlanes, 0xFFFF);
+    for (int32_t i = 0; i < N; ++i) {
+        int32_t g = i / 64;
+        const int32_t run = g / waves, lo = run * waves, hi = std::min(lo + waves, groups);
+        if (!even && g < groups && (run & 1)) g = lo + hi - 1 - g;
+        perm[(size_t)g * 64 + i % 64] = by[i];
+    }
+    nch.assign((size_t)nlanes / 64, 0u);
+    for (int32_t i = 0; i < nlanes; ++i)
+        if (perm[i] != 0xFFFF) {
+            const uint32_t k = (uint32_t)(hp[perm[i] + 1] - hp[perm[i]]);
+            nch[i / 64] = std::max(nch[i / 64], (k + 7) / 8);
+        }
+}
+
 }  // namespace spdnn

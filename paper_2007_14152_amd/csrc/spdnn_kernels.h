@@ -2101,6 +2101,22 @@ __global__ void csr_round_kernel(const int32_t* __restrict__ ptr, const int32_t*
     }
 }
 
+// Connections 32 part .. 32 part + 31 of a general layer's neurons, lane by lane (perm: the lane's neuron, 0xFFFF: none),
+// as a fixed-32 layer of nlanes rows: out_idx / out_val [nlanes][32], padded with weight 0, out_len the number that counts.
+__global__ void csr_part_kernel(const int32_t* __restrict__ ptr, const int32_t* __restrict__ idx, const float* __restrict__ val,
+                                const uint16_t* __restrict__ perm, int nlanes, int part, int32_t* __restrict__ out_idx,
+                                float* __restrict__ out_val, uint8_t* __restrict__ out_len) {
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = e >> 5, k = e & 31;
+    if (i >= nlanes) return;
+    const int j = perm[i];
+    const int a = j == 0xFFFF ? 0 : ptr[j] + part * kNnz;
+    const int n = j == 0xFFFF ? 0 : max(0, min(ptr[j + 1] - a, kNnz));
+    out_idx[e] = k < n ? idx[a + k] : 0;
+    out_val[e] = k < n ? val[a + k] : 0.0f;
+    if (k == 0) out_len[i] = (uint8_t)n;
+}
+
 // Smallest and largest column of every four neighbouring neurons of a general layer ({N, -1}: no connection):
 // what the host packs the workgroups of a several-lanes-per-neuron layer by.
 __global__ void csr_quartet_window_kernel(const int32_t* __restrict__ ptr, const int32_t* __restrict__ idx, int N,
@@ -2278,7 +2294,8 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const int32_t*
                                                                   const int* __restrict__ widest,
                                                                   uint16_t* __restrict__ slot_tab,
                                                                   uint32_t* __restrict__ qsel,
-                                                                  int nrows = -1) {  // rows of idx, if not N
+                                                                  int nrows = -1,    // rows of idx, if not N
+                                                                  const uint8_t* __restrict__ len = nullptr) {  // entries of a row that count
     extern __shared__ __align__(16) char balance_scratch[];
     BalanceScratch<UB>& B = *reinterpret_cast<BalanceScratch<UB>*>(balance_scratch);
     if (*widest > kCap) return;
@@ -2292,6 +2309,7 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const int32_t*
     auto rel_of = [&](int e) -> int {
         const int j = b * kBlk + (e >> 5);
         if (j >= (nrows < 0 ? N : nrows)) return -1;
+        if (len && (e & 31) >= len[j]) return -1;
         const int c = idx[(size_t)j * kNnz + (e & 31)];
         return (c < 0 || c >= N) ? 0 : win_rel(c, c_lo, N);  // out-of-range columns were reported; keep them harmless
     };

@@ -94,4 +94,15 @@ int spdnn_cut_workgroups_host(const int32_t* ptr, const int32_t* qw, int N, int 
     return (int)cut.size();
 }
 
+// Neurons by length (spdnn_cut.h).  perm: nlanes entries, nch: nlanes / 64.
+void spdnn_order_by_length_host(const int32_t* ptr, int N, int nlanes, int waves, uint16_t* perm, uint32_t* nch) {
+    std::vector<uint16_t> p;
+    std::vector<uint32_t> c;
+    spdnn::order_by_length(ptr, N, nlanes, waves, p, c);
+    std::copy(p.begin(), p.end(), perm);
+    std::copy(c.begin(), c.end(), nch);
+}
+uint32_t spdnn_res_code_host(uint32_t slot, int planes_log2) { return spdnn::res_code(slot, planes_log2); }
+uint32_t spdnn_res_slot_host(uint32_t code, int planes_log2) { return spdnn::res_slot(code, planes_log2); }
+
 }  // extern "C"

@@ -24,7 +24,8 @@
 // connections, 768 KB per layer and pass, which a CU pulls out of L2 at 25 bytes per clock.  One workgroup on its own:
 // latency.  The copies between LDS and memory happen once per launch instead of once per layer.
 // Whole passes, one launch per layer -> this kernel: 1000 rows x 120 layers of 1024 neurons 0.85 -> 0.28 ms, 60 000 rows
-// 7.40 -> 5.12; 4096 neurons, 24 layers, 60 000 rows 5.82 -> 5.19; 10 007 rows, 12 layers with weights of their own
+// 7.40 -> 5.12; neurons of 16 to 64 connections, 4096 of them, 6 layers, 10 000 rows 1.26 -> 0.75 (several lanes per
+// neuron and two launches per layer before), 0 to 40 connections, 1500 neurons, 12 layers, 777 rows 309 -> 87 us; 4096 neurons, 24 layers, 60 000 rows 5.82 -> 5.19; 10 007 rows, 12 layers with weights of their own
 // 1.19 -> 0.95; one row, 12 layers of 1024 neurons 133 -> 67 us.
 //
 // Workgroups.  Networks of one block whose rows are more than a quad per CU run two workgroups per CU of eight waves
@@ -41,13 +42,23 @@ struct ResidentLayer {   // one layer, in device memory
     const uint16_t* rel;   // LayerWeights::rel, slots as entry codes (res_code)
     const float* val;
     const uint32_t* qsel;  // quads of the columns of this layer's input (LayerWeights::qsel, block 0: all blocks share it)
-    float wuni;            // the layer's weight, if all layers of the network have only one
+    float wuni;            // kResUniform: the layer's weight
+    // kResParts:
+    const uint16_t* perm;  // neuron of every lane (64 to a group), 0xFFFF: none
+    const uint32_t* nch;   // chunks of 8 connections that a group of 64 lanes has
 };
+// What the layers of a network have in common.  kResWeights: 32 connections per neuron.  kResUniform: the same, one weight
+// per layer (it takes a scalar register, and half the bytes are read).  kResParts: any number of connections; the neurons
+// are given to the lanes by length, longest first, so that the 64 lanes of a group have about equally many, and a group
+// runs the chunks of 8 that its longest lane needs (the zero padding of Section III-A-3, per wave).  Every 32 connections
+// are summed by themselves and added to the neuron's sum, in order.
+enum { kResWeights = 0, kResUniform = 1, kResParts = 2 };
 struct ResidentArgs {
     const ResidentLayer* layers;
     int l0, lmid, l1;  // layers l0 .. l1-1; rows of a share of several passes are packed together again at lmid
     int L;             // layers of the network
     int A;             // rows on entry, if the lists are not there yet (rl.count == NULL): row i is in slot i
+    uint32_t part_stride;  // kResParts: bytes from a group's connections 32p .. 32p+31 to the next 32, slots and weights alike
     int* layer_rows;   // NULL, or [L + 1] counters: [l] += rows alive on entry to layer l
 };
 
@@ -122,11 +133,10 @@ __device__ __forceinline__ void res_fma8(f32x4 (&acc)[P], u32x4 codes, float wu,
     SPDNN_RES_CASE(4)
 }
 
-// NB = most groups of 64 neurons a wave owns (output blocks), PM = most planes, UNI = every layer of the network has one
-// weight for all its connections (which then takes a scalar register, and half the bytes).  blockDim.x = 64 * W with W = ceil(U / NB),
-// U = ceil(N / 64) groups of 64 neurons; wave w owns the groups w, w + W, ...  Q = workgroups, each with a run of
-// neighbouring rows; gridDim.x = Q.
-template <int NB, int PM, bool UNI>
+// NB = most groups of 64 neurons a wave owns, PM = most planes.  blockDim.x = 64 * W with W = ceil(U / NB),
+// U = ceil(N / 64) groups of 64 neurons; wave w owns the groups w, w + W, ...  Every workgroup has a run of
+// neighbouring rows.
+template <int NB, int PM, int MODE>
 __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict__ Yin, float* Ymid, float* Yout,
                                                         uint8_t* __restrict__ flags, RowLists rl, ResidentArgs ra,
                                                         const float* __restrict__ bias, int N) {
@@ -153,11 +163,16 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
     if (nrows <= 0) return;
 
     const int nb_w = (U - wave + W - 1) / W;  // my groups of 64 neurons (at least one: W <= U)
-    float bj[NB];  // lanes past the last neuron: minus infinity, which makes their outputs 0
+    float bj[NB];  // lanes without a neuron: minus infinity, which makes their outputs 0
+    float* bias_lds = reinterpret_cast<float*>(res_lds + misc + kResMiscBytes);  // kResParts: [N]
+    if constexpr (MODE == kResParts) {
+        for (int j = tid; j < N; j += T) bias_lds[j] = bias[j];
+    } else {
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int j = 64 * (b * W + wave) + lane;
-        bj[b] = j < N ? bias[j] : -__builtin_inff();
+        for (int b = 0; b < NB; ++b) {
+            const int j = 64 * (b * W + wave) + lane;
+            bj[b] = j < N ? bias[j] : -__builtin_inff();
+        }
     }
     {  // waves of one SIMD take turns rather than meet at the LDS all at once (see fused_layer_kernel)
         const int pw = __builtin_amdgcn_readfirstlane(3 - ((threadIdx.x >> 8) & 3));
@@ -174,27 +189,34 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
     using gu32x4 = const __attribute__((address_space(1))) u32x4;
     using gf32x4 = const __attribute__((address_space(1))) f32x4;
     using gu32 = const __attribute__((address_space(1))) uint32_t;
+    using gu16 = const __attribute__((address_space(1))) uint16_t;
+    using cu32 = const __attribute__((address_space(4))) uint32_t;
     struct Item {  // a layer's connections of one group of 64 neurons
         gchar *c, *w;
+        int nch;  // chunks of 8
     };
     auto item = [&](const ResidentLayer& d, int b) -> Item {
         const int u = b * W + wave;
         const uint32_t at = ((u >> 4) * (kNnz / 8) * kBlk + (u & 15) * 64) * 16;
         const uint32_t wat = ((u >> 4) * (kNnz / 4) * kBlk + (u & 15) * 64) * 16;
-        return Item{(gchar*)(uintptr_t)d.rel + at, (gchar*)(uintptr_t)d.val + wat};
+        const int nch = MODE == kResParts ? (int)((cu32*)(uintptr_t)d.nch)[u] : kNnz / 8;
+        return Item{(gchar*)(uintptr_t)d.rel + at, (gchar*)(uintptr_t)d.val + wat, nch};
     };
     const uint32_t lane16 = 16u * lane;
-    auto fetch_codes = [&](const Item& it, int c) { cbuf[c] = *(gu32x4*)(it.c + (lane16 + (uint32_t)c * (16 * kBlk))); };
-    auto fetch_weights = [&](const Item& it, int c) {
-        if constexpr (UNI) return;
-        wbuf[2 * (c & 1)] = *(gf32x4*)(it.w + (lane16 + (uint32_t)(2 * c) * (16 * kBlk)));
-        wbuf[2 * (c & 1) + 1] = *(gf32x4*)(it.w + (lane16 + (uint32_t)(2 * c + 1) * (16 * kBlk)));
+    // chunk c (0..3) of the 32 connections that start at part_off bytes from the group's first
+    auto fetch_codes = [&](const Item& it, int c, size_t part_off = 0) {
+        cbuf[c] = *(gu32x4*)(it.c + part_off + (lane16 + (uint32_t)c * (16 * kBlk)));
+    };
+    auto fetch_weights = [&](const Item& it, int c, size_t part_off = 0) {
+        if constexpr (MODE == kResUniform) return;
+        wbuf[2 * (c & 1)] = *(gf32x4*)(it.w + part_off + (lane16 + (uint32_t)(2 * c) * (16 * kBlk)));
+        wbuf[2 * (c & 1) + 1] = *(gf32x4*)(it.w + part_off + (lane16 + (uint32_t)(2 * c + 1) * (16 * kBlk)));
     };
     // The descriptors are constant while the kernel runs: scalar loads.
     using clayer = const __attribute__((address_space(4))) ResidentLayer;
     auto layer_at = [&](int l) -> ResidentLayer {
         clayer* d = (clayer*)(uintptr_t)(ra.layers + l);
-        return ResidentLayer{d->rel, d->val, d->qsel, d->wuni};
+        return ResidentLayer{d->rel, d->val, d->qsel, d->wuni, d->perm, d->nch};
     };
 
     int nalive = nrows;  // of my rows, on entry to the current run of layers
@@ -260,9 +282,21 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
                     // after the last layer comes, for the connections, the next pass's first
                     const ResidentLayer nxt = layer_at(l + 1 < lb ? l + 1 : la);
                     gu32* q_next = (gu32*)(uintptr_t)(l + 1 < lb ? nxt.qsel : q_out);
-                    uint32_t at[NB];  // where my neurons' outputs go
+                    int jn[NB];       // my neurons
+                    uint32_t at[NB];  // where their outputs go
 #pragma unroll
-                    for (int b = 0; b < NB; ++b) at[b] = q_next[min(64 * (b * W + wave) + lane, N - 1) >> 2];
+                    for (int b = 0; b < NB; ++b) {
+                        jn[b] = 64 * (b * W + wave) + lane;
+                        if constexpr (MODE == kResParts) jn[b] = ((gu16*)(uintptr_t)cur.perm)[jn[b]];
+                        else at[b] = q_next[min(jn[b], N - 1) >> 2];
+                    }
+                    auto place = [&]() {  // out of the way of the first chunk's arithmetic
+#pragma unroll
+                        for (int b = 0; b < NB; ++b) {
+                            if constexpr (MODE == kResParts) at[b] = q_next[min(jn[b], N - 1) >> 2];
+                            else at[b] = store_group((uint32_t)jn[b]) * CH + ((at[b] >> (8 * (jn[b] & 3))) & 0xffu);
+                        }
+                    };
                     f32x4 res[NB][PP];
 #pragma unroll
                     for (int b = 0; b < NB; ++b) {
@@ -274,24 +308,49 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
                             for (int p = 0; p < PP; ++p) acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
                             const Item mine = item(cur, b);
                             const Item next = b + 1 < nb_w ? item(cur, b + 1) : item(nxt, 0);
+                            if constexpr (MODE != kResParts) {
 #pragma unroll
-                            for (int c = 0; c < 4; ++c) {
-                                res_fma8<PP, UNI>(acc, cbuf[c], cur.wuni, wbuf[2 * (c & 1)], wbuf[2 * (c & 1) + 1]);
-                                fetch_codes(next, c);
-                                if (c < 2) fetch_weights(mine, c + 2);
-                                else fetch_weights(next, c - 2);
-                                if (b == 0 && c == 0) {
+                                for (int c = 0; c < 4; ++c) {
+                                    res_fma8<PP, MODE == kResUniform>(acc, cbuf[c], cur.wuni, wbuf[2 * (c & 1)], wbuf[2 * (c & 1) + 1]);
+                                    fetch_codes(next, c);
+                                    if (c < 2) fetch_weights(mine, c + 2);
+                                    else fetch_weights(next, c - 2);
+                                    if (b == 0 && c == 0) place();
+                                }
 #pragma unroll
-                                    for (int i = 0; i < NB; ++i) {
-                                        const int j = 64 * (i * W + wave) + lane;
-                                        at[i] = store_group((uint32_t)j) * CH + ((at[i] >> (8 * (j & 3))) & 0xffu);
+                                for (int p = 0; p < PP; ++p) res[b][p] = acc[p];
+                            } else {
+                                // 32 connections per turn; a chunk's registers are refilled with the group's next chunk for
+                                // them, or with the next group's first
+                                size_t off = 0;
+                                for (int g = 0; g == 0 || 4 * g < mine.nch; ++g, off += ra.part_stride) {
+#pragma unroll
+                                    for (int i = 0; i < 4; ++i) {
+                                        const int c = 4 * g + i;
+                                        if (c < mine.nch) res_fma8<PP, false>(acc, cbuf[i], 0.0f, wbuf[2 * (i & 1)], wbuf[2 * (i & 1) + 1]);
+                                        if (c < mine.nch || g == 0) {
+                                            if (c + 4 < mine.nch) fetch_codes(mine, i, off + ra.part_stride);
+                                            else fetch_codes(next, i);
+                                        }
+                                        if (c < mine.nch || c < 2) {
+                                            if (c + 2 < mine.nch) fetch_weights(mine, (i + 2) & 3, i < 2 ? off : off + ra.part_stride);
+                                            else fetch_weights(next, i & 1);
+                                        }
+                                        if (b == 0 && i == 0 && g == 0) place();
+                                    }
+#pragma unroll
+                                    for (int p = 0; p < PP; ++p) {
+                                        res[b][p] += acc[p];
+                                        acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
                                     }
                                 }
+                                bj[b] = jn[b] < N ? bias_lds[min(jn[b], N - 1)] : -__builtin_inff();
+                                at[b] = store_group((uint32_t)jn[b]) * CH + ((at[b] >> (8 * (jn[b] & 3))) & 0xffu);
                             }
 #pragma unroll
                             for (int p = 0; p < PP; ++p)
 #pragma unroll
-                                for (int r = 0; r < kRows; ++r) res[b][p][r] = fminf(fmaxf(acc[p][r] + bj[b], 0.0f), kClip);
+                                for (int r = 0; r < kRows; ++r) res[b][p][r] = fminf(fmaxf(res[b][p][r] + bj[b], 0.0f), kClip);
                         }
                     }
                     // which rows have a positive output in my neurons
@@ -314,8 +373,7 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
                     if (P == PP) {
 #pragma unroll
                         for (int b = 0; b < NB; ++b) {
-                            const int j = 64 * (b * W + wave) + lane;
-                            if (j < N)
+                            if (b < nb_w && jn[b] < N)
 #pragma unroll
                                 for (int p = 0; p < PP; ++p) *reinterpret_cast<lds_f4*>(at[b] + 256u * p) = res[b][p];
                         }
@@ -323,8 +381,7 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
                         using lds_f = __attribute__((address_space(3))) float;
 #pragma unroll
                         for (int b = 0; b < NB; ++b) {
-                            const int j = 64 * (b * W + wave) + lane;
-                            if (j < N) {
+                            if (b < nb_w && jn[b] < N) {
 #pragma unroll
                                 for (int s = 0; s < kRows * PP; ++s)
                                     if ((live >> s) & 1u) {

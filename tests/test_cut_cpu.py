@@ -136,3 +136,44 @@ def test_all_neurons_of_the_longest_kind_fall_back_to_the_cut_by_neurons(lib):
     ranges, P, nblk = cut(lib, deg, whole_row_windows(N))
     check_partition(ranges, deg)
     assert [tuple(r) for r in ranges] == [(j, 512) for j in range(0, N, 512)]
+
+
+@pytest.mark.parametrize("N,waves,kmin,kmax", [
+    (32, 1, 0, 9), (64, 1, 32, 32), (100, 1, 0, 40), (1024, 8, 0, 100), (1028, 9, 8, 32), (1500, 12, 0, 40),
+    (3000, 12, 1, 64), (4096, 16, 16, 64), (4096, 16, 32, 32)])
+def test_neurons_by_length(lib, N, waves, kmin, kmax):
+    """Rows that stay on the chip: every neuron on exactly one lane, lanes of a group of about one length, groups dealt
+    to the waves so that none has much more to do than another; neurons of one length stay where they are."""
+    deg = np.random.default_rng(N + kmax).integers(kmin, kmax + 1, size=N)
+    ptr = np.zeros(N + 1, dtype=np.int32)
+    np.cumsum(deg, out=ptr[1:])
+    nlanes = -(-N // 1024) * 1024
+    perm, nch = np.zeros(nlanes, dtype=np.uint16), np.zeros(nlanes // 64, dtype=np.uint32)
+    f = lib.spdnn_order_by_length_host
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
+    f.restype = None
+    f(ptr.ctypes.data, N, nlanes, waves, perm.ctypes.data, nch.ctypes.data)
+    used = perm[perm != 0xFFFF]
+    assert np.array_equal(np.sort(used), np.arange(N)) and np.all(perm[N:] == 0xFFFF)
+    if kmin == kmax:
+        assert np.array_equal(perm[:N], np.arange(N))
+    length = np.where(perm == 0xFFFF, 0, deg[np.minimum(perm, N - 1)])
+    per_group = length.reshape(-1, 64)
+    assert np.array_equal(nch, -(-per_group.max(1) // 8))
+    full = N // 64
+    order = np.sort(deg)[::-1]
+    want = sorted((tuple(order[64 * g:64 * g + 64]) for g in range(full)), reverse=True)
+    assert sorted((tuple(r) for r in per_group[:full].tolist()), reverse=True) == want   # groups are runs of the sorted lengths
+    if full >= 2 * waves and full % (2 * waves) == 0:   # an even number of whole runs: the waves' loads
+        load = nch[:full].reshape(-1, waves).sum(0)
+        assert load.max() - load.min() <= 2 * full // waves
+
+
+@pytest.mark.parametrize("planes_log2", [0, 1, 2])
+def test_entry_codes(lib, planes_log2):
+    """An entry code is the LDS address / 16 of plane 0's entry: chunks of 16 slots, one 256-byte row per plane."""
+    code, slot = lib.spdnn_res_code_host, lib.spdnn_res_slot_host
+    for s in range(4096 >> max(0, planes_log2 - 1)):
+        c = code(s, planes_log2)
+        assert 16 * c == (s // 16) * 256 * (1 << planes_log2) + (s % 16) * 16 and c < 1 << 16
+        assert slot(c, planes_log2) == s

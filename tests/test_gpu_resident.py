@@ -58,3 +58,38 @@ def test_rows_stay_on_chip_through_the_layers(N, batch, L, uniform):
     n2, rows2, Y2 = m.infer(torch.from_numpy(Y0).to("cuda:0"))
     m.close()
     assert n2 == n and np.array_equal(rows2.cpu().numpy(), rows) and np.array_equal(Y2.cpu().numpy(), Y)
+
+
+@pytest.mark.parametrize("N,batch,L,kmin,kmax", [
+    (64, 3000, 3, 0, 300),      # ten parts of 32 connections per neuron, one group of lanes
+    (100, 1100, 4, 0, 9),       # two chunks at most; a ragged last group
+    (1024, 4500, 3, 0, 100),    # several passes per share, uneven neurons
+    (1500, 700, 4, 0, 40),
+    (1028, 2500, 3, 33, 64),    # two parts everywhere
+    (2052, 1300, 3, 1, 32),     # one part, three blocks
+    (4096, 2300, 4, 16, 64),    # two launches
+])
+def test_neurons_of_any_length_stay_on_chip(N, batch, L, kmin, kmax):
+    """The same for general layers: neurons sorted by length, as many chunks of connections as a group's longest needs."""
+    import torch
+    import paper_2007_14152_amd as sp
+    rng = np.random.default_rng(N + kmax)
+    ptr, idx, val = [], [], []
+    for l in range(L):
+        deg = rng.integers(kmin, kmax + 1, size=N)
+        if kmin == 0:
+            deg[: 70] = 0                    # a whole group of lanes without a connection, where there are that many
+        p = np.zeros(N + 1, dtype=np.int32)
+        np.cumsum(deg, out=p[1:])
+        ptr.append(p)
+        idx.append(rng.integers(0, N, size=int(p[N])).astype(np.int32))
+        val.append((rng.uniform(0.5, 1.5, size=int(p[N])) * np.repeat(2.0 / np.maximum(deg, 1), deg)).astype(np.float32))
+    bias = -rng.uniform(0.0, 0.3, size=N).astype(np.float32)
+    Y0 = synth.gen_y0(batch, N, 29, density="mixed")
+    Y0[1] = 0
+    ref = oracle.infer(idx, val, bias, Y0, ptr=ptr)
+    m = sp.Model.from_csr(ptr, idx, val, bias)
+    n, rows, Y = m.infer(torch.from_numpy(Y0).to("cuda:0"))
+    m.close()
+    check_against_oracle(ref, n, rows.cpu().numpy(), Y.cpu().numpy(), what="general N=%d" % N)
+    assert n == 0 or n < batch

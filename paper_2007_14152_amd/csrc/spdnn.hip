@@ -79,6 +79,8 @@ struct LayerDesc {
     spdnn::VirtInfo virt;
     int virt_lanes = 1;  // multi: lanes of the layer's longest neuron (the layer's passes)
     int virt_blocks = 0;  // multi: workgroups of this launch that have neurons
+    bool flat_uniform = false;
+    bool flat = false;     // runs fused_flat_kernel; mode says what the layer's windows are like
     bool relabel = false;  // kPair under new names for neurons and columns (spdnn::PairRelabel)
     spdnn::PairRelabel rn{};
 };
@@ -222,6 +224,13 @@ hipError_t allow_big_lds() {
                                hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)spdnn::tile_pair_bytes(spdnn::kCap) + (VIRT ? kVirtLds : 0));
 }
+template <int R>
+hipError_t allow_flat_lds() {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::fused_flat_kernel<R, false>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, spdnn::flat_lds_bytes(R));
+    return e != hipSuccess ? e : hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::fused_flat_kernel<R, true>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, spdnn::flat_lds_bytes(R));
+}
 template <int NB, int PM>
 hipError_t allow_resident_lds(int bytes) {
     for (const void* f : {reinterpret_cast<const void*>(&spdnn::resident_kernel<NB, PM, spdnn::kResWeights>),
@@ -266,6 +275,10 @@ int allow_large_lds() {
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::balance_kernel<4>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(spdnn::BalanceScratch<4>)));
     const int res_lds = (int)spdnn::res_tile_bytes(spdnn::kCap, 2) + spdnn::kResMiscBytes + 4 * spdnn::kCap;
+    HIP_TRY((allow_flat_lds<1>()));
+    HIP_TRY((allow_flat_lds<2>()));
+    HIP_TRY((allow_flat_lds<3>()));
+    HIP_TRY((allow_flat_lds<4>()));
     HIP_TRY((allow_resident_lds<1, 4>(res_lds)));
     HIP_TRY((allow_resident_lds<2, 4>(res_lds)));
     HIP_TRY((allow_resident_lds<4, 2>(res_lds)));
@@ -825,6 +838,28 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
             if (where == SPDNN_HOST) HIP_TRY(hipStreamSynchronize(stream));  // staging is reused
             continue;
         }
+        {  // Rows of up to 16384 columns that the blocks read more of than one LDS stage: whole rows in LDS, whatever the
+           // weights (two-row tiles, which hold four neurons per lane for one weight and N a multiple of 4096, were
+           // taken above).  The arena's wide format stays empty.
+            int widest = 4;
+            for (int32_t b = 0; b < nblk; ++b) widest = std::max(widest, hw[(size_t)l * nblk + b].y);
+            const int nst = stages_of(widest);
+            if (!d.multi && !pair && nst >= 2 && N <= spdnn::kFlatCols) {
+                spdnn::flat_pack_kernel<<<nblk * spdnn::kBlk / spdnn::kGroup32, spdnn::kRow2PackThreads, 0, stream>>>(
+                    di, dv, N, const_cast<uint16_t*>(d.w.rel), const_cast<float*>(d.w.val));
+                HIP_TRY(hipGetLastError());
+                d.flat = true;
+                d.lds_cols = N;
+                std::memcpy(&d.wuni, &pair_info[1], sizeof(float));
+                d.mode = nst > nstage_cap ? kStaged : wide_pair && spdnn::wide_steps(nst) >= 16 && d.ww.ps ? kWidePair : nst >= 3 ? kWide : kStaged;
+                d.pair4 = nst <= 4;
+                if (ooc)
+                    HIP_TRY(hipMemcpyAsync(static_cast<char*>(host_arena) + (size_t)l * blk_bytes, m->ooc_slot[l & 1], blk_bytes,
+                                           hipMemcpyDeviceToHost, stream));
+                if (where == SPDNN_HOST) HIP_TRY(hipStreamSynchronize(stream));  // staging is reused
+                continue;
+            }
+        }
         const int unit = whole ? nblk : pair ? 2 : 1;  // blocks that share a tile layout
         if (unit > 2)
             spdnn::balance_kernel<4><<<1, spdnn::kBalanceThreads, sizeof(spdnn::BalanceScratch<4>), stream>>>(
@@ -879,6 +914,13 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
     if (herr[0]) return fail(SPDNN_EINVAL, "a column index is outside [0, N)");
     for (int32_t l = 0; l < P; ++l)
         if ((m->layers[l].mode == kWide || m->layers[l].mode == kWidePair) && herr[1 + l]) m->layers[l].mode = kStaged;
+    // flat layers: is there one weight for all connections?
+    if (N > spdnn::kCap && N <= spdnn::kFlatCols) {
+        std::vector<int> differ((size_t)P);
+        HIP_TRY(hipMemcpyAsync(differ.data(), err_dev + 1 + 2 * P, sizeof(int) * (size_t)P, hipMemcpyDeviceToHost, stream));
+        HIP_TRY(hipStreamSynchronize(stream));
+        for (int32_t l = 0; l < P; ++l) m->layers[l].flat_uniform = differ[l] == 0;
+    }
     // Rows of at most one LDS stage: they can stay in LDS from layer to layer (resident_kernel, which takes the layers'
     // descriptors from device memory).
     if (N <= spdnn::kCap && !ooc) {
@@ -997,6 +1039,30 @@ hipError_t launch_resident(spdnn_t h, const ResidentShape& r, int32_t Q, const f
     if (r.nb == 1) run_mode(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
     else if (r.nb == 2) run_mode(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
     else run_mode(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{});
+    return hipGetLastError();
+}
+
+// One layer through fused_flat_kernel on at most `bound` rows.  The units of a row chunk go to one XCD (32 CUs, one L2), so
+// that a row is fetched from memory once; no more chunks than an XCD has CUs for all their units at once.
+hipError_t launch_flat(spdnn_t h, const LayerDesc& d, const float* Yin, float* Yout, uint8_t* flags, const spdnn::RowLists& rl,
+                       int32_t bound) {
+    const int32_t N = h->N, groups = (N + 63) / 64;
+    const int rows = spdnn::flat_rows(N), slots = d.flat_uniform ? 4 : 2;
+    const int32_t ncb = (groups + 16 * slots - 1) / (16 * slots), gpu = (groups + ncb - 1) / ncb;
+    const int32_t Q = std::max(1, std::min(8 * std::max(1, h->num_cu / 8 / ncb), (bound + rows - 1) / rows));
+    const int32_t grid = (Q + 7) / 8 * 8 * ncb;
+    const auto run = [&](auto r, auto uni) {
+        spdnn::fused_flat_kernel<decltype(r)::value, decltype(uni)::value><<<grid, spdnn::kBlk, spdnn::flat_lds_bytes(rows), h->stream>>>(
+            Yin, Yout, flags, rl, d.w, h->bias_dev, N, ncb, ncb, Q, gpu, d.wuni);
+    };
+    const auto run_r = [&](auto r) {
+        if (d.flat_uniform) run(r, std::true_type{});
+        else run(r, std::false_type{});
+    };
+    if (rows == 1) run_r(std::integral_constant<int, 1>{});
+    else if (rows == 2) run_r(std::integral_constant<int, 2>{});
+    else if (rows == 3) run_r(std::integral_constant<int, 3>{});
+    else run_r(std::integral_constant<int, 4>{});
     return hipGetLastError();
 }
 
@@ -1202,6 +1268,9 @@ int infer_impl(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv
             rl.count = wv.count[l & 1];
             rl.host_count = h->host_counts + l;
             rl.flags_clear = wv.flags[(l + 1) % 3];
+            if (d.flat) {
+                HIP_TRY(launch_flat(h, d, Yin, Yout, wv.flags[l % 3], rl, bound));
+            } else {
             // launch shape: one workgroup per CU; the rows are cut into Q chunks per output block
             const int32_t rows_per_group = d.mode == kRow2 ? spdnn::kRows2 : spdnn::kRows;
             const int32_t ngroups = (bound + rows_per_group - 1) / rows_per_group;
@@ -1272,6 +1341,7 @@ int infer_impl(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv
             else
                 spdnn::fused_layer_kernel<false><<<grid, spdnn::kBlk, lds, s>>>(
                     Yin, Yout, wv.flags[l % 3], rl, d.w, h->bias_dev, N, h->nblk, G, Q);
+            }
             if (h->ooc_host) {  // the slot is free once this kernel is done: refill it with pass p + 2
                 HIP_TRY(hipEventRecord(h->ooc_freed[p & 1], s));
                 if (p + 2 < P) {

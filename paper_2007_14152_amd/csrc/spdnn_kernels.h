@@ -533,6 +533,10 @@ struct ListWindow {
         const int k = e - lo;
         return make_int2(__builtin_amdgcn_readlane(v, k), __builtin_amdgcn_readlane(v, k + 1));
     }
+    __device__ __forceinline__ int get1(int e) {
+        seek(e);
+        return __builtin_amdgcn_readlane(v, e - lo);
+    }
     __device__ __forceinline__ int last() const { return identity ? end - 1 : __builtin_amdgcn_readfirstlane(cat[end - 1]); }
 };
 
@@ -1763,6 +1767,7 @@ __global__ __launch_bounds__(kBlk) void fused_wide_pair4_kernel(
 
 }  // namespace spdnn
 #include "spdnn_row2.h"
+#include "spdnn_flat.h"
 #include "spdnn_resident.h"
 namespace spdnn {
 

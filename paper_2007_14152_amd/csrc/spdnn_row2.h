@@ -431,31 +431,13 @@ __device__ __forceinline__ int wave32_min(int v) {
     v = row16_min(v);
     return min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16));
 }
-__global__ __launch_bounds__(kRow2PackThreads) void row2_pack_kernel(const int32_t* __restrict__ idx, int N,
-                                                                     const int2* __restrict__ win,
-                                                                     const uint16_t* __restrict__ rank,  // NULL: contiguous windows
-                                                                     int seg_log2, int seg_stride,
-                                                                     uint16_t* __restrict__ codes) {
-    __shared__ Pack32Scratch S;
-    const int g = blockIdx.x;  // group: unit, slot, 32 lanes
-    const int groups_per_unit = kUnit4 / kGroup32;
-    const int u = g / groups_per_unit;
-    if (u * kUnit4 >= N) return;
-    const int in_unit = g - u * groups_per_unit;
-    const int s = in_unit / (kBlk / kGroup32);
-    const int lane0 = (in_unit - s * (kBlk / kGroup32)) * kGroup32;
-    const int c_lo = rank ? 0 : row2_window(win, u, N).x;
+// The search for one group, by a wave.  exists: my lane's neuron is there (and has 32 connections); bank_of(k): bank pair
+// (0..31) of connection k of lane (threadIdx.x & 31); place(step, k): that connection goes to step `step`.
+template <typename BankOf, typename Place>
+__device__ __forceinline__ void order32_wave(Pack32Scratch& S, bool exists, BankOf bank_of, Place place) {
     const int lane = threadIdx.x;
     const bool on = lane < 32;       // the upper half of the wave only keeps the reductions company
     const int l = lane & 31;
-    const int32_t* mine = idx + (size_t)unit_neuron(u, s * kBlk + lane0 + l, seg_log2, seg_stride) * kNnz;
-    auto pos_of = [&](int k) -> uint32_t {  // out-of-range columns were reported; keep them harmless
-        int c = mine[k];
-        if (c < 0 || c >= N) c = c_lo;
-        // tile column: inside the window, or in the gathered list group rank[c >> 2], column c & 3 of it
-        const uint32_t tc = rank ? 4u * rank[(size_t)u * (N / 4) + (c >> 2)] + (uint32_t)(c & 3) : (uint32_t)win_rel(c, c_lo, N);
-        return row2_pos(tc & (kRow2Cols - 1));
-    };
     for (int q = 0; q < 32; ++q)
         if (on) S.conn[q][l] = 0;
     if (on) {
@@ -463,9 +445,9 @@ __global__ __launch_bounds__(kRow2PackThreads) void row2_pack_kernel(const int32
         S.remq[l] = 0;
     }
     __syncthreads();
-    if (on)
+    if (on && exists)
         for (int k = 0; k < 32; ++k) {
-            const int q = (int)(pos_of(k) & 31u);
+            const int q = (int)bank_of(k);
             S.conn[q][l] |= 1u << k;  // my own column of the table
         }
     __syncthreads();
@@ -479,6 +461,7 @@ __global__ __launch_bounds__(kRow2PackThreads) void row2_pack_kernel(const int32
         }
     __syncthreads();
     uint32_t unplaced = 0xFFFFFFFFu;  // lane l's connections not placed yet
+    const uint32_t lanes = (uint32_t)__builtin_amdgcn_ballot_w64(on && exists);  // lanes that have connections
     for (int step = 0; step < 32; ++step) {
         const int left = 32 - step;
         const uint32_t adj = on ? S.adj[l] : 0u;  // as pair q = l
@@ -486,7 +469,7 @@ __global__ __launch_bounds__(kRow2PackThreads) void row2_pack_kernel(const int32
         int lane_of_pair = -1;  // as pair
         int pair_of_lane = -1;  // as lane
         int parent = -1;        // as lane: the pair from which the search reached me
-        uint32_t free_lanes = 0xFFFFFFFFu;  // lanes without a pair (the same in every lane)
+        uint32_t free_lanes = lanes;        // lanes without a pair (the same in every lane)
         uint32_t done = 0;                  // pairs already offered
         for (int r = 0; r < 32; ++r) {
             // the most urgent pair not offered yet, the lowest-numbered one among equals
@@ -540,17 +523,46 @@ __global__ __launch_bounds__(kRow2PackThreads) void row2_pack_kernel(const int32
             if (lane == bq) ++mult;
         }
         // place: the lowest unplaced connection of my pair
-        if (on) {
+        if (on && exists) {
             const uint32_t in_pair = S.conn[pair_of_lane][l];
             const int k = __builtin_ctz(in_pair & unplaced);
             unplaced &= ~(1u << k);
             atomicSub(&S.remq[pair_of_lane], 1u);
             if ((in_pair & unplaced) == 0) atomicAnd(&S.adj[pair_of_lane], ~(1u << l));
-            const size_t word = ((size_t)(u * 4 + s) * 4 + (step >> 3)) * kBlk + lane0 + l;
-            codes[word * 8 + (step & 7)] = (uint16_t)pos_of(k);
+            place(step, k);
         }
         __syncthreads();
     }
+}
+__global__ __launch_bounds__(kRow2PackThreads) void row2_pack_kernel(const int32_t* __restrict__ idx, int N,
+                                                                     const int2* __restrict__ win,
+                                                                     const uint16_t* __restrict__ rank,  // NULL: contiguous windows
+                                                                     int seg_log2, int seg_stride,
+                                                                     uint16_t* __restrict__ codes) {
+    __shared__ Pack32Scratch S;
+    const int g = blockIdx.x;  // group: unit, slot, 32 lanes
+    const int groups_per_unit = kUnit4 / kGroup32;
+    const int u = g / groups_per_unit;
+    if (u * kUnit4 >= N) return;
+    const int in_unit = g - u * groups_per_unit;
+    const int s = in_unit / (kBlk / kGroup32);
+    const int lane0 = (in_unit - s * (kBlk / kGroup32)) * kGroup32;
+    const int c_lo = rank ? 0 : row2_window(win, u, N).x;
+    const int lane = threadIdx.x;
+    const int l = lane & 31;
+    const int32_t* mine = idx + (size_t)unit_neuron(u, s * kBlk + lane0 + l, seg_log2, seg_stride) * kNnz;
+    auto pos_of = [&](int k) -> uint32_t {  // out-of-range columns were reported; keep them harmless
+        int c = mine[k];
+        if (c < 0 || c >= N) c = c_lo;
+        // tile column: inside the window, or in the gathered list group rank[c >> 2], column c & 3 of it
+        const uint32_t tc = rank ? 4u * rank[(size_t)u * (N / 4) + (c >> 2)] + (uint32_t)(c & 3) : (uint32_t)win_rel(c, c_lo, N);
+        return row2_pos(tc & (kRow2Cols - 1));
+    };
+    order32_wave(S, true, [&](int k) { return pos_of(k) & 31u; },
+                 [&](int step, int k) {
+                     const size_t word = ((size_t)(u * 4 + s) * 4 + (step >> 3)) * kBlk + lane0 + l;
+                     codes[word * 8 + (step & 7)] = (uint16_t)pos_of(k);
+                 });
 }
 
 // ---------------------------------------------------------------------------

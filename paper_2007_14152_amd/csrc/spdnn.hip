@@ -1092,9 +1092,11 @@ int wait_count(spdnn_t h, int32_t l, int32_t* count) {
 // batch), their numbers ascending to active_rows_dev and their values, from Y_last, to Y_final_dev.  Nothing here waits
 // for the count but the host at the end: rows are numbered straight into the caller's array, and the gather takes the
 // count from device memory (at most `bound` rows).  Returns with the stream drained.
+// Y_last == Y_final_dev: the last launch wrote its rows there, row i of its list to row i (write_through); if all of them
+// survived they are in place, else they move together by way of `spare`, the work buffer that launch read.
 int finish_infer(spdnn_t h, const uint8_t* flags, const int* count_in, const int* gid_in, int32_t batch, int32_t row_offset,
-                 int* count_out, int* cat_out, int32_t slot, const float* Y_last, int32_t bound, int32_t* n_active_host,
-                 int32_t* active_rows_dev, float* Y_final_dev) {
+                 int* count_out, int* cat_out, int32_t slot, const float* Y_last, float* spare, int32_t bound,
+                 int32_t* n_active_host, int32_t* active_rows_dev, float* Y_final_dev) {
     hipStream_t s = h->stream;
     h->host_counts[slot] = -1;
     spdnn::compact_kernel<<<spdnn::kCompactWGs, 1024, 0, s>>>(flags, nullptr, count_in, count_out, gid_in, active_rows_dev, cat_out,
@@ -1103,9 +1105,16 @@ int finish_infer(spdnn_t h, const uint8_t* flags, const int* count_in, const int
     if (Y_final_dev && bound > 0) {
         const int n4 = h->N / 4;
         const size_t total = (size_t)bound * n4;
-        const int g = (int)std::min<size_t>((total + 255) / 256, 65536);
-        spdnn::gather_rows_kernel<<<g, 256, 0, s>>>(reinterpret_cast<const float4*>(Y_last), cat_out, count_out, n4,
-                                                   reinterpret_cast<float4*>(Y_final_dev));
+        const float4* from = reinterpret_cast<const float4*>(Y_last);
+        float4* to = reinterpret_cast<float4*>(Y_final_dev);
+        if (Y_last != Y_final_dev)
+            spdnn::gather_rows_kernel<<<(int)std::min<size_t>((total + 255) / 256, 65536), 256, 0, s>>>(from, cat_out, count_out, nullptr, n4, to);
+        else {
+            const int g = (int)std::min<size_t>((total + 255) / 256, 2048);
+            float4* by = reinterpret_cast<float4*>(spare);
+            spdnn::gather_rows_kernel<<<g, 256, 0, s>>>(from, cat_out, count_out, count_in, n4, by);
+            spdnn::gather_rows_kernel<<<g, 256, 0, s>>>(by, nullptr, count_out, count_in, n4, to);
+        }
         HIP_TRY(hipGetLastError());
     }
     HIP_TRY(hipStreamSynchronize(s));
@@ -1113,6 +1122,13 @@ int finish_infer(spdnn_t h, const uint8_t* flags, const int* count_in, const int
     if (n < 0) return fail(SPDNN_EHIP, "the last layer finished without reporting its active rows");
     *n_active_host = n;
     return SPDNN_OK;
+}
+
+// Should the last launch write its rows straight to the caller's array?  Saves a pass over them (0.16 ms for 30 000 rows of
+// 4096 neurons) when they all survive, costs one when they do not: only if no row died lately, and not for small results,
+// which the two kernels that make sure would take longer than.
+bool write_through(const spdnn_model* h, const float* Y_final_dev, int32_t rows, bool none_died) {
+    return Y_final_dev && none_died && (size_t)rows * h->N * sizeof(float) >= ((size_t)8 << 20);
 }
 
 // infer_impl for networks whose rows stay in LDS from layer to layer (resident_kernel).
@@ -1145,6 +1161,7 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
     std::vector<Run> runs;
     int32_t alive = batch, before = batch;
     spdnn::RowLists rl{};
+    float* Y_last = nullptr;
     int32_t k = 0;     // launches so far
     int32_t len = 2;   // layers of the next run
     for (int32_t l0 = 0; l0 < L; ++k, len *= 4) {
@@ -1156,7 +1173,9 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
         const bool several = (groups + Q - 1) / Q > shape.planes;
         const spdnn::ResidentArgs ra{h->res_layers, l0, one && several ? std::min(l0 + 2, l1) : l1, l1, L, batch, h->res_part_stride, layer_rows};
         if (h->profiling) HIP_TRY(hipEventRecord(h->t0[l0], s));
-        HIP_TRY(launch_resident(h, shape, Q, k == 0 ? Y0_dev : wv.Y[(k + 1) & 1], wv.Y[(k + 1) & 1], wv.Y[k & 1], wv.flags[0], rl, ra));
+        // (rows that lived through two or more layers mostly live on)
+        Y_last = rest && write_through(h, Y_final_dev, alive, k > 0) ? Y_final_dev : wv.Y[k & 1];
+        HIP_TRY(launch_resident(h, shape, Q, k == 0 ? Y0_dev : wv.Y[(k + 1) & 1], wv.Y[(k + 1) & 1], Y_last, wv.flags[0], rl, ra));
         if (h->profiling) HIP_TRY(hipEventRecord(h->t1[l0], s));
         runs.push_back(Run{l0, l1});
         l0 = l1;
@@ -1176,7 +1195,7 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
     int32_t rc = SPDNN_OK;
     if (alive > 0)
         rc = finish_infer(h, wv.flags[0], rl.count, rl.gid, batch, row_offset, wv.count[k & 1], wv.cat[k & 1], L + 1,
-                          wv.Y[k & 1], alive, n_active_host, active_rows_dev, Y_final_dev);
+                          Y_last, wv.Y[(k + 1) & 1], alive, n_active_host, active_rows_dev, Y_final_dev);
     else {
         HIP_TRY(hipStreamSynchronize(s));
         *n_active_host = 0;
@@ -1229,7 +1248,9 @@ int infer_impl(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv
     spdnn::init_lists_kernel<<<(batch + 255) / 256, 256, 0, s>>>(wv.gid[1], wv.flags[2], wv.flags[0], wv.count[1], batch,
                                                                  row_offset);
     int32_t bound = batch;  // upper bound of the rows active at the layer being launched
+    int32_t before = -1;    // the bound one layer earlier
     int32_t run = 0;        // layers launched
+    float* Y_last = nullptr;  // where the last layer launched writes
     // Out-of-core weights (Section III-B-1): pass p runs from device slot p & 1.  The copy stream fills
     // the two slots, and refills a slot with pass p + 2 as soon as the kernels of pass p are done with
     // it, so the transfer of the next layer runs under the current layer's kernel.
@@ -1251,6 +1272,8 @@ int infer_impl(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv
     for (int32_t l = 0; l < L; ++l) {
         const float* Yin = (l == 0) ? Y0_dev : wv.Y[(l - 1) & 1];
         float* Yout = wv.Y[l & 1];
+        if (l == L - 1 && write_through(h, Y_final_dev, bound, bound == before)) Yout = Y_final_dev;
+        Y_last = Yout;
         if (h->profiling) HIP_TRY(hipEventRecord(h->t0[l], s));
         // one launch per pass: a layer is a single pass unless some neuron has more than 32 connections
         for (int32_t p = h->first_pass[l]; p < h->first_pass[l + 1]; ++p) {
@@ -1362,6 +1385,7 @@ int infer_impl(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv
             int32_t c = 0;
             const int rc = wait_count(h, l + 2 - kLag, &c);
             if (rc != SPDNN_OK) return rc;
+            before = bound;
             bound = c;
             if (bound == 0) break;
         }
@@ -1369,7 +1393,7 @@ int infer_impl(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv
     // the rows that survive the last layer launched: the same compaction, as a kernel of its own; its count goes to
     // host_counts[run] (rows on entry to the layer that would come next)
     const int rc = finish_infer(h, wv.flags[(run + 2) % 3], wv.count[(run + 1) & 1], wv.gid[(run + 1) & 1], batch, row_offset, wv.count[run & 1],
-                                wv.cat[run & 1], run, wv.Y[(run - 1) & 1], bound, n_active_host, active_rows_dev, Y_final_dev);
+                                wv.cat[run & 1], run, Y_last, wv.Y[run & 1], bound, n_active_host, active_rows_dev, Y_final_dev);
     if (rc != SPDNN_OK) return rc;
     drain_model.armed = false;
     if (h->profiling) {

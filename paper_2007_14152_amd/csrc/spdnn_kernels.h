@@ -1928,16 +1928,18 @@ __global__ void clear_counters_kernel(int* __restrict__ counters, int n) {
     for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) counters[k] = 0;
 }
 
-// a4: surviving rows of Y_L, gathered into a dense [n][N] array (16-byte pieces).
-// n: device memory -- the host need not know it to launch this.
-__global__ void gather_rows_kernel(const float4* __restrict__ src, const int* __restrict__ cat,
-                                   const int* __restrict__ n, int n4, float4* __restrict__ dst) {
+// a4: surviving rows of Y_L, gathered into a dense [n][N] array (16-byte pieces).  n: device memory -- the host need not
+// know it to launch this.  cat == NULL: row i comes from row i.  n_in: nothing to do if it says n too (every row is
+// where it belongs already).
+__global__ void gather_rows_kernel(const float4* __restrict__ src, const int* __restrict__ cat, const int* __restrict__ n,
+                                   const int* __restrict__ n_in, int n4, float4* __restrict__ dst) {
+    if (n_in && *n_in == *n) return;
     const size_t total = (size_t)*n * n4;
     for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
          e += (size_t)gridDim.x * blockDim.x) {
         const size_t row = e / n4;
         const size_t c = e - row * n4;
-        dst[e] = src[(size_t)cat[row] * n4 + c];
+        dst[e] = src[cat ? (size_t)cat[row] * n4 + c : e];
     }
 }
 

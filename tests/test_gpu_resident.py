@@ -93,3 +93,67 @@ def test_neurons_of_any_length_stay_on_chip(N, batch, L, kmin, kmax):
     m.close()
     check_against_oracle(ref, n, rows.cpu().numpy(), Y.cpu().numpy(), what="general N=%d" % N)
     assert n == 0 or n < batch
+
+
+@pytest.mark.parametrize("N,batch,L,die", [
+    (4096, 1600, 9, True),     # rows in LDS, two launches
+    (4096, 1600, 9, False),
+    (8192, 700, 5, True),      # a launch per layer
+    (8192, 700, 5, False),
+])
+def test_last_layer_writes_to_the_callers_array(N, batch, L, die):
+    """When no row has died lately, the last launch writes its rows where the caller wants them; those that die in the
+    very last layer leave gaps, which the survivors close.  Row r holds the integer v_r in every column, a layer turns v
+    into v - 1, exactly."""
+    import torch
+    import paper_2007_14152_amd as sp
+    dev = "cuda:0"
+    rng = np.random.default_rng(N + die)
+    v = rng.integers(L + 1, L + 9, size=batch)
+    if die:
+        v[rng.uniform(size=batch) < 0.3] = L
+        v[[0, batch - 1]] = L
+    idx = [torch.from_numpy(np.sort(rng.integers(0, N, size=(N, 32)), axis=1).astype(np.int32)).to(dev) for _ in range(L)]
+    val = torch.full((N, 32), 1.0 / 32, dtype=torch.float32, device=dev)
+    m = sp.Model(idx, [val] * L, torch.full((N,), -1.0, device=dev), device=dev)
+    y0 = torch.from_numpy(v.astype(np.float32)).to(dev)[:, None].expand(batch, N).contiguous()
+    for _ in range(2):
+        n, rows, Y = m.infer(y0)
+        alive = np.nonzero(v > L)[0]
+        assert n == len(alive) and np.array_equal(rows.cpu().numpy(), alive)
+        assert bool((Y == torch.from_numpy((v[alive] - L).astype(np.float32)).to(dev)[:, None]).all())
+    m.close()
+
+
+@pytest.mark.parametrize("N,batch,uniform", [
+    (4100, 37, False),     # four rows per tile, units of 33 groups of 64 neurons, a ragged last one
+    (4864, 1030, True),    # the widest rows of four per tile; more tiles than workgroups
+    (4868, 700, False),    # three rows per tile
+    (6656, 95, True),
+    (6660, 501, False),    # two
+    (9984, 130, True),
+    (9988, 260, False),    # one
+    (13000, 67, True),
+    (16384, 515, False),   # the widest row there is
+])
+def test_whole_rows_in_lds(N, batch, uniform):
+    """Rows of 4097 to 16384 columns read from anywhere (fused_flat_kernel): one to four rows per tile, ragged ends."""
+    import torch
+    import paper_2007_14152_amd as sp
+    rng = np.random.default_rng(N)
+    L = 2
+    idx = [np.sort(rng.integers(0, N, size=(N, 32)), axis=1).astype(np.int32) for _ in range(L)]
+    val = [np.full((N, 32), 0.0625, np.float32) if uniform else rng.uniform(0.02, 0.11, size=(N, 32)).astype(np.float32)
+           for _ in range(L)]
+    bias = -rng.uniform(0.0, 0.4, size=N).astype(np.float32)
+    Y0 = synth.gen_y0(batch, N, 31, density="mixed")
+    Y0[5] = 0
+    ids = np.arange(batch) if batch <= 300 else np.r_[0:100, batch - 100:batch]
+    ref = oracle.infer(idx, val, bias, Y0[ids])
+    m = sp.Model(idx, val, bias)
+    n, rows, Y = m.infer(torch.from_numpy(Y0).to("cuda:0"))
+    m.close()
+    rows, Y = rows.cpu().numpy(), Y.cpu().numpy()
+    mine = np.isin(rows, ids)
+    common, _ = check_against_oracle(ref, int(mine.sum()), rows[mine], Y[mine], row_ids=ids, what="whole rows N=%d" % N)
+    assert common > 0 and n == len(rows) < batch

@@ -27,114 +27,69 @@ SPDNN_HD inline int flat_rows(int N) { return N <= 4864 ? 4 : N <= 6656 ? 3 : N 
 SPDNN_HD constexpr int flat_stride(int rows) { return rows == 4 ? 4864 * 4 : rows == 3 ? 6656 * 4 : rows == 2 ? 9984 * 4 : 16384 * 4; }
 SPDNN_HD inline int flat_lds_bytes(int rows) { return kFlatMisc + 2 * rows * flat_stride(rows); }
 
-// Sixteen connections of one neuron on R rows: acc[r] += row r[column i] * w_i, i = 0..15 in that order.  c0..c7 hold the
-// connections' byte offsets in a row, two to a register; an SDWA add makes a half an address in the tile at `base`; reads
-// run G connections ahead (v118..v125).
-#define SPDNN_FLAT_READ(I, C, H)                                                                                          \
-    "v_add_u32_sdwa v[126+" I "%%2], %[base], %[" C "] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_" H "\n\t" \
-    ".set spdnn_r, 0\n\t"                                                                                                 \
-    ".rept %[R]\n\t"                                                                                                      \
-    "ds_read_b32 v[118+(" I "%%%[G])*%[R]+spdnn_r], v[126+" I "%%2] offset:%[S]*spdnn_r\n\t"                               \
-    ".set spdnn_r, spdnn_r+1\n\t"                                                                                         \
+// All connections of a lane's NS neurons on R rows, one pipeline of reads from the first to the last: acc[s * R + r] +=
+// row r[column] * weight over neuron s's 32 connections, in order.  Everything sits in fixed registers, so that the
+// assembler's own loop can number it: byte offsets in a row in v[16..], two to a register (an SDWA add makes a half an
+// address in the tile at `base`), weights in v[48..111], sums in v[8..15] -- with one weight per layer, of four neurons,
+// offsets in v[16..79] and sums in v[80..95] -- and reads, G connections ahead, from v112 on.  (As blocks of 16
+// connections with a drained pipeline between them a layer of 16384 neurons on 7000 rows took 0.52 ms.)
+#define SPDNN_FLAT_READ(K)                                                                                                 \
+    ".if ((" K ")&1)==0\n\t"                                                                                               \
+    "v_add_u32_sdwa v[126+((" K ")&1)], %[base], v[16+(" K ")/2] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t" \
+    ".else\n\t"                                                                                                            \
+    "v_add_u32_sdwa v[126+((" K ")&1)], %[base], v[16+(" K ")/2] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t" \
+    ".endif\n\t"                                                                                                           \
+    ".set spdnn_r, 0\n\t"                                                                                                  \
+    ".rept %[R]\n\t"                                                                                                       \
+    "ds_read_b32 v[112+((" K ")%%%[G])*%[R]+spdnn_r], v[126+((" K ")&1)] offset:%[S]*spdnn_r\n\t"                           \
+    ".set spdnn_r, spdnn_r+1\n\t"                                                                                          \
     ".endr\n\t"
-#define SPDNN_FLAT_STEP(I, W)                                   \
-    ".if " I "+%[G] <= 16\n\t"                                  \
-    "s_waitcnt lgkmcnt((%[G]-1)*%[R])\n\t"                      \
-    ".else\n\t"                                                 \
-    "s_waitcnt lgkmcnt((15-" I ")*%[R])\n\t"                    \
-    ".endif\n\t"                                                \
-    "v_fmac_f32 %[a0], " W ", v[118+(" I "%%%[G])*%[R]]\n\t"    \
-    ".if %[R] > 1\n\t"                                          \
-    "v_fmac_f32 %[a1], " W ", v[119+(" I "%%%[G])*%[R]]\n\t"    \
-    ".endif\n\t"                                                \
-    ".if %[R] > 2\n\t"                                          \
-    "v_fmac_f32 %[a2], " W ", v[120+(" I "%%%[G])*%[R]]\n\t"    \
-    ".endif\n\t"                                                \
-    ".if %[R] > 3\n\t"                                          \
-    "v_fmac_f32 %[a3], " W ", v[121+(" I "%%%[G])*%[R]]\n\t"    \
-    ".endif\n\t"
-#define SPDNN_FLAT_ASM_W8 \
-    SPDNN_FLAT_READ("0", "c0", "0") SPDNN_FLAT_READ("1", "c0", "1") SPDNN_FLAT_READ("2", "c1", "0") SPDNN_FLAT_READ("3", "c1", "1") SPDNN_FLAT_READ("4", "c2", "0") SPDNN_FLAT_READ("5", "c2", "1") SPDNN_FLAT_READ("6", "c3", "0") SPDNN_FLAT_READ("7", "c3", "1") \
-    SPDNN_FLAT_STEP("0", "%[w0]") SPDNN_FLAT_READ("8", "c4", "0") SPDNN_FLAT_STEP("1", "%[w1]") SPDNN_FLAT_READ("9", "c4", "1") \
-    SPDNN_FLAT_STEP("2", "%[w2]") SPDNN_FLAT_READ("10", "c5", "0") SPDNN_FLAT_STEP("3", "%[w3]") SPDNN_FLAT_READ("11", "c5", "1") \
-    SPDNN_FLAT_STEP("4", "%[w4]") SPDNN_FLAT_READ("12", "c6", "0") SPDNN_FLAT_STEP("5", "%[w5]") SPDNN_FLAT_READ("13", "c6", "1") \
-    SPDNN_FLAT_STEP("6", "%[w6]") SPDNN_FLAT_READ("14", "c7", "0") SPDNN_FLAT_STEP("7", "%[w7]") SPDNN_FLAT_READ("15", "c7", "1") \
-    SPDNN_FLAT_STEP("8", "%[w8]") SPDNN_FLAT_STEP("9", "%[w9]") \
-    SPDNN_FLAT_STEP("10", "%[w10]") SPDNN_FLAT_STEP("11", "%[w11]") \
-    SPDNN_FLAT_STEP("12", "%[w12]") SPDNN_FLAT_STEP("13", "%[w13]") \
-    SPDNN_FLAT_STEP("14", "%[w14]") SPDNN_FLAT_STEP("15", "%[w15]")
-#define SPDNN_FLAT_ASM_U8 \
-    SPDNN_FLAT_READ("0", "c0", "0") SPDNN_FLAT_READ("1", "c0", "1") SPDNN_FLAT_READ("2", "c1", "0") SPDNN_FLAT_READ("3", "c1", "1") SPDNN_FLAT_READ("4", "c2", "0") SPDNN_FLAT_READ("5", "c2", "1") SPDNN_FLAT_READ("6", "c3", "0") SPDNN_FLAT_READ("7", "c3", "1") \
-    SPDNN_FLAT_STEP("0", "%[w]") SPDNN_FLAT_READ("8", "c4", "0") SPDNN_FLAT_STEP("1", "%[w]") SPDNN_FLAT_READ("9", "c4", "1") \
-    SPDNN_FLAT_STEP("2", "%[w]") SPDNN_FLAT_READ("10", "c5", "0") SPDNN_FLAT_STEP("3", "%[w]") SPDNN_FLAT_READ("11", "c5", "1") \
-    SPDNN_FLAT_STEP("4", "%[w]") SPDNN_FLAT_READ("12", "c6", "0") SPDNN_FLAT_STEP("5", "%[w]") SPDNN_FLAT_READ("13", "c6", "1") \
-    SPDNN_FLAT_STEP("6", "%[w]") SPDNN_FLAT_READ("14", "c7", "0") SPDNN_FLAT_STEP("7", "%[w]") SPDNN_FLAT_READ("15", "c7", "1") \
-    SPDNN_FLAT_STEP("8", "%[w]") SPDNN_FLAT_STEP("9", "%[w]") \
-    SPDNN_FLAT_STEP("10", "%[w]") SPDNN_FLAT_STEP("11", "%[w]") \
-    SPDNN_FLAT_STEP("12", "%[w]") SPDNN_FLAT_STEP("13", "%[w]") \
-    SPDNN_FLAT_STEP("14", "%[w]") SPDNN_FLAT_STEP("15", "%[w]")
-#define SPDNN_FLAT_ASM_W4 \
-    SPDNN_FLAT_READ("0", "c0", "0") SPDNN_FLAT_READ("1", "c0", "1") SPDNN_FLAT_READ("2", "c1", "0") SPDNN_FLAT_READ("3", "c1", "1") \
-    SPDNN_FLAT_STEP("0", "%[w0]") SPDNN_FLAT_READ("4", "c2", "0") SPDNN_FLAT_STEP("1", "%[w1]") SPDNN_FLAT_READ("5", "c2", "1") \
-    SPDNN_FLAT_STEP("2", "%[w2]") SPDNN_FLAT_READ("6", "c3", "0") SPDNN_FLAT_STEP("3", "%[w3]") SPDNN_FLAT_READ("7", "c3", "1") \
-    SPDNN_FLAT_STEP("4", "%[w4]") SPDNN_FLAT_READ("8", "c4", "0") SPDNN_FLAT_STEP("5", "%[w5]") SPDNN_FLAT_READ("9", "c4", "1") \
-    SPDNN_FLAT_STEP("6", "%[w6]") SPDNN_FLAT_READ("10", "c5", "0") SPDNN_FLAT_STEP("7", "%[w7]") SPDNN_FLAT_READ("11", "c5", "1") \
-    SPDNN_FLAT_STEP("8", "%[w8]") SPDNN_FLAT_READ("12", "c6", "0") SPDNN_FLAT_STEP("9", "%[w9]") SPDNN_FLAT_READ("13", "c6", "1") \
-    SPDNN_FLAT_STEP("10", "%[w10]") SPDNN_FLAT_READ("14", "c7", "0") SPDNN_FLAT_STEP("11", "%[w11]") SPDNN_FLAT_READ("15", "c7", "1") \
-    SPDNN_FLAT_STEP("12", "%[w12]") SPDNN_FLAT_STEP("13", "%[w13]") \
-    SPDNN_FLAT_STEP("14", "%[w14]") SPDNN_FLAT_STEP("15", "%[w15]")
-#define SPDNN_FLAT_ASM_U4 \
-    SPDNN_FLAT_READ("0", "c0", "0") SPDNN_FLAT_READ("1", "c0", "1") SPDNN_FLAT_READ("2", "c1", "0") SPDNN_FLAT_READ("3", "c1", "1") \
-    SPDNN_FLAT_STEP("0", "%[w]") SPDNN_FLAT_READ("4", "c2", "0") SPDNN_FLAT_STEP("1", "%[w]") SPDNN_FLAT_READ("5", "c2", "1") \
-    SPDNN_FLAT_STEP("2", "%[w]") SPDNN_FLAT_READ("6", "c3", "0") SPDNN_FLAT_STEP("3", "%[w]") SPDNN_FLAT_READ("7", "c3", "1") \
-    SPDNN_FLAT_STEP("4", "%[w]") SPDNN_FLAT_READ("8", "c4", "0") SPDNN_FLAT_STEP("5", "%[w]") SPDNN_FLAT_READ("9", "c4", "1") \
-    SPDNN_FLAT_STEP("6", "%[w]") SPDNN_FLAT_READ("10", "c5", "0") SPDNN_FLAT_STEP("7", "%[w]") SPDNN_FLAT_READ("11", "c5", "1") \
-    SPDNN_FLAT_STEP("8", "%[w]") SPDNN_FLAT_READ("12", "c6", "0") SPDNN_FLAT_STEP("9", "%[w]") SPDNN_FLAT_READ("13", "c6", "1") \
-    SPDNN_FLAT_STEP("10", "%[w]") SPDNN_FLAT_READ("14", "c7", "0") SPDNN_FLAT_STEP("11", "%[w]") SPDNN_FLAT_READ("15", "c7", "1") \
-    SPDNN_FLAT_STEP("12", "%[w]") SPDNN_FLAT_STEP("13", "%[w]") \
-    SPDNN_FLAT_STEP("14", "%[w]") SPDNN_FLAT_STEP("15", "%[w]")
-#define SPDNN_FLAT_ASM_W2 \
-    SPDNN_FLAT_READ("0", "c0", "0") SPDNN_FLAT_READ("1", "c0", "1") \
-    SPDNN_FLAT_STEP("0", "%[w0]") SPDNN_FLAT_READ("2", "c1", "0") SPDNN_FLAT_STEP("1", "%[w1]") SPDNN_FLAT_READ("3", "c1", "1") \
-    SPDNN_FLAT_STEP("2", "%[w2]") SPDNN_FLAT_READ("4", "c2", "0") SPDNN_FLAT_STEP("3", "%[w3]") SPDNN_FLAT_READ("5", "c2", "1") \
-    SPDNN_FLAT_STEP("4", "%[w4]") SPDNN_FLAT_READ("6", "c3", "0") SPDNN_FLAT_STEP("5", "%[w5]") SPDNN_FLAT_READ("7", "c3", "1") \
-    SPDNN_FLAT_STEP("6", "%[w6]") SPDNN_FLAT_READ("8", "c4", "0") SPDNN_FLAT_STEP("7", "%[w7]") SPDNN_FLAT_READ("9", "c4", "1") \
-    SPDNN_FLAT_STEP("8", "%[w8]") SPDNN_FLAT_READ("10", "c5", "0") SPDNN_FLAT_STEP("9", "%[w9]") SPDNN_FLAT_READ("11", "c5", "1") \
-    SPDNN_FLAT_STEP("10", "%[w10]") SPDNN_FLAT_READ("12", "c6", "0") SPDNN_FLAT_STEP("11", "%[w11]") SPDNN_FLAT_READ("13", "c6", "1") \
-    SPDNN_FLAT_STEP("12", "%[w12]") SPDNN_FLAT_READ("14", "c7", "0") SPDNN_FLAT_STEP("13", "%[w13]") SPDNN_FLAT_READ("15", "c7", "1") \
-    SPDNN_FLAT_STEP("14", "%[w14]") SPDNN_FLAT_STEP("15", "%[w15]")
-#define SPDNN_FLAT_ASM_U2 \
-    SPDNN_FLAT_READ("0", "c0", "0") SPDNN_FLAT_READ("1", "c0", "1") \
-    SPDNN_FLAT_STEP("0", "%[w]") SPDNN_FLAT_READ("2", "c1", "0") SPDNN_FLAT_STEP("1", "%[w]") SPDNN_FLAT_READ("3", "c1", "1") \
-    SPDNN_FLAT_STEP("2", "%[w]") SPDNN_FLAT_READ("4", "c2", "0") SPDNN_FLAT_STEP("3", "%[w]") SPDNN_FLAT_READ("5", "c2", "1") \
-    SPDNN_FLAT_STEP("4", "%[w]") SPDNN_FLAT_READ("6", "c3", "0") SPDNN_FLAT_STEP("5", "%[w]") SPDNN_FLAT_READ("7", "c3", "1") \
-    SPDNN_FLAT_STEP("6", "%[w]") SPDNN_FLAT_READ("8", "c4", "0") SPDNN_FLAT_STEP("7", "%[w]") SPDNN_FLAT_READ("9", "c4", "1") \
-    SPDNN_FLAT_STEP("8", "%[w]") SPDNN_FLAT_READ("10", "c5", "0") SPDNN_FLAT_STEP("9", "%[w]") SPDNN_FLAT_READ("11", "c5", "1") \
-    SPDNN_FLAT_STEP("10", "%[w]") SPDNN_FLAT_READ("12", "c6", "0") SPDNN_FLAT_STEP("11", "%[w]") SPDNN_FLAT_READ("13", "c6", "1") \
-    SPDNN_FLAT_STEP("12", "%[w]") SPDNN_FLAT_READ("14", "c7", "0") SPDNN_FLAT_STEP("13", "%[w]") SPDNN_FLAT_READ("15", "c7", "1") \
-    SPDNN_FLAT_STEP("14", "%[w]") SPDNN_FLAT_STEP("15", "%[w]")
-#define SPDNN_FLAT_IO                                                                                                   \
-    : [a0] "+v"(acc[0]), [a1] "+v"(acc[1]), [a2] "+v"(acc[2]), [a3] "+v"(acc[3])                                          \
-    : [c0] "v"(c[0]), [c1] "v"(c[1]), [c2] "v"(c[2]), [c3] "v"(c[3]), [c4] "v"(c[4]), [c5] "v"(c[5]), [c6] "v"(c[6]),       \
-      [c7] "v"(c[7]), [base] "s"(base), [R] "n"(R), [G] "n"(G), [S] "n"(flat_stride(R))
-#define SPDNN_FLAT_WEIGHTS                                                                                              \
-    , [w0] "v"(w[0]), [w1] "v"(w[1]), [w2] "v"(w[2]), [w3] "v"(w[3]), [w4] "v"(w[4]), [w5] "v"(w[5]), [w6] "v"(w[6]),       \
-        [w7] "v"(w[7]), [w8] "v"(w[8]), [w9] "v"(w[9]), [w10] "v"(w[10]), [w11] "v"(w[11]), [w12] "v"(w[12]),               \
-        [w13] "v"(w[13]), [w14] "v"(w[14]), [w15] "v"(w[15])
-#define SPDNN_FLAT_CLOBBER : "v118", "v119", "v120", "v121", "v122", "v123", "v124", "v125", "v126", "v127", "memory"
-#define SPDNN_FLAT_CASE(Q)                                                                      \
-    if constexpr (G == Q) {                                                                     \
-        if constexpr (UNI)                                                                      \
-            asm volatile(SPDNN_FLAT_ASM_U##Q SPDNN_FLAT_IO, [w] "s"(wu) SPDNN_FLAT_CLOBBER);     \
-        else                                                                                    \
-            asm volatile(SPDNN_FLAT_ASM_W##Q SPDNN_FLAT_IO SPDNN_FLAT_WEIGHTS SPDNN_FLAT_CLOBBER); \
+#define SPDNN_FLAT_ASM(ACC, W)                                                                                             \
+    ".set spdnn_k, 0\n\t"                                                                                                  \
+    ".rept %[G]\n\t" SPDNN_FLAT_READ("spdnn_k") ".set spdnn_k, spdnn_k+1\n\t"                                               \
+    ".endr\n\t"                                                                                                            \
+    ".set spdnn_k, 0\n\t"                                                                                                  \
+    ".rept 32*%[NS]\n\t"                                                                                                   \
+    ".if spdnn_k+%[G] <= 32*%[NS]\n\t"                                                                                     \
+    "s_waitcnt lgkmcnt((%[G]-1)*%[R])\n\t"                                                                                 \
+    ".else\n\t"                                                                                                            \
+    "s_waitcnt lgkmcnt((32*%[NS]-1-spdnn_k)*%[R])\n\t"                                                                     \
+    ".endif\n\t"                                                                                                           \
+    ".set spdnn_r, 0\n\t"                                                                                                  \
+    ".rept %[R]\n\t"                                                                                                       \
+    "v_fmac_f32 v[" ACC "+(spdnn_k/32)*%[R]+spdnn_r], " W ", v[112+(spdnn_k%%%[G])*%[R]+spdnn_r]\n\t"                       \
+    ".set spdnn_r, spdnn_r+1\n\t"                                                                                          \
+    ".endr\n\t"                                                                                                            \
+    ".if spdnn_k+%[G] < 32*%[NS]\n\t" SPDNN_FLAT_READ("spdnn_k+%[G]") ".endif\n\t"                                          \
+    ".set spdnn_k, spdnn_k+1\n\t"                                                                                          \
+    ".endr\n\t"
+#define SPDNN_FLAT_CLOBBER                                                                                                 \
+    "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v120", "v121", "v122", "v123", "v126", "v127", "memory"
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x32 __attribute__((ext_vector_type(32)));
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+constexpr int flat_ahead(int R) { return 12 / R; }
+#define SPDNN_FLAT_W(SUMS, REGS)                                                                                           \
+    template <int R, int NS>                                                                                               \
+    __device__ __forceinline__ void fma_flat(SUMS& acc, const u32x16 (&c)[2], const f32x32 (&w)[2], uint32_t base) {        \
+        asm volatile(SPDNN_FLAT_ASM("8", "v[48+spdnn_k]")                                                                  \
+                     : "+{" REGS "}"(acc)                                                                                  \
+                     : "{v[16:31]}"(c[0]), "{v[32:47]}"(c[1]), "{v[48:79]}"(w[0]), "{v[80:111]}"(w[1]), [base] "s"(base),   \
+                       [R] "n"(R), [G] "n"(flat_ahead(R)), [S] "n"(flat_stride(R)), [NS] "n"(NS)                            \
+                     : SPDNN_FLAT_CLOBBER);                                                                                \
     }
-template <int R, bool UNI>
-__device__ __forceinline__ void fma_flat16(float (&acc)[4], const uint32_t* c, const float* w, float wu, uint32_t base) {
-    constexpr int G = R == 1 ? 8 : R == 2 ? 4 : 2;
-    SPDNN_FLAT_CASE(8)
-    SPDNN_FLAT_CASE(4)
-    SPDNN_FLAT_CASE(2)
+SPDNN_FLAT_W(f32x2, "v[8:9]")    // sums of two neurons on one row,
+SPDNN_FLAT_W(f32x4, "v[8:11]")   // on two,
+SPDNN_FLAT_W(f32x8, "v[8:15]")   // on three or four
+template <int R, int NS>
+__device__ __forceinline__ void fma_flat(f32x16& acc, const u32x16 (&c)[4], float wu, uint32_t base) {
+    asm volatile(SPDNN_FLAT_ASM("80", "%[w]")
+                 : "+{v[80:95]}"(acc)
+                 : "{v[16:31]}"(c[0]), "{v[32:47]}"(c[1]), "{v[48:63]}"(c[2]), "{v[64:79]}"(c[3]), [w] "s"(wu), [base] "s"(base),
+                   [R] "n"(R), [G] "n"(flat_ahead(R)), [S] "n"(flat_stride(R)), [NS] "n"(NS)
+                 : SPDNN_FLAT_CLOBBER);
 }
 
 // A launch: ncb units of at most `gpu` groups of 64 neurons times Q chunks of tiles of R rows; wave w of a workgroup owns
@@ -158,8 +113,8 @@ __global__ __launch_bounds__(kBlk) void fused_flat_kernel(const float* __restric
     const int first = wi.cb * gpu;
     const int ng = min(gpu, ((N + 63) >> 6) - first);  // the unit's groups
     const int nslots = wave < ng ? (ng - wave + 15) >> 4 : 0;
-    uint32_t code[SLOTS][kNnz / 2];
-    float wv[UNI ? 1 : SLOTS][kNnz];
+    u32x16 code[SLOTS];
+    f32x32 wv[2];  // (not with one weight per layer)
     float bj[SLOTS];
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) {
@@ -174,7 +129,17 @@ __global__ __launch_bounds__(kBlk) void fused_flat_kernel(const float* __restric
             code[s][4 * c + 2] = v.z;
             code[s][4 * c + 3] = v.w;
         }
-        if constexpr (!UNI) load_weights(wv[s], lw.val, b, ln);
+        if constexpr (!UNI) {
+            const f32x4* p = reinterpret_cast<const f32x4*>(lw.val + val_entry(b, 0, ln));
+#pragma unroll
+            for (int c = 0; c < kNnz / 4; ++c) {
+                const f32x4 v = p[c * kBlk];
+                wv[s][4 * c] = v.x;
+                wv[s][4 * c + 1] = v.y;
+                wv[s][4 * c + 2] = v.z;
+                wv[s][4 * c + 3] = v.w;
+            }
+        }
         const int j = 64 * g + lane;
         bj[s] = j < N ? bias[j] : 0.0f;
     }
@@ -194,12 +159,6 @@ __global__ __launch_bounds__(kBlk) void fused_flat_kernel(const float* __restric
                     (__attribute__((address_space(3))) void*)(flat_lds + kFlatMisc + (p * R + r) * S + k * 1024), 16, 0, 0);
         }
     };
-    {  // waves of one SIMD take turns rather than meet at the LDS all at once (see fused_layer_kernel)
-        const int pw = __builtin_amdgcn_readfirstlane(3 - ((threadIdx.x >> 8) & 3));
-        if (pw == 1) __builtin_amdgcn_s_setprio(1);
-        else if (pw == 2) __builtin_amdgcn_s_setprio(2);
-        else if (pw == 3) __builtin_amdgcn_s_setprio(3);
-    }
     __syncthreads();  // the lists' scratch in front of the tiles is not touched again; rows_of has been read
     load_tile(0, 0);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -209,20 +168,27 @@ __global__ __launch_bounds__(kBlk) void fused_flat_kernel(const float* __restric
         const uint32_t base = kFlatMisc + (t & 1) * R * S;
         const int row0 = (g0 + t) * R;
         unsigned pos = 0;
+        const auto run = [&](auto NStag) {
+            constexpr int NS = decltype(NStag)::value;
+            std::conditional_t<UNI, f32x16, std::conditional_t<R == 1, f32x2, std::conditional_t<R == 2, f32x4, f32x8>>> acc = {};
+            if constexpr (UNI) fma_flat<R, NS>(acc, code, wuni, base);
+            else fma_flat<R, NS>(acc, code, wv, base);
 #pragma unroll
-        for (int s = 0; s < SLOTS; ++s) {
-            if (s < nslots) {
-                float acc[4] = {0.f, 0.f, 0.f, 0.f};
-                fma_flat16<R, UNI>(acc, &code[s][0], UNI ? nullptr : &wv[UNI ? 0 : s][0], wuni, base);
-                fma_flat16<R, UNI>(acc, &code[s][8], UNI ? nullptr : &wv[UNI ? 0 : s][16], wuni, base);
+            for (int s = 0; s < NS; ++s) {
                 const int j = 64 * (first + 16 * s + wave) + lane;
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    const float y = j < N ? fminf(fmaxf(acc[r] + bj[s], 0.0f), kClip) : 0.0f;
+                    const float y = j < N ? fminf(fmaxf(acc[s * R + r] + bj[s], 0.0f), kClip) : 0.0f;
                     if (__builtin_amdgcn_ballot_w64(y > 0.0f) != 0ull) pos |= 1u << r;
                     if (j < N && row0 + r < A) __builtin_nontemporal_store(y, Yout + (size_t)(row0 + r) * N + j);
                 }
             }
+        };
+        if (nslots == SLOTS) run(std::integral_constant<int, SLOTS>{});
+        else if (nslots == 1) run(std::integral_constant<int, 1>{});
+        else if constexpr (UNI) {
+            if (nslots == 2) run(std::integral_constant<int, 2>{});
+            else if (nslots == 3) run(std::integral_constant<int, 3>{});
         }
         if (lane < R && row0 + lane < A && ((pos >> lane) & 1u)) flags[row0 + lane] = 1;  // lane r speaks for row r of the tile
         // The next tile has landed when at most the stores behind its loads are still under way.

@@ -174,13 +174,6 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
             bj[b] = j < N ? bias[j] : -__builtin_inff();
         }
     }
-    {  // waves of one SIMD take turns rather than meet at the LDS all at once (see fused_layer_kernel)
-        const int pw = __builtin_amdgcn_readfirstlane(3 - ((threadIdx.x >> 8) & 3));
-        if (pw == 1) __builtin_amdgcn_s_setprio(1);
-        else if (pw == 2) __builtin_amdgcn_s_setprio(2);
-        else if (pw == 3) __builtin_amdgcn_s_setprio(3);
-    }
-
     // Connections, fetched ahead: slots a whole group of 64 neurons (4 chunks of 8), weights two chunks.
     // (Address spaces are spelled out: as generic pointers these loads would wait, and be waited for, with the LDS reads.)
     u32x4 cbuf[4];
@@ -275,12 +268,13 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
 
             // Layers l .. as long as PP planes are needed: a loop of its own for every number of planes.
             int l = la;
+            ResidentLayer cur = first, nxt = layer_at(la + 1 < lb ? la + 1 : la);
             auto layers = [&](auto Ptag) {
                 constexpr int PP = decltype(Ptag)::value;
                 while (l < lb && P == PP) {
-                    const ResidentLayer cur = layer_at(l);
-                    // after the last layer comes, for the connections, the next pass's first
-                    const ResidentLayer nxt = layer_at(l + 1 < lb ? l + 1 : la);
+                    // Descriptors are asked for a layer ahead.  After the last layer comes, for the connections, the next
+                    // pass's first.
+                    const ResidentLayer after = layer_at(l + 2 < lb ? l + 2 : la);
                     gu32* q_next = (gu32*)(uintptr_t)(l + 1 < lb ? nxt.qsel : q_out);
                     int jn[NB];       // my neurons
                     uint32_t at[NB];  // where their outputs go
@@ -366,18 +360,18 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
                         }
                     if (lane == 0 && pos) atomicOr(&live_word[l & 1], pos);
                     __syncthreads();  // every wave has read what it needs of the rows
-                    live &= __builtin_amdgcn_readfirstlane(live_word[l & 1]);
+                    const uint32_t raised = live_word[l & 1];  // (on its way while the results go out)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        if (b < nb_w && jn[b] < N)
+#pragma unroll
+                            for (int p = 0; p < PP; ++p) *reinterpret_cast<lds_f4*>(at[b] + 256u * p) = res[b][p];
+                    }
+                    live &= __builtin_amdgcn_readfirstlane(raised);
                     if (tid == 0) live_word[(l + 1) & 1] = 0u;
                     const int n = __popc(live);
                     P = (n + kRows - 1) / kRows;
-                    if (P == PP) {
-#pragma unroll
-                        for (int b = 0; b < NB; ++b) {
-                            if (b < nb_w && jn[b] < N)
-#pragma unroll
-                                for (int p = 0; p < PP; ++p) *reinterpret_cast<lds_f4*>(at[b] + 256u * p) = res[b][p];
-                        }
-                    } else if (n > 0) {  // fewer planes will do: the survivors move together
+                    if (P < PP && n > 0) {  // fewer planes will do: the survivors move together, over what was just written
                         using lds_f = __attribute__((address_space(3))) float;
 #pragma unroll
                         for (int b = 0; b < NB; ++b) {
@@ -400,6 +394,8 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
                     }
                     __syncthreads();
                     if (tid == 0 && n > 0 && ra.layer_rows) atomicAdd(&ra.layer_rows[l + 1], n);
+                    cur = nxt;
+                    nxt = after;
                     ++l;
                 }
             };

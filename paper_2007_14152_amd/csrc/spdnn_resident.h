@@ -133,6 +133,14 @@ __device__ __forceinline__ void res_fma8(f32x4 (&acc)[P], u32x4 codes, float wu,
     SPDNN_RES_CASE(4)
 }
 
+// A wave's issue priority inside its SIMD (p: a constant once loops are unrolled).
+__device__ __forceinline__ void set_wave_prio(int p) {
+    if (p == 0) __builtin_amdgcn_s_setprio(0);
+    else if (p == 1) __builtin_amdgcn_s_setprio(1);
+    else if (p == 2) __builtin_amdgcn_s_setprio(2);
+    else __builtin_amdgcn_s_setprio(3);
+}
+
 // NB = most groups of 64 neurons a wave owns, PM = most planes.  blockDim.x = 64 * W with W = ceil(U / NB),
 // U = ceil(N / 64) groups of 64 neurons; wave w owns the groups w, w + W, ...  Every workgroup has a run of
 // neighbouring rows.
@@ -305,6 +313,7 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
                             if constexpr (MODE != kResParts) {
 #pragma unroll
                                 for (int c = 0; c < 4; ++c) {
+                                    if ((b * 4 + c) % NB == 0) set_wave_prio(3 - (b * 4 + c) / NB);
                                     res_fma8<PP, MODE == kResUniform>(acc, cbuf[c], cur.wuni, wbuf[2 * (c & 1)], wbuf[2 * (c & 1) + 1]);
                                     fetch_codes(next, c);
                                     if (c < 2) fetch_weights(mine, c + 2);
@@ -317,6 +326,7 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
                                 // 32 connections per turn; a chunk's registers are refilled with the group's next chunk for
                                 // them, or with the next group's first
                                 size_t off = 0;
+                                set_wave_prio(3 - b * 4 / NB);
                                 for (int g = 0; g == 0 || 4 * g < mine.nch; ++g, off += ra.part_stride) {
 #pragma unroll
                                     for (int i = 0; i < 4; ++i) {
@@ -347,6 +357,7 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
                                 for (int r = 0; r < kRows; ++r) res[b][p][r] = fminf(fmaxf(res[b][p][r] + bj[b], 0.0f), kClip);
                         }
                     }
+                    set_wave_prio(3);
                     // which rows have a positive output in my neurons
                     uint32_t pos = 0;
 #pragma unroll

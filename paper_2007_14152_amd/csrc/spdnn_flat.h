@@ -50,6 +50,9 @@ SPDNN_HD inline int flat_lds_bytes(int rows) { return kFlatMisc + 2 * rows * fla
     ".endr\n\t"                                                                                                            \
     ".set spdnn_k, 0\n\t"                                                                                                  \
     ".rept 32*%[NS]\n\t"                                                                                                   \
+    ".if (spdnn_k%%(8*%[NS]))==0\n\t"                                                                                      \
+    "s_setprio 3-spdnn_k/(8*%[NS])\n\t" /* see set_wave_prio */                                                           \
+    ".endif\n\t"                                                                                                         \
     ".if spdnn_k+%[G] <= 32*%[NS]\n\t"                                                                                     \
     "s_waitcnt lgkmcnt((%[G]-1)*%[R])\n\t"                                                                                 \
     ".else\n\t"                                                                                                            \
@@ -173,6 +176,7 @@ __global__ __launch_bounds__(kBlk) void fused_flat_kernel(const float* __restric
             std::conditional_t<UNI, f32x16, std::conditional_t<R == 1, f32x2, std::conditional_t<R == 2, f32x4, f32x8>>> acc = {};
             if constexpr (UNI) fma_flat<R, NS>(acc, code, wuni, base);
             else fma_flat<R, NS>(acc, code, wv, base);
+            set_wave_prio(3);
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 const int j = 64 * (first + 16 * s + wave) + lane;

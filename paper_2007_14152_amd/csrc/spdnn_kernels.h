@@ -75,6 +75,18 @@ constexpr uint32_t kPadSlot = kCap;
 // lane with all their steps in registers (2 x 32 = 4 x 16 = 64 steps per neuron).
 __host__ __device__ inline int wide_steps(int nstage) { return nstage > 8 ? 8 : nstage <= 2 ? 32 : 16; }
 
+// A wave's issue priority inside its SIMD (p: a constant once loops are unrolled).  Kernels bound by what the CU does start
+// a step at 3 and go down as they get through it: the four waves of a SIMD are otherwise served oldest first, the first is done when the last
+// is half way, and the last then has the LDS for itself and waits for it.  Whole
+// passes: resident_kernel -8 % at 1024 neurons, -6 % at 4096; fused_row2_kernel -5 %, fused_flat_kernel -5 %.  Not for
+// fused_pair_kernel, which memory bounds (+4 % at 65536 neurons: a fixed order of the waves spreads its loads).
+__device__ __forceinline__ void set_wave_prio(int p) {
+    if (p == 0) __builtin_amdgcn_s_setprio(0);
+    else if (p == 1) __builtin_amdgcn_s_setprio(1);
+    else if (p == 2) __builtin_amdgcn_s_setprio(2);
+    else __builtin_amdgcn_s_setprio(3);
+}
+
 // Where connection `step` of lane `lane` of output block b is kept in LayerWeights::rel and ::val.
 __device__ __forceinline__ size_t rel_entry(int b, int step, int lane) {
     return (((size_t)b * (kNnz / 8) + (step >> 3)) * kBlk + lane) * 8 + (step & 7);

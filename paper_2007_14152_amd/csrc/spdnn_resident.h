@@ -133,14 +133,6 @@ __device__ __forceinline__ void res_fma8(f32x4 (&acc)[P], u32x4 codes, float wu,
     SPDNN_RES_CASE(4)
 }
 
-// A wave's issue priority inside its SIMD (p: a constant once loops are unrolled).
-__device__ __forceinline__ void set_wave_prio(int p) {
-    if (p == 0) __builtin_amdgcn_s_setprio(0);
-    else if (p == 1) __builtin_amdgcn_s_setprio(1);
-    else if (p == 2) __builtin_amdgcn_s_setprio(2);
-    else __builtin_amdgcn_s_setprio(3);
-}
-
 // NB = most groups of 64 neurons a wave owns, PM = most planes.  blockDim.x = 64 * W with W = ceil(U / NB),
 // U = ceil(N / 64) groups of 64 neurons; wave w owns the groups w, w + W, ...  Every workgroup has a run of
 // neighbouring rows.

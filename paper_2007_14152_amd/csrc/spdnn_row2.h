@@ -293,6 +293,7 @@ __global__ __launch_bounds__(kBlk) void fused_row2_kernel(
 #pragma unroll
                     for (int i = 0; i < every; ++i) load_piece(4 * h + b + i);
                 }
+                if (b % 2 == 0) set_wave_prio(3 - (4 * h + b) / 2);
                 fma_row2_block16(b < 2 ? a0 : a1, &p[2 * h + (b >> 1)][8 * (b & 1)], wuni, s3);
             }
             const float b0 = *reinterpret_cast<const lds_f1*>(bias_addr + (2 * h) * (4 * kBlk));
@@ -307,6 +308,7 @@ __global__ __launch_bounds__(kBlk) void fused_row2_kernel(
                 __builtin_nontemporal_store(f32x4{y0, y1, y2, y3}, reinterpret_cast<f32x4*>(out_row + (out_row_off + 4u * nrn)));  // see finish_rows
             }
         }
+        set_wave_prio(3);
         if (lane < nlive && ((pos >> lane) & 1u)) flags[row0 + lane] = 1;  // lane r raises row r's flag
         __syncthreads();  // every wave is done reading tile t
         if (more) {

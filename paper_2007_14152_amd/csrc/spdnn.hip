@@ -1152,9 +1152,10 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
     }
     // Runs of layers.  In one launch the workgroups pack their shares together once, behind the first two layers, if
     // they are of several passes.  Otherwise the batch is compacted and shared out anew after two layers, where most
-    // of the rows that die have died.  If fewer than a quarter died, all layers that are left are one launch; if
-    // not, the next run is four times as long, and so on.  (A launch costs the gap before it, 20 us, and the rows'
-    // way through memory; a share of rows that die unevenly costs the workgroups' waiting for the fullest one.)
+    // of the rows that die have died.  If fewer than a quarter died, or not many layers are left, they are one launch;
+    // if not, the next run is four times as long, and so on.  (A launch costs the gap before it, 20 us, and the rows'
+    // way through memory, together what two to three layers of 4096 neurons take; passes whose rows die unevenly
+    // afterwards may cost a third of what is left.)
     struct Run {
         int32_t l0, l1;
     };
@@ -1165,7 +1166,7 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
     int32_t k = 0;     // launches so far
     int32_t len = 2;   // layers of the next run
     for (int32_t l0 = 0; l0 < L; ++k, len *= 4) {
-        const bool rest = one || (k > 0 && (int64_t)alive * 4 > (int64_t)before * 3) || len >= L - l0;
+        const bool rest = one || (k > 0 && ((int64_t)alive * 4 > (int64_t)before * 3 || L - l0 <= 32)) || len >= L - l0;
         const int32_t l1 = rest ? L : l0 + len;
         const ResidentShape shape = resident_shape(h, alive);
         const int32_t groups = (alive + spdnn::kRows - 1) / spdnn::kRows;

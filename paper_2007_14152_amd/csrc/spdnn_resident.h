@@ -229,7 +229,10 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
         int i1 = 0;
         for (int pass = 0; pass < npass; ++pass) {
             const int i0 = i1;  // this pass: rows i0 .. i1 - 1 of the share (seg 1: of the list of survivors)
-            i1 = min(nalive, (int)(((pass + 1) * quads) / npass) * kRows);
+            // (the shorter passes first in one half of the workgroups, last in the other: the passes get out of step, and
+            // with them the workgroups' turns at the memory)
+            const int upto = (wg & 1) ? quads - ((npass - 1 - pass) * quads) / npass : ((pass + 1) * quads) / npass;
+            i1 = min(nalive, upto * kRows);
             const int n0 = i1 - i0;
             int P = (n0 + kRows - 1) / kRows;
             uint32_t live = n0 >= 32 ? 0xffffffffu : (1u << n0) - 1u;

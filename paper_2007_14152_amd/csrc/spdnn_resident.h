@@ -225,7 +225,8 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
         const int quads = (nalive + kRows - 1) / kRows;
         const int npass = (quads + PM - 1) / PM;
         int kept = 0;         // rows alive at the end of the passes so far
-        bool primed = false;  // cbuf / wbuf hold the first group's connections of layer la
+        bool primed = false;  // cbuf / wbuf hold the first group's connections of layer la ...
+        Item ahead{};         // ... which is this (in general: the group whose connections come next)
         int i1 = 0;
         for (int pass = 0; pass < npass; ++pass) {
             const int i0 = i1;  // this pass: rows i0 .. i1 - 1 of the share (seg 1: of the list of survivors)
@@ -243,11 +244,11 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
             if (seg == 0 && tid < n0) flags[r0 + rid] = 0;  // wave 0, like every other store to the flags
             if (tid < 2) live_word[tid] = 0u;
             if (!primed) {
-                const Item it = item(first, 0);
+                ahead = item(first, 0);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) fetch_codes(it, c);
-                fetch_weights(it, 0);
-                fetch_weights(it, 1);
+                for (int c = 0; c < 4; ++c) fetch_codes(ahead, c);
+                fetch_weights(ahead, 0);
+                fetch_weights(ahead, 1);
             }
             __syncthreads();  // also: the pass before has left the tile
             const int n4 = N >> 2;
@@ -275,9 +276,6 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
             auto layers = [&](auto Ptag) {
                 constexpr int PP = decltype(Ptag)::value;
                 while (l < lb && P == PP) {
-                    // Descriptors are asked for a layer ahead.  After the last layer comes, for the connections, the next
-                    // pass's first.
-                    const ResidentLayer after = layer_at(l + 2 < lb ? l + 2 : la);
                     gu32* q_next = (gu32*)(uintptr_t)(l + 1 < lb ? nxt.qsel : q_out);
                     int jn[NB];       // my neurons
                     uint32_t at[NB];  // where their outputs go
@@ -303,8 +301,9 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
                             f32x4 acc[PP];
 #pragma unroll
                             for (int p = 0; p < PP; ++p) acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
-                            const Item mine = item(cur, b);
+                            const Item mine = ahead;
                             const Item next = b + 1 < nb_w ? item(cur, b + 1) : item(nxt, 0);
+                            ahead = next;
                             if constexpr (MODE != kResParts) {
 #pragma unroll
                                 for (int c = 0; c < 4; ++c) {
@@ -353,6 +352,9 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
                         }
                     }
                     set_wave_prio(3);
+                    // Descriptors are asked for a layer ahead, and not before the arithmetic: its waits for the LDS would wait
+                    // for them too.  After the last layer comes, for the connections, the next pass's first.
+                    const ResidentLayer after = layer_at(l + 2 < lb ? l + 2 : la);
                     // which rows have a positive output in my neurons
                     uint32_t pos = 0;
 #pragma unroll

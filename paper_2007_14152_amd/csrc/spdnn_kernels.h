@@ -2311,7 +2311,7 @@ __global__ __launch_bounds__(64) void pair_merge_kernel(int2* __restrict__ win, 
 // column first.  Measured on the 65536-neuron patterns: busiest quad 33.6 on average,
 // 4.3 LDS cycles per 64-lane read instead of 5.7 (4 is conflict-free).
 //
-// One wave per output block.  Output: slot_tab[b][c] = LDS slot of stage-local column
+// Four waves per output block or unit.  Output: slot_tab[b][c] = LDS slot of stage-local column
 // c, qsel[b][t] = quads (times 16, one per byte) of staging lane t's four columns.
 // A layer with a wider window is left alone (order_pack_kernel then uses col_slot()).
 // UB = output blocks per unit: 1, or 2 for layers that run two neurons per lane, or all of
@@ -2324,7 +2324,8 @@ struct BalanceScratch {
     uint32_t load[UB * kBlk / kGroup][8];  // connections lane set S already has in quad q, two quads to a word
     uint16_t cost[16][16];
 };
-constexpr int kBalanceThreads = 64;
+constexpr int kBalanceThreads = 256;
+constexpr int kBalanceSub = kBalanceThreads / 16;  // lanes that share a column's connections
 template <int UB>
 __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const int32_t* __restrict__ idx, int N,
                                                                   const int2* __restrict__ win,
@@ -2339,6 +2340,7 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const int32_t*
     const int b = blockIdx.x * UB;
     const int lane = threadIdx.x;
     const int c_lo = win[b].x;
+    const int ngroups = (win[b].y + 255) / 256 * 16;  // store groups with columns of the window
     for (int c = lane; c < kCap; c += kBalanceThreads) B.cursor[c] = 0;
     for (int i = lane; i < UB * (kBlk / kGroup) * 8; i += kBalanceThreads) (&B.load[0][0])[i] = 0;
     __syncthreads();
@@ -2361,11 +2363,15 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const int32_t*
         uint32_t sum = 0;
         for (int i = 0; i < per; ++i) sum += B.cursor[lane * per + i];
         uint32_t incl = sum;
-        for (int d = 1; d < kBalanceThreads; d <<= 1) {
+        for (int d = 1; d < 64; d <<= 1) {
             const uint32_t v = __shfl_up(incl, d);
-            if (lane >= d) incl += v;
+            if ((lane & 63) >= d) incl += v;
         }
+        uint32_t* wave_sum = reinterpret_cast<uint32_t*>(&B.cost[0][0]);
+        if ((lane & 63) == 63) wave_sum[lane >> 6] = incl;
+        __syncthreads();
         uint32_t run = incl - sum;
+        for (int w = 0; w < (lane >> 6); ++w) run += wave_sum[w];
         for (int i = 0; i < per; ++i) {
             const uint32_t n = B.cursor[lane * per + i];
             B.cursor[lane * per + i] = run;
@@ -2383,12 +2389,12 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const int32_t*
     __syncthreads();
     auto ofs = [&](int c) -> uint32_t { return c ? B.cursor[c - 1] : 0u; };  // where column c's entries start
 
-    // Cost phase: lanes 4 i .. 4 i + 3 share column i of the group, each takes every fourth of its connections
-    // and adds up, for all 16 quads, what the connections' lane sets already hold there.
-    const int row = lane >> 2;
-    const int sub = lane & 3;
+    // Cost phase: 16 lanes share a column of the group, each takes every sixteenth of its connections and adds up, for
+    // all 16 quads, what the connections' lane sets already hold there.
+    const int row = lane / kBalanceSub;
+    const int sub = lane % kBalanceSub;
     uint32_t packed = 0;  // lanes 0..15: quads (times 16) chosen so far for the staging lane's columns
-    for (int g = 0; g < kCap / 16; ++g) {
+    for (int g = 0; g < ngroups; ++g) {
         const int a = g & 3, set = (g >> 2) & 3, wave = g >> 4;
         auto column_of = [&](int i) { return 4 * (wave * 64 + lane_of_group(set, i)) + a; };
         const int c_row = column_of(row);
@@ -2411,7 +2417,7 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const int32_t*
             uint32_t acc[16];
 #pragma unroll
             for (int q = 0; q < 16; ++q) acc[q] = 0;
-            for (uint32_t e = e0 + sub; e < e1; e += 4) {
+            for (uint32_t e = e0 + sub; e < e1; e += kBalanceSub) {
                 const uint4* ld = reinterpret_cast<const uint4*>(&B.load[B.ent[e]][0]);
 #pragma unroll
                 for (int v = 0; v < 2; ++v) {
@@ -2428,8 +2434,10 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const int32_t*
             }
 #pragma unroll
             for (int q = 0; q < 16; ++q) {
-                acc[q] += (uint32_t)__builtin_amdgcn_mov_dpp((int)acc[q], 0xB1, 0xF, 0xF, true);  // lanes ^ 1
-                acc[q] += (uint32_t)__builtin_amdgcn_mov_dpp((int)acc[q], 0x4E, 0xF, 0xF, true);  // lanes ^ 2
+                acc[q] += (uint32_t)__builtin_amdgcn_mov_dpp((int)acc[q], 0x128, 0xF, 0xF, true);  // rotated by 8, 4, 2, 1 in the
+                acc[q] += (uint32_t)__builtin_amdgcn_mov_dpp((int)acc[q], 0x124, 0xF, 0xF, true);  // row of 16 lanes
+                acc[q] += (uint32_t)__builtin_amdgcn_mov_dpp((int)acc[q], 0x122, 0xF, 0xF, true);
+                acc[q] += (uint32_t)__builtin_amdgcn_mov_dpp((int)acc[q], 0x121, 0xF, 0xF, true);
             }
             if (sub == 0) {
                 uint32_t* out = reinterpret_cast<uint32_t*>(&B.cost[rank_row][0]);
@@ -2452,10 +2460,10 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const int32_t*
             if (rank == it) chosen = q;
             if ((lane & 15) == q) quad_free = false;
         }
-        // the chosen quads take the columns' connections on board (all 64 lanes: column `row`, every fourth entry)
+        // the chosen quads take the columns' connections on board (all lanes: column `row`, every sixteenth entry)
         {
             const int ch = __shfl(chosen, row);
-            for (uint32_t e = e0 + sub; e < e1; e += 4) atomicAdd(&B.load[B.ent[e]][ch >> 1], 1u << (16 * (ch & 1)));
+            for (uint32_t e = e0 + sub; e < e1; e += kBalanceSub) atomicAdd(&B.load[B.ent[e]][ch >> 1], 1u << (16 * (ch & 1)));
         }
         if (lane < 16) {
             slot_tab[(size_t)b * kCap + c_mine] = (uint16_t)((g << 4) | chosen);

@@ -15,6 +15,10 @@
 // rule: lanes l and l + 32 never collide, columns that are equal mod 32 do), so the set-up orders the connections of
 // 32 neighbouring neurons like row2_pack_kernel, with bank = column mod 32 (flat_pack_kernel).  Every neuron's 32
 // products are one chain of fused multiply-adds in that order, bias last.
+//
+// What bounds it: the LDS reads, 3.1 clocks each with the conflicts the ordering leaves, and next to them the rows'
+// way into LDS.  16384 neurons with weights of their own, 6 layers, 8000 rows: 5.42 -> 2.75 ms (one neuron per lane and
+// the row in four stages before, so every row went to 16 workgroups).
 #pragma once
 
 namespace spdnn {

@@ -3,7 +3,7 @@
 // A workgroup that computes EVERY neuron of the rows it is given has the next layer's input in its own hands: rows
 // are independent (Eq. 1), so it can take a few rows through many layers without touching memory in between.  Up to
 // 4096 columns fit: a pass holds 4 * P feature rows as P planes of 4 rows (an entry = 4 rows of one column, 16
-// bytes), P <= 8, 4, 2 for 1, 2, 3-4 output blocks of 1024 neurons: at most 128 KB of LDS.  What moves instead are
+// bytes), P = 4 for 1 and 2, 2 for 3 and 4 output blocks of 1024 neurons: at most 128 KB of LDS.  What moves instead are
 // the connections, which every workgroup reads once per layer and pass (64 KB per 1024 neurons where the layer has
 // one weight, 192 KB otherwise) straight into registers, a neuron-group ahead of their use.  A layer is
 //
@@ -23,14 +23,15 @@
 // clocks, a fifth of that bank conflicts, vector instructions 72 %).  Weights of their own at 4096 neurons: the stream of
 // connections, 768 KB per layer and pass, which a CU pulls out of L2 at 25 bytes per clock.  One workgroup on its own:
 // latency.  The copies between LDS and memory happen once per launch instead of once per layer.
-// Whole passes, one launch per layer -> this kernel: 1000 rows x 120 layers of 1024 neurons 0.85 -> 0.28 ms, 60 000 rows
-// 7.40 -> 5.12; neurons of 16 to 64 connections, 4096 of them, 6 layers, 10 000 rows 1.26 -> 0.75 (several lanes per
-// neuron and two launches per layer before), 0 to 40 connections, 1500 neurons, 12 layers, 777 rows 309 -> 87 us; 4096 neurons, 24 layers, 60 000 rows 5.82 -> 5.19; 10 007 rows, 12 layers with weights of their own
-// 1.19 -> 0.95; one row, 12 layers of 1024 neurons 133 -> 67 us.
+// Whole passes, one launch per layer -> this kernel: 120 layers of 1024 neurons, 1000 rows 0.85 -> 0.27 ms, 60 000 rows
+// 7.40 -> 4.70; 24 layers of 4096 neurons, 60 000 rows 5.85 -> 4.59; 12 of them with weights of their own, 10 007 rows
+// 1.19 -> 0.88; 6 with 16 to 64 connections per neuron, 10 000 rows 1.26 -> 0.72 (several lanes per neuron and two
+// launches per layer before); 12 layers of 1500 neurons with 0 to 40 connections, 777 rows 309 -> 86 us; 12 layers of
+// 1024 neurons, one row 133 -> 60 us.
 //
 // Workgroups.  Networks of one block whose rows are more than a quad per CU run two workgroups per CU of eight waves
 // (two groups of 64 neurons per wave), so that one computes while the other writes or waits at a barrier (120 layers,
-// 60 000 rows: 5.19 -> 5.12 ms against one workgroup with eight planes); fewer rows, one of sixteen waves.
+// 60 000 rows, when this was chosen: 5.12 ms against 5.19 for one workgroup with eight planes); fewer rows, one of sixteen waves.
 #pragma once
 
 namespace spdnn {

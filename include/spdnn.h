@@ -32,7 +32,7 @@ extern "C" {
 #endif
 
 typedef struct spdnn_model* spdnn_t; /* opaque; owns small host metadata, two HIP events and a
-                                        pinned host array of L+1 counters, nothing the caller allocated */
+                                        pinned host array of L+2 counters, nothing the caller allocated */
 
 enum {
     SPDNN_OK = 0,
@@ -234,9 +234,10 @@ int spdnn_set_profiling(spdnn_t h, int32_t on);
 int spdnn_get_profile(spdnn_t h, int32_t cap, int32_t* layers_run, int32_t* rows_in,
                       float* fused_ms);
 
-/* Measurement and test aid: which of the library's per-layer fused kernels layer l is set up for (models of at most
- * 4096 neurons whose weights are resident run their layers inside one kernel of their own instead), chosen at
- * spdnn_create from the layer's pattern (Section III-A-2's shared-memory stages) and weights:
+/* Measurement and test aid: which of the library's per-layer fused kernels layer l is set up for, chosen at
+ * spdnn_create from the layer's pattern (Section III-A-2's shared-memory stages) and weights.  Models of at most 4096
+ * neurons whose weights are resident keep their rows on the chip over several layers in a kernel of their own instead
+ * (spdnn_get_launches tells what the last inference ran).
  * SPDNN_KERNEL_SINGLE  every 1024-neuron block's column window fits one LDS stage;
  * SPDNN_KERNEL_STAGED  two stages (or a wider pattern that does not fit the wide format);
  * SPDNN_KERNEL_WIDE    three or more stages;
@@ -247,6 +248,8 @@ int spdnn_get_profile(spdnn_t h, int32_t cap, int32_t* layers_run, int32_t* rows
  *                      registers).
  * SPDNN_KERNEL_ROW2    one weight, N a multiple of 4096, windows wider than one stage but every
  *                      4096-neuron unit within 16384 columns: four neurons per lane, tiles of two rows.
+ * SPDNN_KERNEL_FLAT    N at most 16384, at most 32 connections per neuron, windows of two or more stages and none of
+ *                      the kernels for one weight above: whole rows side by side in LDS.
  * Returns SPDNN_EINVAL for a NULL handle or pointer or l outside [0, L). */
 /* (A layer of several passes reports the kernel of its first pass.) */
 #define SPDNN_KERNEL_SINGLE 0
@@ -256,18 +259,24 @@ int spdnn_get_profile(spdnn_t h, int32_t cap, int32_t* layers_run, int32_t* rows
 #define SPDNN_KERNEL_WIDE_PAIR 4
 #define SPDNN_KERNEL_WIDE_PAIR4 5
 #define SPDNN_KERNEL_ROW2 6
+#define SPDNN_KERNEL_FLAT 7
 int spdnn_layer_kernel(spdnn_t h, int32_t l, int32_t* kind);
 
-/* Whether spdnn_infer on `batch` rows runs all layers of the model in ONE launch (*yes = 1).  Answered for models of
- * at most 1024 neurons per layer (one workgroup then computes every neuron of its rows, so Listing 1's loop over the
- * layers -- kernel, pruning, buffer swap -- can run inside the workgroup) whose layers all fit one LDS stage: 1 when a
- * workgroup's share of the rows is small (at most 128).  Larger batches, and models of up to 4096 neurons (always
- * reported as 0), keep their rows on the chip for several layers per launch.  With profiling on, a launch's duration is
- * shared out among its layers in proportion to the rows they had (spdnn_get_profile). */
+/* Whether spdnn_infer on `batch` rows runs all layers of the model in ONE launch (*yes = 1).  Models of at most 4096
+ * neurons per layer whose weights are resident do so -- one workgroup then computes every neuron of its rows, so
+ * Listing 1's loop over the layers (kernel, pruning, buffer swap) can run inside the workgroup -- when a workgroup's
+ * share of the rows is small: at most 128 rows for models of at most 1024 neurons, what it holds at a time for larger
+ * ones.  Larger batches keep their rows on the chip for several layers per launch.  With profiling on, a launch's
+ * duration is shared out among its layers in proportion to the rows they had (spdnn_get_profile). */
 int spdnn_one_launch(spdnn_t h, int32_t batch, int32_t* yes);
 
-/* Number of fused-kernel launches (passes) layer l takes: 1, or for a general layer whose
- * longest neuron has K > 32 connections ceil(K/32) rounded up to a power of two. */
+/* Measurement and test aid: what the last spdnn_infer (or _static, _host: all its batches) on this handle launched.
+ * *launches = fused kernels (any number of layers each), *resident (may be NULL) = those among them that kept their
+ * rows on the chip from layer to layer. */
+int spdnn_get_launches(spdnn_t h, int32_t* launches, int32_t* resident);
+
+/* Passes of layer l -- its share of the weights arena, and, where layers are launched one by one, the most launches it
+ * takes: 1, or for a general layer whose longest neuron has K > 32 connections ceil(K/32) rounded up to a power of two. */
 int spdnn_layer_passes(spdnn_t h, int32_t l, int32_t* passes);
 
 #ifdef __cplusplus

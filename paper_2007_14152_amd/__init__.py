@@ -28,15 +28,17 @@ SPDNN_KERNEL_PAIR = 3
 SPDNN_KERNEL_WIDE_PAIR = 4
 SPDNN_KERNEL_WIDE_PAIR4 = 5
 SPDNN_KERNEL_ROW2 = 6
+SPDNN_KERNEL_FLAT = 7
 
 EXPORTS = ("spdnn_weights_bytes", "spdnn_work_bytes", "spdnn_create", "spdnn_infer", "spdnn_destroy",
            "spdnn_last_error", "spdnn_set_profiling", "spdnn_get_profile", "spdnn_infer_static",
            "spdnn_host_work_bytes", "spdnn_infer_host",
            "spdnn_weights_bytes_for_window", "spdnn_scan_windows", "spdnn_layer_kernel",
            "spdnn_csr_passes", "spdnn_create_csr", "spdnn_layer_passes", "spdnn_ooc_bytes", "spdnn_create_ooc",
-           "spdnn_one_launch")
+           "spdnn_one_launch", "spdnn_get_launches")
 KERNEL_NAMES = {0: "fused_layer_kernel<false>", 1: "fused_layer_kernel<true>", 2: "fused_wide_kernel",
-                3: "fused_pair_kernel", 4: "fused_wide_pair_kernel", 5: "fused_wide_pair4_kernel", 6: "fused_row2_kernel"}
+                3: "fused_pair_kernel", 4: "fused_wide_pair_kernel", 5: "fused_wide_pair4_kernel", 6: "fused_row2_kernel",
+                7: "fused_flat_kernel"}
 
 
 class SpdnnError(RuntimeError):
@@ -72,6 +74,7 @@ def lib():
         L.spdnn_layer_kernel.argtypes = [vp, i32, ctypes.POINTER(i32)]
         L.spdnn_layer_passes.argtypes = [vp, i32, ctypes.POINTER(i32)]
         L.spdnn_one_launch.argtypes = [vp, i32, ctypes.POINTER(i32)]
+        L.spdnn_get_launches.argtypes = [vp, ctypes.POINTER(i32), ctypes.POINTER(i32)]
         L.spdnn_ooc_bytes.argtypes = [i32, i32, i32, ctypes.POINTER(sz), ctypes.POINTER(sz)]
         L.spdnn_create_ooc.argtypes = [ctypes.POINTER(vp), i32, i32, ctypes.POINTER(vp), ctypes.POINTER(vp), vp,
                                        i32, vp, sz, vp, sz, vp]
@@ -208,14 +211,14 @@ def spdnn_get_profile(h, cap: int):
 
 
 def spdnn_layer_kernel(h, l: int) -> int:
-    """Kernel kind (SPDNN_KERNEL_*: 0 single, 1 staged, 2 wide, 3 pair, 4 wide pair, 5 wide pair of 3-4 stages) of layer l."""
+    """Kernel kind (SPDNN_KERNEL_*, named in KERNEL_NAMES) that layer l is set up for."""
     k = ctypes.c_int32(-1)
     _check(lib().spdnn_layer_kernel(ctypes.c_void_p(h), l, ctypes.byref(k)))
     return k.value
 
 
 def spdnn_layer_passes(h, l: int) -> int:
-    """Fused-kernel passes of layer l (1 unless some neuron has more than 32 connections)."""
+    """Passes of layer l (1 unless some neuron has more than 32 connections)."""
     k = ctypes.c_int32(-1)
     _check(lib().spdnn_layer_passes(ctypes.c_void_p(h), l, ctypes.byref(k)))
     return k.value
@@ -226,6 +229,13 @@ def spdnn_one_launch(h, batch: int) -> bool:
     k = ctypes.c_int32(-1)
     _check(lib().spdnn_one_launch(ctypes.c_void_p(h), batch, ctypes.byref(k)))
     return bool(k.value)
+
+
+def spdnn_get_launches(h):
+    """(fused launches of the last inference, those among them that kept their rows on the chip over layers)."""
+    n, r = ctypes.c_int32(-1), ctypes.c_int32(-1)
+    _check(lib().spdnn_get_launches(ctypes.c_void_p(h), ctypes.byref(n), ctypes.byref(r)))
+    return n.value, r.value
 
 
 SPDNN_STATIC_SCRATCH_BYTES = 64 << 20
@@ -413,6 +423,9 @@ class Model:
 
     def one_launch(self, batch):
         return spdnn_one_launch(self.h, batch)
+
+    def launches(self):
+        return spdnn_get_launches(self.h)
 
     def close(self):
         if getattr(self, "h", None):

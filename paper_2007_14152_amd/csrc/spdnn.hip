@@ -58,7 +58,7 @@ constexpr int kLag = 2;  // the host runs at most this many layers ahead of the 
 // are single-wave, latency-bound searches that fill a fraction of the chip, so several layers overlap.
 constexpr int kSetupStreams = 8;
 
-enum LayerMode { kSingle = 0, kStaged = 1, kWide = 2, kPair = 3, kWidePair = 4, kRow2 = 5 };
+enum LayerMode { kSingle = 0, kStaged = 1, kWide = 2, kPair = 3, kWidePair = 4, kRow2 = 5, kFlat = 6 };
 struct LayerDesc {
     spdnn::LayerWeights w;
     spdnn::WideWeights ww;
@@ -69,18 +69,18 @@ struct LayerDesc {
     // kRow2: one weight for the whole layer, N a multiple of 4096, every 4096-neuron unit's window within 16384
     // columns but wider than one LDS stage: four neurons per lane, two rows per tile (fused_row2_kernel);
     // kSingle: every window fits one LDS stage; kStaged: 2 stages (or fallback); kWide: 3+ stages;
-    // kPair: one stage, one weight for the whole layer, two output neurons per lane; kWidePair: the same for 3-8 stages
+    // kPair: one stage, one weight for the whole layer, two output neurons per lane; kWidePair: the same for 2-8 stages;
+    // kFlat: whole rows of at most 16384 columns in LDS (fused_flat_kernel)
     int mode;
     int lds_cols;  // columns the LDS tile must hold for this layer
-    float wuni;    // kPair, kWidePair: the layer's weight
-    bool pair4;    // kWidePair: 3 or 4 stages -> slot lists resident in registers
+    float wuni;    // kPair, kWidePair, kRow2, kFlat with one weight: the layer's weight
+    bool pair4;    // kWidePair: 2 to 4 stages -> slot lists resident in registers
     bool multi;    // one of several launches of a layer with more than 32 connections per neuron: each computes the
                    // outputs of a slice of the neurons, several lanes per neuron (spdnn::VirtInfo)
     spdnn::VirtInfo virt;
     int virt_lanes = 1;  // multi: lanes of the layer's longest neuron (the layer's passes)
     int virt_blocks = 0;  // multi: workgroups of this launch that have neurons
-    bool flat_uniform = false;
-    bool flat = false;     // runs fused_flat_kernel; mode says what the layer's windows are like
+    bool flat_uniform = false;  // kFlat: one weight for the whole layer
     bool relabel = false;  // kPair under new names for neurons and columns (spdnn::PairRelabel)
     spdnn::PairRelabel rn{};
 };
@@ -94,9 +94,9 @@ struct spdnn_model {
     const float* bias_dev = nullptr;
     std::vector<LayerDesc> layers;     // one per pass (launch); a layer is one pass unless some neuron has more than 32 connections
     std::vector<int32_t> first_pass;   // L+1 entries: layer l is passes first_pass[l] .. first_pass[l+1]-1
-    int* host_counts = nullptr;  // pinned, L+1 entries: rows active on entry to layer l
-    // rows that stay in LDS from layer to layer (resident_kernel): networks of at most 4096 neurons whose layers are one
-    // pass each
+    int* host_counts = nullptr;  // pinned, L+2 entries: rows active on entry to layer l; [L + 1]: rows that survive a
+                                 // resident_kernel run
+    // rows that stay in LDS from layer to layer (resident_kernel): networks of at most 4096 neurons
     const spdnn::ResidentLayer* res_layers = nullptr;  // device copy of the layers' descriptors (NULL: not possible)
     int* res_rows = nullptr;                           // device, L + 1 counters
     int res_mode = spdnn::kResWeights;
@@ -111,6 +111,7 @@ struct spdnn_model {
     // inputs in host memory (spdnn_infer_host): copy stream and "batch has landed" events, made on first use
     hipStream_t in_stream = nullptr;
     hipEvent_t in_ready[2] = {nullptr, nullptr};
+    int32_t launches = 0, res_launches = 0;  // of fused kernels in the last inference; of resident_kernel among them
     // profiling
     int profiling = 0;
     std::vector<hipEvent_t> t0, t1;
@@ -848,11 +849,9 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
                 spdnn::flat_pack_kernel<<<nblk * spdnn::kBlk / spdnn::kGroup32, spdnn::kRow2PackThreads, 0, stream>>>(
                     di, dv, N, const_cast<uint16_t*>(d.w.rel), const_cast<float*>(d.w.val));
                 HIP_TRY(hipGetLastError());
-                d.flat = true;
+                d.mode = kFlat;
                 d.lds_cols = N;
                 std::memcpy(&d.wuni, &pair_info[1], sizeof(float));
-                d.mode = nst > nstage_cap ? kStaged : wide_pair && spdnn::wide_steps(nst) >= 16 && d.ww.ps ? kWidePair : nst >= 3 ? kWide : kStaged;
-                d.pair4 = nst <= 4;
                 if (ooc)
                     HIP_TRY(hipMemcpyAsync(static_cast<char*>(host_arena) + (size_t)l * blk_bytes, m->ooc_slot[l & 1], blk_bytes,
                                            hipMemcpyDeviceToHost, stream));
@@ -968,6 +967,7 @@ int check_infer_args(spdnn_t h, const float* Y0_dev, int32_t batch, int32_t* n_a
     if (!n_active_host) return fail(SPDNN_EINVAL, "n_active_host is NULL");
     if (batch < 0) return fail(SPDNN_EINVAL, "batch < 0");
     h->prof_layers = 0;
+    h->launches = h->res_launches = 0;
     if (batch == 0) {
         *n_active_host = 0;
         return SPDNN_OK;
@@ -1177,6 +1177,8 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
         // (rows that lived through two or more layers mostly live on)
         Y_last = rest && write_through(h, Y_final_dev, alive, k > 0) ? Y_final_dev : wv.Y[k & 1];
         HIP_TRY(launch_resident(h, shape, Q, k == 0 ? Y0_dev : wv.Y[(k + 1) & 1], wv.Y[(k + 1) & 1], Y_last, wv.flags[0], rl, ra));
+        ++h->launches;
+        ++h->res_launches;
         if (h->profiling) HIP_TRY(hipEventRecord(h->t1[l0], s));
         runs.push_back(Run{l0, l1});
         l0 = l1;
@@ -1292,7 +1294,7 @@ int infer_impl(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv
             rl.count = wv.count[l & 1];
             rl.host_count = h->host_counts + l;
             rl.flags_clear = wv.flags[(l + 1) % 3];
-            if (d.flat) {
+            if (d.mode == kFlat) {
                 HIP_TRY(launch_flat(h, d, Yin, Yout, wv.flags[l % 3], rl, bound));
             } else {
             // launch shape: one workgroup per CU; the rows are cut into Q chunks per output block
@@ -1366,6 +1368,7 @@ int infer_impl(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv
                 spdnn::fused_layer_kernel<false><<<grid, spdnn::kBlk, lds, s>>>(
                     Yin, Yout, wv.flags[l % 3], rl, d.w, h->bias_dev, N, h->nblk, G, Q);
             }
+            ++h->launches;
             if (h->ooc_host) {  // the slot is free once this kernel is done: refill it with pass p + 2
                 HIP_TRY(hipEventRecord(h->ooc_freed[p & 1], s));
                 if (p + 2 < P) {
@@ -1613,14 +1616,24 @@ int spdnn_layer_kernel(spdnn_t h, int32_t l, int32_t* kind) {
                       kPair == SPDNN_KERNEL_PAIR && kWidePair == SPDNN_KERNEL_WIDE_PAIR,
                   "layer modes are the header's kernel kinds");
     const LayerDesc& d = h->layers[h->first_pass[l]];
-    *kind = (d.mode == kWidePair && d.pair4) ? SPDNN_KERNEL_WIDE_PAIR4 : d.mode == kRow2 ? SPDNN_KERNEL_ROW2 : d.mode;
+    *kind = d.mode == kWidePair && d.pair4 ? SPDNN_KERNEL_WIDE_PAIR4
+            : d.mode == kRow2              ? SPDNN_KERNEL_ROW2
+            : d.mode == kFlat              ? SPDNN_KERNEL_FLAT
+                                           : d.mode;
     return SPDNN_OK;
 }
 
 int spdnn_one_launch(spdnn_t h, int32_t batch, int32_t* yes) {
     if (!h || !yes) return fail(SPDNN_EINVAL, "null argument");
     if (batch < 0) return fail(SPDNN_EINVAL, "batch < 0");
-    *yes = h->nblk == 1 && one_launch(h, batch) ? 1 : 0;
+    *yes = one_launch(h, batch) ? 1 : 0;
+    return SPDNN_OK;
+}
+
+int spdnn_get_launches(spdnn_t h, int32_t* launches, int32_t* resident) {
+    if (!h || !launches) return fail(SPDNN_EINVAL, "null argument");
+    *launches = h->launches;
+    if (resident) *resident = h->res_launches;
     return SPDNN_OK;
 }
 
@@ -1693,6 +1706,7 @@ int spdnn_infer_host(spdnn_t h, const float* Y0_host, int32_t batch, int32_t row
         if (!n_active_host) return fail(SPDNN_EINVAL, "n_active_host is NULL");
         if (batch < 0 || rows_per_batch < 1) return fail(SPDNN_EINVAL, "need batch >= 0 and rows_per_batch >= 1");
         h->prof_layers = 0;
+        h->launches = h->res_launches = 0;
         *n_active_host = 0;
         if (batch == 0) return SPDNN_OK;
         if (!Y0_host || !work_arena || !active_rows_dev) return fail(SPDNN_EINVAL, "null argument");

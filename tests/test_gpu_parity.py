@@ -336,7 +336,7 @@ def test_kernel_choice():
         (4096, 4096, sp.SPDNN_KERNEL_PAIR),
         (8192, 8192, sp.SPDNN_KERNEL_ROW2),        # one weight, N a multiple of 4096, window within 16384 columns
         (16384, 16384, sp.SPDNN_KERNEL_ROW2),
-        (6144, 6144, sp.SPDNN_KERNEL_WIDE_PAIR4),  # two LDS stages, one weight, N not a multiple of 4096
+        (6144, 6144, sp.SPDNN_KERNEL_FLAT),        # two LDS stages, one weight, N not a multiple of 4096: whole rows in LDS
         (32768, 32768, sp.SPDNN_KERNEL_WIDE_PAIR),   # window wider than 16384 columns
         (17408, 17408, sp.SPDNN_KERNEL_WIDE),       # five stages, N not a multiple of 2048
     ]
@@ -351,7 +351,7 @@ def test_kernel_choice():
 
 @pytest.mark.parametrize("N,L,batch", [
     (8192, 3, 23),     # tiles of two rows, four neurons per lane: two segments of 4096 columns
-    (6144, 2, 7),      # two stages of 32 steps, the second narrower
+    (6144, 2, 7),      # whole rows of 6144 columns
     (16384, 2, 19),    # tiles of two rows, four segments
     (16384, 3, 1),     # ... a single row (ragged group of two)
     (18432, 2, 6),     # five stages, the last one narrower than the others
@@ -359,8 +359,9 @@ def test_kernel_choice():
 ])
 def test_wide_two_neurons_per_lane(N, L, batch):
     """Wide layers with a single weight value: four neurons per lane on two-row tiles where N
-    allows it, else two output neurons per lane (compact slots, zero entry for unused steps,
-    spill list).  One different weight sends the model to the one-neuron wide kernel."""
+    allows it, whole rows in LDS up to 16384 columns, else two output neurons per lane (compact
+    slots, zero entry for unused steps, spill list).  One different weight sends the model to the
+    one-neuron wide kernel, or to whole rows in LDS."""
     import paper_2007_14152_amd as sp
     rng = np.random.default_rng(N + 3 * L)
     idx, val, bias = _uniform_model(rng, N, L, N)
@@ -368,7 +369,7 @@ def test_wide_two_neurons_per_lane(N, L, batch):
     ref = oracle.infer(idx, val, bias, Y0)
     m = sp.Model(idx, val, bias)
     want = (sp.SPDNN_KERNEL_ROW2 if N % 4096 == 0 and N <= 16384 else
-            sp.SPDNN_KERNEL_WIDE_PAIR4 if N <= 16384 else sp.SPDNN_KERNEL_WIDE_PAIR)
+            sp.SPDNN_KERNEL_FLAT if N <= 16384 else sp.SPDNN_KERNEL_WIDE_PAIR)
     assert [m.layer_kernel(l) for l in range(L)] == [want] * L
     n, rows, Y = gpu_infer(idx, val, bias, Y0, model=m)
     m.close()
@@ -379,7 +380,7 @@ def test_wide_two_neurons_per_lane(N, L, batch):
         v[7, 0] = np.float32(0.0625 * (1.0 + 2.0 ** -20))
     ref2 = oracle.infer(idx, val2, bias, Y0)
     m2 = sp.Model(idx, val2, bias)
-    assert [m2.layer_kernel(l) for l in range(L)] == [sp.SPDNN_KERNEL_WIDE if N > 8192 else sp.SPDNN_KERNEL_STAGED] * L
+    assert [m2.layer_kernel(l) for l in range(L)] == [sp.SPDNN_KERNEL_WIDE if N > 16384 else sp.SPDNN_KERNEL_FLAT] * L
     n2, rows2, Y2 = gpu_infer(idx, val2, bias, Y0, model=m2)
     m2.close()
     check_against_oracle(ref2, n2, rows2, Y2, what="wide N=%d" % N)
@@ -387,9 +388,8 @@ def test_wide_two_neurons_per_lane(N, L, batch):
 
 @pytest.mark.parametrize("N", [10240, 12288])
 def test_wide_two_neurons_per_lane_three_stages(N):
-    """Three LDS stages (N = 10240: two neurons per lane, the fourth step of every row group is
-    idle; N = 12288: three segments of a two-row tile): every neuron has 11, 11 and 10 connections
-    in the three 4096-column stages, a few neurons 17 + 15 + 0 (one spilled in the staged format)."""
+    """Rows of three LDS stages (N = 10240: whole rows; N = 12288: three segments of a two-row tile): every
+    neuron has 11, 11 and 10 connections in the three 4096-column stages, a few neurons 17 + 15 + 0."""
     import paper_2007_14152_amd as sp
     L, batch = 2, 11
     rng = np.random.default_rng(77)
@@ -406,12 +406,53 @@ def test_wide_two_neurons_per_lane_three_stages(N):
     Y0 = (rng.uniform(0, 1, size=(batch, N)) < 0.3).astype(np.float32)
     ref = oracle.infer(idx, val, bias, Y0)
     m = sp.Model(idx, val, bias)
-    want = sp.SPDNN_KERNEL_ROW2 if N % 4096 == 0 else sp.SPDNN_KERNEL_WIDE_PAIR4
+    want = sp.SPDNN_KERNEL_ROW2 if N % 4096 == 0 else sp.SPDNN_KERNEL_FLAT
     assert [m.layer_kernel(l) for l in range(L)] == [want] * L
     n, rows, Y = gpu_infer(idx, val, bias, Y0, model=m)
     m.close()
     common, _ = check_against_oracle(ref, n, rows, Y, what="wide pair, 3 stages")
     assert common > 0
+
+
+@pytest.mark.parametrize("counts,uniform,kind", [
+    ((32, 0), True, "WIDE_PAIR4"),          # two stages of 32 steps: one of them full, the other padding
+    ((17, 15), True, "WIDE_PAIR4"),
+    ((11, 11, 10), True, "WIDE_PAIR4"),     # three of 16
+    ((17, 15, 0), True, "WIDE_PAIR4"),      # ... the 17th connection is spilled
+    ((8, 8, 8, 8), True, "WIDE_PAIR4"),     # four of 16
+    ((0, 15, 1, 16), True, "WIDE_PAIR4"),
+    ((17, 15), False, "STAGED"),            # weights of their own: one neuron per lane, two stages
+    ((17, 15, 0), False, "WIDE"),           # three and four: the staged format, spilled connections with weights
+    ((8, 8, 8, 8), False, "WIDE"),
+])
+def test_windows_of_several_stages_in_long_rows(counts, uniform, kind):
+    """Rows of more than 16384 columns, windows of two to four LDS stages: most neurons have equally many connections
+    in every stage, one in 97 `counts`."""
+    import paper_2007_14152_amd as sp
+    N, L, batch = 18432, 2, 9
+    S = len(counts)
+    rng = np.random.default_rng(sum(c << i for i, c in enumerate(counts)))
+    idx = []
+    for l in range(L):
+        base = rng.permutation(N // 2048)[:9] * 2048 % (N - 4096 * S + 4)   # a window for every 2048 neurons
+        a = np.empty((N, 32), dtype=np.int64)
+        for j in range(N):
+            c = counts if j % 97 == 0 else [32 // S + (s0 < 32 % S) for s0 in range(S)]
+            a[j] = base[j // 2048] + np.concatenate([s0 * 4096 + rng.choice(4096, k, replace=False) for s0, k in enumerate(c)])
+        idx.append(np.sort(a, axis=1).astype(np.int32))
+    val = [np.full((N, 32), 0.0625, np.float32) if uniform else rng.uniform(0.02, 0.11, size=(N, 32)).astype(np.float32)
+           for _ in range(L)]
+    bias = np.full(N, -0.05, dtype=np.float32)
+    Y0 = (rng.uniform(0, 1, size=(batch, N)) < 0.3).astype(np.float32)
+    Y0[4] = 0
+    ref = oracle.infer(idx, val, bias, Y0)
+    m = sp.Model(idx, val, bias)
+    assert [m.layer_kernel(l) for l in range(L)] == [getattr(sp, "SPDNN_KERNEL_" + kind)] * L
+    n, rows, Y = gpu_infer(idx, val, bias, Y0, model=m)
+    assert m.launches() == (L, 0)
+    m.close()
+    common, _ = check_against_oracle(ref, n, rows, Y, what="%s stages of a long row" % S)
+    assert 0 < common < batch
 
 
 def test_layers_with_fewer_stages_than_the_widest():
@@ -590,6 +631,35 @@ def test_all_layers_in_one_launch_equals_one_launch_per_layer(N, L):
     m.close()
 
 
+@pytest.mark.parametrize("N,batch,one", [(1024, 500, True), (1028, 500, True), (4096, 1000, True), (4096, 2048, True),
+                                         (4096, 2052, False), (8192, 3, False)])
+def test_launches_are_what_the_library_says(N, batch, one):
+    """One launch for all layers where spdnn_one_launch says so, whatever the number of output blocks, and what
+    spdnn_get_launches counts; a launch per layer above 4096 neurons and with weights in host memory."""
+    import paper_2007_14152_amd as sp
+    L = 5
+    rng = np.random.default_rng(N + batch)
+    idx = [np.sort(rng.integers(0, N, size=(N, 32)), axis=1).astype(np.int32) for _ in range(L)]
+    val = [rng.uniform(0.02, 0.11, size=(N, 32)).astype(np.float32) for _ in range(L)]
+    bias = -rng.uniform(0.0, 0.2, size=N).astype(np.float32)
+    Y0 = rng.uniform(0.2, 1.0, size=(batch, N)).astype(np.float32)
+    m = sp.Model(idx, val, bias)
+    assert m.one_launch(batch) == one
+    want = gpu_infer(idx, val, bias, Y0, model=m)
+    n, resident = m.launches()
+    m.close()
+    if N <= 4096:
+        assert resident > 0 and n < L and (not one or n == 1)
+        m = sp.Model(idx, val, bias, out_of_core=True)
+        assert not m.one_launch(batch)
+        got = gpu_infer(idx, val, bias, Y0, model=m)
+        assert m.launches() == (L, 0)
+        m.close()
+        assert all(np.array_equal(a, b) for a, b in zip(got, want))
+    else:
+        assert (n, resident) == (L, 0)
+
+
 @pytest.mark.parametrize("uniform", [True, False])
 def test_largest_n_with_columns_anywhere(uniform):
     """N = 65536 (the largest the 16-bit column offsets allow) with columns drawn from the whole
@@ -661,10 +731,14 @@ def test_scattered_windows_gathered_footprint(N, w, batch):
     (1024, (1, 32), True, "SINGLE"),            # one block: the whole row is its window
     (8192, (1, 32), True, "PAIR"),              # the last unit's window runs over the row end
     (8192, (32, 1), False, "SINGLE"),           # the same with two weight values: one neuron per lane
-    (8192, (160,), False, "STAGED"),            # two stages, cyclic
+    (8192, (160,), False, "FLAT"),              # two stages, cyclic: whole rows
     (16384, (256, 1, 32), True, "PAIR PAIR PAIR"),  # stride 256: two neurons per lane under new names for neurons and columns
-    (16384, (256,), False, "WIDE"),             # three stages, one neuron per lane
-    (10240, (256,), True, "WIDE_PAIR4"),        # three stages, two neurons per lane, step lists in registers
+    (16384, (256,), False, "FLAT"),             # three stages, weights of their own: whole rows
+    (10240, (256,), True, "FLAT"),              # three stages, one weight: whole rows
+    (18432, (160,), False, "STAGED"),           # two stages, one neuron per lane, rows too long to be held whole
+    (18432, (270,), False, "WIDE"),             # three stages, one neuron per lane
+    (18432, (150,), True, "WIDE_PAIR4"),        # two stages, two neurons per lane, step lists in registers
+    (18432, (270,), True, "WIDE_PAIR4"),        # three
     (32768, (700,), True, "WIDE_PAIR"),         # six stages, two neurons per lane
     (65536, (1500,), False, "WIDE"),            # twelve stages of eight steps
     (65536, (1024, 2048, 32), True, "PAIR PAIR PAIR"),  # units of 64 segments of 32 and 32 segments of 64 neurons, renamed
@@ -735,8 +809,11 @@ def test_seeded_sweep_over_layer_shapes(seed):
         m = sp.Model(idx, val, bias)
         what = "sweep %d/%d N=%d L=%d batch=%d one launch=%s kernels=%s" % (
             seed, case, N, L, batch, m.one_launch(batch), [sp.KERNEL_NAMES[m.layer_kernel(l)] for l in range(L)])
-        seen.add("one launch" if m.one_launch(batch) else sp.KERNEL_NAMES[m.layer_kernel(0)])
         n, rows, Y = gpu_infer(idx, val, bias, Y0, model=m)
+        launches, resident = m.launches()
+        assert not m.one_launch(batch) or (launches, resident) == (1, 1), what
+        seen.add("rows on the chip, %d blocks, %d launches" % (-(-N // 1024), launches) if resident
+                 else sp.KERNEL_NAMES[m.layer_kernel(0)])
         m.close()
         check_against_oracle(ref, n, rows, Y, what=what)
     assert len(seen) >= 3, seen

@@ -551,16 +551,24 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
         }
     }
 
-    // General layers of a network that resident_kernel takes, not all of them of exactly 32 connections per neuron:
-    // neurons by length (kResParts).
+    // Do rows stay in LDS from layer to layer (resident_kernel)?  General layers, not all of them of exactly 32
+    // connections per neuron: neurons by length (kResParts), unless they are too uneven for a lane per neuron.
+    bool resident = N <= spdnn::kCap && !ooc;
     bool parts = false;
     std::vector<int32_t> hp((size_t)N + 1);
-    if (ptr && N <= spdnn::kCap)
-        for (int32_t ll = 0; ll < L && !parts; ++ll) {
+    if (ptr && resident) {
+        double uneven = 0.0;
+        std::vector<uint16_t> perm;
+        std::vector<uint32_t> nch;
+        for (int32_t ll = 0; ll < L; ++ll) {
             HIP_TRY(hipMemcpyAsync(hp.data(), ptr[ll], sizeof(int32_t) * hp.size(), hipMemcpyDeviceToHost, stream));
             HIP_TRY(hipStreamSynchronize(stream));
             for (int32_t j = 0; j < N && !parts; ++j) parts = hp[j + 1] - hp[j] != spdnn::kNnz;
+            spdnn::order_by_length(hp.data(), N, nblk * spdnn::kBlk, resident_waves(N, resident_groups_per_wave(nblk, false)), perm, nch);
+            uneven += spdnn::uneven_chunks(hp.data(), N, nch, resident_waves(N, resident_groups_per_wave(nblk, true)));
         }
+        if (uneven > 0.0) resident = parts = false;
+    }
 
     const size_t raw = (size_t)N * spdnn::kNnz;
     std::vector<int2> hw((size_t)P * nblk);
@@ -685,7 +693,7 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
                                                                        err_dev + 1 + 2 * P + l, nrows);
         // A row that fits one LDS stage: the blocks share one tile layout, that of the whole row, which is what
         // resident_kernel needs (out-of-core weights, which it does not take, are laid out the same: same sums).
-        const bool whole = N <= spdnn::kCap && !d.multi;
+        const bool whole = resident || (ooc && N <= spdnn::kCap);
         if (whole) {
             spdnn::whole_row_window_kernel<<<1, 64, 0, stream>>>(win_dev[l], nblk, N, widest_dev);
             d.w.planes_log2 = spdnn::res_planes_log2(nblk);
@@ -922,7 +930,7 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
     }
     // Rows of at most one LDS stage: they can stay in LDS from layer to layer (resident_kernel, which takes the layers'
     // descriptors from device memory).
-    if (N <= spdnn::kCap && !ooc) {
+    if (resident) {
         std::vector<int> differ((size_t)P);  // passes with more than one weight value
         std::vector<int> info(2 * (size_t)P);
         HIP_TRY(hipMemcpyAsync(differ.data(), err_dev + 1 + 2 * P, sizeof(int) * (size_t)P, hipMemcpyDeviceToHost, stream));

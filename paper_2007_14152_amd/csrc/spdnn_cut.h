@@ -128,4 +128,22 @@ inline void order_by_length(const int32_t* hp, int32_t N, int32_t nlanes, int wa
         }
 }
 
+// Is a layer too uneven for that?  A lane keeps its neuron, so a layer takes at least as long as the busiest wave's
+// chunks one behind the other (0.25 to 0.45 us each), where several lanes per neuron and launches of their own take some
+// 20 us and 9 more for every further launch, a launch per 1024 lanes of 32 connections and output block.
+// Returns by how many chunks the busiest of the `waves` waves exceeds what those launches are worth (negative: by how
+// many it stays below); the model's layers are added up.  Whole passes of 6 layers, by length -> several lanes, on one
+// row / 1000 / 10 000 rows: 4096 neurons of 8 connections and one of 320: 161 -> 162, 173 -> 459, 976 -> 1552 us; of
+// 384: 179 -> 163, 192 -> 460, 1085 -> 1553; of 512: 208 -> 143, 225 -> 395, 1286 -> 1439; of 4096 (100 rows, 10 000):
+// 1173 -> 180, 7559 -> 2522; all of 200 to 256 (100 rows, 10 000): 382 -> 506, 2817 -> 5575; 1024 neurons of 8, 300 of
+// them of 512: 194 -> 375, 197 -> 406, 614 -> 1868.
+inline double uneven_chunks(const int32_t* hp, int32_t N, const std::vector<uint32_t>& nch, int waves) {
+    std::vector<uint32_t> busy((size_t)waves, 0u);
+    for (size_t g = 0; g < nch.size(); ++g) busy[g % waves] += nch[g];
+    double lanes = 0;
+    for (int32_t j = 0; j < N; ++j) lanes += (hp[j + 1] - hp[j] + 31) / 32;
+    const int nblk = (N + 1023) / 1024;
+    return (double)*std::max_element(busy.begin(), busy.end()) - (48.0 + 30.0 * std::max(0.0, lanes / (1024.0 * nblk) - 1.0));
+}
+
 }  // namespace spdnn

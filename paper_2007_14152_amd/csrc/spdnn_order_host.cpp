@@ -102,6 +102,9 @@ void spdnn_order_by_length_host(const int32_t* ptr, int N, int nlanes, int waves
     std::copy(p.begin(), p.end(), perm);
     std::copy(c.begin(), c.end(), nch);
 }
+double spdnn_uneven_chunks_host(const int32_t* ptr, int N, const uint32_t* nch, int groups, int waves) {
+    return spdnn::uneven_chunks(ptr, N, std::vector<uint32_t>(nch, nch + groups), waves);
+}
 uint32_t spdnn_res_code_host(uint32_t slot, int planes_log2) { return spdnn::res_code(slot, planes_log2); }
 uint32_t spdnn_res_slot_host(uint32_t code, int planes_log2) { return spdnn::res_slot(code, planes_log2); }
 

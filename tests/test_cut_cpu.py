@@ -177,3 +177,34 @@ def test_entry_codes(lib, planes_log2):
         c = code(s, planes_log2)
         assert 16 * c == (s // 16) * 256 * (1 << planes_log2) + (s % 16) * 16 and c < 1 << 16
         assert slot(c, planes_log2) == s
+
+
+def by_length(lib, deg, few):
+    """Neurons by length as the set-up has them, and uneven_chunks for the waves of many or few rows."""
+    N, nblk = len(deg), -(-len(deg) // 1024)
+    ptr = np.zeros(N + 1, dtype=np.int32)
+    np.cumsum(deg, out=ptr[1:])
+    waves = [-(-(-(-N // 64)) // nb) for nb in ((4, 4) if nblk > 2 else (2, 1) if nblk == 1 else (2, 2))]
+    perm, nch = np.zeros(nblk * 1024, dtype=np.uint16), np.zeros(nblk * 16, dtype=np.uint32)
+    lib.spdnn_order_by_length_host.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
+    lib.spdnn_order_by_length_host.restype = None
+    lib.spdnn_order_by_length_host(ptr.ctypes.data, N, nblk * 1024, waves[0], perm.ctypes.data, nch.ctypes.data)
+    f = lib.spdnn_uneven_chunks_host
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p, ctypes.c_int, ctypes.c_int]
+    f.restype = ctypes.c_double
+    return f(ptr.ctypes.data, N, nch.ctypes.data, len(nch), waves[few])
+
+
+@pytest.mark.parametrize("N,short,long,count,uneven", [
+    (4096, 8, 320, 1, False), (4096, 8, 512, 1, True), (4096, 8, 4096, 1, True), (4096, 8, 512, 300, False),
+    (1024, 8, 384, 32, False), (1024, 8, 1024, 1, True), (1024, 8, 512, 300, False), (256, 8, 512, 1, True),
+    (256, 256, 256, 0, False), (1024, 1024, 1024, 0, False), (64, 64, 64, 0, False), (64, 8, 2100, 20, True)])
+def test_uneven_neurons(lib, N, short, long, count, uneven):
+    """A few neurons much longer than the others would hold up the wave that has them; neurons that are all long, or
+    many long ones, are what several lanes per neuron would need many launches for."""
+    deg = np.full(N, short)
+    deg[np.random.default_rng(N).choice(N, count, replace=False)] = long
+    assert (by_length(lib, deg, True) > 0) == uneven
+    # lengths without outliers, whatever their mean, never are
+    for lo, hi in ((0, 9), (0, 100), (16, 64), (33, 64), (200, 256)):
+        assert by_length(lib, np.random.default_rng(hi).integers(lo, hi + 1, size=N), True) <= 0

@@ -110,6 +110,36 @@ def test_long_neurons_several_passes(N, L, batch, kmax, width):
     assert common > 0
 
 
+@pytest.mark.parametrize("N,L,longest,on_chip", [(1024, 1, 40, True), (1024, 3, 1500, False), (2052, 2, 2052, False),
+                                                 (4096, 2, 4096, False), (4096, 2, 4096, True), (96, 2, 8192, False)])
+def test_a_few_very_long_neurons(N, L, longest, on_chip):
+    """Some neurons many times longer than the others: several lanes each, in a launch per layer, instead of one lane
+    that the whole workgroup waits for; on the chip all the same where the network's other layers are worth it."""
+    import paper_2007_14152_amd as sp
+    rng = np.random.default_rng(N + longest)
+    ptr, idx, val, bias = rand_general(rng, N, L, 0, 12, hi=0.3)
+    if on_chip and longest > 64:    # one such layer behind enough others
+        p2, i2, v2, _ = rand_general(rng, N, 40, 0, 12, hi=0.3)
+        ptr, idx, val = p2 + ptr[:1], i2 + idx[:1], v2 + val[:1]
+    for l in ([len(ptr) - 1] if on_chip else range(L)):
+        deg = np.diff(ptr[l])
+        who = rng.choice(N, 3, replace=False)
+        deg[who] = longest
+        ptr[l] = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+        idx[l] = rng.integers(0, N, size=ptr[l][-1]).astype(np.int32)
+        val[l] = (rng.uniform(0, 1, size=ptr[l][-1]) * np.repeat(3.0 / np.maximum(deg, 1), deg)).astype(np.float32)
+    Y0 = rng.uniform(0, 1, size=(150, N)).astype(np.float32)
+    Y0[1] = 0
+    ref = oracle.infer(idx, val, bias, Y0, ptr=ptr)
+    m = sp.Model.from_csr(ptr, idx, val, bias)
+    n, rows, Y = gpu_infer_general(ptr, idx, val, bias, Y0, model=m)
+    launches, resident = m.launches()
+    m.close()
+    assert (resident > 0) == on_chip and (launches == resident if on_chip else launches >= L)
+    common, _ = check_against_oracle(ref, n, rows, Y, what="a few neurons of %d" % longest)
+    assert on_chip or common > 0
+
+
 def test_layers_of_different_kinds_in_one_model():
     """Short, long and exactly-32 uniform layers in one model: the exactly-32 layer with one
     weight value still gets the two-neurons-per-lane kernel."""

@@ -1033,11 +1033,11 @@ bool one_launch(spdnn_t h, int32_t batch) {
     return share <= (h->nblk == 1 ? spdnn::kShareRows : spdnn::kRows * (1 << spdnn::res_planes_log2(h->nblk)));
 }
 
-hipError_t launch_resident(spdnn_t h, const ResidentShape& r, int32_t Q, const float* Yin, float* Ymid, float* Yout, uint8_t* flags,
+hipError_t launch_resident(spdnn_t h, const ResidentShape& r, int32_t Q, const float* Yin, float* Yout, uint8_t* flags,
                            const spdnn::RowLists& rl, const spdnn::ResidentArgs& ra) {
     const auto run = [&](auto nb, auto planes, auto mode) {
         spdnn::resident_kernel<decltype(nb)::value, decltype(planes)::value, decltype(mode)::value>
-            <<<Q, r.threads, r.lds, h->stream>>>(Yin, Ymid, Yout, flags, rl, ra, h->bias_dev, h->N);
+            <<<Q, r.threads, r.lds, h->stream>>>(Yin, Yout, flags, rl, ra, h->bias_dev, h->N);
     };
     const auto run_mode = [&](auto nb, auto planes) {
         if (h->res_mode == spdnn::kResUniform) run(nb, planes, std::integral_constant<int, spdnn::kResUniform>{});
@@ -1162,8 +1162,12 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
     // they are of several passes.  Otherwise the batch is compacted and shared out anew after two layers, where most
     // of the rows that die have died.  If fewer than a quarter died, or not many layers are left, they are one launch;
     // if not, the next run is four times as long, and so on.  (A launch costs the gap before it, 20 us, and the rows'
-    // way through memory, together what two to three layers of 4096 neurons take; passes whose rows die unevenly
-    // afterwards may cost a third of what is left.)
+    // way through memory, together what two to three layers of 4096 neurons take; rows that die afterwards are the
+    // kernel's own business, which stops and merges passes.)
+    // With weights of their own above 2048 neurons a layer's connections are 576 KB and more: workgroups that stop at
+    // different layers no longer find them in L2.  There the rest is cut in half as long as rows die (24 layers of 4096
+    // neurons, 30 000 rows that die evenly: 4.54 -> 3.75 ms) and more than 12 layers are left.
+    const bool halves = h->res_mode != spdnn::kResUniform && h->nblk > 2;
     struct Run {
         int32_t l0, l1;
     };
@@ -1174,7 +1178,8 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
     int32_t k = 0;     // launches so far
     int32_t len = 2;   // layers of the next run
     for (int32_t l0 = 0; l0 < L; ++k, len *= 4) {
-        const bool rest = one || (k > 0 && ((int64_t)alive * 4 > (int64_t)before * 3 || L - l0 <= 32)) || len >= L - l0;
+        if (halves && k > 0) len = (int64_t)alive * 32 > (int64_t)before * 31 || L - l0 <= 12 ? L : std::max(8, (L - l0 + 1) / 2);
+        const bool rest = one || (!halves && k > 0 && ((int64_t)alive * 4 > (int64_t)before * 3 || L - l0 <= 32)) || len >= L - l0;
         const int32_t l1 = rest ? L : l0 + len;
         const ResidentShape shape = resident_shape(h, alive);
         const int32_t groups = (alive + spdnn::kRows - 1) / spdnn::kRows;
@@ -1184,7 +1189,7 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
         if (h->profiling) HIP_TRY(hipEventRecord(h->t0[l0], s));
         // (rows that lived through two or more layers mostly live on)
         Y_last = rest && write_through(h, Y_final_dev, alive, k > 0) ? Y_final_dev : wv.Y[k & 1];
-        HIP_TRY(launch_resident(h, shape, Q, k == 0 ? Y0_dev : wv.Y[(k + 1) & 1], wv.Y[(k + 1) & 1], Y_last, wv.flags[0], rl, ra));
+        HIP_TRY(launch_resident(h, shape, Q, k == 0 ? Y0_dev : wv.Y[(k + 1) & 1], Y_last, wv.flags[0], rl, ra));
         ++h->launches;
         ++h->res_launches;
         if (h->profiling) HIP_TRY(hipEventRecord(h->t1[l0], s));

@@ -18,6 +18,14 @@
 // them zero) until so many are dead that the survivors need fewer planes: then the write packs them together
 // (Listing 1's pruning inside the pass).  A pass whose rows have all died is over.
 //
+// A workgroup's share of the rows is a number of passes, and a pass reads a layer's connections whole whatever lives in
+// it.  So rows that die later make passes worth merging: a pass that has lost half its rows stops behind that layer,
+// its survivors' rows go to memory, and the share's other passes stop there too; as soon as a pass's worth of rows
+// waits there, it goes on from that layer.  A pass of those may stop again further on (kResLevels).  Nothing of this
+// happens, or costs anything, as long as rows live.  Shares are dealt out quad by quad, so that rows that die together
+// because they came in together are spread over the workgroups.  Whole passes, 24 layers on 60 000 rows of 4096 neurons
+// with weights of their own: nine in ten die in layer 3 6.97 -> 3.41 ms; seven in ten, the first of the batch, 8.36 -> 4.44.
+//
 // What bounds it.  One weight per layer: LDS reads (16 bytes per connection, plane and lane; 256 B per clock and CU) and
 // the FMAs behind them, which take nearly the same time (counters at 1024 neurons, 30 000 rows: LDS active 82 % of the
 // clocks, a fifth of that bank conflicts, vector instructions 72 %).  Weights of their own at 4096 neurons: the stream of
@@ -56,7 +64,7 @@ struct ResidentLayer {   // one layer, in device memory
 enum { kResWeights = 0, kResUniform = 1, kResParts = 2 };
 struct ResidentArgs {
     const ResidentLayer* layers;
-    int l0, lmid, l1;  // layers l0 .. l1-1; rows of a share of several passes are packed together again at lmid
+    int l0, lmid, l1;  // layers l0 .. l1-1; passes stop and are merged at lmid (l1: only where rows die)
     int L;             // layers of the network
     int A;             // rows on entry, if the lists are not there yet (rl.count == NULL): row i is in slot i
     uint32_t part_stride;  // kResParts: bytes from a group's connections 32p .. 32p+31 to the next 32, slots and weights alike
@@ -65,6 +73,11 @@ struct ResidentArgs {
 
 // Bytes of LDS: the planes, then the bookkeeping.
 constexpr int kResMiscBytes = 1024;
+constexpr int kResLevels = 6;  // layers a launch's passes may start at: l0, and five where they were stopped
+// A pass stops where 5/8 of its rows or fewer live and at least three layers are left.  (Stopping costs the survivors' way
+// through memory, about a layer's time.  Half and two layers, 24 layers of 4096 neurons on 30 000 rows that die evenly: 3.24
+// instead of 3.17 ms; of 2048 neurons, 30 layers: 1.92 instead of 1.88; three quarters and four layers: 3.19, 1.92.)
+constexpr int kStopNum = 5, kStopDen = 8, kStopLeft = 3;
 SPDNN_HD inline uint32_t res_chunk_bytes(int planes) { return 256u * (uint32_t)planes; }
 SPDNN_HD inline uint32_t res_tile_bytes(int N, int planes) { return (uint32_t)((N + 255) / 256) * 16u * res_chunk_bytes(planes); }
 
@@ -135,10 +148,11 @@ __device__ __forceinline__ void res_fma8(f32x4 (&acc)[P], u32x4 codes, float wu,
 }
 
 // NB = most groups of 64 neurons a wave owns, PM = most planes.  blockDim.x = 64 * W with W = ceil(U / NB),
-// U = ceil(N / 64) groups of 64 neurons; wave w owns the groups w, w + W, ...  Every workgroup has a run of
-// neighbouring rows.
+// U = ceil(N / 64) groups of 64 neurons; wave w owns the groups w, w + W, ...  Workgroup i has the quads of rows i,
+// i + gridDim.x, ... of the list on entry; a row keeps its place in the list in Yout, where it also waits while its pass
+// is stopped.
 template <int NB, int PM, int MODE>
-__global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict__ Yin, float* Ymid, float* Yout,
+__global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict__ Yin, float* Yout,
                                                         uint8_t* __restrict__ flags, RowLists rl, ResidentArgs ra,
                                                         const float* __restrict__ bias, int N) {
     // The entry codes are addresses from the start of the workgroup's LDS: everything is dynamic, nothing static.
@@ -151,17 +165,20 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
     const uint32_t misc = res_tile_bytes(N, PM);
     uint32_t* live_word = reinterpret_cast<uint32_t*>(res_lds + misc);             // [2], raised by the layers in turn
     int* row_at = reinterpret_cast<int*>(res_lds + misc + 16);                     // [4 * PM] row to copy to or from, per slot; -1: none
-    uint16_t* loc = reinterpret_cast<uint16_t*>(res_lds + misc + 16 + 4 * 4 * 4);  // [kShareRows] rows alive at lmid
+    constexpr int F = kRows * PM;  // rows of a full pass
+    int* level_at = row_at + 16;               // [kResLevels + 1]
+    int* level_n = level_at + kResLevels + 1;  // [kResLevels + 1]
+    int* waiting = level_n + kResLevels + 1;   // [kResLevels - 1][2 * F] rows that wait, per level
+    static_assert(16 + 4 * (16 + 2 * (kResLevels + 1) + (kResLevels - 1) * 2 * 16) <= kResMiscBytes, "the lists fit behind the planes");
 
-    // my rows: r0 .. r0 + nrows - 1 of the list on entry, and of the output
+    // my rows: `quads` quads, the last one of the list perhaps ragged
     const int A = rl.count ? __builtin_amdgcn_readfirstlane(*rl.count) : ra.A;
     const bool identity = !rl.count;
     const int groups = (A + kRows - 1) / kRows;
-    const int per = groups / (int)gridDim.x, extra = groups - per * (int)gridDim.x;  // the first `extra` take one more
-    const int wg = blockIdx.x;
-    const int r0 = (wg * per + min(wg, extra)) * kRows;
-    const int nrows = min(A - r0, (per + (wg < extra ? 1 : 0)) * kRows);
-    if (nrows <= 0) return;
+    const int wg = blockIdx.x, nwg = gridDim.x;
+    if (wg >= groups) return;
+    const int quads = (groups - wg + nwg - 1) / nwg;
+    const int nrows = quads * kRows - ((groups - 1) % nwg == wg ? groups * kRows - A : 0);
 
     const int nb_w = (U - wave + W - 1) / W;  // my groups of 64 neurons (at least one: W <= U)
     float bj[NB];  // lanes without a neuron: minus infinity, which makes their outputs 0
@@ -213,38 +230,61 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
         return ResidentLayer{d->rel, d->val, d->qsel, d->wuni, d->perm, d->nch};
     };
 
-    int nalive = nrows;  // of my rows, on entry to the current run of layers
-    for (int seg = 0; seg < 2; ++seg) {
-        const int la = seg == 0 ? ra.l0 : ra.lmid, lb = seg == 0 ? ra.lmid : ra.l1;
-        if (la >= lb || nalive == 0) continue;
-        const bool last_seg = lb == ra.l1;
-        const float* src = seg == 0 ? Yin : Ymid;
-        float* dst = last_seg ? Yout : Ymid;
-        const ResidentLayer first = layer_at(la);
-        const uint32_t* q_in = first.qsel;
-        const uint32_t* q_out = layer_at(min(lb, ra.L - 1)).qsel;  // any layout does for the last layer's output
-        const int quads = (nalive + kRows - 1) / kRows;
-        const int npass = (quads + PM - 1) / PM;
-        int kept = 0;         // rows alive at the end of the passes so far
-        bool primed = false;  // cbuf / wbuf hold the first group's connections of layer la ...
-        Item ahead{};         // ... which is this (in general: the group whose connections come next)
-        int i1 = 0;
-        for (int pass = 0; pass < npass; ++pass) {
-            const int i0 = i1;  // this pass: rows i0 .. i1 - 1 of the share (seg 1: of the list of survivors)
+    // Level v: rows that have come to layer level_at[v] and wait there for a pass (level 0: my rows on entry).
+    const int npass = (quads + PM - 1) / PM;
+    if (tid <= kResLevels) {  // seen from the second pass on
+        level_at[tid] = tid == 0 ? ra.l0 : tid == 1 ? ra.lmid : ra.l1;
+        level_n[tid] = 0;
+    }
+    int own = 0, i1 = 0;  // passes and rows of level 0 so far
+    int primed = -1;      // the layer whose first group's connections cbuf / wbuf hold ...
+    Item ahead{};         // ... which is this (in general: the group whose connections come next)
+    for (;;) {
+        // the furthest level with a full pass; when my own rows are used up, the nearest with any
+        int v = 0, la = ra.l0, lb = ra.lmid, n = 0;
+        bool more = npass > 1;  // rows to come at this level or before it, which this pass could be merged with
+        if (own > 0) {
+            const int at = level_at[min(lane, kResLevels)], w = level_n[min(lane, kResLevels)];
+            const uint32_t full = (uint32_t)__builtin_amdgcn_ballot_w64(lane < kResLevels && w >= F);
+            const uint32_t any = (uint32_t)__builtin_amdgcn_ballot_w64(lane < kResLevels && w > 0);
+            if (full) v = 31 - __builtin_clz(full);
+            else if (own == npass && any) v = __builtin_ctz(any);
+            else if (own == npass) break;
+            la = __builtin_amdgcn_readlane(at, v);
+            lb = __builtin_amdgcn_readlane(at, v + 1);
+            n = __builtin_amdgcn_readlane(w, v);
+            more = own + (v == 0) < npass || (any & ((1u << v) - 1u)) || n > F;
+        }
+        int n0;   // rows of this pass
+        int rid;  // lane s (of every wave): place in the list of the row in slot s
+        if (v == 0) {
             // (the shorter passes first in one half of the workgroups, last in the other: the passes get out of step, and
             // with them the workgroups' turns at the memory)
-            const int upto = (wg & 1) ? quads - ((npass - 1 - pass) * quads) / npass : ((pass + 1) * quads) / npass;
-            i1 = min(nalive, upto * kRows);
-            const int n0 = i1 - i0;
+            const int upto = (wg & 1) ? quads - ((npass - 1 - own) * quads) / npass : ((own + 1) * quads) / npass;
+            const int i0 = i1;
+            i1 = min(nrows, upto * kRows);
+            n0 = i1 - i0;
+            const int i = i0 + min(lane, n0 - 1);
+            rid = ((i / kRows) * nwg + wg) * kRows + i % kRows;
+            ++own;
+        } else {
+            n0 = min(n, F);
+            n -= n0;
+            rid = waiting[(v - 1) * 2 * F + n + min(lane, n0 - 1)];
+        }
+        // So few rows stop the pass, if there is a level left and rows it could be merged with.
+        const int few = more && v < kResLevels - 1 && lb == ra.l1 ? n0 * kStopNum / kStopDen : 0;
+        {
+            const float* src = v == 0 ? Yin : Yout;
+            const ResidentLayer first = layer_at(la);
+            const uint32_t* q_in = first.qsel;
+            const uint32_t* q_out = layer_at(min(lb, ra.L - 1)).qsel;  // any layout does for the last layer's output
             int P = (n0 + kRows - 1) / kRows;
             uint32_t live = n0 >= 32 ? 0xffffffffu : (1u << n0) - 1u;
-            // lane s (of every wave): number, inside my share, of the row in slot s
-            int rid = lane < n0 ? i0 + lane : 0;
-            if (seg == 1 && lane < n0) rid = loc[i0 + lane];
-            if (tid < kRows * PM) row_at[tid] = tid >= n0 ? -1 : seg == 0 && !identity ? rl.cat[r0 + rid] : r0 + rid;
-            if (seg == 0 && tid < n0) flags[r0 + rid] = 0;  // wave 0, like every other store to the flags
+            if (tid < F) row_at[tid] = tid >= n0 ? -1 : v == 0 && !identity ? rl.cat[rid] : rid;
+            if (v == 0 && tid < n0) flags[rid] = 0;  // wave 0, like every other store to the flags
             if (tid < 2) live_word[tid] = 0u;
-            if (!primed) {
+            if (primed != la) {
                 ahead = item(first, 0);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) fetch_codes(ahead, c);
@@ -272,11 +312,12 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
             __syncthreads();
 
             // Layers l .. as long as PP planes are needed: a loop of its own for every number of planes.
-            int l = la;
+            int l = la, stop = lb;
             ResidentLayer cur = first, nxt = layer_at(la + 1 < lb ? la + 1 : la);
             auto layers = [&](auto Ptag) {
                 constexpr int PP = decltype(Ptag)::value;
-                while (l < lb && P == PP) {
+                const int enough = max(kRows * (PP - 1), few);  // as long as more rows live, all stays as it is
+                while (l < stop && P == PP) {
                     gu32* q_next = (gu32*)(uintptr_t)(l + 1 < lb ? nxt.qsel : q_out);
                     int jn[NB];       // my neurons
                     uint32_t at[NB];  // where their outputs go
@@ -379,27 +420,30 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
                     live &= __builtin_amdgcn_readfirstlane(raised);
                     if (tid == 0) live_word[(l + 1) & 1] = 0u;
                     const int n = __popc(live);
-                    P = (n + kRows - 1) / kRows;
-                    if (P < PP && n > 0) {  // fewer planes will do: the survivors move together, over what was just written
-                        using lds_f = __attribute__((address_space(3))) float;
+                    if (n <= enough) {
+                        P = (n + kRows - 1) / kRows;
+                        if (P < PP && n > 0) {  // fewer planes will do: the survivors move together, over what was just written
+                            using lds_f = __attribute__((address_space(3))) float;
 #pragma unroll
-                        for (int b = 0; b < NB; ++b) {
-                            if (b < nb_w && jn[b] < N) {
+                            for (int b = 0; b < NB; ++b) {
+                                if (b < nb_w && jn[b] < N) {
 #pragma unroll
-                                for (int s = 0; s < kRows * PP; ++s)
-                                    if ((live >> s) & 1u) {
-                                        const int to = __popc(live & ((1u << s) - 1u));
-                                        *reinterpret_cast<lds_f*>(at[b] + 256u * (to >> 2) + 4u * (to & 3)) = res[b][s >> 2][s & 3];
-                                    }
-                                for (int s = n; s < kRows * P; ++s) *reinterpret_cast<lds_f*>(at[b] + 256u * (s >> 2) + 4u * (s & 3)) = 0.0f;
+                                    for (int s = 0; s < kRows * PP; ++s)
+                                        if ((live >> s) & 1u) {
+                                            const int to = __popc(live & ((1u << s) - 1u));
+                                            *reinterpret_cast<lds_f*>(at[b] + 256u * (to >> 2) + 4u * (to & 3)) = res[b][s >> 2][s & 3];
+                                        }
+                                    for (int s = n; s < kRows * P; ++s) *reinterpret_cast<lds_f*>(at[b] + 256u * (s >> 2) + 4u * (s & 3)) = 0.0f;
+                                }
                             }
+                            // slot s now holds what the s-th live slot held
+                            int from = 0;
+                            for (uint32_t rest = live, k = 0; rest; rest &= rest - 1u, ++k)
+                                if (lane == (int)k) from = __builtin_ctz(rest);
+                            rid = __shfl(rid, from, 64);
+                            live = n >= 32 ? 0xffffffffu : (1u << n) - 1u;
                         }
-                        // slot s now holds what the s-th live slot held
-                        int from = 0;
-                        for (uint32_t rest = live, k = 0; rest; rest &= rest - 1u, ++k)
-                            if (lane == (int)k) from = __builtin_ctz(rest);
-                        rid = __shfl(rid, from, 64);
-                        live = n >= 32 ? 0xffffffffu : (1u << n) - 1u;
+                        if (n > 0 && n <= few && l + 1 + kStopLeft <= ra.l1) stop = l + 1;
                     }
                     __syncthreads();
                     if (tid == 0 && n > 0 && ra.layer_rows) atomicAdd(&ra.layer_rows[l + 1], n);
@@ -414,16 +458,32 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
             }
             layers(std::integral_constant<int, 2>{});
             layers(std::integral_constant<int, 1>{});
-            primed = live != 0u;
-            if (!live) continue;
-
-            // the survivors' rows go to memory, under the slots they came with
-            if (tid < kRows * PM) row_at[tid] = (live >> tid) & 1u ? r0 + rid : -1;
-            if (wave == 0 && lane < 32 && ((live >> lane) & 1u)) {
-                if (last_seg) flags[r0 + rid] = 1;
-                else loc[kept + __popc(live & ((1u << lane) - 1u))] = (uint16_t)rid;
+            if (!live) {
+                primed = -1;
+                if (v > 0) {
+                    if (tid == 0) level_n[v] = n;
+                    __syncthreads();
+                }
+                continue;
             }
-            kept += __popc(live);
+            // a stopped pass asked for the next layer's connections, one that ran through for those of its first layer
+            primed = stop < lb ? stop : la;
+            if (stop < lb) q_out = cur.qsel;
+
+            // the survivors' rows go to memory; those of a stopped pass wait for the next level's
+            if (tid < F) row_at[tid] = (live >> tid) & 1u ? rid : -1;
+            if (wave == 0) {
+                const int before = l < ra.l1 ? level_n[v + 1] : 0;
+                if (lane < 32 && ((live >> lane) & 1u)) {
+                    if (l == ra.l1) flags[rid] = 1;
+                    else waiting[v * 2 * F + before + __popc(live & ((1u << lane) - 1u))] = rid;
+                }
+                if (lane == 0) {
+                    if (v > 0) level_n[v] = n;
+                    if (l < ra.l1) level_n[v + 1] = before + __popc(live);
+                    if (stop < lb) level_at[v + 1] = stop;
+                }
+            }
             __syncthreads();
             for (int e = tid; e < P * n4; e += T) {
                 const int p = e / n4, t = e - p * n4;
@@ -435,15 +495,13 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
                 const f32x4 c1 = *reinterpret_cast<const lds_f4*>(base + CH + ((qp >> 8) & 0xffu));
                 const f32x4 c2 = *reinterpret_cast<const lds_f4*>(base + 2u * CH + ((qp >> 16) & 0xffu));
                 const f32x4 c3 = *reinterpret_cast<const lds_f4*>(base + 3u * CH + (qp >> 24));
-                if (at.x >= 0) *reinterpret_cast<f32x4*>(dst + (size_t)at.x * N + col) = f32x4{c0.x, c1.x, c2.x, c3.x};
-                if (at.y >= 0) *reinterpret_cast<f32x4*>(dst + (size_t)at.y * N + col) = f32x4{c0.y, c1.y, c2.y, c3.y};
-                if (at.z >= 0) *reinterpret_cast<f32x4*>(dst + (size_t)at.z * N + col) = f32x4{c0.z, c1.z, c2.z, c3.z};
-                if (at.w >= 0) *reinterpret_cast<f32x4*>(dst + (size_t)at.w * N + col) = f32x4{c0.w, c1.w, c2.w, c3.w};
+                if (at.x >= 0) *reinterpret_cast<f32x4*>(Yout + (size_t)at.x * N + col) = f32x4{c0.x, c1.x, c2.x, c3.x};
+                if (at.y >= 0) *reinterpret_cast<f32x4*>(Yout + (size_t)at.y * N + col) = f32x4{c0.y, c1.y, c2.y, c3.y};
+                if (at.z >= 0) *reinterpret_cast<f32x4*>(Yout + (size_t)at.z * N + col) = f32x4{c0.z, c1.z, c2.z, c3.z};
+                if (at.w >= 0) *reinterpret_cast<f32x4*>(Yout + (size_t)at.w * N + col) = f32x4{c0.w, c1.w, c2.w, c3.w};
             }
-            __syncthreads();  // row_at is free for the next pass
+            __syncthreads();  // row_at is free for the next pass, and the rows that wait are in place
         }
-        nalive = kept;
-        __syncthreads();
     }
 }
 

@@ -95,6 +95,62 @@ def test_neurons_of_any_length_stay_on_chip(N, batch, L, kmin, kmax):
     assert n == 0 or n < batch
 
 
+@pytest.mark.parametrize("N,batch,L,general,order", [
+    (100, 70000, 12, False, "mixed"),    # one group of lanes; several workgroups per CU
+    (1024, 9001, 12, False, "mixed"),    # one launch, passes stopped at the second layer
+    (1024, 41003, 16, False, "sorted"),  # sixteen rows per pass, two launches
+    (1028, 22001, 12, True, "mixed"),    # neurons by length
+    (2048, 20002, 12, False, "sorted"),
+    (3072, 9003, 12, False, "mixed"),    # eight rows per pass
+    (4096, 13001, 18, False, "mixed"),
+    (4096, 13001, 18, False, "sorted"),
+    (4096, 11001, 12, True, "late"),
+    (4096, 9001, 30, False, "late"),
+])
+def test_rows_that_die_late(N, batch, L, general, order):
+    """Passes that lose half their rows on the way are stopped and merged, more than once.  Row r holds the integer v_r
+    in every column, a layer turns v into v - 1, exactly; most die in layers 3, 5, 8 and 9, some in every layer.  Sorted:
+    the first rows of the batch die first."""
+    import torch
+    import paper_2007_14152_amd as sp
+    dev = "cuda:0"
+    rng = np.random.default_rng(N + L)
+    top = L + 2   # the first layer's outputs stay below the clip
+    u = rng.uniform(size=batch)
+    if order == "late":
+        v = np.where(u < 0.6, L - 6, np.where(u < 0.9, L - 3, top))
+    else:
+        v = np.select([u < 0.55, u < 0.75, u < 0.9, u < 0.93], [3, 5, 8, 9], top)
+    odd = rng.uniform(size=batch) < 0.05
+    v[odd] = rng.integers(1, top + 1, size=int(odd.sum()))
+    if order == "sorted":
+        v.sort()
+    ptr, idx, val = [], [], []
+    for l in range(L):
+        deg = rng.choice([8, 16, 64], size=N) if general else np.full(N, 32)
+        p = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+        ptr.append(p)
+        idx.append(rng.integers(0, N, size=int(p[N])).astype(np.int32))
+        val.append(np.repeat(1.0 / deg, deg).astype(np.float32))
+    bias = np.full(N, -1.0, np.float32)
+    if general:
+        m = sp.Model.from_csr(ptr, idx, val, bias)
+    else:
+        m = sp.Model([a.reshape(N, 32) for a in idx], [a.reshape(N, 32) for a in val], bias)
+    y0 = torch.from_numpy(v.astype(np.float32)).to(dev)[:, None].expand(batch, N).contiguous()
+    alive = np.nonzero(v > L)[0]
+    m.set_profiling(True)
+    for _ in range(2):
+        n, rows, Y = m.infer(y0)
+        assert n == len(alive) and np.array_equal(rows.cpu().numpy(), alive)
+        assert bool((Y == torch.from_numpy((v[alive] - L).astype(np.float32)).to(dev)[:, None]).all())
+        run, rows_in, _ = m.profile()
+        want = [int((v > l).sum()) for l in range(L)]
+        assert [int(x) for x in rows_in[:run]] == want[:run] and not any(want[run:])
+    assert m.launches()[1] > 0
+    m.close()
+
+
 @pytest.mark.parametrize("N,batch,L,die", [
     (4096, 1600, 9, True),     # rows in LDS, two launches
     (4096, 1600, 9, False),

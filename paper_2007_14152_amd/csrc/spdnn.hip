@@ -219,9 +219,9 @@ size_t carve_work(int32_t N, int32_t batch, char* base, WorkView* v) {
 }
 
 constexpr int kVirtLds = 2 * spdnn::kBlk * 16;  // two sets of slots for the lanes' sums (spdnn::VirtInfo)
-template <bool MULTI, bool VIRT>
+template <bool MULTI, bool VIRT, bool WHOLE = false>
 hipError_t allow_big_lds() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::fused_layer_kernel<MULTI, VIRT>),
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::fused_layer_kernel<MULTI, VIRT, WHOLE>),
                                hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)spdnn::tile_pair_bytes(spdnn::kCap) + (VIRT ? kVirtLds : 0));
 }
@@ -251,6 +251,7 @@ int allow_large_lds() {
     HIP_TRY((allow_big_lds<true, false>()));
     HIP_TRY((allow_big_lds<false, true>()));
     HIP_TRY((allow_big_lds<true, true>()));
+    HIP_TRY((allow_big_lds<false, false, true>()));
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::wide_pack_kernel),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)wide_lds));
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::balance_kernel<1>),
@@ -258,6 +259,8 @@ int allow_large_lds() {
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::balance_kernel<2>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(spdnn::BalanceScratch<2>)));
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::fused_pair_kernel<false>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, tile_lds));
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>((&spdnn::fused_pair_kernel<false, true>)),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, tile_lds));
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::fused_pair_kernel<true>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, tile_lds));
@@ -601,7 +604,7 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
             int* pair_dev = err_dev + 1 + 3 * P + 2 * l;
             spdnn::block_window_kernel<<<nblk, spdnn::kBlk, 0, stream>>>(st_idx, N, win_dev[l], err_dev, widest_dev, st_val,
                                                                          err_dev + 1 + 2 * P + l, nlanes);
-            spdnn::whole_row_window_kernel<<<1, 64, 0, stream>>>(win_dev[l], nblk, N, widest_dev);
+            spdnn::whole_row_window_kernel<<<1, 64, 0, stream>>>(win_dev[l], const_cast<int2*>(d.virt.range), nblk, N, widest_dev);
             d.w.planes_log2 = spdnn::res_planes_log2(nblk);
             int pair_info[2] = {0, 0};
             if (r == 0) {
@@ -695,7 +698,7 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
         // resident_kernel needs (out-of-core weights, which it does not take, are laid out the same: same sums).
         const bool whole = resident || (ooc && N <= spdnn::kCap);
         if (whole) {
-            spdnn::whole_row_window_kernel<<<1, 64, 0, stream>>>(win_dev[l], nblk, N, widest_dev);
+            spdnn::whole_row_window_kernel<<<1, 64, 0, stream>>>(win_dev[l], const_cast<int2*>(d.virt.range), nblk, N, widest_dev);
             d.w.planes_log2 = spdnn::res_planes_log2(nblk);
         }
         // a layer of several passes runs the one-neuron-per-lane kernels, whose epilogue knows about passes
@@ -718,7 +721,7 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
             HIP_TRY(hipGetLastError());
             HIP_TRY(hipMemcpyAsync(ngr.data(), d.r2_map, sizeof(int) * ngr.size(), hipMemcpyDeviceToHost, stream));
         }
-        HIP_TRY(hipMemcpyAsync(&hw[(size_t)l * nblk], win_dev[l], sizeof(int2) * nblk, hipMemcpyDeviceToHost, stream));
+        HIP_TRY(hipMemcpyAsync(&hw[(size_t)l * nblk], whole ? d.virt.range : win_dev[l], sizeof(int2) * nblk, hipMemcpyDeviceToHost, stream));
         HIP_TRY(hipMemcpyAsync(pair_info, pair_dev, sizeof(pair_info), hipMemcpyDeviceToHost, stream));
         HIP_TRY(hipStreamSynchronize(stream));
         // One weight, but the windows are too wide for two neurons per lane.  If units of 2048 neurons in segments
@@ -881,6 +884,19 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
             di, dv, N, win_dev[l], widest_dev, slot_tab, unit, d.w.planes_log2, const_cast<uint16_t*>(d.w.rel),
             const_cast<float*>(d.w.val), nrows, lens, lens ? const_cast<uint8_t*>(d.virt.nb8) : nullptr);
         HIP_TRY(hipGetLastError());
+        if (whole) {  // what the blocks (pairs of blocks) read of the row, from a multiple of 256 columns on (LayerWeights)
+            for (int32_t b = 0; b < nblk; ++b) {
+                int2& w = hw[(size_t)l * nblk + b];
+                if (pair && (b & 1)) {
+                    w = hw[(size_t)l * nblk + b - 1];
+                    continue;
+                }
+                if (pair) spdnn::win_union(w.x, w.y, hw[(size_t)l * nblk + b + 1].x, hw[(size_t)l * nblk + b + 1].y, N, w.x, w.y);
+                if (w.x + w.y > N) w = make_int2(0, N);  // it wraps around the row end
+                w = make_int2(w.x & ~255, w.y + (w.x & 255));
+            }
+            HIP_TRY(hipMemcpyAsync(win_dev[l], &hw[(size_t)l * nblk], sizeof(int2) * nblk, hipMemcpyHostToDevice, stream));
+        }
         int widest = 4;
         for (int32_t b = 0; b < nblk; ++b) widest = std::max(widest, hw[(size_t)l * nblk + b].y);
         const int nst = stages_of(widest);
@@ -1026,7 +1042,7 @@ ResidentShape resident_shape(const spdnn_model* h, int32_t rows) {
 // All layers in one launch?  With rows in LDS from layer to layer, if a workgroup's share of the rows is small: they
 // stay with the workgroup they started in, and a share that is packed together again as rows die is all the
 // rebalancing there is.  One output block: up to kShareRows rows per CU; more blocks: what one pass holds.
-bool one_launch(spdnn_t h, int32_t batch) {
+bool one_launch(const spdnn_model* h, int32_t batch) {
     if (batch <= 0 || h->res_layers == nullptr) return false;
     const int32_t groups = (batch + spdnn::kRows - 1) / spdnn::kRows;
     const int32_t share = (groups + h->num_cu - 1) / h->num_cu * spdnn::kRows;
@@ -1071,6 +1087,113 @@ hipError_t launch_flat(spdnn_t h, const LayerDesc& d, const float* Yin, float* Y
     else if (rows == 2) run_r(std::integral_constant<int, 2>{});
     else if (rows == 3) run_r(std::integral_constant<int, 3>{});
     else run_r(std::integral_constant<int, 4>{});
+    return hipGetLastError();
+}
+
+// The row lists of layer l's launch.  The layer's first kernel compacts the list of active rows on its way in (the flags
+// layer l-1 raised -> slots and row numbers); later passes of the same layer find the lists in place.
+spdnn::RowLists layer_lists(const spdnn_model* h, const WorkView& wv, int32_t l, bool first) {
+    spdnn::RowLists rl;
+    rl.flags_prev = first ? wv.flags[(l + 2) % 3] : nullptr;
+    rl.count_prev = wv.count[(l + 1) & 1];
+    rl.gid_prev = wv.gid[(l + 1) & 1];
+    rl.cat = wv.cat[l & 1];
+    rl.gid = wv.gid[l & 1];
+    rl.count = wv.count[l & 1];
+    rl.host_count = h->host_counts + l;
+    rl.flags_clear = wv.flags[(l + 1) % 3];
+    return rl;
+}
+
+// "Layer -1": every row of the batch is flagged alive, under its own number.
+hipError_t launch_init_lists(spdnn_t h, const WorkView& wv, int32_t batch, int32_t row_offset) {
+    spdnn::init_lists_kernel<<<(batch + 255) / 256, 256, 0, h->stream>>>(wv.gid[1], wv.flags[2], wv.flags[0], wv.count[1], batch,
+                                                                         row_offset);
+    return hipGetLastError();
+}
+
+// One launch of a layer: one pass of it, through the kernel it is set up for, on at most `bound` rows.
+hipError_t launch_layer(spdnn_t h, const LayerDesc& d, const float* Yin, float* Yout, uint8_t* flags, const spdnn::RowLists& rl,
+                        int32_t bound) {
+    if (d.mode == kFlat) return launch_flat(h, d, Yin, Yout, flags, rl, bound);
+    const int32_t N = h->N;
+    hipStream_t s = h->stream;
+    // launch shape: one workgroup per CU; the rows are cut into Q chunks per output block
+    const int32_t rows_per_group = d.mode == kRow2 ? spdnn::kRows2 : spdnn::kRows;
+    const int32_t ngroups = (bound + rows_per_group - 1) / rows_per_group;
+    // kPair: the workgroups' column blocks are pairs of output blocks
+    const bool two = d.mode == kPair || d.mode == kWidePair;
+    const int32_t ncb = d.mode == kRow2 ? h->nblk / 4 : two ? h->nblk / 2 : h->nblk;
+    // Workgroups that read the same rows go to one XCD (32 CUs, one L2).  In a wide layer every
+    // column block reads whole rows: as many of them as possible share an XCD, so that a row is
+    // fetched from memory once, not once per XCD.
+    int32_t G = d.mode == kPair ? ((ncb % 2 == 0) ? 2 : 1) : h->G;
+    if (d.multi)  // fewer neurons per workgroup: up to P times as many workgroups read the same window
+        for (int32_t g : {32, 16, 8, 4, 3, 2, 1})
+            if (g <= h->G * d.virt_lanes && ncb % g == 0) {
+                G = g;
+                break;
+            }
+    if (d.mode == kWide || d.mode == kWidePair || d.mode == kRow2)
+        for (int32_t g : {32, 16, 8, 4, 3, 2, 1})
+            if (ncb % g == 0) {
+                G = g;
+                break;
+            }
+    int32_t Q = std::max(1, h->num_cu / ncb);
+    // several lanes per neuron: the launches of a layer have different numbers of workgroups with neurons,
+    // rarely a divisor of the CUs; four times as many workgroups as CUs, taken up as CUs fall free
+    if (d.multi) Q = (4 * h->num_cu + std::max(1, d.virt_blocks) - 1) / std::max(1, d.virt_blocks);
+    Q = std::max(1, std::min(Q, ngroups));
+    const int32_t units = (ncb / G) * Q;
+    const int32_t grid = (units + 7) / 8 * 8 * G;
+    const size_t lds = spdnn::tile_pair_bytes((d.lds_cols + 255) / 256 * 256);  // whole waves of 256 columns
+    if (d.mode == kRow2)
+        spdnn::fused_row2_kernel<<<grid, spdnn::kBlk, spdnn::kRow2LdsBytes, s>>>(
+            Yin, Yout, flags, rl, d.r2, h->bias_dev, N, ncb, G, Q, d.wuni);
+    else if (d.multi) {  // several lanes per neuron: the lanes' sums meet in LDS behind the tile pair
+        spdnn::VirtInfo vi = d.virt;
+        vi.part_off = (uint32_t)lds;
+        if (d.mode == kStaged)
+            spdnn::fused_layer_kernel<true, true><<<grid, spdnn::kBlk, lds + kVirtLds, s>>>(
+                Yin, Yout, flags, rl, d.w, h->bias_dev, N, h->nblk, G, Q, vi);
+        else
+            spdnn::fused_layer_kernel<false, true><<<grid, spdnn::kBlk, lds + kVirtLds, s>>>(
+                Yin, Yout, flags, rl, d.w, h->bias_dev, N, h->nblk, G, Q, vi);
+    }
+    else if (d.mode == kPair && d.relabel)
+        spdnn::fused_pair_kernel<true><<<grid, spdnn::kBlk, lds, s>>>(
+            Yin, Yout, flags, rl, d.w, h->bias_dev, N, ncb, G, Q, d.wuni, d.rn);
+    else if (d.mode == kPair && d.w.planes_log2)
+        spdnn::fused_pair_kernel<false, true><<<grid, spdnn::kBlk, lds, s>>>(
+            Yin, Yout, flags, rl, d.w, h->bias_dev, N, ncb, G, Q, d.wuni);
+    else if (d.mode == kPair)
+        spdnn::fused_pair_kernel<false><<<grid, spdnn::kBlk, lds, s>>>(
+            Yin, Yout, flags, rl, d.w, h->bias_dev, N, ncb, G, Q, d.wuni);
+    else if (d.mode == kWidePair && d.pair4 && d.ww.nstage == 2)  // + the all-zero entries and the spill table
+        spdnn::fused_wide_pair4_kernel<2, 32><<<grid, spdnn::kBlk, lds + spdnn::kPair4LdsExtra, s>>>(
+            Yin, Yout, flags, rl, d.ww, h->bias_dev, N, ncb, G, Q, d.wuni);
+    else if (d.mode == kWidePair && d.pair4)
+        spdnn::fused_wide_pair4_kernel<4, 16><<<grid, spdnn::kBlk, lds + spdnn::kPair4LdsExtra, s>>>(
+            Yin, Yout, flags, rl, d.ww, h->bias_dev, N, ncb, G, Q, d.wuni);
+    else if (d.mode == kWidePair)
+        spdnn::fused_wide_pair_kernel<<<grid, spdnn::kBlk, lds + spdnn::kPadLds, s>>>(
+            Yin, Yout, flags, rl, d.ww, h->bias_dev, N, ncb, G, Q, d.wuni);
+    else if (d.mode == kWide && d.ww.nstage > 8)
+        spdnn::fused_wide_kernel<8><<<grid, spdnn::kBlk, lds, s>>>(
+            Yin, Yout, flags, rl, d.ww, h->bias_dev, N, ncb, G, Q);
+    else if (d.mode == kWide)
+        spdnn::fused_wide_kernel<16><<<grid, spdnn::kBlk, lds, s>>>(
+            Yin, Yout, flags, rl, d.ww, h->bias_dev, N, ncb, G, Q);
+    else if (d.mode == kStaged)
+        spdnn::fused_layer_kernel<true><<<grid, spdnn::kBlk, lds, s>>>(
+            Yin, Yout, flags, rl, d.w, h->bias_dev, N, h->nblk, G, Q);
+    else if (d.w.planes_log2)
+        spdnn::fused_layer_kernel<false, false, true><<<grid, spdnn::kBlk, lds, s>>>(
+            Yin, Yout, flags, rl, d.w, h->bias_dev, N, h->nblk, G, Q);
+    else
+        spdnn::fused_layer_kernel<false><<<grid, spdnn::kBlk, lds, s>>>(
+            Yin, Yout, flags, rl, d.w, h->bias_dev, N, h->nblk, G, Q);
     return hipGetLastError();
 }
 
@@ -1173,11 +1296,28 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
     };
     std::vector<Run> runs;
     int32_t alive = batch, before = batch;
-    spdnn::RowLists rl{};
+    spdnn::RowLists rl{};    // the rows on entry to the next run (rl.count == NULL: the whole batch)
+    const float* Yin = Y0_dev;
     float* Y_last = nullptr;
-    int32_t k = 0;     // launches so far
-    int32_t len = 2;   // layers of the next run
-    for (int32_t l0 = 0; l0 < L; ++k, len *= 4) {
+    int yo = 0, lo = 0;      // the work buffer and the lists that the next run writes
+    int32_t k = 0;           // runs so far
+    int32_t len = 2;         // layers of the next run
+    int32_t l0 = 0;
+    // the lists of the rows that the last run left, for the next one at layer l
+    const auto compact = [&](const uint8_t* flags, const int* count_in, const int* gid_in, int32_t l) -> int {
+        h->host_counts[l] = -1;
+        spdnn::compact_kernel<<<spdnn::kCompactWGs, 1024, 0, s>>>(flags, nullptr, count_in, wv.count[lo], gid_in, wv.gid[lo], wv.cat[lo],
+                                                                  h->host_counts + l, batch, row_offset);
+        HIP_TRY(hipGetLastError());
+        before = alive;
+        const int rc = wait_count(h, l, &alive);
+        rl.count = wv.count[lo];
+        rl.gid = wv.gid[lo];
+        rl.cat = wv.cat[lo];
+        lo ^= 1;
+        return rc;
+    };
+    for (; l0 < L && alive > 0; ++k, len *= 4) {
         if (halves && k > 0) len = (int64_t)alive * 32 > (int64_t)before * 31 || L - l0 <= 12 ? L : std::max(8, (L - l0 + 1) / 2);
         const bool rest = one || (!halves && k > 0 && ((int64_t)alive * 4 > (int64_t)before * 3 || L - l0 <= 32)) || len >= L - l0;
         const int32_t l1 = rest ? L : l0 + len;
@@ -1188,30 +1328,23 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
         const spdnn::ResidentArgs ra{h->res_layers, l0, one && several ? std::min(l0 + 2, l1) : l1, l1, L, batch, h->res_part_stride, layer_rows};
         if (h->profiling) HIP_TRY(hipEventRecord(h->t0[l0], s));
         // (rows that lived through two or more layers mostly live on)
-        Y_last = rest && write_through(h, Y_final_dev, alive, k > 0) ? Y_final_dev : wv.Y[k & 1];
-        HIP_TRY(launch_resident(h, shape, Q, k == 0 ? Y0_dev : wv.Y[(k + 1) & 1], Y_last, wv.flags[0], rl, ra));
+        Y_last = rest && write_through(h, Y_final_dev, alive, k > 0) ? Y_final_dev : wv.Y[yo];
+        HIP_TRY(launch_resident(h, shape, Q, Yin, Y_last, wv.flags[0], rl, ra));
         ++h->launches;
         ++h->res_launches;
         if (h->profiling) HIP_TRY(hipEventRecord(h->t1[l0], s));
         runs.push_back(Run{l0, l1});
         l0 = l1;
         if (l1 == L) break;
-        h->host_counts[l1] = -1;
-        spdnn::compact_kernel<<<spdnn::kCompactWGs, 1024, 0, s>>>(wv.flags[0], nullptr, rl.count, wv.count[k & 1], rl.gid, wv.gid[k & 1],
-                                                                  wv.cat[k & 1], h->host_counts + l1, batch, row_offset);
-        HIP_TRY(hipGetLastError());
-        before = alive;
-        const int rc = wait_count(h, l1, &alive);
+        const int rc = compact(wv.flags[0], rl.count, rl.gid, l1);
         if (rc != SPDNN_OK) return rc;
-        rl.count = wv.count[k & 1];
-        rl.gid = wv.gid[k & 1];
-        rl.cat = wv.cat[k & 1];
-        if (alive == 0) break;
+        Yin = wv.Y[yo];
+        yo ^= 1;
     }
     int32_t rc = SPDNN_OK;
     if (alive > 0)
-        rc = finish_infer(h, wv.flags[0], rl.count, rl.gid, batch, row_offset, wv.count[k & 1], wv.cat[k & 1], L + 1,
-                          Y_last, wv.Y[(k + 1) & 1], alive, n_active_host, active_rows_dev, Y_final_dev);
+        rc = finish_infer(h, wv.flags[0], rl.count, rl.gid, batch, row_offset, wv.count[lo], wv.cat[lo], L + 1,
+                          Y_last, wv.Y[yo ^ 1], alive, n_active_host, active_rows_dev, Y_final_dev);
     else {
         HIP_TRY(hipStreamSynchronize(s));
         *n_active_host = 0;
@@ -1246,8 +1379,9 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
 // work memory.  Returns with the model's stream drained, also when a HIP call fails half way.
 int infer_impl(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv, int32_t row_offset,
                int32_t* n_active_host, int32_t* active_rows_dev, float* Y_final_dev) {
-    if (h->res_layers) return infer_resident(h, Y0_dev, batch, wv, row_offset, n_active_host, active_rows_dev, Y_final_dev);
-    const int32_t N = h->N, L = h->L;
+    const int32_t L = h->L;
+    if (h->res_layers)
+        return infer_resident(h, Y0_dev, batch, wv, row_offset, n_active_host, active_rows_dev, Y_final_dev);
     hipStream_t s = h->stream;
     // Kernels may be queued when a later HIP call fails: nothing of this call is left running on return.
     struct DrainModel {
@@ -1260,9 +1394,7 @@ int infer_impl(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv
 
     for (int32_t l = 1; l <= L; ++l) h->host_counts[l] = -1;  // "not reported yet"
     h->host_counts[0] = batch;
-    // "layer -1": every row of the batch is flagged alive, under its own number
-    spdnn::init_lists_kernel<<<(batch + 255) / 256, 256, 0, s>>>(wv.gid[1], wv.flags[2], wv.flags[0], wv.count[1], batch,
-                                                                 row_offset);
+    HIP_TRY(launch_init_lists(h, wv, batch, row_offset));
     int32_t bound = batch;  // upper bound of the rows active at the layer being launched
     int32_t before = -1;    // the bound one layer earlier
     int32_t run = 0;        // layers launched
@@ -1296,91 +1428,8 @@ int infer_impl(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv
             const LayerDesc& d = h->layers[p];
             if (d.multi && d.virt_blocks == 0 && p != h->first_pass[l]) continue;  // no workgroup of the layer is left for this launch
             if (h->ooc_host) HIP_TRY(hipStreamWaitEvent(s, h->ooc_ready[p & 1], 0));
-            // The layer's first kernel compacts the list of active rows on its way in (the flags layer l-1
-            // raised -> slots and row numbers); later passes of the same layer find the lists in place.
-            spdnn::RowLists rl;
-            rl.flags_prev = p == h->first_pass[l] ? wv.flags[(l + 2) % 3] : nullptr;
-            rl.count_prev = wv.count[(l + 1) & 1];
-            rl.gid_prev = wv.gid[(l + 1) & 1];
-            rl.cat = wv.cat[l & 1];
-            rl.gid = wv.gid[l & 1];
-            rl.count = wv.count[l & 1];
-            rl.host_count = h->host_counts + l;
-            rl.flags_clear = wv.flags[(l + 1) % 3];
-            if (d.mode == kFlat) {
-                HIP_TRY(launch_flat(h, d, Yin, Yout, wv.flags[l % 3], rl, bound));
-            } else {
-            // launch shape: one workgroup per CU; the rows are cut into Q chunks per output block
-            const int32_t rows_per_group = d.mode == kRow2 ? spdnn::kRows2 : spdnn::kRows;
-            const int32_t ngroups = (bound + rows_per_group - 1) / rows_per_group;
-            // kPair: the workgroups' column blocks are pairs of output blocks
-            const bool two = d.mode == kPair || d.mode == kWidePair;
-            const int32_t ncb = d.mode == kRow2 ? h->nblk / 4 : two ? h->nblk / 2 : h->nblk;
-            // Workgroups that read the same rows go to one XCD (32 CUs, one L2).  In a wide layer every
-            // column block reads whole rows: as many of them as possible share an XCD, so that a row is
-            // fetched from memory once, not once per XCD.
-            int32_t G = d.mode == kPair ? ((ncb % 2 == 0) ? 2 : 1) : h->G;
-            if (d.multi)  // fewer neurons per workgroup: up to P times as many workgroups read the same window
-                for (int32_t g : {32, 16, 8, 4, 3, 2, 1})
-                    if (g <= h->G * d.virt_lanes && ncb % g == 0) {
-                        G = g;
-                        break;
-                    }
-            if (d.mode == kWide || d.mode == kWidePair || d.mode == kRow2)
-                for (int32_t g : {32, 16, 8, 4, 3, 2, 1})
-                    if (ncb % g == 0) {
-                        G = g;
-                        break;
-                    }
-            int32_t Q = std::max(1, h->num_cu / ncb);
-            // several lanes per neuron: the launches of a layer have different numbers of workgroups with neurons,
-            // rarely a divisor of the CUs; four times as many workgroups as CUs, taken up as CUs fall free
-            if (d.multi) Q = (4 * h->num_cu + std::max(1, d.virt_blocks) - 1) / std::max(1, d.virt_blocks);
-            Q = std::max(1, std::min(Q, ngroups));
-            const int32_t units = (ncb / G) * Q;
-            const int32_t grid = (units + 7) / 8 * 8 * G;
-            const size_t lds = spdnn::tile_pair_bytes((d.lds_cols + 255) / 256 * 256);  // whole waves of 256 columns
-            if (d.mode == kRow2)
-                spdnn::fused_row2_kernel<<<grid, spdnn::kBlk, spdnn::kRow2LdsBytes, s>>>(
-                    Yin, Yout, wv.flags[l % 3], rl, d.r2, h->bias_dev, N, ncb, G, Q, d.wuni);
-            else if (d.multi) {  // several lanes per neuron: the lanes' sums meet in LDS behind the tile pair
-                spdnn::VirtInfo vi = d.virt;
-                vi.part_off = (uint32_t)lds;
-                if (d.mode == kStaged)
-                    spdnn::fused_layer_kernel<true, true><<<grid, spdnn::kBlk, lds + kVirtLds, s>>>(
-                        Yin, Yout, wv.flags[l % 3], rl, d.w, h->bias_dev, N, h->nblk, G, Q, vi);
-                else
-                    spdnn::fused_layer_kernel<false, true><<<grid, spdnn::kBlk, lds + kVirtLds, s>>>(
-                        Yin, Yout, wv.flags[l % 3], rl, d.w, h->bias_dev, N, h->nblk, G, Q, vi);
-            }
-            else if (d.mode == kPair && d.relabel)
-                spdnn::fused_pair_kernel<true><<<grid, spdnn::kBlk, lds, s>>>(
-                    Yin, Yout, wv.flags[l % 3], rl, d.w, h->bias_dev, N, ncb, G, Q, d.wuni, d.rn);
-            else if (d.mode == kPair)
-                spdnn::fused_pair_kernel<false><<<grid, spdnn::kBlk, lds, s>>>(
-                    Yin, Yout, wv.flags[l % 3], rl, d.w, h->bias_dev, N, ncb, G, Q, d.wuni);
-            else if (d.mode == kWidePair && d.pair4 && d.ww.nstage == 2)  // + the all-zero entries and the spill table
-                spdnn::fused_wide_pair4_kernel<2, 32><<<grid, spdnn::kBlk, lds + spdnn::kPair4LdsExtra, s>>>(
-                    Yin, Yout, wv.flags[l % 3], rl, d.ww, h->bias_dev, N, ncb, G, Q, d.wuni);
-            else if (d.mode == kWidePair && d.pair4)
-                spdnn::fused_wide_pair4_kernel<4, 16><<<grid, spdnn::kBlk, lds + spdnn::kPair4LdsExtra, s>>>(
-                    Yin, Yout, wv.flags[l % 3], rl, d.ww, h->bias_dev, N, ncb, G, Q, d.wuni);
-            else if (d.mode == kWidePair)
-                spdnn::fused_wide_pair_kernel<<<grid, spdnn::kBlk, lds + spdnn::kPadLds, s>>>(
-                    Yin, Yout, wv.flags[l % 3], rl, d.ww, h->bias_dev, N, ncb, G, Q, d.wuni);
-            else if (d.mode == kWide && d.ww.nstage > 8)
-                spdnn::fused_wide_kernel<8><<<grid, spdnn::kBlk, lds, s>>>(
-                    Yin, Yout, wv.flags[l % 3], rl, d.ww, h->bias_dev, N, ncb, G, Q);
-            else if (d.mode == kWide)
-                spdnn::fused_wide_kernel<16><<<grid, spdnn::kBlk, lds, s>>>(
-                    Yin, Yout, wv.flags[l % 3], rl, d.ww, h->bias_dev, N, ncb, G, Q);
-            else if (d.mode == kStaged)
-                spdnn::fused_layer_kernel<true><<<grid, spdnn::kBlk, lds, s>>>(
-                    Yin, Yout, wv.flags[l % 3], rl, d.w, h->bias_dev, N, h->nblk, G, Q);
-            else
-                spdnn::fused_layer_kernel<false><<<grid, spdnn::kBlk, lds, s>>>(
-                    Yin, Yout, wv.flags[l % 3], rl, d.w, h->bias_dev, N, h->nblk, G, Q);
-            }
+            const spdnn::RowLists rl = layer_lists(h, wv, l, p == h->first_pass[l]);
+            HIP_TRY(launch_layer(h, d, Yin, Yout, wv.flags[l % 3], rl, bound));
             ++h->launches;
             if (h->ooc_host) {  // the slot is free once this kernel is done: refill it with pass p + 2
                 HIP_TRY(hipEventRecord(h->ooc_freed[p & 1], s));
@@ -1391,7 +1440,6 @@ int infer_impl(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv
             }
         }
         if (h->profiling) HIP_TRY(hipEventRecord(h->t1[l], s));
-        HIP_TRY(hipGetLastError());
         run = l + 1;
         // Feedback with bounded lag: the number of rows active on entry to layer l+2-kLag bounds all later
         // ones.  That layer's kernel stores it to pinned host memory as it starts, which is polled here

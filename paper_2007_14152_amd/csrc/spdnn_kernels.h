@@ -39,8 +39,26 @@ struct LayerWeights {
     const float* val;     // [nblk][8][kBlk][4]
     const int2* win;      // [nblk] {c_lo, ncols}, both multiples of 4
     const uint32_t* qsel;  // [nblk][kBlk] balanced single-stage layers: see balance_kernel
-    int planes_log2;       // 0, or for layers whose slots are kept as entry codes (res_code): log2 of the planes
+    int planes_log2;       // 0, or for layers whose slots are kept as entry codes (res_code): log2 of the planes.
+                           // Such a layer's blocks share the tile layout of the whole row, in which a window that
+                           // starts at a multiple of 256 columns is a run of store groups: its tile is that run.
 };
+// A lane's slots (load_slots) as LDS byte addresses, buffer 0.  WHOLE: the layer has the layout of the whole row, and c_lo is
+// the first column of the block's window.  (The slots of lanes past the last neuron, which have weight 0, may lie in front of
+// it.)  A kernel of its own, because elsewhere nothing on the way in need wait for the window (48 strided layers of 16384
+// neurons on 2000 rows: 1955 us, 2032 with the two in one kernel).
+template <bool WHOLE>
+__device__ __forceinline__ void slot_addresses(uint32_t (&r)[kNnz], const LayerWeights& w, uint32_t lds_base, int c_lo) {
+    const uint32_t first = WHOLE ? tile_offset((uint32_t)c_lo) : 0u;
+#pragma unroll
+    for (int k = 0; k < kNnz; ++k)
+        r[k] = lds_base + (WHOLE ? max(tile_offset(res_slot(r[k], w.planes_log2)), first) - first : tile_offset(r[k]));
+}
+// Quads of staging lane t's columns (LayerWeights::qsel).
+template <bool WHOLE>
+__device__ __forceinline__ uint32_t staging_quads(const LayerWeights& w, int b, int t, int c_lo) {
+    return w.qsel[(size_t)b * kBlk + (WHOLE ? min(t + (c_lo >> 2), kBlk - 1) : t)];
+}
 
 // Layout for layers whose column windows need 3 or more LDS stages ("wide" layers).
 // Connections are grouped by stage; stage s of a block offers S steps (16, or 8 when
@@ -792,8 +810,9 @@ struct VirtInfo {
 // share one L2.  A workgroup handles row groups [q*per, (q+1)*per) of ceil(A/4).
 //
 // VIRT: several lanes per neuron (VirtInfo); the launch computes the outputs of its workgroups' neurons.
+// WHOLE: the layer has the tile layout of the whole row (LayerWeights::planes_log2).
 // ---------------------------------------------------------------------------
-template <bool MULTI, bool VIRT = false>
+template <bool MULTI, bool VIRT = false, bool WHOLE = false>
 __global__ __launch_bounds__(kBlk) void fused_layer_kernel(
     const float* __restrict__ Yin, float* __restrict__ Yout, uint8_t* __restrict__ flags,
     RowLists rl, LayerWeights w,
@@ -838,10 +857,14 @@ __global__ __launch_bounds__(kBlk) void fused_layer_kernel(
     {
         load_slots(off, w.rel, b, tid);
         load_weights(wv, w.val, b, tid);
+        if constexpr (MULTI) {
 #pragma unroll
-        for (int k = 0; k < kNnz; ++k) {
-            if (MULTI) stg[k >> 3] |= (off[k] >> kCapLog2) << (4 * (k & 7));
-            off[k] = lds_base + tile_offset(MULTI ? off[k] & (kCap - 1) : res_slot(off[k], w.planes_log2));
+            for (int k = 0; k < kNnz; ++k) {
+                stg[k >> 3] |= (off[k] >> kCapLog2) << (4 * (k & 7));
+                off[k] = lds_base + tile_offset(off[k] & (kCap - 1));
+            }
+        } else {
+            slot_addresses<WHOLE>(off, w, lds_base, c_lo);
         }
     }
     if (MULTI) {
@@ -875,7 +898,7 @@ __global__ __launch_bounds__(kBlk) void fused_layer_kernel(
     uint32_t qp = 0;  // byte a = quad of column 4t + a, times 16
     if (!MULTI) {
         st_addr = lds_base + tile_offset(store_group(4 * tid) << 4);
-        qp = w.qsel[(size_t)b * kBlk + tid];
+        qp = staging_quads<WHOLE>(w, b, tid, c_lo);
     }
     ListWindow rows_of(cat, g0 * kRows, min(A, g1 * kRows), wi.identity);
     const int cat_last = rows_of.last();  // used by the last, ragged group only: then the list's last entry
@@ -1046,7 +1069,7 @@ struct PairRelabel {
     int seg_log2;        // a unit's neurons: segments of 1 << seg_log2 neighbours, one every seg_stride neurons
     int seg_stride;
 };
-template <bool RELABEL = false>
+template <bool RELABEL = false, bool WHOLE = false>
 __global__ __launch_bounds__(kBlk) void fused_pair_kernel(
     const float* __restrict__ Yin, float* __restrict__ Yout, uint8_t* __restrict__ flags,
     RowLists rl, LayerWeights w,
@@ -1074,13 +1097,8 @@ __global__ __launch_bounds__(kBlk) void fused_pair_kernel(
     const int ncols = win.y;
     const uint32_t lds_base = (uint32_t)(uintptr_t)lds4;
 
-    {
-#pragma unroll
-        for (int k = 0; k < kNnz; ++k) {
-            offA[k] = lds_base + tile_offset(res_slot(offA[k], w.planes_log2));
-            offB[k] = lds_base + tile_offset(res_slot(offB[k], w.planes_log2));
-        }
-    }
+    slot_addresses<WHOLE>(offA, w, lds_base, c_lo);
+    slot_addresses<WHOLE>(offB, w, lds_base, c_lo);
     const float bjA = bias[jA], bjB = bias[jB];
 
     const int T = g1 - g0;
@@ -1088,7 +1106,7 @@ __global__ __launch_bounds__(kBlk) void fused_pair_kernel(
     const int wave_col = (tid & ~63) * 4;
     const bool staging = wave_col < ncols;  // waves whose columns lie past the window stage nothing
     const uint32_t st_addr = lds_base + tile_offset(store_group(4 * tid) << 4);
-    const uint32_t qp = w.qsel[(size_t)b * kBlk + tid];
+    const uint32_t qp = staging_quads<WHOLE>(w, b, tid, c_lo);
     ListWindow rows_of(cat, g0 * kRows, min(A, g1 * kRows), wi.identity);
     const int cat_last = rows_of.last();  // used by the last, ragged group only: then the list's last entry
     // byte offset of my four columns in a row; lanes past the window re-read its last columns
@@ -2039,10 +2057,13 @@ __global__ __launch_bounds__(kBlk) void block_window_kernel(const int32_t* __res
 }
 
 // Networks whose rows fit one LDS stage: every block's window is the whole row, whatever it reads of it, so that all
-// blocks share one tile layout.
-__global__ void whole_row_window_kernel(int2* __restrict__ win, int nblk, int N, int* __restrict__ widest) {
+// blocks share one tile layout.  own: the blocks' windows as they were.
+__global__ void whole_row_window_kernel(int2* __restrict__ win, int2* __restrict__ own, int nblk, int N, int* __restrict__ widest) {
     const int b = threadIdx.x;
-    if (b < nblk) win[b] = make_int2(0, N);
+    if (b < nblk) {
+        own[b] = win[b];
+        win[b] = make_int2(0, N);
+    }
     if (b == 0) *widest = N;
 }
 

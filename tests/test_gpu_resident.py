@@ -151,6 +151,36 @@ def test_rows_that_die_late(N, batch, L, general, order):
     m.close()
 
 
+@pytest.mark.parametrize("N,stride,uniform", [(1024, 8, True), (1500, 20, False), (2048, 24, True), (2048, 24, False),
+                                              (3072, 40, False), (4096, 16, True), (4096, 64, False), (4092, 50, False)])
+def test_windows_inside_the_row(N, stride, uniform):
+    """Layers whose blocks read a part of the row only, over the row end in the last blocks: the kernels of single layers
+    stage that part (weights in host memory) in the layout of the whole row, with the same
+    sums as on the chip; against the oracle."""
+    import torch
+    import paper_2007_14152_amd as sp
+    rng = np.random.default_rng(N + stride)
+    L = 3
+    j, k = np.arange(N, dtype=np.int64)[:, None], np.arange(32, dtype=np.int64)[None, :]
+    idx = [np.sort((j + 300 * l + k * stride + rng.integers(0, 4, size=(N, 32))) % N, axis=1).astype(np.int32) for l in range(L)]
+    val = [np.full((N, 32), 0.0625, np.float32) if uniform else rng.uniform(0.02, 0.11, size=(N, 32)).astype(np.float32)
+           for _ in range(L)]
+    bias = -rng.uniform(0.0, 0.4, size=N).astype(np.float32)
+    Y0 = synth.gen_y0(600, N, 37, density="mixed")
+    Y0[7] = 0
+    ref = oracle.infer(idx, val, bias, Y0)
+    y0 = torch.from_numpy(Y0).to("cuda:0")
+    got = []
+    for ooc in (False, True):
+        m = sp.Model(idx, val, bias, out_of_core=ooc)
+        got.append(m.infer(y0))
+        assert m.launches() == ((L, 0) if ooc else (1, 1))
+        m.close()
+    assert got[0][0] == got[1][0] and torch.equal(got[0][1], got[1][1]) and torch.equal(got[0][2], got[1][2])
+    common, _ = check_against_oracle(ref, got[0][0], got[0][1].cpu().numpy(), got[0][2].cpu().numpy(), what="windows N=%d" % N)
+    assert 0 < common < 600
+
+
 @pytest.mark.parametrize("N,batch,L,die", [
     (4096, 1600, 9, True),     # rows in LDS, two launches
     (4096, 1600, 9, False),

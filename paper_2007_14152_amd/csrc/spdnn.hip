@@ -570,7 +570,10 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
             spdnn::order_by_length(hp.data(), N, nblk * spdnn::kBlk, resident_waves(N, resident_groups_per_wave(nblk, false)), perm, nch);
             uneven += spdnn::uneven_chunks(hp.data(), N, nch, resident_waves(N, resident_groups_per_wave(nblk, true)));
         }
-        if (uneven > 0.0) resident = parts = false;
+        // A single layer of at most 32 connections per neuron: what one_by_one() says of one layer, for any batch (the
+        // layouts differ).  8 to 32 connections, 30 000 rows: 2048 neurons 319 -> 253 us, 4096 600 -> 472; 100 rows 48 ->
+        // 54, 53 -> 55.
+        if (uneven > 0.0 || (parts && P == 1 && (nblk == 2 || nblk == 4))) resident = parts = false;
     }
 
     const size_t raw = (size_t)N * spdnn::kNnz;
@@ -1023,6 +1026,8 @@ int static_scratch(void** out) {
     return SPDNN_OK;
 }
 
+constexpr int32_t kFewLayers = 4;  // networks of so few layers are not cut into launches that keep rows in LDS
+
 // How resident_kernel runs a network: the most groups of 64 neurons a wave owns, the most planes of 4 rows a pass
 // holds, the workgroup's threads and LDS, and how many workgroups fit the GPU at once.
 struct ResidentShape {
@@ -1047,6 +1052,31 @@ bool one_launch(const spdnn_model* h, int32_t batch) {
     const int32_t groups = (batch + spdnn::kRows - 1) / spdnn::kRows;
     const int32_t share = (groups + h->num_cu - 1) / h->num_cu * spdnn::kRows;
     return share <= (h->nblk == 1 ? spdnn::kShareRows : spdnn::kRows * (1 << spdnn::res_planes_log2(h->nblk)));
+}
+
+// How many layers, from the first on, run one by one, through the kernels they are set up for: all, two or none.  A launch that
+// keeps rows in LDS brings them in and out again beside its arithmetic, not under it, which a few layers of many passes
+// do not make up for (once most of the rows that die have died, the rest is fewer passes and more layers).
+// Whole passes on 60 000 rows, rows in LDS -> one by one, the layers of 4096 neurons with one weight: 1 layer 1073 -> 812 us;
+// half the rows dead behind the first layer 816 -> 610; 2 layers 1408 -> 1211; the first 2 of 6 1690 -> 1469; with weights
+// of their own 1 layer 1136 -> 891, 2 layers 1496 -> 1411; 2048 neurons, one weight, 1 layer 536 -> 419, the first 2 of 6 873 ->
+// 792, weights 562 -> 414, 1015 -> 944.  20 000 rows of 4096 neurons with weights and windows of 300 columns, 2 layers:
+// 508 -> 400; 60 000 rows of 1024 neurons, 1 layer: 284 -> 221 (512 neurons on the chip: 166).  Not for three output blocks, which the CUs cannot share evenly (3072 neurons, 3 layers, 1003 -> 1347), nor for four
+// where the last one is ragged and there is no pair of neurons per lane (4000 neurons, one weight, 3 layers: 1208 -> 1194).
+int32_t one_by_one(const spdnn_model* h, int32_t batch) {
+    if (h->N <= 512 || h->nblk == 3 || h->res_mode == spdnn::kResParts || one_launch(h, batch)) return 0;
+    const ResidentShape shape = resident_shape(h, batch);
+    const int32_t rows = shape.slots * shape.planes * spdnn::kRows;
+    const int32_t passes = (batch + rows - 1) / rows;
+    if (h->L == 1) return passes >= 2 ? 1 : 0;
+    if (h->nblk == 1 || (h->nblk == 4 && h->N != spdnn::kCap)) return 0;
+    bool pair = true, narrow = true;  // the first two layers: two neurons per lane; windows of at most half a row
+    for (int32_t l = 0; l < 2; ++l) {
+        pair = pair && h->layers[l].mode == kPair;
+        narrow = narrow && 2 * h->layers[l].lds_cols <= h->N;
+    }
+    if (h->L <= kFewLayers) return passes >= (narrow ? 4 : pair ? (h->L == 2 ? 5 : 8) : 12) ? h->L : 0;
+    return passes >= (pair ? 8 : h->nblk == 2 ? 12 : INT32_MAX) ? 2 : 0;
 }
 
 hipError_t launch_resident(spdnn_t h, const ResidentShape& r, int32_t Q, const float* Yin, float* Yout, uint8_t* flags,
@@ -1260,7 +1290,7 @@ int finish_infer(spdnn_t h, const uint8_t* flags, const int* count_in, const int
 // which the two kernels that make sure would take longer than, and not in a network of so few layers that little is known
 // and the pass counts (4 layers of 65536 neurons on 4000 rows, half of them dead in the last: 1.82 -> 2.02 ms with it).
 bool write_through(const spdnn_model* h, const float* Y_final_dev, int32_t rows, bool none_died) {
-    return Y_final_dev && none_died && h->L > 4 && (size_t)rows * h->N * sizeof(float) >= ((size_t)8 << 20);
+    return Y_final_dev && none_died && h->L > kFewLayers && (size_t)rows * h->N * sizeof(float) >= ((size_t)8 << 20);
 }
 
 // infer_impl for networks whose rows stay in LDS from layer to layer (resident_kernel).
@@ -1283,7 +1313,7 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
         HIP_TRY(hipGetLastError());
     }
     // Runs of layers.  In one launch the workgroups pack their shares together once, behind the first two layers, if
-    // they are of several passes.  Otherwise the batch is compacted and shared out anew after two layers, where most
+    // they are of several passes.  Few layers are one launch as well.  Otherwise the batch is compacted and shared out anew after two layers, where most
     // of the rows that die have died.  If fewer than a quarter died, or not many layers are left, they are one launch;
     // if not, the next run is four times as long, and so on.  (A launch costs the gap before it, 20 us, and the rows'
     // way through memory, together what two to three layers of 4096 neurons take; rows that die afterwards are the
@@ -1318,9 +1348,25 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
         lo ^= 1;
         return rc;
     };
+    if (one_by_one(h, batch) == 2) {
+        HIP_TRY(launch_init_lists(h, wv, batch, row_offset));
+        for (int32_t l = 0; l < 2; ++l) {
+            if (h->profiling) HIP_TRY(hipEventRecord(h->t0[l], s));
+            HIP_TRY(launch_layer(h, h->layers[l], l == 0 ? Y0_dev : wv.Y[0], wv.Y[l], wv.flags[l], layer_lists(h, wv, l, true), batch));
+            ++h->launches;
+            if (h->profiling) HIP_TRY(hipEventRecord(h->t1[l], s));
+            runs.push_back(Run{l, l + 1});
+        }
+        const int rc = compact(wv.flags[1], wv.count[1], wv.gid[1], 2);
+        if (rc != SPDNN_OK) return rc;
+        Yin = wv.Y[1];
+        l0 = 2;
+        k = 1;
+        len = 8;
+    }
     for (; l0 < L && alive > 0; ++k, len *= 4) {
         if (halves && k > 0) len = (int64_t)alive * 32 > (int64_t)before * 31 || L - l0 <= 12 ? L : std::max(8, (L - l0 + 1) / 2);
-        const bool rest = one || (!halves && k > 0 && ((int64_t)alive * 4 > (int64_t)before * 3 || L - l0 <= 32)) || len >= L - l0;
+        const bool rest = one || L <= kFewLayers || (!halves && k > 0 && ((int64_t)alive * 4 > (int64_t)before * 3 || L - l0 <= 32)) || len >= L - l0;
         const int32_t l1 = rest ? L : l0 + len;
         const ResidentShape shape = resident_shape(h, alive);
         const int32_t groups = (alive + spdnn::kRows - 1) / spdnn::kRows;
@@ -1356,6 +1402,10 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
         std::vector<int> rows((size_t)L + 1);
         HIP_TRY(hipMemcpy(rows.data(), layer_rows, sizeof(int) * rows.size(), hipMemcpyDeviceToHost));
         rows[0] = batch;
+        if (runs[0].l1 == 1) {  // the first two layers were launches of their own
+            rows[1] = h->host_counts[1];
+            rows[2] = h->host_counts[2];
+        }
         int32_t run = L;  // "launched": up to the first layer without rows
         for (int32_t l = 1; l < L; ++l)
             if (rows[l] == 0) {
@@ -1381,7 +1431,7 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
 int infer_impl(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv, int32_t row_offset,
                int32_t* n_active_host, int32_t* active_rows_dev, float* Y_final_dev) {
     const int32_t L = h->L;
-    if (h->res_layers)
+    if (h->res_layers && one_by_one(h, batch) < L)
         return infer_resident(h, Y0_dev, batch, wv, row_offset, n_active_host, active_rows_dev, Y_final_dev);
     hipStream_t s = h->stream;
     // Kernels may be queued when a later HIP call fails: nothing of this call is left running on return.

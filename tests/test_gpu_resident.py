@@ -106,6 +106,8 @@ def test_neurons_of_any_length_stay_on_chip(N, batch, L, kmin, kmax):
     (4096, 13001, 18, False, "sorted"),
     (4096, 11001, 12, True, "late"),
     (4096, 9001, 30, False, "late"),
+    (4096, 17001, 12, False, "mixed"),   # the first two layers one by one, two neurons per lane
+    (1500, 49300, 7, False, "sorted"),   # ... one neuron per lane
 ])
 def test_rows_that_die_late(N, batch, L, general, order):
     """Passes that lose half their rows on the way are stopped and merged, more than once.  Row r holds the integer v_r
@@ -151,11 +153,48 @@ def test_rows_that_die_late(N, batch, L, general, order):
     m.close()
 
 
+@pytest.mark.parametrize("N,batch,L,uniform,one_by_one", [
+    (516, 40000, 1, False, 1), (512, 40000, 1, False, 0), (1028, 9000, 1, True, 1), (2048, 9000, 1, False, 1),
+    (2048, 21000, 2, True, 2), (2048, 9000, 2, True, 0), (4096, 17000, 3, True, 3), (4096, 9000, 4, False, 0),
+    (4096, 25000, 4, False, 4), (1500, 50000, 3, False, 3), (4092, 25000, 2, False, 0), (3072, 20000, 1, True, 0),
+    (4096, 17000, 5, True, 2), (2048, 50000, 5, False, 2), (4096, 25000, 5, False, 0),
+])
+def test_few_layers_on_many_rows_run_one_by_one(N, batch, L, uniform, one_by_one):
+    """Layers that are not worth a launch that keeps rows in LDS: a launch each, and the same bits as the same rows get
+    on the chip, in batches small enough for one launch."""
+    import torch
+    import paper_2007_14152_amd as sp
+    dev = "cuda:0"
+    g = torch.Generator(device=dev).manual_seed(N + batch + L)
+    rng = np.random.default_rng(N + batch + L)
+    idx = [np.sort(rng.integers(0, N, size=(N, 32)), axis=1).astype(np.int32) for _ in range(L)]
+    val = [np.full((N, 32), 0.0625, np.float32) if uniform else rng.uniform(0.02, 0.11, size=(N, 32)).astype(np.float32)
+           for _ in range(L)]
+    m = sp.Model(idx, val, -rng.uniform(0.0, 0.5, size=N).astype(np.float32))
+    density = torch.rand((batch, 1), generator=g, device=dev) * 0.5
+    y0 = (torch.rand((batch, N), generator=g, device=dev) < density).float()
+    y0[::97] = 0
+    m.set_profiling(True)
+    n, rows, Y = m.infer(y0)
+    launches, resident = m.launches()
+    assert launches - resident == one_by_one and (resident > 0) == (one_by_one < L)
+    run, rows_in, ms = m.profile()
+    assert run == L and rows_in[0] == batch and np.all(np.diff(rows_in) <= 0) and n <= rows_in[L - 1] and np.all(ms > 0)
+    assert 0 < n < batch
+    step = 1000
+    for r in (0, batch // 2 // step * step, batch - step):
+        ns, rs, Ys = m.infer(y0[r:r + step].contiguous())
+        assert m.launches() == (1, 1)
+        mine = (rows >= r) & (rows < r + step)
+        assert ns == int(mine.sum()) and torch.equal(rows[mine] - r, rs) and torch.equal(Y[mine], Ys)
+    m.close()
+
+
 @pytest.mark.parametrize("N,stride,uniform", [(1024, 8, True), (1500, 20, False), (2048, 24, True), (2048, 24, False),
                                               (3072, 40, False), (4096, 16, True), (4096, 64, False), (4092, 50, False)])
 def test_windows_inside_the_row(N, stride, uniform):
     """Layers whose blocks read a part of the row only, over the row end in the last blocks: the kernels of single layers
-    stage that part (weights in host memory) in the layout of the whole row, with the same
+    stage that part (weights in host memory; single layers on many rows) in the layout of the whole row, with the same
     sums as on the chip; against the oracle."""
     import torch
     import paper_2007_14152_amd as sp
@@ -179,6 +218,14 @@ def test_windows_inside_the_row(N, stride, uniform):
     assert got[0][0] == got[1][0] and torch.equal(got[0][1], got[1][1]) and torch.equal(got[0][2], got[1][2])
     common, _ = check_against_oracle(ref, got[0][0], got[0][1].cpu().numpy(), got[0][2].cpu().numpy(), what="windows N=%d" % N)
     assert 0 < common < 600
+    # one layer, many rows
+    m = sp.Model(idx[:1], val[:1], bias)
+    big = y0.repeat(30, 1)
+    n, rows, Y = m.infer(big)
+    one = m.infer(y0)
+    m.close()
+    keep = rows < 600
+    assert n == 30 * one[0] and torch.equal(rows[keep], one[1]) and torch.equal(Y[keep], one[2])
 
 
 @pytest.mark.parametrize("N,batch,L,die", [

@@ -248,8 +248,8 @@ int spdnn_get_profile(spdnn_t h, int32_t cap, int32_t* layers_run, int32_t* rows
  *                      registers).
  * SPDNN_KERNEL_ROW2    one weight, N a multiple of 4096, windows wider than one stage but every
  *                      4096-neuron unit within 16384 columns: four neurons per lane, tiles of two rows.
- * SPDNN_KERNEL_FLAT    N at most 16384, at most 32 connections per neuron, windows of two or more stages and none of
- *                      the kernels for one weight above: whole rows side by side in LDS.
+ * SPDNN_KERNEL_FLAT    N at most 16384, at most 32 connections per neuron, windows of two or more stages and neither
+ *                      ROW2 nor (two stages, N above 8192) WIDE_PAIR4: whole rows side by side in LDS.
  * Returns SPDNN_EINVAL for a NULL handle or pointer or l outside [0, L). */
 /* (A layer of several passes reports the kernel of its first pass.) */
 #define SPDNN_KERNEL_SINGLE 0

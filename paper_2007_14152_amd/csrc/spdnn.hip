@@ -856,10 +856,15 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
         {  // Rows of up to 16384 columns that the blocks read more of than one LDS stage: whole rows in LDS, whatever the
            // weights (two-row tiles, which hold four neurons per lane for one weight and N a multiple of 4096, were
            // taken above).  The arena's wide format stays empty.
+           // But one weight, pairs of blocks and windows of two stages in rows of more than two: a window takes fewer bytes
+           // than the row (4 layers on 8000 rows, whole rows -> windows: 10240 neurons, 4200 columns 1.30 -> 1.02 ms, 8000
+           // columns 1.30 -> 1.21; 14336 neurons, 4200 columns 1.69 -> 1.39, 6500 columns 1.68 -> 1.69, 9000 columns, three
+           // stages, 1.67 -> 3.45; 6144 neurons, 5500 columns 0.80 -> 1.27.  On 100 rows windows take 0.13 ms, whole rows 0.10.)
             int widest = 4;
             for (int32_t b = 0; b < nblk; ++b) widest = std::max(widest, hw[(size_t)l * nblk + b].y);
             const int nst = stages_of(widest);
-            if (!d.multi && !pair && nst >= 2 && N <= spdnn::kFlatCols) {
+            const bool windows = wide_pair && nst == 2 && nst <= nstage_cap && d.ww.ps && N > 2 * spdnn::kCap;
+            if (!d.multi && !pair && nst >= 2 && N <= spdnn::kFlatCols && !windows) {
                 spdnn::flat_pack_kernel<<<nblk * spdnn::kBlk / spdnn::kGroup32, spdnn::kRow2PackThreads, 0, stream>>>(
                     di, dv, N, const_cast<uint16_t*>(d.w.rel), const_cast<float*>(d.w.val));
                 HIP_TRY(hipGetLastError());

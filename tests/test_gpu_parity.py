@@ -735,6 +735,9 @@ def test_scattered_windows_gathered_footprint(N, w, batch):
     (16384, (256, 1, 32), True, "PAIR PAIR PAIR"),  # stride 256: two neurons per lane under new names for neurons and columns
     (16384, (256,), False, "FLAT"),             # three stages, weights of their own: whole rows
     (10240, (256,), True, "FLAT"),              # three stages, one weight: whole rows
+    (10240, (128,), True, "WIDE_PAIR4"),        # two stages of a row of three: the windows
+    (14336, (140,), True, "WIDE_PAIR4"),
+    (10240, (128,), False, "FLAT"),
     (18432, (160,), False, "STAGED"),           # two stages, one neuron per lane, rows too long to be held whole
     (18432, (270,), False, "WIDE"),             # three stages, one neuron per lane
     (18432, (150,), True, "WIDE_PAIR4"),        # two stages, two neurons per lane, step lists in registers

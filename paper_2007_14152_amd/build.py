@@ -24,6 +24,11 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
 
 
 NO_SCRATCH_KERNELS = ["fused_row2_kernel", "fused_pair_kernel"]
+# Kernels that count LDS addresses from the start of the workgroup's LDS: all of it must be dynamic.
+LDS_FROM_ZERO_KERNELS = ["resident_kernel", "fused_flat_kernel"]
+# Bytes of scratch per lane that these may spill: outside the arithmetic, at what was measured with them.  (Spills are
+# memory operations more, which the waits written out by hand cover: they count at most what comes after the loads.)
+SCRATCH_LIMIT = {"resident_kernel": 96, "fused_flat_kernel": 24}
 
 
 def _resource_usage(text):
@@ -60,6 +65,17 @@ def build(verbose: bool = False, extra=()) -> str:
             if v.get("ScratchSize [bytes/lane]", 0) != 0:
                 raise RuntimeError("build check: %s uses %d bytes of scratch per lane; it must use none"
                                    % (k, v["ScratchSize [bytes/lane]"]))
+    for kernel in LDS_FROM_ZERO_KERNELS:
+        hits = {k: v for k, v in usage.items() if kernel in k}
+        if not hits:
+            raise RuntimeError("build check: kernel %s not found in the compiler's resource report" % kernel)
+        for k, v in hits.items():
+            if v.get("LDS Size [bytes/block]", 1) != 0:
+                raise RuntimeError("build check: %s has %s bytes of static LDS; its addresses start at 0" % (
+                    k, v.get("LDS Size [bytes/block]", "an unknown number of")))
+            if v.get("ScratchSize [bytes/lane]", 0) > SCRATCH_LIMIT[kernel]:
+                raise RuntimeError("build check: %s uses %d bytes of scratch per lane, more than %d"
+                                   % (k, v["ScratchSize [bytes/lane]"], SCRATCH_LIMIT[kernel]))
     if verbose:
         for k, v in sorted(usage.items()):
             if "fused_" in k or "resident_" in k:

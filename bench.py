@@ -17,6 +17,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0       # MI355X published peak HBM3E bandwidth
+FMA_PEAK_T = 256 * 64 * 2.4e9 / 1e12   # multiply-adds: 256 CUs, one per lane and clock
 
 
 def parse():
@@ -178,7 +179,7 @@ def timed_leg(model, y0, steps, warmup, N, nnz, events_in_timed_region=True):
         dt_plain = time.perf_counter() - t0
     model.set_profiling(True)
     sum_ms = sum_bytes = full_ms = 0.0
-    launches = full = 0
+    layers = full = 0
     batch = int(y0.shape[0])
     rows_trace = None
     torch.cuda.synchronize()
@@ -188,19 +189,32 @@ def timed_leg(model, y0, steps, warmup, N, nnz, events_in_timed_region=True):
         run, rows_in, ms = model.profile()
         sum_ms += float(ms.sum())
         sum_bytes += sum(algorithmic_bytes(r, N, nnz[l] if nnz else None) for l, r in enumerate(rows_in))
-        launches += run
+        layers += run
         sel = rows_in == batch
         full += int(sel.sum())
         full_ms += float(ms[sel].sum())
         rows_trace = rows_in
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
+    launches, resident = (n * steps for n in model.launches())   # every step's are the same
     model.set_profiling(False)
     if dt_plain is not None:
         dt = dt_plain
     return {"s_per_step": dt / steps, "sum_ms": sum_ms, "sum_bytes": sum_bytes, "launches": launches,
-            "full_launches": full, "full_ms": full_ms, "rows_trace": np.asarray(rows_trace), "n_active": int(n_active),
+            "resident": resident, "layers": layers, "full_launches": full, "full_ms": full_ms, "rows_trace": np.asarray(rows_trace), "n_active": int(n_active),
             "rows_final": rows_final.cpu().numpy()}
+
+
+def roofline(leg, executed_edges):
+    """What bounds the fused launches, and how near they are to it.  A launch per layer: HBM, which a layer's input and
+    output go through.  Rows that stay on the chip over several layers: the multiply-adds of the edges, one per lane and
+    clock, whose operands take the LDS as long; how many bytes such launches move is not counted here."""
+    s = leg["sum_ms"] * 1e-3
+    if leg["resident"]:
+        achieved = executed_edges / s / 1e12 if s > 0 else 0.0
+        return {"bound": "fma", "achieved": achieved, "peak": FMA_PEAK_T, "unit": "T multiply-adds/s", "frac": achieved / FMA_PEAK_T}
+    achieved = leg["sum_bytes"] / s / 1e9 if s > 0 else 0.0
+    return {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS}
 
 
 def rows_summary(rows_trace):
@@ -285,19 +299,17 @@ def main():
         edges = synth.nominal_edges(N, L, batch)
         executed = float(sum(int(r) for r in rows_trace)) * N * 32
     ms_per_step = dt / a.steps * 1e3
-    achieved = sum_bytes / (sum_ms * 1e-3) / 1e9 if sum_ms > 0 else 0.0
-    one_launch = model.one_launch(batch)   # small networks: every layer inside one launch of resident_kernel
-    resident = N <= 4096 and not a.out_of_core   # ... which runs several layers per launch at any batch
-    kinds = {}
-    for l in range(int(launches // a.steps)):
-        k = "resident_kernel" if resident else sp.KERNEL_NAMES[model.layer_kernel(l)]
+    layers_run = int(leg["layers"] // a.steps)
+    # layers that ran on the chip several to a launch, and layers with a launch each (the first two, or all)
+    on_chip = layers_run - (leg["launches"] - leg["resident"]) // a.steps if leg["resident"] else 0
+    kinds = {"resident_kernel": on_chip} if on_chip else {}
+    for l in range(min(layers_run - on_chip, launches // a.steps)):   # (a layer no row reached may not have been launched)
+        k = sp.KERNEL_NAMES[model.layer_kernel(l)]
         kinds[k] = kinds.get(k, 0) + 1
-    kernel0 = "resident_kernel" if resident else sp.KERNEL_NAMES[model.layer_kernel(0)]
-    layers_run = int(launches // a.steps)
-    if one_launch:   # the library shares the launch's duration out among the layers; the launch is the unit here
-        launches = a.steps
+    kernel0 = "resident_kernel" if on_chip == layers_run else sp.KERNEL_NAMES[model.layer_kernel(0)]
     full_bytes = algorithmic_bytes(batch, N, nnz[0] if nnz else None)
-    full_ms = leg["full_ms"] / leg["full_launches"] if leg["full_launches"] else None
+    per_layer = not leg["resident"]   # a launch per layer: then a layer's time is its launch's
+    full_ms = leg["full_ms"] / leg["full_launches"] if leg["full_launches"] and per_layer else None
     traffic, traffic_source = measured_traffic("cfg%d_batch%d_%s" % (a.config, batch, density), kernel0)
     if a.scatter or a.general or a.out_of_core or a.strided:
         traffic, traffic_source = None, None
@@ -318,19 +330,18 @@ def main():
             "executed_TeraEdges_per_s": executed * a.steps / dt / 1e12,
             "rows_in_per_layer": rows_summary(rows_trace),
             "kernels_of_launched_layers": kinds,
-            "launches_per_inference": 1 if one_launch else layers_run,
+            "launches_per_inference": launches // a.steps,
             "n_active_final": int(n_active),
             "setup_s": t_create, "generate_inputs_s": t_setup - t_create},
-        # achieved = algorithmic bytes of all fused launches / their summed duration (HIP events on the
-        # model's stream); full_launch_* = the launches on all `batch` rows alone
-        "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": achieved / HBM_PEAK_GBS,
+        # all fused launches / their summed duration (HIP events on the model's stream); full_launch_* = the launches on
+        # all `batch` rows alone
+        "roofline": {**roofline(leg, executed * a.steps),
                      "traffic": traffic, "traffic_source": traffic_source,
                      "kernel": kernel0, "launches": int(launches),
                      "avg_launch_ms": sum_ms / max(launches, 1),
-                     "algorithmic_bytes_per_launch": sum_bytes / max(launches, 1),
-                     "full_launch_ms": full_ms, "full_launches": int(leg["full_launches"]),
-                     "algorithmic_bytes_full_launch": full_bytes,
+                     "algorithmic_bytes_per_launch": sum_bytes / max(launches, 1) if per_layer else None,
+                     "full_launch_ms": full_ms, "full_launches": int(leg["full_launches"]) if per_layer else None,
+                     "algorithmic_bytes_full_launch": full_bytes if per_layer else None,
                      "full_launch_frac": (full_bytes / (full_ms * 1e-3) / 1e9 / HBM_PEAK_GBS) if full_ms else None},
     }
     if not a.no_cpu_baseline:
@@ -353,8 +364,10 @@ def main():
             "nominal_TeraEdges_per_s": edges / sl["s_per_step"] / 1e12,
             "executed_TeraEdges_per_s": ex / sl["s_per_step"] / 1e12,
             "rows_in_per_layer": rows_summary(sl["rows_trace"]), "n_active_final": sl["n_active"],
-            "fused_ms_per_layer": sl["sum_ms"] / max(sl["launches"], 1),
-            "roofline_frac": sl["sum_bytes"] / (sl["sum_ms"] * 1e-3) / 1e9 / HBM_PEAK_GBS if sl["sum_ms"] > 0 else None}
+            "launches_per_inference": sl["launches"] // a.sustained_steps,
+            "fused_ms_per_layer": sl["sum_ms"] / max(sl["layers"], 1),
+            "roofline_bound": roofline(sl, ex * a.sustained_steps)["bound"],
+            "roofline_frac": roofline(sl, ex * a.sustained_steps)["frac"] if sl["sum_ms"] > 0 else None}
     print(json.dumps(out))
 
 

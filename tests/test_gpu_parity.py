@@ -512,6 +512,29 @@ def test_out_of_core_weights_match_resident_weights(cfg, layers, batch, density)
     ooc.close()
 
 
+@pytest.mark.parametrize("N,layers,batch", [(5000, 4, 300), (8192, 3, 130), (13000, 2, 40)])
+def test_out_of_core_whole_rows(N, layers, batch):
+    """The same for layers that run on whole rows in LDS (weights of their own, 4097 to 16384 columns)."""
+    import torch
+    import paper_2007_14152_amd as sp
+    rng = np.random.default_rng(N)
+    idx, val, bias = rand_model(rng, N, layers, True, True, lo=0.02, hi=0.11)
+    Y0 = synth.gen_y0(batch, N, 41, density="mixed")
+    y0 = torch.from_numpy(Y0).to("cuda:0")
+    res = sp.Model(idx, val, bias)
+    ooc = sp.Model(idx, val, bias, out_of_core=True)
+    assert [m.layer_kernel(l) for m in (res, ooc) for l in range(layers)] == [sp.SPDNN_KERNEL_FLAT] * (2 * layers)
+    want = res.infer(y0)
+    for _ in range(2):
+        n, rows, Y = ooc.infer(y0)
+        assert n == want[0] and torch.equal(rows, want[1]) and torch.equal(Y, want[2])
+        assert ooc.launches() == (layers, 0)
+    res.close()
+    ooc.close()
+    ref = oracle.infer(idx, val, bias, Y0)
+    check_against_oracle(ref, n, rows.cpu().numpy(), Y.cpu().numpy(), what="out of core, whole rows N=%d" % N)
+
+
 def test_out_of_core_sizes_and_errors():
     import torch
     import paper_2007_14152_amd as sp
@@ -550,10 +573,11 @@ def test_batch_larger_than_one_compaction_chunk():
 
 
 @pytest.mark.parametrize("N,batch,kernel", [
-    (1024, 50001, "fused_layer_kernel<false>"),   # one neuron per lane, one column block, 250 row chunks
-    (4096, 30001, "fused_pair_kernel"),           # two neurons per lane
+    (1024, 50001, "fused_layer_kernel<false>"),   # rows on the chip, several passes per workgroup
+    (4096, 30001, "fused_pair_kernel"),           # two layers of two neurons per lane, then rows on the chip
+    (6144, 20001, "fused_flat_kernel"),           # whole rows of three per tile
     (8192, 12002, "fused_row2_kernel"),           # two-row tiles: slices of the list in pairs of rows
-    (4100, 9999, None),                           # ragged last output block, window wider than one stage
+    (4100, 9999, "fused_flat_kernel"),            # ragged last output block
 ])
 def test_rows_die_in_every_layer_closed_form(N, batch, kernel):
     """The list of active rows is derived by every layer's own kernel from the flags of the layer before
@@ -587,6 +611,31 @@ def test_rows_die_in_every_layer_closed_form(N, batch, kernel):
     ref = oracle.infer([i.cpu().numpy() for i in idx], [val.cpu().numpy()] * L, bias.cpu().numpy(),
                        np.repeat(v[ids].astype(np.float32)[:, None], N, axis=1))
     assert np.array_equal(ids[ref.active_rows], np.intersect1d(ids, alive))
+    m.close()
+
+
+@pytest.mark.parametrize("N,batch", [(1024, 50001), (1028, 20001), (4096, 30001)])
+def test_rows_die_in_every_layer_weights_out_of_core(N, batch):
+    """The closed form above with the weights in host memory: networks of at most 4096 neurons then run a launch per
+    layer, whose lists are derived from the flags of the layer before, on one and on several output blocks."""
+    import torch
+    import paper_2007_14152_amd as sp
+    dev = "cuda:0"
+    L, vmax = 8, 12
+    rng = np.random.default_rng(N + batch)
+    v = rng.integers(1, vmax + 1, size=batch)
+    idx = [np.sort(rng.integers(0, N, size=(N, 32)), axis=1).astype(np.int32) for _ in range(L)]
+    val = np.full((N, 32), 1.0 / 32, np.float32)
+    m = sp.Model(idx, [val] * L, np.full(N, -1.0, np.float32), out_of_core=True)
+    assert m.layer_kernel(0) == (sp.SPDNN_KERNEL_PAIR if N % 2048 == 0 else sp.SPDNN_KERNEL_SINGLE)
+    m.set_profiling(True)
+    n, rows, Y = m.infer(torch.from_numpy(v.astype(np.float32)).to(dev)[:, None].expand(batch, N).contiguous())
+    run, rows_in, _ = m.profile()
+    assert m.launches() == (L, 0) and run == L
+    assert [int(x) for x in rows_in[:L]] == [int((v > l).sum()) for l in range(L)]
+    alive = np.nonzero(v > L)[0]
+    assert n == len(alive) and np.array_equal(rows.cpu().numpy(), alive)
+    assert bool((Y == torch.from_numpy((v[alive] - L).astype(np.float32)).to(dev)[:, None]).all())
     m.close()
 
 

@@ -1294,8 +1294,10 @@ int finish_infer(spdnn_t h, const uint8_t* flags, const int* count_in, const int
 // 4096 neurons) when they all survive, costs one when they do not: only if no row died lately, not for small results,
 // which the two kernels that make sure would take longer than, and not in a network of so few layers that little is known
 // and the pass counts (4 layers of 65536 neurons on 4000 rows, half of them dead in the last: 1.82 -> 2.02 ms with it).
+// Three layers will do up to 16384 columns (3 layers of 16384 neurons on 8000 rows: all alive 1.12 -> 0.99 ms, half of them
+// dead in the last 1.03 -> 1.15).
 bool write_through(const spdnn_model* h, const float* Y_final_dev, int32_t rows, bool none_died) {
-    return Y_final_dev && none_died && h->L > kFewLayers && (size_t)rows * h->N * sizeof(float) >= ((size_t)8 << 20);
+    return Y_final_dev && none_died && (h->L > kFewLayers || (h->L > 2 && h->N > spdnn::kCap && h->N <= spdnn::kFlatCols)) && (size_t)rows * h->N * sizeof(float) >= ((size_t)8 << 20);
 }
 
 // infer_impl for networks whose rows stay in LDS from layer to layer (resident_kernel).

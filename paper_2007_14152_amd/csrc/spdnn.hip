@@ -559,16 +559,18 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
     bool resident = N <= spdnn::kCap && !ooc;
     bool parts = false;
     std::vector<int32_t> hp((size_t)N + 1);
+    std::vector<std::vector<uint16_t>> perm;  // kResParts, per layer: order_by_length()
+    std::vector<std::vector<uint32_t>> nch;
     if (ptr && resident) {
         double uneven = 0.0;
-        std::vector<uint16_t> perm;
-        std::vector<uint32_t> nch;
+        perm.resize((size_t)L);
+        nch.resize((size_t)L);
         for (int32_t ll = 0; ll < L; ++ll) {
             HIP_TRY(hipMemcpyAsync(hp.data(), ptr[ll], sizeof(int32_t) * hp.size(), hipMemcpyDeviceToHost, stream));
             HIP_TRY(hipStreamSynchronize(stream));
             for (int32_t j = 0; j < N && !parts; ++j) parts = hp[j + 1] - hp[j] != spdnn::kNnz;
-            spdnn::order_by_length(hp.data(), N, nblk * spdnn::kBlk, resident_waves(N, resident_groups_per_wave(nblk, false)), perm, nch);
-            uneven += spdnn::uneven_chunks(hp.data(), N, nch, resident_waves(N, resident_groups_per_wave(nblk, true)));
+            spdnn::order_by_length(hp.data(), N, nblk * spdnn::kBlk, resident_waves(N, resident_groups_per_wave(nblk, false)), perm[ll], nch[ll]);
+            uneven += spdnn::uneven_chunks(hp.data(), N, nch[ll], resident_waves(N, resident_groups_per_wave(nblk, true)));
         }
         // A single layer of at most 32 connections per neuron: what one_by_one() says of one layer, for any batch (the
         // layouts differ).  8 to 32 connections, 30 000 rows: 2048 neurons 319 -> 253 us, 4096 600 -> 472; 100 rows 48 ->
@@ -592,14 +594,8 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
             uint16_t* perm_dev = const_cast<uint16_t*>(m->layers[first].virt.slot);
             const int nlanes = nblk * spdnn::kBlk;
             if (r == 0) {
-                HIP_TRY(hipMemcpyAsync(hp.data(), ptr[ll], sizeof(int32_t) * hp.size(), hipMemcpyDeviceToHost, stream));
-                HIP_TRY(hipStreamSynchronize(stream));
-                std::vector<uint16_t> perm;
-                std::vector<uint32_t> nch;
-                spdnn::order_by_length(hp.data(), N, nlanes, resident_waves(N, resident_groups_per_wave(nblk, false)), perm, nch);
-                HIP_TRY(hipMemcpyAsync(perm_dev, perm.data(), sizeof(uint16_t) * perm.size(), hipMemcpyHostToDevice, stream));
-                HIP_TRY(hipMemcpyAsync(const_cast<uint32_t*>(d.virt.fin), nch.data(), sizeof(uint32_t) * nch.size(), hipMemcpyHostToDevice, stream));
-                HIP_TRY(hipStreamSynchronize(stream));  // both go out of scope
+                HIP_TRY(hipMemcpyAsync(perm_dev, perm[ll].data(), sizeof(uint16_t) * perm[ll].size(), hipMemcpyHostToDevice, stream));
+                HIP_TRY(hipMemcpyAsync(const_cast<uint32_t*>(d.virt.fin), nch[ll].data(), sizeof(uint32_t) * nch[ll].size(), hipMemcpyHostToDevice, stream));
             }
             spdnn::csr_part_kernel<<<(unsigned)((size_t)nlanes * spdnn::kNnz / 256), 256, 0, stream>>>(ptr[ll], idx[ll], val[ll], perm_dev, nlanes, r,
                                                                                                  st_idx, st_val, st_len);
@@ -893,6 +889,7 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
             const_cast<float*>(d.w.val), nrows, lens, lens ? const_cast<uint8_t*>(d.virt.nb8) : nullptr);
         HIP_TRY(hipGetLastError());
         if (whole) {  // what the blocks (pairs of blocks) read of the row, from a multiple of 256 columns on (LayerWeights)
+            bool narrow = false;
             for (int32_t b = 0; b < nblk; ++b) {
                 int2& w = hw[(size_t)l * nblk + b];
                 if (pair && (b & 1)) {
@@ -902,8 +899,9 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
                 if (pair) spdnn::win_union(w.x, w.y, hw[(size_t)l * nblk + b + 1].x, hw[(size_t)l * nblk + b + 1].y, N, w.x, w.y);
                 if (w.x + w.y > N) w = make_int2(0, N);  // it wraps around the row end
                 w = make_int2(w.x & ~255, w.y + (w.x & 255));
+                narrow = narrow || w.y < N;
             }
-            HIP_TRY(hipMemcpyAsync(win_dev[l], &hw[(size_t)l * nblk], sizeof(int2) * nblk, hipMemcpyHostToDevice, stream));
+            if (narrow) HIP_TRY(hipMemcpyAsync(win_dev[l], &hw[(size_t)l * nblk], sizeof(int2) * nblk, hipMemcpyHostToDevice, stream));
         }
         int widest = 4;
         for (int32_t b = 0; b < nblk; ++b) widest = std::max(widest, hw[(size_t)l * nblk + b].y);

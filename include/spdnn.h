@@ -112,9 +112,9 @@ int spdnn_create(spdnn_t* out, int32_t N, int32_t L, const int32_t* const* idx,
  * III-A-3, per wave), and the lanes' sums are added inside the workgroup before bias and ReLU.
  * Such a layer runs as up to P launches, P = ceil(K/32) rounded up to a power of two, each of
  * which computes the outputs of a share of the neurons and takes one layer's room in the
- * weights arena; P is what is called the layer's passes here.  (Models of at most 4096 neurons do without the launches:
- * the neurons are sorted by length and a lane keeps its neuron, 32 connections after 32; the passes then only say how
- * much room a layer takes.)
+ * weights arena; P is what is called the layer's passes here.  (Models of at most 4096 neurons do without the launches,
+ * unless a few neurons are much longer than the others: the neurons are sorted by length and a lane keeps its neuron, 32
+ * connections after 32; the passes then only say how much room a layer takes.)
  *
  * spdnn_csr_passes: passes[l] (host, may be NULL) = passes of layer l, *total = their sum,
  * which is the "L" to size the weights arena with (spdnn_weights_bytes(N, *total, ...)); if
@@ -236,8 +236,8 @@ int spdnn_get_profile(spdnn_t h, int32_t cap, int32_t* layers_run, int32_t* rows
 
 /* Measurement and test aid: which of the library's per-layer fused kernels layer l is set up for, chosen at
  * spdnn_create from the layer's pattern (Section III-A-2's shared-memory stages) and weights.  Models of at most 4096
- * neurons whose weights are resident keep their rows on the chip over several layers in a kernel of their own instead
- * (spdnn_get_launches tells what the last inference ran).
+ * neurons whose weights are resident keep their rows on the chip over several layers in a kernel of their own instead,
+ * except for a few layers on many rows (spdnn_get_launches tells what the last inference ran).
  * SPDNN_KERNEL_SINGLE  every 1024-neuron block's column window fits one LDS stage;
  * SPDNN_KERNEL_STAGED  two stages (or a wider pattern that does not fit the wide format);
  * SPDNN_KERNEL_WIDE    three or more stages;

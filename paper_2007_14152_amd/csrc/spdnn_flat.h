@@ -1,7 +1,7 @@
-// a1 for layers whose blocks read (nearly) whole feature rows of 4097 to 16384 columns, with any weights: whole rows
-// side by side in LDS, just as they lie in memory.
+// a1 for layers whose blocks read more than one LDS stage of feature rows of 4097 to 16384 columns, with any weights: whole
+// rows side by side in LDS, just as they lie in memory.
 //
-// Such a pattern makes every workgroup stage the row, whatever neurons it owns, and what a CU can pull out of L2 is the
+// A pattern that reads the whole row makes every workgroup stage the row, whatever neurons it owns, and what a CU can pull out of L2 is the
 // scarce resource: 64 KB per row at 16384 neurons.  So a workgroup owns as many neurons as the register file holds --
 // two per lane with their 32 weights and 16-bit column offsets (96 registers), four with one weight for the layer --
 // and the rows go from memory straight into LDS (global_load_lds, 16 bytes per lane) without passing through
@@ -18,7 +18,9 @@
 //
 // What bounds it: the LDS reads, 3.1 clocks each with the conflicts the ordering leaves, and next to them the rows'
 // way into LDS.  16384 neurons with weights of their own, 6 layers, 8000 rows: 5.42 -> 2.75 ms (one neuron per lane and
-// the row in four stages before, so every row went to 16 workgroups).
+// the row in four stages before, so every row went to 16 workgroups).  Blocks that read less take it too: 4 layers on
+// 8000 rows, windows -> whole rows, weights of their own: 16384 neurons, 5000 columns 2.69 -> 2.07 ms, 8192 neurons, 4300
+// columns 1.34 -> 1.12, 10240 neurons, 5000 columns 1.78 -> 1.30 (one weight and windows of two stages: see create_impl).
 #pragma once
 
 namespace spdnn {

@@ -2378,7 +2378,7 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const int32_t*
         if (r >= 0) atomicAdd(&B.cursor[r], 1u);
     }
     __syncthreads();
-    // exclusive prefix sum over the columns: lane owns 64 consecutive ones
+    // exclusive prefix sum over the columns: a lane owns 16 consecutive ones
     {
         constexpr int per = kCap / kBalanceThreads;
         uint32_t sum = 0;

@@ -19,7 +19,7 @@
 // (Listing 1's pruning inside the pass).  A pass whose rows have all died is over.
 //
 // A workgroup's share of the rows is a number of passes, and a pass reads a layer's connections whole whatever lives in
-// it.  So rows that die later make passes worth merging: a pass that has lost half its rows stops behind that layer,
+// it.  So rows that die later make passes worth merging: a pass that has lost 3/8 of its rows stops behind that layer,
 // its survivors' rows go to memory, and the share's other passes stop there too; as soon as a pass's worth of rows
 // waits there, it goes on from that layer.  A pass of those may stop again further on (kResLevels).  Nothing of this
 // happens, or costs anything, as long as rows live.  Shares are dealt out quad by quad, so that rows that die together
@@ -32,10 +32,10 @@
 // connections, 768 KB per layer and pass, which a CU pulls out of L2 at 25 bytes per clock.  One workgroup on its own:
 // latency.  The copies between LDS and memory happen once per launch instead of once per layer.
 // Whole passes, one launch per layer -> this kernel: 120 layers of 1024 neurons, 1000 rows 0.85 -> 0.27 ms, 60 000 rows
-// 7.40 -> 4.70; 24 layers of 4096 neurons, 60 000 rows 5.85 -> 4.59; 12 of them with weights of their own, 10 007 rows
-// 1.19 -> 0.88; 6 with 16 to 64 connections per neuron, 10 000 rows 1.26 -> 0.72 (several lanes per neuron and two
-// launches per layer before); 12 layers of 1500 neurons with 0 to 40 connections, 777 rows 309 -> 86 us; 12 layers of
-// 1024 neurons, one row 133 -> 60 us.
+// 7.40 -> 4.70; 24 layers of 4096 neurons, 60 000 rows 5.85 -> 4.53 (the first two layers one by one); 12 of them with
+// weights of their own, 10 007 rows 1.19 -> 0.85; 6 with 16 to 64 connections per neuron, 10 000 rows 1.26 -> 0.68 (several
+// lanes per neuron and two launches per layer before); 12 layers of 1500 neurons with 0 to 40 connections, 777 rows
+// 309 -> 80 us; 12 layers of 1024 neurons, one row 133 -> 56 us.
 //
 // Workgroups.  Networks of one block whose rows are more than a quad per CU run two workgroups per CU of eight waves
 // (two groups of 64 neurons per wave), so that one computes while the other writes or waits at a barrier (120 layers,

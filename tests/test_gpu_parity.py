@@ -642,7 +642,7 @@ def test_rows_die_in_every_layer_weights_out_of_core(N, batch):
 @pytest.mark.parametrize("N,L", [(1024, 7), (96, 5)])
 def test_all_layers_in_one_launch_equals_one_launch_per_layer(N, L):
     """Networks of at most 1024 neurons run all layers in one launch when a workgroup's share of the rows is
-    small (Listing 1's loop over the layers inside the workgroup), one launch per layer otherwise.  The
+    small (Listing 1's loop over the layers inside the workgroup), a few launches otherwise.  The
     arithmetic per row is the same: the rows of a small batch must come out bit for bit as the same rows do
     inside a large batch, with the same rows alive on entry to every layer; and both agree with the oracle."""
     import torch

@@ -153,6 +153,48 @@ def test_rows_that_die_late(N, batch, L, general, order):
     m.close()
 
 
+@pytest.mark.parametrize("N,batch,L,kind", [
+    (100, 60000, 9, "weights"), (1024, 20001, 14, "uniform"), (1024, 41003, 12, "weights"), (1028, 21001, 10, "general"),
+    (2048, 20002, 12, "weights"), (3072, 9003, 11, "uniform"), (4096, 13001, 18, "weights"), (4096, 13001, 12, "uniform"),
+    (4092, 9001, 10, "general"), (4096, 17001, 9, "uniform"),
+])
+def test_rows_that_die_late_keep_their_columns(N, batch, L, kind):
+    """Rows that wait while their pass is stopped go to memory in one layer's layout and come back in another's.  Values
+    differ from column to column here, rows die in every layer, and each row must come out with the bits that it has in
+    a batch of a thousand, whose passes never stop."""
+    import torch
+    import paper_2007_14152_amd as sp
+    dev = "cuda:0"
+    rng = np.random.default_rng(N + L)
+    ptr, idx, val = [], [], []
+    for l in range(L):
+        deg = rng.integers(4, 61, size=N) if kind == "general" else np.full(N, 32)
+        p = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+        w = np.full(p[N], 1.0) if kind == "uniform" else rng.uniform(0.5, 1.5, size=p[N])
+        ptr.append(p)
+        idx.append(rng.integers(0, N, size=p[N]).astype(np.int32))
+        val.append((w / np.repeat(deg, deg)).astype(np.float32))
+    bias = -rng.uniform(0.8, 1.2, size=N).astype(np.float32)   # a layer takes about one off
+    if kind == "general":
+        m = sp.Model.from_csr(ptr, idx, val, bias)
+    else:
+        m = sp.Model([a.reshape(N, 32) for a in idx], [a.reshape(N, 32) for a in val], bias)
+    g = torch.Generator(device=dev).manual_seed(N + L)
+    v = 1.5 + torch.rand((batch, 1), generator=g, device=dev) * (1.1 * L)
+    v[: batch // 5] = L / 2      # the first fifth of the batch dies together
+    y0 = v * (0.9 + 0.2 * torch.rand((batch, N), generator=g, device=dev))
+    n, rows, Y = m.infer(y0)
+    assert m.launches()[1] > 0 and 0 < n < batch
+    assert bool((Y.max(1).values > Y.min(1).values).all())
+    step = 1000
+    for r in (0, batch // 5 - 500, batch // 2, batch - step):
+        ns, rs, Ys = m.infer(y0[r:r + step].contiguous())
+        assert m.launches() == (1, 1)
+        mine = (rows >= r) & (rows < r + step)
+        assert ns == int(mine.sum()) and torch.equal(rows[mine] - r, rs) and torch.equal(Y[mine], Ys)
+    m.close()
+
+
 @pytest.mark.parametrize("N,batch,L,uniform,one_by_one", [
     (516, 40000, 1, False, 1), (512, 40000, 1, False, 0), (1028, 9000, 1, True, 1), (2048, 9000, 1, False, 1),
     (2048, 21000, 2, True, 2), (2048, 9000, 2, True, 0), (4096, 17000, 3, True, 3), (4096, 9000, 4, False, 0),

@@ -237,7 +237,8 @@ int spdnn_get_profile(spdnn_t h, int32_t cap, int32_t* layers_run, int32_t* rows
 /* Measurement and test aid: which of the library's per-layer fused kernels layer l is set up for, chosen at
  * spdnn_create from the layer's pattern (Section III-A-2's shared-memory stages) and weights.  Models of at most 4096
  * neurons whose weights are resident keep their rows on the chip over several layers in a kernel of their own instead,
- * except for a few layers on many rows (spdnn_get_launches tells what the last inference ran).
+ * except for a few layers on many rows, and so do networks of strided sums (see spdnn_one_launch); spdnn_get_launches
+ * tells what the last inference ran.
  * SPDNN_KERNEL_SINGLE  every 1024-neuron block's column window fits one LDS stage;
  * SPDNN_KERNEL_STAGED  two stages (or a wider pattern that does not fit the wide format);
  * SPDNN_KERNEL_WIDE    three or more stages;
@@ -266,7 +267,9 @@ int spdnn_layer_kernel(spdnn_t h, int32_t l, int32_t* kind);
  * neurons per layer whose weights are resident do so -- one workgroup then computes every neuron of its rows, so
  * Listing 1's loop over the layers (kernel, pruning, buffer swap) can run inside the workgroup -- when a workgroup's
  * share of the rows is small: at most 128 rows for models of at most 1024 neurons, what it holds at a time for larger
- * ones.  Larger batches keep their rows on the chip for several layers per launch.  With profiling on, a launch's
+ * ones.  So do models of at most 16384 neurons whose layers are all strided sums -- neuron j reads the columns
+ * (j + off + k S) mod N, k = 0 .. 31, with one weight per layer, off and S the layer's -- with one bias for all neurons,
+ * wherever their weights live, when a workgroup holds its share of the rows at a time.  Larger batches keep their rows on the chip for several layers per launch.  With profiling on, a launch's
  * duration is shared out among its layers in proportion to the rows they had (spdnn_get_profile). */
 int spdnn_one_launch(spdnn_t h, int32_t batch, int32_t* yes);
 

@@ -14,6 +14,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <numeric>
 #include <string>
 #include <vector>
 
@@ -53,6 +54,7 @@ int static_scratch(void** out);  // defined below
 constexpr size_t kAlign = 256;
 inline size_t up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
+constexpr int32_t kStridedColumns = 16384;  // rows of strided_kernel: two of them fit the LDS
 constexpr int kLag = 2;  // the host runs at most this many layers ahead of the GPU
 // Set-up of device-resident layers runs on this many streams, a layer per stream in turn: its kernels
 // are single-wave, latency-bound searches that fill a fraction of the chip, so several layers overlap.
@@ -101,6 +103,10 @@ struct spdnn_model {
     int* res_rows = nullptr;                           // device, L + 1 counters
     int res_mode = spdnn::kResWeights;
     uint32_t res_part_stride = 0;                      // kResParts
+    // every layer a strided sum, one bias: strided_kernel
+    const spdnn::StridedLayer* strided = nullptr;  // device copy of the layers' descriptors (NULL: not such a network)
+    int32_t strided_lanes = 0;                     // lanes a pair of rows takes in the layer that takes most
+    float strided_bias = 0.0f;
     // out-of-core weights: pass p's block lives in host memory and is copied into device slot p & 1
     const char* ooc_host = nullptr;
     char* ooc_slot[2] = {nullptr, nullptr};
@@ -232,6 +238,12 @@ hipError_t allow_flat_lds() {
     return e != hipSuccess ? e : hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::fused_flat_kernel<R, true>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, spdnn::flat_lds_bytes(R));
 }
+constexpr int kLdsBytes = 160 * 1024;
+template <bool PAIRS>
+hipError_t allow_strided_lds() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::strided_kernel<PAIRS>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               kLdsBytes);
+}
 template <int NB, int PM>
 hipError_t allow_resident_lds(int bytes) {
     for (const void* f : {reinterpret_cast<const void*>(&spdnn::resident_kernel<NB, PM, spdnn::kResWeights>),
@@ -247,6 +259,8 @@ hipError_t allow_resident_lds(int bytes) {
 int allow_large_lds() {
     constexpr size_t wide_lds = spdnn::kOrderThreads * sizeof(spdnn::WideScratch);
     const int tile_lds = (int)spdnn::tile_pair_bytes(spdnn::kCap);
+    HIP_TRY(allow_strided_lds<false>());
+    HIP_TRY(allow_strided_lds<true>());
     HIP_TRY((allow_big_lds<false, false>()));
     HIP_TRY((allow_big_lds<true, false>()));
     HIP_TRY((allow_big_lds<false, true>()));
@@ -579,6 +593,11 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
     }
 
     const size_t raw = (size_t)N * spdnn::kNnz;
+    // A network of strided sums?  Looked at layer by layer until one is not.  (The descriptors and the rows-per-layer counters
+    // take the place of the staged weights, which is free once the set-up is over.)
+    std::vector<spdnn::StridedLayer> strided;
+    bool all_strided = !ptr && N <= kStridedColumns && std::all_of(hb.begin(), hb.end(), [&](float b) { return b == hb[0]; }) &&
+                       (size_t)L * (sizeof(spdnn::StridedLayer) + sizeof(int)) + sizeof(int) <= lanes * spdnn::kNnz * sizeof(float);
     std::vector<int2> hw((size_t)P * nblk);
     std::vector<int2> virt_ranges;  // several lanes per neuron: {first neuron, neurons} of the current layer's workgroups
     for (int32_t l = 0; l < P; ++l) {  // l = pass; it belongs to layer ll
@@ -722,7 +741,23 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
         }
         HIP_TRY(hipMemcpyAsync(&hw[(size_t)l * nblk], whole ? d.virt.range : win_dev[l], sizeof(int2) * nblk, hipMemcpyDeviceToHost, stream));
         HIP_TRY(hipMemcpyAsync(pair_info, pair_dev, sizeof(pair_info), hipMemcpyDeviceToHost, stream));
+        int strided_info[4] = {1, 0, 0, 0};
+        if (all_strided) {
+            int* info_dev = reinterpret_cast<int*>(slot_tab);  // this stream's table as scratch
+            HIP_TRY(hipMemsetAsync(info_dev, 0, sizeof(strided_info), stream));
+            spdnn::strided_detect_kernel<<<(N + 255) / 256, 256, 0, stream>>>(di, dv, N, info_dev);
+            HIP_TRY(hipGetLastError());
+            HIP_TRY(hipMemcpyAsync(strided_info, info_dev, sizeof(strided_info), hipMemcpyDeviceToHost, stream));
+        }
         HIP_TRY(hipStreamSynchronize(stream));
+        if (all_strided && (all_strided = strided_info[0] == 0)) {
+            spdnn::StridedLayer sl{strided_info[1], strided_info[2], std::gcd(N, strided_info[1]), 0, 1, 0.0f};
+            sl.T = N / sl.orbits;
+            if (sl.T > spdnn::kNnz) sl.per = (sl.T + spdnn::kStrideOut - 1) / spdnn::kStrideOut;
+            std::memcpy(&sl.w, &strided_info[3], sizeof(float));
+            all_strided = spdnn::strided_lanes(sl) <= spdnn::kStrideThreads;
+            strided.push_back(sl);
+        }
         // One weight, but the windows are too wide for two neurons per lane.  If units of 2048 neurons in segments
         // (unit_neuron) read columns that do not overlap, at most 2048 each -- the strided patterns that RadiX-Net
         // layers are (Section II-A) -- neurons and columns get new names under which every unit has a contiguous
@@ -972,6 +1007,15 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
         m->res_rows = res_rows_dev;
         m->res_part_stride = (uint32_t)blk_bytes;
     }
+    if (all_strided) {
+        spdnn::StridedLayer* layers_dev = reinterpret_cast<spdnn::StridedLayer*>(st_val);
+        HIP_TRY(hipMemcpyAsync(layers_dev, strided.data(), sizeof(spdnn::StridedLayer) * (size_t)L, hipMemcpyHostToDevice, stream));
+        HIP_TRY(hipStreamSynchronize(stream));
+        m->strided = layers_dev;
+        m->res_rows = reinterpret_cast<int*>(layers_dev + L);
+        m->strided_bias = hb[0];
+        for (const spdnn::StridedLayer& sl : strided) m->strided_lanes = std::max(m->strided_lanes, spdnn::strided_lanes(sl));
+    }
     guard.m = nullptr;
     *out = m;
     return SPDNN_OK;
@@ -1047,10 +1091,33 @@ ResidentShape resident_shape(const spdnn_model* h, int32_t rows) {
     return r;
 }
 
+// How strided_kernel runs a network on `rows` rows: pairs of rows per pass, the workgroup's threads and LDS, and how many
+// workgroups fit the GPU at once.  The kernel's registers leave a CU eight waves: two workgroups of four, one of which adds
+// while the other waits at a barrier, where two pairs of rows fit the LDS; else one of eight.  Few rows: as few per
+// workgroup as it takes to give every slot some.
+struct StridedShape {
+    int pairs, threads, lds, slots;
+};
+StridedShape strided_shape(const spdnn_model* h, int32_t rows) {
+    StridedShape r;
+    const int pair = 8 * h->N;
+    const bool two = 2 * h->strided_lanes <= spdnn::kStrideThreads && 2 * (pair + spdnn::kStrideMisc) <= kLdsBytes;
+    r.threads = two ? spdnn::kStrideThreads / 2 : spdnn::kStrideThreads;
+    r.slots = h->num_cu * (two ? 2 : 1);
+    r.pairs = std::min({16, r.threads / h->strided_lanes, (kLdsBytes / (two ? 2 : 1) - spdnn::kStrideMisc) / pair});
+    r.pairs = std::max(1, std::min(r.pairs, ((rows + 1) / 2 + r.slots - 1) / r.slots));
+    r.lds = r.pairs * pair + spdnn::kStrideMisc;
+    return r;
+}
+
 // All layers in one launch?  With rows in LDS from layer to layer, if a workgroup's share of the rows is small: they
 // stay with the workgroup they started in, and a share that is packed together again as rows die is all the
 // rebalancing there is.  One output block: up to kShareRows rows per CU; more blocks: what one pass holds.
 bool one_launch(const spdnn_model* h, int32_t batch) {
+    if (batch > 0 && h->strided) {  // what the workgroups hold at a time
+        const StridedShape s = strided_shape(h, batch);
+        return (batch + 2 * s.pairs - 1) / (2 * s.pairs) <= s.slots;
+    }
     if (batch <= 0 || h->res_layers == nullptr) return false;
     const int32_t groups = (batch + spdnn::kRows - 1) / spdnn::kRows;
     const int32_t share = (groups + h->num_cu - 1) / h->num_cu * spdnn::kRows;
@@ -1067,7 +1134,7 @@ bool one_launch(const spdnn_model* h, int32_t batch) {
 // 508 -> 400; 60 000 rows of 1024 neurons, 1 layer: 284 -> 221 (512 neurons on the chip: 166).  Not for three output blocks, which the CUs cannot share evenly (3072 neurons, 3 layers, 1003 -> 1347), nor for four
 // where the last one is ragged and there is no pair of neurons per lane (4000 neurons, one weight, 3 layers: 1208 -> 1194).
 int32_t one_by_one(const spdnn_model* h, int32_t batch) {
-    if (h->N <= 512 || h->nblk == 3 || h->res_mode == spdnn::kResParts || one_launch(h, batch)) return 0;
+    if (h->strided || h->N <= 512 || h->nblk == 3 || h->res_mode == spdnn::kResParts || one_launch(h, batch)) return 0;
     const ResidentShape shape = resident_shape(h, batch);
     const int32_t rows = shape.slots * shape.planes * spdnn::kRows;
     const int32_t passes = (batch + rows - 1) / rows;
@@ -1096,6 +1163,17 @@ hipError_t launch_resident(spdnn_t h, const ResidentShape& r, int32_t Q, const f
     if (r.nb == 1) run_mode(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
     else if (r.nb == 2) run_mode(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
     else run_mode(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{});
+    return hipGetLastError();
+}
+
+// Layers l0 .. l1-1 through strided_kernel on `rows` rows.
+hipError_t launch_strided(spdnn_t h, int32_t l0, int32_t l1, int32_t rows, const float* Yin, float* Yout, uint8_t* flags,
+                          const spdnn::RowLists& rl, int* layer_rows) {
+    const StridedShape r = strided_shape(h, rows);
+    const spdnn::StridedArgs sa{h->strided, l0, l1, rows, r.pairs, h->strided_bias, layer_rows};
+    const int grid = std::min((rows + 2 * r.pairs - 1) / (2 * r.pairs), r.slots);
+    if (r.pairs > 1) spdnn::strided_kernel<true><<<grid, r.threads, r.lds, h->stream>>>(Yin, Yout, flags, rl, sa, h->N);
+    else spdnn::strided_kernel<false><<<grid, r.threads, r.lds, h->stream>>>(Yin, Yout, flags, rl, sa, h->N);
     return hipGetLastError();
 }
 
@@ -1298,7 +1376,7 @@ bool write_through(const spdnn_model* h, const float* Y_final_dev, int32_t rows,
     return Y_final_dev && none_died && (h->L > kFewLayers || (h->L > 2 && h->N > spdnn::kCap && h->N <= spdnn::kFlatCols)) && (size_t)rows * h->N * sizeof(float) >= ((size_t)8 << 20);
 }
 
-// infer_impl for networks whose rows stay in LDS from layer to layer (resident_kernel).
+// infer_impl for networks whose rows stay in LDS from layer to layer (resident_kernel, strided_kernel).
 int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv, int32_t row_offset,
                    int32_t* n_active_host, int32_t* active_rows_dev, float* Y_final_dev) {
     const int32_t L = h->L;
@@ -1326,7 +1404,9 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
     // With weights of their own above 2048 neurons a layer's connections are 576 KB and more: workgroups that stop at
     // different layers no longer find them in L2.  There the rest is cut in half as long as rows die (24 layers of 4096
     // neurons, 30 000 rows that die evenly: 4.54 -> 3.75 ms) and more than 12 layers are left.
-    const bool halves = h->res_mode != spdnn::kResUniform && h->nblk > 2;
+    // Strided sums take a third of the time per layer: more layers are one launch.
+    const int32_t last_layers = h->strided ? 64 : 32;
+    const bool halves = !h->strided && h->res_mode != spdnn::kResUniform && h->nblk > 2;
     struct Run {
         int32_t l0, l1;
     };
@@ -1371,17 +1451,21 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
     }
     for (; l0 < L && alive > 0; ++k, len *= 4) {
         if (halves && k > 0) len = (int64_t)alive * 32 > (int64_t)before * 31 || L - l0 <= 12 ? L : std::max(8, (L - l0 + 1) / 2);
-        const bool rest = one || L <= kFewLayers || (!halves && k > 0 && ((int64_t)alive * 4 > (int64_t)before * 3 || L - l0 <= 32)) || len >= L - l0;
+        const bool rest = one || L <= kFewLayers || (!halves && k > 0 && ((int64_t)alive * 4 > (int64_t)before * 3 || L - l0 <= last_layers)) || len >= L - l0;
         const int32_t l1 = rest ? L : l0 + len;
-        const ResidentShape shape = resident_shape(h, alive);
-        const int32_t groups = (alive + spdnn::kRows - 1) / spdnn::kRows;
-        const int32_t Q = std::min(groups, shape.slots);
-        const bool several = (groups + Q - 1) / Q > shape.planes;
-        const spdnn::ResidentArgs ra{h->res_layers, l0, one && several ? std::min(l0 + 2, l1) : l1, l1, L, batch, h->res_part_stride, layer_rows};
         if (h->profiling) HIP_TRY(hipEventRecord(h->t0[l0], s));
         // (rows that lived through two or more layers mostly live on)
         Y_last = rest && write_through(h, Y_final_dev, alive, k > 0) ? Y_final_dev : wv.Y[yo];
-        HIP_TRY(launch_resident(h, shape, Q, Yin, Y_last, wv.flags[0], rl, ra));
+        if (h->strided) {
+            HIP_TRY(launch_strided(h, l0, l1, alive, Yin, Y_last, wv.flags[0], rl, layer_rows));
+        } else {
+            const ResidentShape shape = resident_shape(h, alive);
+            const int32_t groups = (alive + spdnn::kRows - 1) / spdnn::kRows;
+            const int32_t Q = std::min(groups, shape.slots);
+            const bool several = (groups + Q - 1) / Q > shape.planes;
+            const spdnn::ResidentArgs ra{h->res_layers, l0, one && several ? std::min(l0 + 2, l1) : l1, l1, L, batch, h->res_part_stride, layer_rows};
+            HIP_TRY(launch_resident(h, shape, Q, Yin, Y_last, wv.flags[0], rl, ra));
+        }
         ++h->launches;
         ++h->res_launches;
         if (h->profiling) HIP_TRY(hipEventRecord(h->t1[l0], s));
@@ -1436,7 +1520,7 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
 int infer_impl(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView& wv, int32_t row_offset,
                int32_t* n_active_host, int32_t* active_rows_dev, float* Y_final_dev) {
     const int32_t L = h->L;
-    if (h->res_layers && one_by_one(h, batch) < L)
+    if (h->strided || (h->res_layers && one_by_one(h, batch) < L))
         return infer_resident(h, Y0_dev, batch, wv, row_offset, n_active_host, active_rows_dev, Y_final_dev);
     hipStream_t s = h->stream;
     // Kernels may be queued when a later HIP call fails: nothing of this call is left running on return.

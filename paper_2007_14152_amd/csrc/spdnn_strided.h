@@ -1,0 +1,293 @@
+// Networks whose layers are strided sums: neuron j of a layer reads the 32 columns (j + off + k * S) mod N, k = 0 .. 31,
+// all with one weight -- the building block of the RadiX-Net topologies (Section II-A) -- and one bias for all neurons.
+//
+// Such a layer is a sliding sum over every orbit of "+S": along an orbit neuron t adds the inputs t .. t + 31, and
+// neighbours share 31 of them.  Five rounds of doubling (x[i] += x[i + 1], x[i] += x[i + 2], ... + 16) make 33 neighbours'
+// sums out of 64 inputs with 263 additions, 8 per neuron instead of 32, from 2 reads per neuron instead of 32, and there
+// are no connections to store or fetch: a layer is {S, off, weight}.  The sums are trees of five levels instead of chains
+// of 32, so their rounding error is smaller; weight and bias come last, in one fused multiply-add.
+//
+// Rows stay in LDS over a run of layers, two of them side by side (an entry = the two rows of a column, 8 bytes).  A lane
+// owns kStrideOut neighbours of an orbit: it reads its 64 entries into registers, adds, and after a barrier writes its 33
+// results over the input.  33 is odd so that lanes next to each other along an orbit of stride 1 (33 entries apart) fall
+// into different bank pairs; lanes of orbits next to each other read neighbouring entries anyway.  The last lane of an
+// orbit starts earlier where 33 does not divide it and computes some neighbours' results a second time, to the same
+// values.  An orbit of exactly 32 (S = N / 32) has one sum for all its neurons: one lane computes it once.
+//
+// What bounds it: vector instructions, about 30 per neuron and pair of rows of which 16 are the additions, on the two
+// waves per SIMD that 256 registers allow.  48 layers of 16384 neurons, strides 1, 32 and 512 in turn, on 2000 rows of which
+// half die: 1.95 -> 0.39 ms (two neurons per lane under new names, one launch per layer before: 40 us a layer, 5.7 now);
+// 24 layers of 4096 neurons, strides 1, 32 and 128, 60 000 rows 4.45 -> 1.59 ms (resident_kernel before), 48 of them on 100
+// rows 324 -> 146 us.
+#pragma once
+
+namespace spdnn {
+
+constexpr int kStrideOut = 33;                      // neurons a lane owns
+constexpr int kStrideIn = kStrideOut + kNnz - 1;    // inputs they read
+constexpr int kStrideThreads = 512;
+constexpr int kStrideMisc = 16;  // bytes of LDS behind the rows
+
+struct StridedLayer {
+    int S, off;     // columns (j + off + k * S) mod N
+    int orbits, T;  // gcd(N, S) orbits of T columns each
+    int per;        // lanes per orbit: ceil(T / 33), 1 if T == 32
+    float w;        // the weight of all connections
+};
+struct StridedArgs {
+    const StridedLayer* layers;
+    int l0, l1;       // layers l0 .. l1-1
+    int A;            // rows, if there are no lists yet (rl.count == NULL): row i is in slot i
+    int pairs;        // pairs of rows a pass holds
+    float bias;
+    int* layer_rows;  // NULL, or counters: [l] += rows alive on entry to layer l
+};
+SPDNN_HD inline int strided_lanes(const StridedLayer& d) { return d.orbits * d.per; }
+
+// n entries of an orbit, from column c on, every S-th, around the row end.
+template <int n>
+__device__ __forceinline__ void read_orbit(f32x2 (&x)[n], __attribute__((address_space(3))) char* row, uint32_t c, uint32_t S, uint32_t N) {
+    using lds_f2 = __attribute__((address_space(3))) f32x2;
+    const uint32_t s8 = 8u * S, back = 8u * S - 8u * N;
+    if (__builtin_amdgcn_ballot_w64(c + (n - 1) * S >= N) == 0ull) {  // no lane of the wave gets to the row end
+#pragma unroll
+        for (int k = 0; k < n; ++k) x[k] = *(const lds_f2*)(row + (8u * c + k * s8));
+    } else {
+        uint32_t at = 8u * c;
+#pragma unroll
+        for (int k = 0; k < n; ++k) {
+            x[k] = *(const lds_f2*)(row + at);
+            at = min(at + s8, at + back);
+        }
+    }
+}
+
+// PAIRS: more than one pair of rows, the lanes shared out among them.
+template <bool PAIRS>
+__global__ __launch_bounds__(kStrideThreads) void strided_kernel(const float* __restrict__ Yin, float* __restrict__ Yout,
+                                                                 uint8_t* __restrict__ flags, RowLists rl, StridedArgs sa, int N) {
+    extern __shared__ __align__(16) char strided_lds[];
+    using lds_f2 = __attribute__((address_space(3))) f32x2;
+    using lds_f4 = __attribute__((address_space(3))) f32x4;
+    using lds_char = __attribute__((address_space(3))) char;
+    lds_char* const tile = (lds_char*)strided_lds;
+    const int tid = threadIdx.x, lane = tid & 63, nthreads = blockDim.x;
+    const int np = PAIRS ? sa.pairs : 1;
+    const uint32_t row_bytes = 8u * (uint32_t)N;  // of a pair
+    uint32_t* live_word = reinterpret_cast<uint32_t*>(strided_lds + (size_t)np * row_bytes);  // [2], raised by the layers in turn
+    const int A = rl.count ? __builtin_amdgcn_readfirstlane(*rl.count) : sa.A;
+    const int npass = (A + 2 * np - 1) / (2 * np), n4 = N >> 2;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    using clayer = const __attribute__((address_space(4))) StridedLayer;  // constant while the kernel runs: scalar loads
+
+    for (int pass = blockIdx.x; pass < npass; pass += gridDim.x) {
+        const int row0 = pass * 2 * np, nrow = min(2 * np, A - row0);
+        if (tid < 2) live_word[tid] = 0u;
+        // the rows; layer 0 sums inputs of any size, so they meet its weight before they are added up
+        const float first_w = sa.l0 == 0 ? ((clayer*)(uintptr_t)sa.layers)->w : 1.0f;
+        for (int p = 0; p < np; ++p) {
+            const bool one = 2 * p < nrow, two = 2 * p + 1 < nrow;
+            const int s0 = !one ? 0 : rl.count ? rl.cat[row0 + 2 * p] : row0 + 2 * p;
+            const int s1 = !two ? 0 : rl.count ? rl.cat[row0 + 2 * p + 1] : row0 + 2 * p + 1;
+            const f32x4* src0 = reinterpret_cast<const f32x4*>(Yin + (size_t)s0 * N);
+            const f32x4* src1 = reinterpret_cast<const f32x4*>(Yin + (size_t)s1 * N);
+            for (int t0 = tid; t0 < n4; t0 += 4 * nthreads) {
+                f32x4 a[4], b[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int t = min(t0 + i * nthreads, n4 - 1);
+                    a[i] = one ? src0[t] : zero;
+                    b[i] = two ? src1[t] : zero;
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int t = t0 + i * nthreads;
+                    if (t < n4) {
+                        a[i] *= first_w;
+                        b[i] *= first_w;
+                        lds_f4* to = (lds_f4*)(tile + p * row_bytes + 32u * t);
+                        to[0] = f32x4{a[i].x, b[i].x, a[i].y, b[i].y};
+                        to[1] = f32x4{a[i].z, b[i].z, a[i].w, b[i].w};
+                    }
+                }
+            }
+        }
+        uint32_t live = 0u;
+        __syncthreads();
+        for (int l = sa.l0; l < sa.l1; ++l) {
+            clayer* d = (clayer*)(uintptr_t)(sa.layers + l);
+            const uint32_t S = (uint32_t)d->S, orbits = (uint32_t)d->orbits, T = (uint32_t)d->T, per = (uint32_t)d->per;
+            const float w = l == 0 ? 1.0f : d->w;
+            const uint32_t lanes = orbits * per;
+            // my pair of rows, my orbit, my place on it
+            const uint32_t p = PAIRS ? (uint32_t)tid / lanes : 0u;
+            const uint32_t i = (uint32_t)tid - p * lanes;
+            const bool mine = PAIRS ? p < (uint32_t)np : (uint32_t)tid < lanes;
+            const uint32_t b = i / orbits, r = i - b * orbits;
+            const uint32_t t0 = per == 1u ? 0u : min(b * kStrideOut, T - kStrideOut);
+            const uint32_t j0 = (r + t0 * S) % (uint32_t)N;
+            uint32_t c0 = j0 + (uint32_t)d->off;
+            c0 = min(c0, c0 - (uint32_t)N);
+            const uint32_t base = PAIRS ? p * row_bytes : 0u;
+            const uint32_t s8 = 8u * S, back = 8u * S - row_bytes;
+            f32x2 y[kStrideOut];
+            uint32_t bits = 0u;
+            if (mine) {
+                const bool whole = T == (uint32_t)kNnz;  // one sum for all of an orbit
+                float m0 = 0.0f, m1 = 0.0f;
+                const auto finish = [&](f32x2 v) -> f32x2 {
+                    v.x = fminf(fmaxf(__builtin_fmaf(w, v.x, sa.bias), 0.0f), kClip);
+                    v.y = fminf(fmaxf(__builtin_fmaf(w, v.y, sa.bias), 0.0f), kClip);
+                    m0 = fmaxf(m0, v.x);
+                    m1 = fmaxf(m1, v.y);
+                    return v;
+                };
+                if (whole) {
+                    f32x2 v[kNnz];
+                    read_orbit<kNnz>(v, tile + base, c0, S, (uint32_t)N);
+#pragma unroll
+                    for (int h = 1; h < kNnz; h *= 2)
+#pragma unroll
+                        for (int k = 0; k + h < kNnz; k += 2 * h) v[k] += v[k + h];
+                    y[0] = finish(v[0]);
+                } else {
+                    f32x2 x[kStrideIn];
+                    read_orbit<kStrideIn>(x, tile + base, c0, S, (uint32_t)N);
+#pragma unroll
+                    for (int k = 0; k < kStrideIn - 1; ++k) x[k] += x[k + 1];
+#pragma unroll
+                    for (int k = 0; k < kStrideIn - 3; ++k) x[k] += x[k + 2];
+#pragma unroll
+                    for (int k = 0; k < kStrideIn - 7; ++k) x[k] += x[k + 4];
+#pragma unroll
+                    for (int k = 0; k < kStrideIn - 15; ++k) x[k] += x[k + 8];
+#pragma unroll
+                    for (int k = 0; k < kStrideOut; ++k) y[k] = finish(x[k] + x[k + 16]);
+                }
+                // which rows have a positive output: the wave's first lane of every pair speaks for it
+                const unsigned long long pos0 = __builtin_amdgcn_ballot_w64(m0 > 0.0f), pos1 = __builtin_amdgcn_ballot_w64(m1 > 0.0f);
+                unsigned long long of_pair = ~0ull;
+                bool first = lane == 0;
+                if constexpr (PAIRS) {
+                    const int from = max((int)(p * lanes) - (tid - lane), 0), to = min((int)((p + 1) * lanes) - (tid - lane), 64);
+                    of_pair = (~0ull >> (64 - (to - from))) << from;
+                    first = lane == from;
+                }
+                bits = (pos0 & of_pair ? 1u : 0u) | (pos1 & of_pair ? 2u : 0u);
+                if (first && bits) atomicOr(&live_word[l & 1], bits << (2u * p));
+            }
+            __syncthreads();  // every wave has read what it needs of the rows
+            live = __builtin_amdgcn_readfirstlane(live_word[l & 1]);
+            if (mine) {
+                if (T == (uint32_t)kNnz) {
+                    uint32_t at = 8u * j0;
+#pragma unroll
+                    for (int k = 0; k < kNnz; ++k) {
+                        *(lds_f2*)(tile + (base + at)) = y[0];
+                        at = min(at + s8, at + back);
+                    }
+                } else if (__builtin_amdgcn_ballot_w64(j0 + (kStrideOut - 1) * S >= (uint32_t)N) == 0ull) {
+#pragma unroll
+                    for (int k = 0; k < kStrideOut; ++k) *(lds_f2*)(tile + (base + 8u * j0 + k * s8)) = y[k];
+                } else {
+                    uint32_t at = 8u * j0;
+#pragma unroll
+                    for (int k = 0; k < kStrideOut; ++k) {
+                        *(lds_f2*)(tile + (base + at)) = y[k];
+                        at = min(at + s8, at + back);
+                    }
+                }
+            }
+            if (tid == 0) {
+                live_word[(l + 1) & 1] = 0u;
+                if (sa.layer_rows && live) atomicAdd(&sa.layer_rows[l + 1], __popc(live));
+            }
+            __syncthreads();
+            if (!live) break;
+        }
+        if (tid < nrow) flags[row0 + tid] = (live >> tid) & 1u;
+        if (live) {
+            for (int p = 0; p < np; ++p) {
+                const bool one = (live >> (2 * p)) & 1u, two = (live >> (2 * p + 1)) & 1u;
+                if (!one && !two) continue;
+                f32x4* dst0 = reinterpret_cast<f32x4*>(Yout + (size_t)(row0 + 2 * p) * N);
+                f32x4* dst1 = reinterpret_cast<f32x4*>(Yout + (size_t)(row0 + 2 * p + 1) * N);
+                for (int t = tid; t < n4; t += nthreads) {
+                    const lds_f4* from = (const lds_f4*)(tile + p * row_bytes + 32u * t);
+                    const f32x4 u = from[0], v = from[1];
+                    if (one) dst0[t] = f32x4{u.x, u.z, v.x, v.z};
+                    if (two) dst1[t] = f32x4{u.y, u.w, v.y, v.w};
+                }
+            }
+        }
+        __syncthreads();  // the tile and the live words are free for the next pass
+    }
+}
+
+// Set-up: is the layer a strided sum?  info[0] != 0: no; info[1] .. info[3]: S, off and the weight's bits, as neuron 0 suggests.  Neuron 0's
+// columns, sorted, are an arithmetic sequence on the circle if all gaps but (at most) one are equal; every other neuron has
+// to read the same columns moved by its number, each exactly once, with the same weight.
+__global__ __launch_bounds__(256) void strided_detect_kernel(const int32_t* __restrict__ idx, const float* __restrict__ val, int N,
+                                                             int* __restrict__ info) {
+    __shared__ int col[kNnz];
+    __shared__ int found[2];
+    const int tid = threadIdx.x;
+    if (tid < kNnz) {  // rank of my column among neuron 0's
+        const int c = idx[tid];
+        int rank = 0;
+        for (int k = 0; k < kNnz; ++k) {
+            const int o = idx[k];
+            rank += o < c || (o == c && k < tid);
+        }
+        col[rank] = c;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        int S = 0, off = 0;
+        if (col[0] >= 0 && col[kNnz - 1] < N) {
+            const auto gap = [&](int k) { return k + 1 < kNnz ? col[k + 1] - col[k] : col[0] + N - col[kNnz - 1]; };
+            // the gap that two of three neighbouring ones have in common is the stride; the sequence starts behind the odd one
+            const int s = gap(0) == gap(1) ? gap(0) : gap(2);
+            int odd = -1, nodd = 0;
+            for (int k = 0; k < kNnz; ++k)
+                if (gap(k) != s) {
+                    odd = k;
+                    ++nodd;
+                }
+            if (s > 0 && nodd <= 1) {
+                S = s;
+                off = nodd ? col[(odd + 1) % kNnz] : col[0];
+            }
+        }
+        found[0] = S;
+        found[1] = off;
+        if (blockIdx.x == 0) {
+            info[1] = S;
+            info[2] = off;
+            info[3] = __float_as_int(val[0]);
+        }
+    }
+    __syncthreads();
+    const int S = found[0], off = found[1];
+    const int j = blockIdx.x * 256 + tid;
+    if (j >= N) return;
+    bool ok = S > 0;
+    if (ok) {
+        const float w = val[0];
+        int from = j + off;
+        from = from >= N ? from - N : from;
+        uint32_t seen = 0u;
+        for (int k = 0; k < kNnz; ++k) {
+            const int c = idx[(size_t)j * kNnz + k];
+            int d = c - from;
+            d = d < 0 ? d + N : d;
+            const int q = d / S;
+            ok = ok && c >= 0 && c < N && q < kNnz && q * S == d && __float_as_uint(val[(size_t)j * kNnz + k]) == __float_as_uint(w);
+            seen |= 1u << (q & 31);
+        }
+        ok = ok && seen == 0xffffffffu;
+    }
+    if (!ok) info[0] = 1;
+}
+
+}  // namespace spdnn

@@ -1,0 +1,99 @@
+"""Networks of strided sums -- neuron j reads the columns (j + off + k S) mod N with one weight -- which strided_kernel runs
+with the rows in LDS and sums shared along the orbits of "+S".  Orbits of 32, of lengths that 33 does and does not divide,
+strides that wrap around the row end inside a lane's span, one and several pairs of rows per pass, odd batches, several
+passes and launches; against the oracle, and the same bits whatever the batch and wherever the weights live."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from parity_util import check_against_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def layer(N, S, off):
+    return np.sort((np.arange(N)[:, None] + off + S * np.arange(32)[None, :]) % N, axis=1).astype(np.int32)
+
+
+def network(N, strides, weight, offs=(0,)):
+    idx = [layer(N, s, offs[l % len(offs)]) for l, s in enumerate(strides)]
+    val = [np.full((N, 32), weight, np.float32)] * len(strides)
+    return idx, val
+
+
+@pytest.mark.parametrize("N,strides,batch,weight,offs", [
+    (32, (1, 1), 5, 0.0625, (0, 31)),                  # one orbit of 32 for the whole row
+    (36, (1, 1, 1), 400, 0.0625, (0, 5)),              # orbits of 36, two lanes with 30 neurons in common
+    (100, (3, 1, 2), 1000, 0.07, (0, 99)),             # 16 pairs of rows per pass
+    (1024, (1, 32, 8, 32), 4001, 0.0625, (0,)),        # several passes, the last of one row
+    (1056, (32, 1), 77, 0.0625, (0,)),                 # orbits of 33
+    (1088, (32, 1, 2), 2000, 0.0625, (7, 0)),          # orbits of 34
+    (4096, (1, 32, 128, 1, 32, 128), 3000, 0.0625, (0,)),  # compacted between two launches
+    (8188, (1, 4, 92), 301, 0.0625, (8187, 3)),
+    (16384, (1, 32, 512, 2, 264, 3), 301, 0.0625, (0, 1, 16383)),
+    (16384, (512, 1), 1, 0.0625, (0,)),
+])
+def test_strided_networks(N, strides, batch, weight, offs):
+    import torch
+    import paper_2007_14152_amd as sp
+    L = len(strides)
+    idx, val = network(N, strides, weight, offs)
+    bias = synth.gen_bias(N, -0.3)
+    Y0 = synth.gen_y0(batch, N, 41, density="mixed")
+    if batch > 8:
+        Y0[5] = 0
+    ids = np.arange(batch) if batch * N <= 1 << 23 else np.r_[0:batch // 8, batch - batch // 8:batch]
+    ref = oracle.infer(idx, val, bias, Y0[ids])
+    m = sp.Model(idx, val, bias)
+    m.set_profiling(True)
+    y0 = torch.from_numpy(Y0).to("cuda:0")
+    n, rows, Y = m.infer(y0)
+    launches, resident = m.launches()
+    assert resident == launches and (L <= 4) <= (launches == 1)   # no layer of its own
+    run, rows_in, _ = m.profile()
+    rows_h, Y_h = rows.cpu().numpy(), Y.cpu().numpy()
+    mine = np.isin(rows_h, ids)
+    check_against_oracle(ref, int(mine.sum()), rows_h[mine], Y_h[mine], row_ids=ids, what="strided N=%d %s" % (N, strides))
+    if len(ids) == batch and not (ref.fragile_layer >= 0).any():
+        assert [int(x) for x in rows_in[:run]] == [int(x) for x in ref.active_per_layer[:run]]
+    # fewer rows, another split into launches: the same rows' bits
+    few = max(1, batch // 3)
+    m.set_profiling(False)
+    n2, rows2, Y2 = m.infer(y0[:few].contiguous())
+    keep = rows < few
+    assert n2 == int(keep.sum()) and torch.equal(rows2, rows[keep]) and torch.equal(Y2, Y[keep])
+    m.close()
+    ooc = sp.Model(idx, val, bias, out_of_core=True)
+    n3, rows3, Y3 = ooc.infer(y0)
+    assert n3 == n and torch.equal(rows3, rows) and torch.equal(Y3, Y)
+    ooc.close()
+
+
+@pytest.mark.parametrize("change", ["column", "weight", "bias", "two strides", "duplicate", "too many lanes"])
+def test_what_is_no_strided_network_runs_as_before(change):
+    """One connection, weight or bias out of line, a pattern that is not one sequence, or orbits that take more lanes than a
+    workgroup has: the general kernels, with the oracle's result."""
+    import paper_2007_14152_amd as sp
+    N, L, batch = (16320, 2, 9) if change == "too many lanes" else (8192, 2, 9)
+    idx, val = network(N, (480, 480) if change == "too many lanes" else (1, 32), 0.0625)
+    val = [v.copy() for v in val]
+    bias = synth.gen_bias(N, -0.3)
+    if change == "column":
+        idx[1][N - 1][7] = (idx[1][N - 1][7] + 1) % N
+    elif change == "weight":
+        val[1][N - 1][31] = np.nextafter(np.float32(0.0625), np.float32(1))
+    elif change == "bias":
+        bias[N - 1] = -0.31
+    elif change == "two strides":
+        idx[1] = np.sort(np.concatenate([layer(N, 1, 0)[:, :16], layer(N, 2, 100)[:, :16]], axis=1), axis=1)
+    elif change == "duplicate":
+        idx[1][5][3] = idx[1][5][4]
+    Y0 = synth.gen_y0(batch, N, 43, density="mixed")
+    ref = oracle.infer(idx, val, bias, Y0)
+    m = sp.Model(idx, val, bias)
+    from parity_util import gpu_infer
+    n, rows, Y = gpu_infer(idx, val, bias, Y0, model=m)
+    assert m.launches()[1] == 0
+    m.close()
+    check_against_oracle(ref, n, rows, Y, what=change)

@@ -1341,23 +1341,30 @@ int finish_infer(spdnn_t h, const uint8_t* flags, const int* count_in, const int
                  int32_t* n_active_host, int32_t* active_rows_dev, float* Y_final_dev) {
     hipStream_t s = h->stream;
     h->host_counts[slot] = -1;
-    spdnn::compact_kernel<<<spdnn::kCompactWGs, 1024, 0, s>>>(flags, nullptr, count_in, count_out, gid_in, active_rows_dev, cat_out,
-                                                              h->host_counts + slot, batch, row_offset);
-    HIP_TRY(hipGetLastError());
-    if (Y_final_dev && bound > 0) {
-        const int n4 = h->N / 4;
-        const size_t total = (size_t)bound * n4;
-        const float4* from = reinterpret_cast<const float4*>(Y_last);
-        float4* to = reinterpret_cast<float4*>(Y_final_dev);
-        if (Y_last != Y_final_dev)
-            spdnn::gather_rows_kernel<<<(int)std::min<size_t>((total + 255) / 256, 65536), 256, 0, s>>>(from, cat_out, count_out, nullptr, n4, to);
-        else {
-            const int g = (int)std::min<size_t>((total + 255) / 256, 2048);
-            float4* by = reinterpret_cast<float4*>(spare);
-            spdnn::gather_rows_kernel<<<g, 256, 0, s>>>(from, cat_out, count_out, count_in, n4, by);
-            spdnn::gather_rows_kernel<<<g, 256, 0, s>>>(by, nullptr, count_out, count_in, n4, to);
-        }
+    const int n4 = h->N / 4;
+    const float4* from = reinterpret_cast<const float4*>(Y_last);
+    float4* to = reinterpret_cast<float4*>(Y_final_dev);
+    if (bound <= spdnn::kFinishRows && (!Y_final_dev || Y_last != Y_final_dev)) {  // both in one launch
+        const int per = std::max(1, (bound + 1023) / 1024), grid = std::max(1, (bound + per - 1) / per);
+        spdnn::finish_rows_kernel<<<grid, spdnn::kFinishThreads, 0, s>>>(flags, count_in, gid_in, batch, row_offset, per, active_rows_dev,
+                                                                         h->host_counts + slot, from, n4, to);
         HIP_TRY(hipGetLastError());
+    } else {
+        spdnn::compact_kernel<<<spdnn::kCompactWGs, 1024, 0, s>>>(flags, nullptr, count_in, count_out, gid_in, active_rows_dev, cat_out,
+                                                                  h->host_counts + slot, batch, row_offset);
+        HIP_TRY(hipGetLastError());
+        if (Y_final_dev && bound > 0) {
+            const size_t total = (size_t)bound * n4;
+            if (Y_last != Y_final_dev)
+                spdnn::gather_rows_kernel<<<(int)std::min<size_t>((total + 255) / 256, 65536), 256, 0, s>>>(from, cat_out, count_out, nullptr, n4, to);
+            else {
+                const int g = (int)std::min<size_t>((total + 255) / 256, 2048);
+                float4* by = reinterpret_cast<float4*>(spare);
+                spdnn::gather_rows_kernel<<<g, 256, 0, s>>>(from, cat_out, count_out, count_in, n4, by);
+                spdnn::gather_rows_kernel<<<g, 256, 0, s>>>(by, nullptr, count_out, count_in, n4, to);
+            }
+            HIP_TRY(hipGetLastError());
+        }
     }
     HIP_TRY(hipStreamSynchronize(s));
     const int n = h->host_counts[slot];

@@ -1903,7 +1903,8 @@ __global__ __launch_bounds__(1024) void compact_kernel(const uint8_t* __restrict
         const int total = count_flags(flags_in, A, red);
         if (tid == 0) {
             *count_out = total;
-            __hip_atomic_store(host_count, total, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+            // (no release, see derive_work: the host reads nothing else before the stream is drained)
+            __hip_atomic_store(host_count, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }
     if (lo >= hi) return;
@@ -1989,6 +1990,58 @@ __global__ void gather_rows_kernel(const float4* __restrict__ src, const int* __
         const size_t row = e / n4;
         const size_t c = e - row * n4;
         dst[e] = src[cat ? (size_t)cat[row] * n4 + c : e];
+    }
+}
+
+// compact_kernel and gather_rows_kernel in one, for up to kFinishRows rows: every workgroup counts the flags before its own
+// rows for itself -- a few kilobytes that all of them read -- and so knows where its rows go.  (Two launches and the gap
+// between them are a fifth of a small call: one row through 12 layers of 1024 neurons 56 -> 51 us.)  dst == NULL: no values.
+constexpr int kFinishRows = 16384;
+constexpr int kFinishThreads = 256;
+constexpr int kFinishMost = 64;  // rows per workgroup, at most
+__global__ __launch_bounds__(kFinishThreads) void finish_rows_kernel(const uint8_t* __restrict__ flags, const int* __restrict__ count_in,
+                                                                     const int* __restrict__ gid_in, int batch, int row_offset, int per,
+                                                                     int* __restrict__ rows_out, int* host_count,
+                                                                     const float4* __restrict__ src, int n4, float4* __restrict__ dst) {
+    __shared__ int red[kFinishThreads / 64];
+    __shared__ int kept[kFinishMost];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int A = count_in ? *count_in : batch;
+    const int lo = blockIdx.x * per, hi = min(A, lo + per);
+    if (blockIdx.x != 0 && lo >= A) return;
+    const int before = blockIdx.x == 0 ? A : lo;  // the first workgroup has none before it and reports the sum
+    int c = 0;
+    for (int i = tid * 16; i < before; i += kFinishThreads * 16) {
+        const uint4 v = flags16(flags, i, before);
+        c += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
+    if (lane == 0) red[wave] = c;
+    const bool keep = tid < per && lo + tid < hi && flags[lo + tid] != 0;  // (per <= 64: the first wave's rows)
+    const unsigned long long m = __ballot(keep);
+    if (keep) kept[__popcll(m & ((1ull << lane) - 1ull))] = lo + tid;
+    __shared__ int nkept;
+    if (tid == 0) nkept = __popcll(m);
+    __syncthreads();
+    int sum = 0;
+#pragma unroll
+    for (int w = 0; w < kFinishThreads / 64; ++w) sum += red[w];
+    if (blockIdx.x == 0 && tid == 0) __hip_atomic_store(host_count, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    const int base = blockIdx.x == 0 ? 0 : sum, n = nkept;
+    if (tid < n) rows_out[base + tid] = gid_in ? gid_in[kept[tid]] : row_offset + kept[tid];
+    if (!dst) return;
+    for (int k = 0; k < n; ++k) {
+        const float4* from = src + (size_t)kept[k] * n4;
+        float4* to = dst + (size_t)(base + k) * n4;
+        for (int i0 = tid; i0 < n4; i0 += 4 * kFinishThreads) {  // four loads in flight
+            float4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = from[min(i0 + u * kFinishThreads, n4 - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (i0 + u * kFinishThreads < n4) to[i0 + u * kFinishThreads] = v[u];
+        }
     }
 }
 

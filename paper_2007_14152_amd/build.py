@@ -12,7 +12,7 @@ LIB = os.path.join(CSRC, "libspdnn.so")
 SOURCES = [os.path.join(CSRC, "spdnn.hip")]
 HEADERS = [os.path.join(CSRC, "spdnn_kernels.h"), os.path.join(CSRC, "spdnn_order.h"),
            os.path.join(CSRC, "spdnn_layout.h"), os.path.join(CSRC, "spdnn_row2.h"),
-           os.path.join(CSRC, "spdnn_flat.h"), os.path.join(CSRC, "spdnn_resident.h"), os.path.join(CSRC, "spdnn_strided.h"), os.path.join(CSRC, "spdnn_cut.h"),
+           os.path.join(CSRC, "spdnn_flat.h"), os.path.join(CSRC, "spdnn_resident.h"), os.path.join(CSRC, "spdnn_few.h"), os.path.join(CSRC, "spdnn_strided.h"), os.path.join(CSRC, "spdnn_cut.h"),
            os.path.join(os.path.dirname(_HERE), "include", "spdnn.h")]
 # host build of the connection-ordering routine, for tests of the set-up logic without a GPU
 ORDER_HOST_LIB = os.path.join(CSRC, "libspdnn_order_host.so")
@@ -25,10 +25,10 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
 
 NO_SCRATCH_KERNELS = ["fused_row2_kernel", "fused_pair_kernel"]
 # Kernels that count LDS addresses from the start of the workgroup's LDS: all of it must be dynamic.
-LDS_FROM_ZERO_KERNELS = ["resident_kernel", "fused_flat_kernel"]
+LDS_FROM_ZERO_KERNELS = ["resident_kernel", "fused_flat_kernel", "few_kernel"]
 # Bytes of scratch per lane that these may spill: outside the arithmetic, at what was measured with them.  (Spills are
 # memory operations more, which the waits written out by hand cover: they count at most what comes after the loads.)
-SCRATCH_LIMIT = {"resident_kernel": 96, "fused_flat_kernel": 24}
+SCRATCH_LIMIT = {"resident_kernel": 96, "fused_flat_kernel": 24, "few_kernel": 0}
 
 
 def _resource_usage(text):
@@ -78,7 +78,7 @@ def build(verbose: bool = False, extra=()) -> str:
                                    % (k, v["ScratchSize [bytes/lane]"], SCRATCH_LIMIT[kernel]))
     if verbose:
         for k, v in sorted(usage.items()):
-            if "fused_" in k or "resident_" in k:
+            if "fused_" in k or "resident_" in k or "few_" in k or "strided_kernel" in k:
                 print("%s: VGPRs %s, scratch %s B/lane" % (k, v.get("VGPRs"), v.get("ScratchSize [bytes/lane]")))
     subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-o", ORDER_HOST_LIB, ORDER_HOST_SRC],
                    check=True)

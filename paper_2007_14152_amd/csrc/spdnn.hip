@@ -244,6 +244,18 @@ hipError_t allow_strided_lds() {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::strided_kernel<PAIRS>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                kLdsBytes);
 }
+int few_lds(int32_t N, int32_t nblk) {
+    return (int)spdnn::res_tile_bytes(N, 1 << spdnn::res_planes_log2(nblk)) + spdnn::kFewMiscBytes;
+}
+hipError_t allow_few_lds() {
+    for (const void* f : {reinterpret_cast<const void*>(&spdnn::few_kernel<spdnn::kResWeights>),
+                          reinterpret_cast<const void*>(&spdnn::few_kernel<spdnn::kResUniform>),
+                          reinterpret_cast<const void*>(&spdnn::few_kernel<spdnn::kResParts>)}) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, few_lds(spdnn::kCap, 4));
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 template <int NB, int PM>
 hipError_t allow_resident_lds(int bytes) {
     for (const void* f : {reinterpret_cast<const void*>(&spdnn::resident_kernel<NB, PM, spdnn::kResWeights>),
@@ -259,6 +271,7 @@ hipError_t allow_resident_lds(int bytes) {
 int allow_large_lds() {
     constexpr size_t wide_lds = spdnn::kOrderThreads * sizeof(spdnn::WideScratch);
     const int tile_lds = (int)spdnn::tile_pair_bytes(spdnn::kCap);
+    HIP_TRY(allow_few_lds());
     HIP_TRY(allow_strided_lds<false>());
     HIP_TRY(allow_strided_lds<true>());
     HIP_TRY((allow_big_lds<false, false>()));
@@ -1110,6 +1123,19 @@ StridedShape strided_shape(const spdnn_model* h, int32_t rows) {
     return r;
 }
 
+// Few rows: few_kernel, in one launch, or, where so many layers follow that it pays to share out anew the rows that are left
+// behind the first two, in two.
+constexpr int32_t kFewSplitLayers = 64;
+// Four rows per workgroup are as many as resident_kernel's smallest pass: not for more than two output blocks, where its
+// second barrier weighs little (24 layers of 4096 neurons, 1000 rows: 192 -> 197 us with four, 500 rows of 12 layers with weights
+// 135 -> 130 with two), nor for neurons of any length, whose chunks it fetches in finer steps (1500 neurons of 0 to 40
+// connections, 777 rows: 83 -> 85; 600 neurons of 0 to 100, 300 rows: 74 -> 63).
+bool few_rows(const spdnn_model* h, int32_t batch) {
+    const int32_t most = h->nblk > 2 || h->res_mode == spdnn::kResParts ? 2 : spdnn::kFewRows;
+    return h->res_layers && !h->strided && batch <= most * h->num_cu;
+}
+bool few_split(const spdnn_model* h, int32_t batch) { return batch > h->num_cu && h->L >= kFewSplitLayers; }
+
 // All layers in one launch?  With rows in LDS from layer to layer, if a workgroup's share of the rows is small: they
 // stay with the workgroup they started in, and a share that is packed together again as rows die is all the
 // rebalancing there is.  One output block: up to kShareRows rows per CU; more blocks: what one pass holds.
@@ -1119,6 +1145,7 @@ bool one_launch(const spdnn_model* h, int32_t batch) {
         return (batch + 2 * s.pairs - 1) / (2 * s.pairs) <= s.slots;
     }
     if (batch <= 0 || h->res_layers == nullptr) return false;
+    if (few_rows(h, batch)) return !few_split(h, batch);
     const int32_t groups = (batch + spdnn::kRows - 1) / spdnn::kRows;
     const int32_t share = (groups + h->num_cu - 1) / h->num_cu * spdnn::kRows;
     return share <= (h->nblk == 1 ? spdnn::kShareRows : spdnn::kRows * (1 << spdnn::res_planes_log2(h->nblk)));
@@ -1134,7 +1161,7 @@ bool one_launch(const spdnn_model* h, int32_t batch) {
 // 508 -> 400; 60 000 rows of 1024 neurons, 1 layer: 284 -> 221 (512 neurons on the chip: 166).  Not for three output blocks, which the CUs cannot share evenly (3072 neurons, 3 layers, 1003 -> 1347), nor for four
 // where the last one is ragged and there is no pair of neurons per lane (4000 neurons, one weight, 3 layers: 1208 -> 1194).
 int32_t one_by_one(const spdnn_model* h, int32_t batch) {
-    if (h->strided || h->N <= 512 || h->nblk == 3 || h->res_mode == spdnn::kResParts || one_launch(h, batch)) return 0;
+    if (h->strided || few_rows(h, batch) || h->N <= 512 || h->nblk == 3 || h->res_mode == spdnn::kResParts || one_launch(h, batch)) return 0;
     const ResidentShape shape = resident_shape(h, batch);
     const int32_t rows = shape.slots * shape.planes * spdnn::kRows;
     const int32_t passes = (batch + rows - 1) / rows;
@@ -1163,6 +1190,17 @@ hipError_t launch_resident(spdnn_t h, const ResidentShape& r, int32_t Q, const f
     if (r.nb == 1) run_mode(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
     else if (r.nb == 2) run_mode(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
     else run_mode(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{});
+    return hipGetLastError();
+}
+
+hipError_t launch_few(spdnn_t h, const spdnn::FewArgs& fa, int32_t workgroups, const float* Yin, float* Yout, uint8_t* flags) {
+    const int threads = 64 * std::min(16, (h->N + 63) / 64);
+    const auto run = [&](auto mode) {
+        spdnn::few_kernel<decltype(mode)::value><<<workgroups, threads, few_lds(h->N, h->nblk), h->stream>>>(Yin, Yout, flags, fa, h->bias_dev, h->N);
+    };
+    if (h->res_mode == spdnn::kResUniform) run(std::integral_constant<int, spdnn::kResUniform>{});
+    else if (h->res_mode == spdnn::kResParts) run(std::integral_constant<int, spdnn::kResParts>{});
+    else run(std::integral_constant<int, spdnn::kResWeights>{});
     return hipGetLastError();
 }
 
@@ -1440,7 +1478,36 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
         lo ^= 1;
         return rc;
     };
-    if (one_by_one(h, batch) == 2) {
+    const uint8_t* last_flags = wv.flags[0];  // of the last launch
+    bool finished = false;  // the last launch has done what finish_infer does
+    if (few_rows(h, batch)) {
+        const bool split = few_split(h, batch);
+        finished = batch == 1;  // (a workgroup with more rows would take longer than the launch it saves)
+        if (finished) h->host_counts[L + 1] = -1;
+        spdnn::FewArgs fa{h->res_layers, 0, split ? 2 : L, L, batch, h->res_part_stride, spdnn::res_planes_log2(h->nblk), layer_rows,
+                          nullptr, wv.gid[0], wv.count[0], row_offset, finished ? active_rows_dev : nullptr, h->host_counts + L + 1};
+        const int32_t workgroups = std::min(batch, h->num_cu);
+        for (int32_t i = 0; i <= (split ? 1 : 0); ++i) {
+            if (h->profiling) HIP_TRY(hipEventRecord(h->t0[fa.l0], s));
+            Y_last = finished ? Y_final_dev : wv.Y[i];
+            HIP_TRY(launch_few(h, fa, workgroups, i == 0 ? Y0_dev : wv.Y[0], Y_last, wv.flags[i]));
+            last_flags = wv.flags[i];
+            ++h->launches;
+            ++h->res_launches;
+            if (h->profiling) HIP_TRY(hipEventRecord(h->t1[fa.l0], s));
+            runs.push_back(Run{fa.l0, fa.l1});
+            fa.l0 = fa.l1;
+            fa.l1 = L;
+            fa.flags_prev = wv.flags[0];
+        }
+        if (split) {  // the second launch has made the list its rows are numbered by
+            rl.count = wv.count[0];
+            rl.gid = wv.gid[0];
+        }
+        yo = split ? 1 : 0;
+        lo = 1;
+        l0 = L;
+    } else if (one_by_one(h, batch) == 2) {
         HIP_TRY(launch_init_lists(h, wv, batch, row_offset));
         for (int32_t l = 0; l < 2; ++l) {
             if (h->profiling) HIP_TRY(hipEventRecord(h->t0[l], s));
@@ -1485,8 +1552,12 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
         yo ^= 1;
     }
     int32_t rc = SPDNN_OK;
-    if (alive > 0)
-        rc = finish_infer(h, wv.flags[0], rl.count, rl.gid, batch, row_offset, wv.count[lo], wv.cat[lo], L + 1,
+    if (finished) {
+        HIP_TRY(hipStreamSynchronize(s));
+        *n_active_host = h->host_counts[L + 1];
+        if (*n_active_host < 0) return fail(SPDNN_EHIP, "the last layer finished without reporting its active rows");
+    } else if (alive > 0)
+        rc = finish_infer(h, last_flags, rl.count, rl.gid, batch, row_offset, wv.count[lo], wv.cat[lo], L + 1,
                           Y_last, wv.Y[yo ^ 1], alive, n_active_host, active_rows_dev, Y_final_dev);
     else {
         HIP_TRY(hipStreamSynchronize(s));

@@ -1,0 +1,332 @@
+// Networks of at most 4096 neurons on few rows -- at most four per workgroup, a workgroup per CU: the rows stay in LDS from
+// layer to layer as in resident_kernel, and with so few of them a layer is a matter of latency and instruction issue.
+//
+// A workgroup has R = 1, 2 or 4 rows, as few as the batch allows: an entry is a column's R values (4, 8 or 16 bytes), and a
+// connection costs one read of R values and R multiply-adds, where resident_kernel always computes four.  The rows are kept
+// twice, a layer reads one copy and writes the other, so that it has one barrier instead of two, results go out as each
+// group of 64 neurons is done, and which rows still live is looked at while the next layer is computed.  The copies are
+// planes 0 and 1 of resident_kernel's tile layout at R / 4 of its size: the connections' entry codes are the same, and the
+// sums are the same products in the same order (kResParts: parts of 32 likewise), so the results have the same bits.
+//
+// The connections of a group are on their way while the group before is computed, all 32 with their weights: 12 KB per wave,
+// which is what it takes for the 53 to 60 bytes per clock that a CU gets out of its L2.
+//
+// What bounds it: the bank conflicts of reads that were ordered for 16-byte entries, 4.7 clocks per read whatever its size,
+// and with weights of their own the stream of connections; 700 to 1000 clocks of a layer's 3500 (1024 neurons) to 17 000
+// (4096 with weights) are the barrier and the waits at its ends.  Whole calls, resident_kernel -> this kernel: one row
+// through 12 layers of 1024 neurons with weights 57 -> 51 us, of 4096 neurons 130 -> 116; 1000 rows, half of which die, through
+// 120 layers of 1024 neurons with one weight 261 -> 228; 100 rows through 24 layers of 4096 neurons 179 -> 147.
+//
+// A deep network in which rows die shares them out anew behind two layers: the second launch's workgroups find their rows by
+// counting the first one's flags themselves (FewArgs::flags_prev), so nothing runs between the two and the host does not wait.
+// A batch that a single workgroup holds is finished there too: survivors numbered, counted and written to the caller.
+#pragma once
+
+namespace spdnn {
+
+constexpr int kFewRows = 4;        // rows per workgroup, at most
+constexpr int kFewMiscBytes = 256;
+
+struct FewArgs {
+    const ResidentLayer* layers;
+    int l0, l1, L;         // layers l0 .. l1-1 of L
+    int A;                 // rows on entry, without flags_prev; else rows that flags_prev speaks about (at most 1024)
+    uint32_t part_stride;  // see ResidentArgs
+    int planes_log2;
+    int* layer_rows;       // see ResidentArgs
+    const uint8_t* flags_prev;  // NULL: row i is in slot i of Yin.  Else its rows are the slots whose flag is set, ...
+    int* gid;                   // ... whose numbers (row_offset + slot) go here ...
+    int* count;                 // ... and how many there are here
+    int row_offset;
+    int* rows_out;         // not NULL: the workgroup is the only one and finishes the call: the survivors' numbers, ...
+    int* host_count;       // ... their count; their rows are the first ones of Yout
+};
+
+template <int R>
+struct FewEntry;
+template <>
+struct FewEntry<1> {
+    typedef float T __attribute__((ext_vector_type(1)));
+};
+template <>
+struct FewEntry<2> {
+    typedef float T __attribute__((ext_vector_type(2)));
+};
+template <>
+struct FewEntry<4> {
+    typedef float T __attribute__((ext_vector_type(4)));
+};
+
+// The two entry codes of a register as LDS addresses of entries of 4 << LOG2R bytes.
+template <int LOG2R>
+__device__ __forceinline__ void few_address(uint32_t codes, uint32_t& lo, uint32_t& hi) {
+    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0" : "=v"(lo) : "s"(2 + LOG2R), "v"(codes));
+    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1" : "=v"(hi) : "s"(2 + LOG2R), "v"(codes));
+}
+
+template <int R, int MODE>
+__device__ __forceinline__ void few_layers(const float* __restrict__ Yin, float* __restrict__ Yout, uint8_t* __restrict__ flags,
+                                           const FewArgs& fa, const float* __restrict__ bias, int N, int A, const int* row_at,
+                                           uint32_t* live_word) {
+    using T = typename FewEntry<R>::T;
+    using lds_T = __attribute__((address_space(3))) T;
+    using gchar = const __attribute__((address_space(1))) char;
+    using gu32x4 = const __attribute__((address_space(1))) u32x4;
+    using gf32x4 = const __attribute__((address_space(1))) f32x4;
+    using gf32 = const __attribute__((address_space(1))) float;
+    using gu32 = const __attribute__((address_space(1))) uint32_t;
+    using gu16 = const __attribute__((address_space(1))) uint16_t;
+    using cu32 = const __attribute__((address_space(4))) uint32_t;
+    using clayer = const __attribute__((address_space(4))) ResidentLayer;
+    constexpr int LOG2R = R == 1 ? 0 : R == 2 ? 1 : 2;
+    constexpr uint32_t COPY = 64u * R;  // bytes from an entry to its place in the other copy: plane 1
+    const int tid = threadIdx.x, lane = tid & 63, T_ = blockDim.x, W = T_ >> 6, U = (N + 63) >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row0 = (int)blockIdx.x * R, nrow = min(R, A - row0);
+    const int nb_w = (U - wave + W - 1) / W;
+    const uint32_t lane16 = 16u * lane;
+    // LDS address of column j of a row laid out by q = its quads' word
+    const auto entry = [&](int j, uint32_t q) -> uint32_t {
+        return ((store_group((uint32_t)j) << (8 + fa.planes_log2)) | ((q >> (8 * (j & 3))) & 0xffu)) >> (2 - LOG2R);
+    };
+    struct Item {  // a layer's connections of one group of 64 neurons
+        gchar *c, *w;
+        int nch;  // chunks of 8
+    };
+    const auto layer_at = [&](int l) -> ResidentLayer {
+        clayer* d = (clayer*)(uintptr_t)(fa.layers + l);
+        return ResidentLayer{d->rel, d->val, d->qsel, d->wuni, d->perm, d->nch};
+    };
+    const auto item = [&](const ResidentLayer& d, int b) -> Item {
+        const int u = b * W + wave;
+        const uint32_t at = ((u >> 4) * (kNnz / 8) * kBlk + (u & 15) * 64) * 16;
+        const uint32_t wat = ((u >> 4) * (kNnz / 4) * kBlk + (u & 15) * 64) * 16;
+        const int nch = MODE == kResParts ? (int)((cu32*)(uintptr_t)d.nch)[u] : kNnz / 8;
+        return Item{(gchar*)(uintptr_t)d.rel + at, (gchar*)(uintptr_t)d.val + wat, nch};
+    };
+    u32x4 cbuf[4];
+    f32x4 wbuf[8] = {};
+    const auto fetch = [&](const Item& it, int c, size_t part_off) {
+        const auto scalar = [](gchar* p) {  // the base of a load, with the lane's offset in one register
+            asm("" : "+s"(p));
+            return p;
+        };
+        cbuf[c] = *(gu32x4*)(scalar(it.c + part_off + (uint32_t)c * (16 * kBlk)) + lane16);
+        if constexpr (MODE != kResUniform) {
+            wbuf[2 * c] = *(gf32x4*)(scalar(it.w + part_off + (uint32_t)(2 * c) * (16 * kBlk)) + lane16);
+            wbuf[2 * c + 1] = *(gf32x4*)(scalar(it.w + part_off + (uint32_t)(2 * c + 1) * (16 * kBlk)) + lane16);
+        }
+    };
+    // the neuron of this lane in its wave's group b of a layer, what comes with it
+    const auto neuron = [&](const ResidentLayer& d, int b) -> int {
+        const int i = 64 * (b * W + wave) + lane;
+        if constexpr (MODE == kResParts) return ((gu16*)(uintptr_t)d.perm)[i];
+        else return i;
+    };
+
+    // the rows
+    ResidentLayer cur = layer_at(fa.l0), nxt = layer_at(fa.l0 + 1 < fa.l1 ? fa.l0 + 1 : fa.l0);
+    const int n4 = N >> 2;
+    int slot[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) slot[r] = r < nrow ? (row_at ? row_at[r] : row0 + r) : -1;
+    Item ahead = item(cur, 0);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) fetch(ahead, c, 0);
+    int jn = neuron(cur, 0);
+    for (int t = tid; t < n4; t += T_) {
+        f32x4 a[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            a[r] = slot[r] < 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : *reinterpret_cast<const f32x4*>(Yin + (size_t)slot[r] * N + 4 * (size_t)t);
+        const uint32_t q = ((gu32*)(uintptr_t)cur.qsel)[t];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            T e;
+#pragma unroll
+            for (int r = 0; r < R; ++r) e[r] = a[r][i];
+            *(lds_T*)(entry(4 * t + i, q)) = e;
+        }
+    }
+    __syncthreads();
+
+    uint32_t live = (1u << nrow) - 1u;
+    gu32* q_out = (gu32*)(uintptr_t)layer_at(min(fa.l1, fa.L - 1)).qsel;  // any layout does for the last layer's output
+    const uint32_t live_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t*)live_word;
+    bool other = false;  // the copy that holds the rows
+    const auto layer = [&](int l, auto from) {
+        constexpr uint32_t FROM = decltype(from)::value, TO = COPY - FROM;
+        // (scalar loads are waited for with the first reads of the rows, so not any later than this)
+        const ResidentLayer after = layer_at(l + 2 < fa.l1 ? l + 2 : fa.l1 - 1);
+        gchar* q_next = (gchar*)(l + 1 < fa.l1 ? (gu32*)(uintptr_t)nxt.qsel : q_out);
+        const uint32_t raised = l > fa.l0 ? live_word[(l + 2) % 3] : live;  // (looked at behind the arithmetic)
+        uint32_t pos = 0;
+#pragma unroll 1
+        for (int b = 0; b < nb_w; ++b) {
+            const int j = jn;
+            const bool mine = j < N;
+            const uint32_t near = (uint32_t)min(j, N - 1);
+            const uint32_t q = *(gu32*)(q_next + (near & ~3u));
+            const float bias_j = *(gf32*)((gchar*)(uintptr_t)bias + 4u * near);
+            const Item it = ahead;
+            ahead = b + 1 < nb_w ? item(cur, b + 1) : item(nxt, 0);
+            jn = b + 1 < nb_w ? neuron(cur, b + 1) : neuron(nxt, 0);
+            T sum = {}, acc = {};
+            const auto read = [&](T (&y)[8], const u32x4& c) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    uint32_t lo, hi;
+                    few_address<LOG2R>(c[k], lo, hi);
+                    y[2 * k] = *(const lds_T*)(lo + FROM);
+                    y[2 * k + 1] = *(const lds_T*)(hi + FROM);
+                }
+            };
+            const auto add = [&](const T (&y)[8], int i) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const float w = MODE == kResUniform ? cur.wuni : wbuf[2 * i + (k >> 2)][k & 3];
+#pragma unroll
+                    for (int r = 0; r < R; ++r) acc[r] = __builtin_fmaf(w, y[k][r], acc[r]);
+                }
+            };
+            if constexpr (MODE != kResParts) {
+                T y[2][8];  // a chunk's values are asked for before the chunk before is added up
+                read(y[0], cbuf[0]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (i < 3) read(y[(i + 1) & 1], cbuf[i + 1]);
+                    add(y[i & 1], i);
+                    fetch(ahead, i, 0);
+                }
+                sum = acc;
+            } else {
+                size_t off = 0;
+                for (int g = 0; g == 0 || 4 * g < it.nch; ++g, off += fa.part_stride) {
+                    const bool last = 4 * (g + 1) >= it.nch;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        if (4 * g + i < it.nch) {
+                            T y[8];
+                            read(y, cbuf[i]);
+                            add(y, i);
+                        }
+                        if (last) fetch(ahead, i, 0);
+                        else if (4 * (g + 1) + i < it.nch) fetch(it, i, off + fa.part_stride);
+                    }
+                    sum += acc;
+                    acc = T{};
+                }
+            }
+            const float bj = mine ? bias_j : -__builtin_inff();  // lanes without a neuron have no output
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                sum[r] = fminf(fmaxf(sum[r] + bj, 0.0f), kClip);
+                if (__builtin_amdgcn_ballot_w64(sum[r] > 0.0f) != 0ull) pos |= 1u << r;
+            }
+            uint32_t to = entry(j, q) + TO;
+            asm volatile("" : "+v"(to));  // (or its load would be moved behind the branch, and wait for all that were asked for since)
+            if (mine) *(lds_T*)to = sum;
+        }
+        cur = nxt;
+        nxt = after;
+        live &= __builtin_amdgcn_readfirstlane(raised);
+        if (tid == 0) {
+            if (fa.layer_rows && l > fa.l0 && live) atomicAdd(&fa.layer_rows[l], __popc(live));
+            live_word[(l + 1) % 3] = 0u;
+        }
+        // (a plain LDS operation of one lane: the compiler's atomic would look for the first active lane on its own)
+        if (lane == 0) asm volatile("ds_or_b32 %0, %1" ::"v"(live_at + 4u * (uint32_t)(l % 3)), "v"(pos) : "memory");
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __syncthreads();
+    };
+    int l = fa.l0;
+    while (l < fa.l1 && live) {
+        layer(l++, std::integral_constant<uint32_t, 0>{});
+        other = true;
+        if (l == fa.l1 || !live) break;
+        layer(l++, std::integral_constant<uint32_t, COPY>{});
+        other = false;
+    }
+    if (live) live &= __builtin_amdgcn_readfirstlane(live_word[(l + 2) % 3]);  // the last layer's
+    if (tid == 0 && live && fa.layer_rows) atomicAdd(&fa.layer_rows[l], __popc(live));
+    if (fa.rows_out) {
+        if (tid < R && ((live >> tid) & 1u)) fa.rows_out[__popc(live & ((1u << tid) - 1u))] = fa.row_offset + tid;
+        if (tid == 0) __hip_atomic_store(fa.host_count, __popc(live), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    } else if (tid < nrow) {
+        flags[row0 + tid] = (live >> tid) & 1u;
+    }
+    if (!live || !Yout) return;
+    for (int t = tid; t < n4; t += T_) {
+        const uint32_t q = q_out[t];
+        T e[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) e[i] = *(const lds_T*)(entry(4 * t + i, q) + (other ? COPY : 0u));
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if ((live >> r) & 1u) {
+                const int to = fa.rows_out ? __popc(live & ((1u << r) - 1u)) : row0 + r;
+                *reinterpret_cast<f32x4*>(Yout + (size_t)to * N + 4 * (size_t)t) = f32x4{e[0][r], e[1][r], e[2][r], e[3][r]};
+            }
+    }
+}
+
+// blockDim.x = 64 * W, W = min(16, U), U = ceil(N / 64) groups of 64 neurons; wave w owns the groups w, w + W, ...
+template <int MODE>
+__global__ __launch_bounds__(kBlk) void few_kernel(const float* __restrict__ Yin, float* __restrict__ Yout, uint8_t* __restrict__ flags,
+                                                   FewArgs fa, const float* __restrict__ bias, int N) {
+    // The entry codes are addresses from the start of the workgroup's LDS: everything is dynamic, nothing static.
+    extern __shared__ __align__(16) char few_lds[];
+    char* misc = few_lds + res_tile_bytes(N, 1 << fa.planes_log2);
+    uint32_t* live_word = reinterpret_cast<uint32_t*>(misc);    // [3], raised by the layers in turn
+    int* row_at = reinterpret_cast<int*>(misc + 16);            // [4] slots of my rows
+    int* kept = row_at + kFewRows;                              // [16] flags set, per wave
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int nwg = gridDim.x;
+    int A = fa.A, R = 0;
+    const auto rows_per = [&](int a) { return a <= nwg ? 1 : a <= 2 * nwg ? 2 : 4; };
+    if (tid < 3) live_word[tid] = 0u;
+    if (fa.flags_prev) {
+        const int waves = blockDim.x >> 6;
+        int total = 0;  // first, because how many rows a workgroup takes depends on it
+        for (int i0 = 0; i0 < fa.A; i0 += blockDim.x) {
+            const int i = i0 + tid;
+            const unsigned long long m = __ballot(i < fa.A && fa.flags_prev[i] != 0);
+            if (lane == 0) kept[wave] = __popcll(m);
+            __syncthreads();
+            for (int w = 0; w < waves; ++w) total += kept[w];
+            __syncthreads();
+        }
+        A = __builtin_amdgcn_readfirstlane(total);
+        R = rows_per(A);
+        const int r0 = blockIdx.x * R;
+        int base = 0;
+        for (int i0 = 0; i0 < fa.A; i0 += blockDim.x) {
+            const int i = i0 + tid;
+            const bool keep = i < fa.A && fa.flags_prev[i] != 0;
+            const unsigned long long m = __ballot(keep);
+            if (lane == 0) kept[wave] = __popcll(m);
+            __syncthreads();
+            int rank = base + __popcll(m & ((1ull << lane) - 1ull));
+            for (int w = 0; w < waves; ++w) {
+                if (w < wave) rank += kept[w];
+                base += kept[w];
+            }
+            if (keep && rank >= r0 && rank < r0 + R) {
+                row_at[rank - r0] = i;
+                fa.gid[rank] = fa.row_offset + i;
+            }
+            __syncthreads();
+        }
+        if (blockIdx.x == 0 && tid == 0) *fa.count = A;
+    } else {
+        R = rows_per(A);
+        __syncthreads();
+    }
+    if ((int)blockIdx.x * R >= A) return;
+    const int* at = fa.flags_prev ? row_at : nullptr;
+    if (R == 1) few_layers<1, MODE>(Yin, Yout, flags, fa, bias, N, A, at, live_word);
+    else if (R == 2) few_layers<2, MODE>(Yin, Yout, flags, fa, bias, N, A, at, live_word);
+    else few_layers<4, MODE>(Yin, Yout, flags, fa, bias, N, A, at, live_word);
+}
+
+}  // namespace spdnn

@@ -1817,6 +1817,7 @@ __global__ __launch_bounds__(kBlk) void fused_wide_pair4_kernel(
 #include "spdnn_row2.h"
 #include "spdnn_flat.h"
 #include "spdnn_resident.h"
+#include "spdnn_few.h"
 #include "spdnn_strided.h"
 namespace spdnn {
 

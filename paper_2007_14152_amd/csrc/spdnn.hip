@@ -602,7 +602,9 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
         // A single layer of at most 32 connections per neuron: what one_by_one() says of one layer, for any batch (the
         // layouts differ).  8 to 32 connections, 30 000 rows: 2048 neurons 319 -> 253 us, 4096 600 -> 472; 100 rows 48 ->
         // 54, 53 -> 55.
-        if (uneven > 0.0 || (parts && P == 1 && (nblk == 2 || nblk == 4))) resident = parts = false;
+        // (and the offsets of a neuron's parts are 32-bit numbers)
+        const bool far = (size_t)*std::max_element(passes_of.begin(), passes_of.end()) * blk_bytes > 0x7fffffff;
+        if (far || uneven > 0.0 || (parts && P == 1 && (nblk == 2 || nblk == 4))) resident = parts = false;
     }
 
     const size_t raw = (size_t)N * spdnn::kNnz;
@@ -1128,10 +1130,9 @@ StridedShape strided_shape(const spdnn_model* h, int32_t rows) {
 constexpr int32_t kFewSplitLayers = 64;
 // Four rows per workgroup are as many as resident_kernel's smallest pass: not for more than two output blocks, where its
 // second barrier weighs little (24 layers of 4096 neurons, 1000 rows: 192 -> 197 us with four, 500 rows of 12 layers with weights
-// 135 -> 130 with two), nor for neurons of any length, whose chunks it fetches in finer steps (1500 neurons of 0 to 40
-// connections, 777 rows: 83 -> 85; 600 neurons of 0 to 100, 300 rows: 74 -> 63).
+// 135 -> 130 with two).
 bool few_rows(const spdnn_model* h, int32_t batch) {
-    const int32_t most = h->nblk > 2 || h->res_mode == spdnn::kResParts ? 2 : spdnn::kFewRows;
+    const int32_t most = h->nblk > 2 ? 2 : spdnn::kFewRows;
     return h->res_layers && !h->strided && batch <= most * h->num_cu;
 }
 bool few_split(const spdnn_model* h, int32_t batch) { return batch > h->num_cu && h->L >= kFewSplitLayers; }

@@ -9,7 +9,7 @@
 // sums are the same products in the same order (kResParts: parts of 32 likewise), so the results have the same bits.
 //
 // The connections of a group are on their way while the group before is computed, all 32 with their weights: 12 KB per wave,
-// which is what it takes for the 53 to 60 bytes per clock that a CU gets out of its L2.
+// which is what it takes for the 53 to 60 bytes per clock that a CU gets out of its L2.  (Neurons of any length: 16 of them.)
 //
 // What bounds it: the bank conflicts of reads that were ordered for 16-byte entries, 4.7 clocks per read whatever its size,
 // and with weights of their own the stream of connections; 700 to 1000 clocks of a layer's 3500 (1024 neurons) to 17 000
@@ -71,8 +71,6 @@ __device__ __forceinline__ void few_layers(const float* __restrict__ Yin, float*
     using T = typename FewEntry<R>::T;
     using lds_T = __attribute__((address_space(3))) T;
     using gchar = const __attribute__((address_space(1))) char;
-    using gu32x4 = const __attribute__((address_space(1))) u32x4;
-    using gf32x4 = const __attribute__((address_space(1))) f32x4;
     using gf32 = const __attribute__((address_space(1))) float;
     using gu32 = const __attribute__((address_space(1))) uint32_t;
     using gu16 = const __attribute__((address_space(1))) uint16_t;
@@ -106,15 +104,11 @@ __device__ __forceinline__ void few_layers(const float* __restrict__ Yin, float*
     };
     u32x4 cbuf[4];
     f32x4 wbuf[8] = {};
-    const auto fetch = [&](const Item& it, int c, size_t part_off) {
-        const auto scalar = [](gchar* p) {  // the base of a load, with the lane's offset in one register
-            asm("" : "+s"(p));
-            return p;
-        };
-        cbuf[c] = *(gu32x4*)(scalar(it.c + part_off + (uint32_t)c * (16 * kBlk)) + lane16);
+    const auto fetch = [&](const Item& it, int slot, uint32_t c) {  // chunk c of the 32 connections that start at `it`
+        cbuf[slot] = load_lanes(it.c, c * (16 * kBlk), lane16);
         if constexpr (MODE != kResUniform) {
-            wbuf[2 * c] = *(gf32x4*)(scalar(it.w + part_off + (uint32_t)(2 * c) * (16 * kBlk)) + lane16);
-            wbuf[2 * c + 1] = *(gf32x4*)(scalar(it.w + part_off + (uint32_t)(2 * c + 1) * (16 * kBlk)) + lane16);
+            wbuf[2 * slot] = __builtin_bit_cast(f32x4, load_lanes(it.w, 2u * c * (16 * kBlk), lane16));
+            wbuf[2 * slot + 1] = __builtin_bit_cast(f32x4, load_lanes(it.w, (2u * c + 1u) * (16 * kBlk), lane16));
         }
     };
     // the neuron of this lane in its wave's group b of a layer, what comes with it
@@ -132,7 +126,7 @@ __device__ __forceinline__ void few_layers(const float* __restrict__ Yin, float*
     for (int r = 0; r < R; ++r) slot[r] = r < nrow ? (row_at ? row_at[r] : row0 + r) : -1;
     Item ahead = item(cur, 0);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) fetch(ahead, c, 0);
+    for (int c = 0; c < (MODE == kResParts ? 2 : 4); ++c) fetch(ahead, c, c);
     int jn = neuron(cur, 0);
     for (int t = tid; t < n4; t += T_) {
         f32x4 a[R];
@@ -196,25 +190,31 @@ __device__ __forceinline__ void few_layers(const float* __restrict__ Yin, float*
                 for (int i = 0; i < 4; ++i) {
                     if (i < 3) read(y[(i + 1) & 1], cbuf[i + 1]);
                     add(y[i & 1], i);
-                    fetch(ahead, i, 0);
+                    fetch(ahead, i, i);
                 }
                 sum = acc;
             } else {
-                size_t off = 0;
-                for (int g = 0; g == 0 || 4 * g < it.nch; ++g, off += fa.part_stride) {
-                    const bool last = 4 * (g + 1) >= it.nch;
+                // Two chunks per turn, as in resident_kernel.  (Four, so that more is on its way: 1500 neurons of 0 to 40
+                // connections, 12 layers, 300 rows 71 -> 79 us, for all that is fetched in vain.)
+                uint32_t off = 0;  // of the part of 32 connections that the next two chunks are of
+                for (int c = 0; c == 0 || c < it.nch; c += 2) {
+                    const bool last = c + 2 >= it.nch;
+                    if (c & 2) off += fa.part_stride;
+                    const uint32_t half = last || (c & 2) ? 0u : 2u;  // the next chunks' place in their part
+                    const Item from = last ? Item{ahead.c, ahead.w, 0} : Item{it.c + off, it.w + off, 0};
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        if (4 * g + i < it.nch) {
+                    for (int i = 0; i < 2; ++i) {
+                        if (c + i < it.nch) {
                             T y[8];
                             read(y, cbuf[i]);
                             add(y, i);
                         }
-                        if (last) fetch(ahead, i, 0);
-                        else if (4 * (g + 1) + i < it.nch) fetch(it, i, off + fa.part_stride);
+                        fetch(from, i, half + i);
                     }
-                    sum += acc;
-                    acc = T{};
+                    if (last || (c & 2)) {
+                        sum += acc;
+                        acc = T{};
+                    }
                 }
             }
             const float bj = mine ? bias_j : -__builtin_inff();  // lanes without a neuron have no output

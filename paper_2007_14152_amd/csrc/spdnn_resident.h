@@ -28,14 +28,17 @@
 //
 // What bounds it.  One weight per layer: LDS reads (16 bytes per connection, plane and lane; 256 B per clock and CU) and
 // the FMAs behind them, which take nearly the same time (counters at 1024 neurons, 30 000 rows: LDS active 82 % of the
-// clocks, a fifth of that bank conflicts, vector instructions 72 %).  Weights of their own at 4096 neurons: the stream of
-// connections, 768 KB per layer and pass, which a CU pulls out of L2 at 25 bytes per clock.  One workgroup on its own:
-// latency.  The copies between LDS and memory happen once per launch instead of once per layer.
+// clocks, a fifth of that bank conflicts, vector instructions 72 %).  Weights of their own: the same two, at 30 000 of 21 000
+// clocks per layer and pass of 4096 neurons (without any one of reads, FMAs and connection loads a layer takes 10 to 18 %
+// less), and the rows' way in and out, 33 000 clocks per pass; the connections, 768 KB per layer and pass, are not what it
+// waits for: a CU gets 53 bytes per clock out of its L2, in loads or beside LDS reads.  One workgroup on its own: latency.
+// The copies between LDS and memory happen once per launch instead of once per layer.  What a wave can find out before the
+// barrier -- which rows have a positive output -- it does group by group, not behind the last one: 12 layers of 4096 neurons
+// with weights, 10 007 rows 889 -> 853 us with that and with buffer loads for the connections (load_lanes).
 // Whole passes, one launch per layer -> this kernel: 120 layers of 1024 neurons, 1000 rows 0.85 -> 0.27 ms, 60 000 rows
 // 7.40 -> 4.70; 24 layers of 4096 neurons, 60 000 rows 5.85 -> 4.53 (the first two layers one by one); 12 of them with
 // weights of their own, 10 007 rows 1.19 -> 0.85; 6 with 16 to 64 connections per neuron, 10 000 rows 1.26 -> 0.68 (several
-// lanes per neuron and two launches per layer before); 12 layers of 1500 neurons with 0 to 40 connections, 777 rows
-// 309 -> 80 us; 12 layers of 1024 neurons, one row 133 -> 56 us.
+// lanes per neuron and two launches per layer before).  Few rows are few_kernel's.
 //
 // Workgroups.  Networks of one block whose rows are more than a quad per CU run two workgroups per CU of eight waves
 // (two groups of 64 neurons per wave), so that one computes while the other writes or waits at a barrier (120 layers,
@@ -82,6 +85,13 @@ SPDNN_HD inline uint32_t res_chunk_bytes(int planes) { return 256u * (uint32_t)p
 SPDNN_HD inline uint32_t res_tile_bytes(int N, int planes) { return (uint32_t)((N + 255) / 256) * 16u * res_chunk_bytes(planes); }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// A lane's 16 bytes of an array that the wave reads at a scalar place: base + scalar offset + the lane's.  As a buffer load it
+// takes no vector instruction and no vector register for the address, where a pointer of the lane's own takes one and two.
+__device__ __forceinline__ u32x4 load_lanes(const __attribute__((address_space(1))) char* base, uint32_t offset, uint32_t lane_offset) {
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0xffffffff, 0x00027000);
+    return __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_offset, offset, 0);
+}
 
 // Eight connections of one neuron on P planes: acc[p] += tile[plane p][column i] * w_i, i = 0..7 in that order.  codes =
 // the eight entry codes, two to a register; an SDWA shift makes a half an LDS address, which serves all planes through
@@ -164,6 +174,7 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
     const int T = blockDim.x, W = T >> 6, U = (N + 63) >> 6;
     const uint32_t misc = res_tile_bytes(N, PM);
     uint32_t* live_word = reinterpret_cast<uint32_t*>(res_lds + misc);             // [2], raised by the layers in turn
+    const uint32_t live_at = misc;                                                 // its LDS address
     int* row_at = reinterpret_cast<int*>(res_lds + misc + 16);                     // [4 * PM] row to copy to or from, per slot; -1: none
     constexpr int F = kRows * PM;  // rows of a full pass
     int* level_at = row_at + 16;               // [kResLevels + 1]
@@ -192,13 +203,12 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
             bj[b] = j < N ? bias[j] : -__builtin_inff();
         }
     }
-    // Connections, fetched ahead: slots a whole group of 64 neurons (4 chunks of 8), weights two chunks.
+    // Connections, fetched ahead: slots a whole group of 64 neurons (4 chunks of 8), weights two chunks.  Neurons of any
+    // length: two chunks of both, and where the next layer's neurons are.
     // (Address spaces are spelled out: as generic pointers these loads would wait, and be waited for, with the LDS reads.)
     u32x4 cbuf[4];
     f32x4 wbuf[4] = {};
     using gchar = const __attribute__((address_space(1))) char;
-    using gu32x4 = const __attribute__((address_space(1))) u32x4;
-    using gf32x4 = const __attribute__((address_space(1))) f32x4;
     using gu32 = const __attribute__((address_space(1))) uint32_t;
     using gu16 = const __attribute__((address_space(1))) uint16_t;
     using cu32 = const __attribute__((address_space(4))) uint32_t;
@@ -215,13 +225,16 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
     };
     const uint32_t lane16 = 16u * lane;
     // chunk c (0..3) of the 32 connections that start at part_off bytes from the group's first
-    auto fetch_codes = [&](const Item& it, int c, size_t part_off = 0) {
-        cbuf[c] = *(gu32x4*)(it.c + part_off + (lane16 + (uint32_t)c * (16 * kBlk)));
-    };
-    auto fetch_weights = [&](const Item& it, int c, size_t part_off = 0) {
+    auto fetch_codes = [&](const Item& it, int c) { cbuf[c] = load_lanes(it.c, (uint32_t)c * (16 * kBlk), lane16); };
+    auto fetch_weights = [&](const Item& it, int c) {
         if constexpr (MODE == kResUniform) return;
-        wbuf[2 * (c & 1)] = *(gf32x4*)(it.w + part_off + (lane16 + (uint32_t)(2 * c) * (16 * kBlk)));
-        wbuf[2 * (c & 1) + 1] = *(gf32x4*)(it.w + part_off + (lane16 + (uint32_t)(2 * c + 1) * (16 * kBlk)));
+        wbuf[2 * (c & 1)] = __builtin_bit_cast(f32x4, load_lanes(it.w, (uint32_t)(2 * c) * (16 * kBlk), lane16));
+        wbuf[2 * (c & 1) + 1] = __builtin_bit_cast(f32x4, load_lanes(it.w, (uint32_t)(2 * c + 1) * (16 * kBlk), lane16));
+    };
+    auto fetch_chunk = [&](const Item& it, int slot, uint32_t c) {  // chunk c of the part that starts at `it`
+        cbuf[slot] = load_lanes(it.c, c * (16 * kBlk), lane16);
+        wbuf[2 * slot] = __builtin_bit_cast(f32x4, load_lanes(it.w, 2u * c * (16 * kBlk), lane16));
+        wbuf[2 * slot + 1] = __builtin_bit_cast(f32x4, load_lanes(it.w, (2u * c + 1u) * (16 * kBlk), lane16));
     };
     // The descriptors are constant while the kernel runs: scalar loads.
     using clayer = const __attribute__((address_space(4))) ResidentLayer;
@@ -237,6 +250,12 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
         level_n[tid] = 0;
     }
     int own = 0, i1 = 0;  // passes and rows of level 0 so far
+    int jn_ahead[NB];     // kResParts: the next layer's neurons
+    const auto neurons_of = [&](const ResidentLayer& d) {
+        if constexpr (MODE == kResParts)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) jn_ahead[b] = b < nb_w ? ((gu16*)(uintptr_t)d.perm)[64 * (b * W + wave) + lane] : 0;
+    };
     int primed = -1;      // the layer whose first group's connections cbuf / wbuf hold ...
     Item ahead{};         // ... which is this (in general: the group whose connections come next)
     for (;;) {
@@ -294,8 +313,9 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
             if (tid < 2) live_word[tid] = 0u;
             if (primed != la) {
                 ahead = item(first, 0);
+                neurons_of(first);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) fetch_codes(ahead, c);
+                for (int c = 0; c < (MODE == kResParts ? 2 : 4); ++c) fetch_codes(ahead, c);
                 fetch_weights(ahead, 0);
                 fetch_weights(ahead, 1);
             }
@@ -331,18 +351,16 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
                     uint32_t at[NB];  // where their outputs go
 #pragma unroll
                     for (int b = 0; b < NB; ++b) {
-                        jn[b] = 64 * (b * W + wave) + lane;
-                        if constexpr (MODE == kResParts) jn[b] = ((gu16*)(uintptr_t)cur.perm)[jn[b]];
-                        else at[b] = q_next[min(jn[b], N - 1) >> 2];
+                        jn[b] = MODE == kResParts ? jn_ahead[b] : 64 * (b * W + wave) + lane;
+                        at[b] = q_next[min(jn[b], N - 1) >> 2];
                     }
+                    neurons_of(nxt);
                     auto place = [&]() {  // out of the way of the first chunk's arithmetic
 #pragma unroll
-                        for (int b = 0; b < NB; ++b) {
-                            if constexpr (MODE == kResParts) at[b] = q_next[min(jn[b], N - 1) >> 2];
-                            else at[b] = store_group((uint32_t)jn[b]) * CH + ((at[b] >> (8 * (jn[b] & 3))) & 0xffu);
-                        }
+                        for (int b = 0; b < NB; ++b) at[b] = store_group((uint32_t)jn[b]) * CH + ((at[b] >> (8 * (jn[b] & 3))) & 0xffu);
                     };
                     f32x4 res[NB][PP];
+                    uint32_t pos = 0;  // rows that have a positive output in my neurons
 #pragma unroll
                     for (int b = 0; b < NB; ++b) {
 #pragma unroll
@@ -367,56 +385,48 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
 #pragma unroll
                                 for (int p = 0; p < PP; ++p) res[b][p] = acc[p];
                             } else {
-                                // 32 connections per turn; a chunk's registers are refilled with the group's next chunk for
-                                // them, or with the next group's first
-                                size_t off = 0;
+                                // Two chunks per turn, each refilled behind its arithmetic, whether it had any or not: what is on
+                                // its way at any point is the same on every path, so a chunk's wait is for that chunk (with
+                                // refills on some paths only, for all that had been asked for: 10 000 rows, 6 layers of 4096
+                                // neurons of 16 to 64 connections 701 us, 670 so).
                                 set_wave_prio(3 - b * 4 / NB);
-                                for (int g = 0; g == 0 || 4 * g < mine.nch; ++g, off += ra.part_stride) {
+                                uint32_t off = 0;  // of the part of 32 connections that the next two chunks are of
+                                for (int c = 0; c == 0 || c < mine.nch; c += 2) {
+                                    const bool last = c + 2 >= mine.nch;
+                                    if (c & 2) off += ra.part_stride;
+                                    const uint32_t half = last || (c & 2) ? 0u : 2u;  // the next chunks' place in their part
+                                    const Item from = last ? Item{next.c, next.w, 0} : Item{mine.c + off, mine.w + off, 0};
 #pragma unroll
-                                    for (int i = 0; i < 4; ++i) {
-                                        const int c = 4 * g + i;
-                                        if (c < mine.nch) res_fma8<PP, false>(acc, cbuf[i], 0.0f, wbuf[2 * (i & 1)], wbuf[2 * (i & 1) + 1]);
-                                        if (c < mine.nch || g == 0) {
-                                            if (c + 4 < mine.nch) fetch_codes(mine, i, off + ra.part_stride);
-                                            else fetch_codes(next, i);
-                                        }
-                                        if (c < mine.nch || c < 2) {
-                                            if (c + 2 < mine.nch) fetch_weights(mine, (i + 2) & 3, i < 2 ? off : off + ra.part_stride);
-                                            else fetch_weights(next, i & 1);
-                                        }
-                                        if (b == 0 && i == 0 && g == 0) place();
+                                    for (int i = 0; i < 2; ++i) {
+                                        if (c + i < mine.nch) res_fma8<PP, false>(acc, cbuf[i], 0.0f, wbuf[2 * i], wbuf[2 * i + 1]);
+                                        fetch_chunk(from, i, half + i);
                                     }
+                                    if (last || (c & 2))
 #pragma unroll
-                                    for (int p = 0; p < PP; ++p) {
-                                        res[b][p] += acc[p];
-                                        acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
-                                    }
+                                        for (int p = 0; p < PP; ++p) {
+                                            res[b][p] += acc[p];
+                                            acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+                                        }
                                 }
                                 bj[b] = jn[b] < N ? bias_lds[min(jn[b], N - 1)] : -__builtin_inff();
-                                at[b] = store_group((uint32_t)jn[b]) * CH + ((at[b] >> (8 * (jn[b] & 3))) & 0xffu);
+                                if (b == 0) place();
                             }
 #pragma unroll
                             for (int p = 0; p < PP; ++p)
 #pragma unroll
-                                for (int r = 0; r < kRows; ++r) res[b][p][r] = fminf(fmaxf(res[b][p][r] + bj[b], 0.0f), kClip);
+                                for (int r = 0; r < kRows; ++r) {
+                                    res[b][p][r] = fminf(fmaxf(res[b][p][r] + bj[b], 0.0f), kClip);
+                                    pos = __builtin_amdgcn_ballot_w64(res[b][p][r] > 0.0f) != 0ull ? pos | 1u << (kRows * p + r) : pos;
+                                }
                         }
                     }
                     set_wave_prio(3);
                     // Descriptors are asked for a layer ahead, and not before the arithmetic: its waits for the LDS would wait
                     // for them too.  After the last layer comes, for the connections, the next pass's first.
                     const ResidentLayer after = layer_at(l + 2 < lb ? l + 2 : la);
-                    // which rows have a positive output in my neurons
-                    uint32_t pos = 0;
-#pragma unroll
-                    for (int p = 0; p < PP; ++p)
-#pragma unroll
-                        for (int r = 0; r < kRows; ++r) {
-                            float m = res[0][p][r];
-#pragma unroll
-                            for (int b = 1; b < NB; ++b) m = fmaxf(m, res[b][p][r]);
-                            if (__builtin_amdgcn_ballot_w64(m > 0.0f) != 0ull) pos |= 1u << (kRows * p + r);
-                        }
-                    if (lane == 0 && pos) atomicOr(&live_word[l & 1], pos);
+                    // (a plain LDS operation of one lane: the compiler's atomic would look for the first active lane on its own)
+                    if (lane == 0) asm volatile("ds_or_b32 %0, %1" ::"v"(live_at + 4u * (uint32_t)(l & 1)), "v"(pos) : "memory");
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                     __syncthreads();  // every wave has read what it needs of the rows
                     const uint32_t raised = live_word[l & 1];  // (on its way while the results go out)
 #pragma unroll

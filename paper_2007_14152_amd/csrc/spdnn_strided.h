@@ -2,23 +2,23 @@
 // all with one weight -- the building block of the RadiX-Net topologies (Section II-A) -- and one bias for all neurons.
 //
 // Such a layer is a sliding sum over every orbit of "+S": along an orbit neuron t adds the inputs t .. t + 31, and
-// neighbours share 31 of them.  Five rounds of doubling (x[i] += x[i + 1], x[i] += x[i + 2], ... + 16) make 33 neighbours'
-// sums out of 64 inputs with 263 additions, 8 per neuron instead of 32, from 2 reads per neuron instead of 32, and there
-// are no connections to store or fetch: a layer is {S, off, weight}.  The sums are trees of five levels instead of chains
-// of 32, so their rounding error is smaller; weight and bias come last, in one fused multiply-add.
+// neighbours share 31 of them.  33 neighbours' 64 inputs are cut in two halves: the sums of x[i .. 31] for every i and of
+// x[32 .. i] are chains of 31 additions each, and a neuron's sum is one of the first plus one of the second -- 93 additions
+// for 33 neurons, 3 per neuron instead of 32 multiply-adds, from 2 reads per neuron instead of 32, and there are no
+// connections to store or fetch: a layer is {S, off, weight}.  A sum is 31 additions as before, in two runs, with weight
+// and bias in one fused multiply-add at the end.  (Nothing is ever subtracted.  Five rounds of doubling, x[i] += x[i + 1],
+// x[i] += x[i + 2], ... + 16, take 263 additions: 383 us where this takes 363.)
 //
 // Rows stay in LDS over a run of layers, two of them side by side (an entry = the two rows of a column, 8 bytes).  A lane
 // owns kStrideOut neighbours of an orbit: it reads its 64 entries into registers, adds, and after a barrier writes its 33
 // results over the input.  33 is odd so that lanes next to each other along an orbit of stride 1 (33 entries apart) fall
 // into different bank pairs; lanes of orbits next to each other read neighbouring entries anyway.  The last lane of an
-// orbit starts earlier where 33 does not divide it and computes some neighbours' results a second time, to the same
-// values.  An orbit of exactly 32 (S = N / 32) has one sum for all its neurons: one lane computes it once.
+// orbit that 33 does not divide writes fewer.  An orbit of exactly 32 (S = N / 32) has one sum for all its neurons: one lane computes it once.
 //
-// What bounds it: vector instructions, about 30 per neuron and pair of rows of which 16 are the additions, on the two
-// waves per SIMD that 256 registers allow.  48 layers of 16384 neurons, strides 1, 32 and 512 in turn, on 2000 rows of which
-// half die: 1.95 -> 0.39 ms (two neurons per lane under new names, one launch per layer before: 40 us a layer, 5.7 now);
-// 24 layers of 4096 neurons, strides 1, 32 and 128, 60 000 rows 4.45 -> 1.59 ms (resident_kernel before), 48 of them on 100
-// rows 324 -> 146 us.
+// What bounds it: reading, adding and writing, one behind the other: 256 registers leave two waves per SIMD, and they meet
+// at two barriers per layer.  48 layers of 16384 neurons, strides 1, 32 and 512 in turn, on 2000 rows of which half die:
+// 1.95 -> 0.36 ms (two neurons per lane under new names, one launch per layer before: 40 us a layer, 5 now); 24 layers of
+// 4096 neurons, strides 1, 32 and 128, 60 000 rows 4.45 -> 1.50 ms (resident_kernel before), 48 of them on 100 rows 324 -> 136 us.
 #pragma once
 
 namespace spdnn {
@@ -26,7 +26,7 @@ namespace spdnn {
 constexpr int kStrideOut = 33;                      // neurons a lane owns
 constexpr int kStrideIn = kStrideOut + kNnz - 1;    // inputs they read
 constexpr int kStrideThreads = 512;
-constexpr int kStrideMisc = 16;  // bytes of LDS behind the rows
+constexpr int kStrideMisc = 16;  // bytes of LDS behind the rows: two words of flags, an entry that nobody reads
 
 struct StridedLayer {
     int S, off;     // columns (j + off + k * S) mod N
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kStrideThreads) void strided_kernel(const float* __
             const uint32_t i = (uint32_t)tid - p * lanes;
             const bool mine = PAIRS ? p < (uint32_t)np : (uint32_t)tid < lanes;
             const uint32_t b = i / orbits, r = i - b * orbits;
-            const uint32_t t0 = per == 1u ? 0u : min(b * kStrideOut, T - kStrideOut);
+            const uint32_t t0 = b * kStrideOut, left = T - t0;  // the last lane of an orbit has fewer neurons: `left`
             const uint32_t j0 = (r + t0 * S) % (uint32_t)N;
             uint32_t c0 = j0 + (uint32_t)d->off;
             c0 = min(c0, c0 - (uint32_t)N);
@@ -154,15 +154,13 @@ __global__ __launch_bounds__(kStrideThreads) void strided_kernel(const float* __
                     f32x2 x[kStrideIn];
                     read_orbit<kStrideIn>(x, tile + base, c0, S, (uint32_t)N);
 #pragma unroll
-                    for (int k = 0; k < kStrideIn - 1; ++k) x[k] += x[k + 1];
+                    for (int k = kNnz - 2; k >= 0; --k) x[k] += x[k + 1];  // x[k .. 31]
 #pragma unroll
-                    for (int k = 0; k < kStrideIn - 3; ++k) x[k] += x[k + 2];
+                    for (int k = kNnz + 1; k < kStrideIn; ++k) x[k] += x[k - 1];  // x[32 .. k]
+                    y[0] = finish(x[0]);
 #pragma unroll
-                    for (int k = 0; k < kStrideIn - 7; ++k) x[k] += x[k + 4];
-#pragma unroll
-                    for (int k = 0; k < kStrideIn - 15; ++k) x[k] += x[k + 8];
-#pragma unroll
-                    for (int k = 0; k < kStrideOut; ++k) y[k] = finish(x[k] + x[k + 16]);
+                    for (int k = 1; k < kNnz; ++k) y[k] = finish(x[k] + x[k + kNnz - 1]);
+                    y[kNnz] = finish(x[kStrideIn - 1]);
                 }
                 // which rows have a positive output: the wave's first lane of every pair speaks for it
                 const unsigned long long pos0 = __builtin_amdgcn_ballot_w64(m0 > 0.0f), pos1 = __builtin_amdgcn_ballot_w64(m1 > 0.0f);
@@ -190,10 +188,12 @@ __global__ __launch_bounds__(kStrideThreads) void strided_kernel(const float* __
 #pragma unroll
                     for (int k = 0; k < kStrideOut; ++k) *(lds_f2*)(tile + (base + 8u * j0 + k * s8)) = y[k];
                 } else {
+                    // an orbit's last lane is always among these: it comes past the row end where the orbit ends
+                    const uint32_t nowhere = (uint32_t)np * row_bytes + 8u;
                     uint32_t at = 8u * j0;
 #pragma unroll
                     for (int k = 0; k < kStrideOut; ++k) {
-                        *(lds_f2*)(tile + (base + at)) = y[k];
+                        *(lds_f2*)(tile + ((uint32_t)k < left ? base + at : nowhere)) = y[k];
                         at = min(at + s8, at + back);
                     }
                 }

@@ -89,6 +89,8 @@ struct LayerDesc {
 
 }  // namespace
 
+constexpr int kInEvents = 2 + 3;  // pieces of inputs under way: one per input buffer, and the last batch's other pieces
+
 struct spdnn_model {
     int32_t N = 0, L = 0, nblk = 0, G = 1;
     hipStream_t stream = nullptr;
@@ -116,7 +118,7 @@ struct spdnn_model {
     hipEvent_t ooc_freed[2] = {nullptr, nullptr};  // the kernels that read the slot are done
     // inputs in host memory (spdnn_infer_host): copy stream and "batch has landed" events, made on first use
     hipStream_t in_stream = nullptr;
-    hipEvent_t in_ready[2] = {nullptr, nullptr};
+    hipEvent_t in_ready[kInEvents] = {};
     int32_t launches = 0, res_launches = 0;  // of fused kernels in the last inference; of resident_kernel among them
     // profiling
     int profiling = 0;
@@ -1088,6 +1090,8 @@ int static_scratch(void** out) {
     return SPDNN_OK;
 }
 
+constexpr int32_t kCopyBoundLayers = 48;             // spdnn_infer_host: so many layers take less time than their input's copy
+constexpr size_t kPieceBytes = (size_t)16 << 20;     // ... and so much of it is cut in two
 constexpr int32_t kFewLayers = 4;  // networks of so few layers are not cut into launches that keep rows in LDS
 
 // How resident_kernel runs a network: the most groups of 64 neurons a wave owns, the most planes of 4 rows a pass
@@ -1863,8 +1867,8 @@ int spdnn_destroy(spdnn_t h) {
             if (h->ooc_freed[i]) (void)hipEventDestroy(h->ooc_freed[i]);
         }
         if (h->ooc_stream) (void)hipStreamDestroy(h->ooc_stream);
-        for (int i = 0; i < 2; ++i)
-            if (h->in_ready[i]) (void)hipEventDestroy(h->in_ready[i]);
+        for (hipEvent_t e : h->in_ready)
+            if (e) (void)hipEventDestroy(e);
         if (h->in_stream) (void)hipStreamDestroy(h->in_stream);
         for (hipEvent_t e : h->t0) (void)hipEventDestroy(e);
         for (hipEvent_t e : h->t1) (void)hipEventDestroy(e);
@@ -2003,29 +2007,61 @@ int spdnn_infer_host(spdnn_t h, const float* Y0_host, int32_t batch, int32_t row
         carve_work(N, step, base + 2 * in_bytes, &wv);
         if (!h->in_stream) {  // made on first use: a second stream of default priority, and one event per input buffer
             HIP_TRY(hipStreamCreateWithFlags(&h->in_stream, hipStreamNonBlocking));
-            for (int i = 0; i < 2; ++i) HIP_TRY(hipEventCreateWithFlags(&h->in_ready[i], hipEventDisableTiming));
+            for (hipEvent_t& e : h->in_ready) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
         }
         // whatever happens below, the copy stream is idle again when the call returns
         struct Drain {
             hipStream_t cs;
             ~Drain() { (void)hipStreamSynchronize(cs); }
         } drain{h->in_stream};
-        const int32_t nb = (batch + step - 1) / step;
-        auto rows_of = [&](int32_t k) { return std::min(step, batch - k * step); };
-        auto fetch = [&](int32_t k) -> hipError_t {  // batch k -> input buffer k & 1, on the copy stream
-            hipError_t e = hipMemcpyAsync(in[k & 1], Y0_host + (size_t)k * step * N, sizeof(float) * (size_t)rows_of(k) * N,
-                                          hipMemcpyHostToDevice, h->in_stream);
-            return e != hipSuccess ? e : hipEventRecord(h->in_ready[k & 1], h->in_stream);
+        // The batches, and the last one in pieces of one half, a quarter, ..., a piece being copied while the one before it is
+        // inferred: what is left to do when the last byte has come is a piece, not a batch (6000 rows of 4096 neurons through 24
+        // layers in batches of 1500: 2110 -> 2026 us; in one batch 2319 -> 2034).  Only where copying takes longer than inferring, which is a question of
+        // the layers alone (4 bytes per neuron and row at PCIe's 55 GB/s against 32 multiply-adds per layer), and where a
+        // piece is worth the launches.
+        struct Piece {
+            int32_t first, rows;
+            float* to;
+            hipEvent_t ready;
         };
-        HIP_TRY(fetch(0));
+        std::vector<Piece> pieces;
+        for (int32_t k = 0, first = 0; first < batch; ++k) {
+            int32_t rows = std::min(step, batch - first);
+            float* to = in[k & 1];
+            if (first + rows == batch && h->L <= kCopyBoundLayers)
+                for (int i = 2; i < kInEvents && (size_t)rows * N * sizeof(float) >= kPieceBytes; ++i) {
+                    const int32_t half = rows / 2 & ~7;
+                    pieces.push_back(Piece{first, half, to, h->in_ready[i]});
+                    first += half;
+                    rows -= half;
+                    to += (size_t)half * N;
+                }
+            pieces.push_back(Piece{first, rows, to, h->in_ready[k & 1]});
+            first += rows;
+        }
+        auto fetch = [&](const Piece& p) -> hipError_t {  // on the copy stream
+            hipError_t e = hipMemcpyAsync(p.to, Y0_host + (size_t)p.first * N, sizeof(float) * (size_t)p.rows * N, hipMemcpyHostToDevice, h->in_stream);
+            return e != hipSuccess ? e : hipEventRecord(p.ready, h->in_stream);
+        };
+        // A batch is fetched while the one before it is inferred: the buffer it goes to was last read by the batch before that,
+        // whose inference has drained the model's stream.
+        size_t fetched = 0;
+        const auto fetch_batch = [&]() -> hipError_t {  // the next batch: the pieces up to the next one at the start of a buffer
+            do {
+                const hipError_t e = fetch(pieces[fetched]);
+                if (e != hipSuccess) return e;
+                ++fetched;
+            } while (fetched < pieces.size() && pieces[fetched].to != in[0] && pieces[fetched].to != in[1]);
+            return hipSuccess;
+        };
+        HIP_TRY(fetch_batch());
         int32_t total = 0;
-        for (int32_t k = 0; k < nb; ++k) {
-            HIP_TRY(hipStreamWaitEvent(h->stream, h->in_ready[k & 1], 0));
-            // the other buffer was last read by batch k-1, whose inference has drained the model's stream:
-            // its refill runs under the kernels of batch k
-            if (k + 1 < nb) HIP_TRY(fetch(k + 1));
+        for (size_t k = 0; k < pieces.size(); ++k) {
+            const Piece& p = pieces[k];
+            HIP_TRY(hipStreamWaitEvent(h->stream, p.ready, 0));
+            if (k + 1 == fetched && fetched < pieces.size()) HIP_TRY(fetch_batch());
             int32_t n = 0;
-            const int rc = infer_impl(h, in[k & 1], rows_of(k), wv, k * step, &n, active_rows_dev + total,
+            const int rc = infer_impl(h, p.to, p.rows, wv, p.first, &n, active_rows_dev + total,
                                       Y_final_dev ? Y_final_dev + (size_t)total * N : nullptr);
             if (rc != SPDNN_OK) return rc;
             total += n;

@@ -31,6 +31,7 @@ constexpr int kCapLog2 = 12;
 constexpr float kClip = 32.0f;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // A lane's connections are stored so that it fetches them with 16-byte loads, consecutive lanes from consecutive
 // addresses: eight slots or four weights per load.
@@ -214,112 +215,138 @@ __device__ __forceinline__ void fma_block8(float (&acc)[4], const uint32_t (&o)[
 
 // Sixteen connections of one output neuron whose layer has one weight for all its
 // connections (held in a scalar register): acc[r] = fma(tile[col_k][r], w, acc[r]),
-// k = 0..15 in that order, four 16-byte LDS reads in flight throughout.
-template <int P>
+// k = 0..15 in that order, four 16-byte LDS reads in flight throughout.  FIRST: acc starts
+// at 0, which the first connection's multiply-adds take for a constant: no registers to clear.
+#define SPDNN_FMA16S_READ \
+    "ds_read_b128 v[112:115], %[o0] offset:%[B]\n\t" \
+    "ds_read_b128 v[116:119], %[o1] offset:%[B]\n\t" \
+    "ds_read_b128 v[120:123], %[o2] offset:%[B]\n\t" \
+    "ds_read_b128 v[124:127], %[o3] offset:%[B]\n\t" \
+    "s_waitcnt lgkmcnt(3)\n\t"
+#define SPDNN_FMA16S_ADD \
+    "v_fmac_f32 %[a0], %[w], v112\n\t" \
+    "v_fmac_f32 %[a1], %[w], v113\n\t" \
+    "v_fmac_f32 %[a2], %[w], v114\n\t" \
+    "v_fmac_f32 %[a3], %[w], v115\n\t"
+#define SPDNN_FMA16S_SET \
+    "v_fma_f32 %[a0], %[w], v112, 0\n\t" \
+    "v_fma_f32 %[a1], %[w], v113, 0\n\t" \
+    "v_fma_f32 %[a2], %[w], v114, 0\n\t" \
+    "v_fma_f32 %[a3], %[w], v115, 0\n\t"
+#define SPDNN_FMA16S_REST \
+    "ds_read_b128 v[112:115], %[o4] offset:%[B]\n\t" \
+    "s_waitcnt lgkmcnt(3)\n\t" \
+    "v_fmac_f32 %[a0], %[w], v116\n\t" \
+    "v_fmac_f32 %[a1], %[w], v117\n\t" \
+    "v_fmac_f32 %[a2], %[w], v118\n\t" \
+    "v_fmac_f32 %[a3], %[w], v119\n\t" \
+    "ds_read_b128 v[116:119], %[o5] offset:%[B]\n\t" \
+    "s_waitcnt lgkmcnt(3)\n\t" \
+    "v_fmac_f32 %[a0], %[w], v120\n\t" \
+    "v_fmac_f32 %[a1], %[w], v121\n\t" \
+    "v_fmac_f32 %[a2], %[w], v122\n\t" \
+    "v_fmac_f32 %[a3], %[w], v123\n\t" \
+    "ds_read_b128 v[120:123], %[o6] offset:%[B]\n\t" \
+    "s_waitcnt lgkmcnt(3)\n\t" \
+    "v_fmac_f32 %[a0], %[w], v124\n\t" \
+    "v_fmac_f32 %[a1], %[w], v125\n\t" \
+    "v_fmac_f32 %[a2], %[w], v126\n\t" \
+    "v_fmac_f32 %[a3], %[w], v127\n\t" \
+    "ds_read_b128 v[124:127], %[o7] offset:%[B]\n\t" \
+    "s_waitcnt lgkmcnt(3)\n\t" \
+    "v_fmac_f32 %[a0], %[w], v112\n\t" \
+    "v_fmac_f32 %[a1], %[w], v113\n\t" \
+    "v_fmac_f32 %[a2], %[w], v114\n\t" \
+    "v_fmac_f32 %[a3], %[w], v115\n\t" \
+    "ds_read_b128 v[112:115], %[o8] offset:%[B]\n\t" \
+    "s_waitcnt lgkmcnt(3)\n\t" \
+    "v_fmac_f32 %[a0], %[w], v116\n\t" \
+    "v_fmac_f32 %[a1], %[w], v117\n\t" \
+    "v_fmac_f32 %[a2], %[w], v118\n\t" \
+    "v_fmac_f32 %[a3], %[w], v119\n\t" \
+    "ds_read_b128 v[116:119], %[o9] offset:%[B]\n\t" \
+    "s_waitcnt lgkmcnt(3)\n\t" \
+    "v_fmac_f32 %[a0], %[w], v120\n\t" \
+    "v_fmac_f32 %[a1], %[w], v121\n\t" \
+    "v_fmac_f32 %[a2], %[w], v122\n\t" \
+    "v_fmac_f32 %[a3], %[w], v123\n\t" \
+    "ds_read_b128 v[120:123], %[o10] offset:%[B]\n\t" \
+    "s_waitcnt lgkmcnt(3)\n\t" \
+    "v_fmac_f32 %[a0], %[w], v124\n\t" \
+    "v_fmac_f32 %[a1], %[w], v125\n\t" \
+    "v_fmac_f32 %[a2], %[w], v126\n\t" \
+    "v_fmac_f32 %[a3], %[w], v127\n\t" \
+    "ds_read_b128 v[124:127], %[o11] offset:%[B]\n\t" \
+    "s_waitcnt lgkmcnt(3)\n\t" \
+    "v_fmac_f32 %[a0], %[w], v112\n\t" \
+    "v_fmac_f32 %[a1], %[w], v113\n\t" \
+    "v_fmac_f32 %[a2], %[w], v114\n\t" \
+    "v_fmac_f32 %[a3], %[w], v115\n\t" \
+    "ds_read_b128 v[112:115], %[o12] offset:%[B]\n\t" \
+    "s_waitcnt lgkmcnt(3)\n\t" \
+    "v_fmac_f32 %[a0], %[w], v116\n\t" \
+    "v_fmac_f32 %[a1], %[w], v117\n\t" \
+    "v_fmac_f32 %[a2], %[w], v118\n\t" \
+    "v_fmac_f32 %[a3], %[w], v119\n\t" \
+    "ds_read_b128 v[116:119], %[o13] offset:%[B]\n\t" \
+    "s_waitcnt lgkmcnt(3)\n\t" \
+    "v_fmac_f32 %[a0], %[w], v120\n\t" \
+    "v_fmac_f32 %[a1], %[w], v121\n\t" \
+    "v_fmac_f32 %[a2], %[w], v122\n\t" \
+    "v_fmac_f32 %[a3], %[w], v123\n\t" \
+    "ds_read_b128 v[120:123], %[o14] offset:%[B]\n\t" \
+    "s_waitcnt lgkmcnt(3)\n\t" \
+    "v_fmac_f32 %[a0], %[w], v124\n\t" \
+    "v_fmac_f32 %[a1], %[w], v125\n\t" \
+    "v_fmac_f32 %[a2], %[w], v126\n\t" \
+    "v_fmac_f32 %[a3], %[w], v127\n\t" \
+    "ds_read_b128 v[124:127], %[o15] offset:%[B]\n\t" \
+    "s_waitcnt lgkmcnt(3)\n\t" \
+    "v_fmac_f32 %[a0], %[w], v112\n\t" \
+    "v_fmac_f32 %[a1], %[w], v113\n\t" \
+    "v_fmac_f32 %[a2], %[w], v114\n\t" \
+    "v_fmac_f32 %[a3], %[w], v115\n\t" \
+    "s_waitcnt lgkmcnt(2)\n\t" \
+    "v_fmac_f32 %[a0], %[w], v116\n\t" \
+    "v_fmac_f32 %[a1], %[w], v117\n\t" \
+    "v_fmac_f32 %[a2], %[w], v118\n\t" \
+    "v_fmac_f32 %[a3], %[w], v119\n\t" \
+    "s_waitcnt lgkmcnt(1)\n\t" \
+    "v_fmac_f32 %[a0], %[w], v120\n\t" \
+    "v_fmac_f32 %[a1], %[w], v121\n\t" \
+    "v_fmac_f32 %[a2], %[w], v122\n\t" \
+    "v_fmac_f32 %[a3], %[w], v123\n\t" \
+    "s_waitcnt lgkmcnt(0)\n\t" \
+    "v_fmac_f32 %[a0], %[w], v124\n\t" \
+    "v_fmac_f32 %[a1], %[w], v125\n\t" \
+    "v_fmac_f32 %[a2], %[w], v126\n\t" \
+    "v_fmac_f32 %[a3], %[w], v127\n\t"
+#define SPDNN_FMA16S_IN \
+    [o0] "v"(o[0]), [o1] "v"(o[1]), [o2] "v"(o[2]), [o3] "v"(o[3]), [o4] "v"(o[4]), [o5] "v"(o[5]), [o6] "v"(o[6]), [o7] "v"(o[7]), \
+        [o8] "v"(o[8]), [o9] "v"(o[9]), [o10] "v"(o[10]), [o11] "v"(o[11]), [o12] "v"(o[12]), [o13] "v"(o[13]), [o14] "v"(o[14]), \
+        [o15] "v"(o[15]), [w] "s"(w), [B] "n"(P * kBufSkew)
+#define SPDNN_FMA16S_CLOBBER                                                                                               \
+    "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v120", "v121", "v122", "v123", "v124", "v125", "v126", \
+        "v127", "memory"
+template <int P, bool FIRST>
 __device__ __forceinline__ void fma_block16s(float (&acc)[4], const uint32_t (&o)[16], float w) {
-    asm volatile(
-        "ds_read_b128 v[112:115], %[o0] offset:%[B]\n\t"
-        "ds_read_b128 v[116:119], %[o1] offset:%[B]\n\t"
-        "ds_read_b128 v[120:123], %[o2] offset:%[B]\n\t"
-        "ds_read_b128 v[124:127], %[o3] offset:%[B]\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v112\n\t"
-        "v_fmac_f32 %[a1], %[w], v113\n\t"
-        "v_fmac_f32 %[a2], %[w], v114\n\t"
-        "v_fmac_f32 %[a3], %[w], v115\n\t"
-        "ds_read_b128 v[112:115], %[o4] offset:%[B]\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v116\n\t"
-        "v_fmac_f32 %[a1], %[w], v117\n\t"
-        "v_fmac_f32 %[a2], %[w], v118\n\t"
-        "v_fmac_f32 %[a3], %[w], v119\n\t"
-        "ds_read_b128 v[116:119], %[o5] offset:%[B]\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v120\n\t"
-        "v_fmac_f32 %[a1], %[w], v121\n\t"
-        "v_fmac_f32 %[a2], %[w], v122\n\t"
-        "v_fmac_f32 %[a3], %[w], v123\n\t"
-        "ds_read_b128 v[120:123], %[o6] offset:%[B]\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v124\n\t"
-        "v_fmac_f32 %[a1], %[w], v125\n\t"
-        "v_fmac_f32 %[a2], %[w], v126\n\t"
-        "v_fmac_f32 %[a3], %[w], v127\n\t"
-        "ds_read_b128 v[124:127], %[o7] offset:%[B]\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v112\n\t"
-        "v_fmac_f32 %[a1], %[w], v113\n\t"
-        "v_fmac_f32 %[a2], %[w], v114\n\t"
-        "v_fmac_f32 %[a3], %[w], v115\n\t"
-        "ds_read_b128 v[112:115], %[o8] offset:%[B]\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v116\n\t"
-        "v_fmac_f32 %[a1], %[w], v117\n\t"
-        "v_fmac_f32 %[a2], %[w], v118\n\t"
-        "v_fmac_f32 %[a3], %[w], v119\n\t"
-        "ds_read_b128 v[116:119], %[o9] offset:%[B]\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v120\n\t"
-        "v_fmac_f32 %[a1], %[w], v121\n\t"
-        "v_fmac_f32 %[a2], %[w], v122\n\t"
-        "v_fmac_f32 %[a3], %[w], v123\n\t"
-        "ds_read_b128 v[120:123], %[o10] offset:%[B]\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v124\n\t"
-        "v_fmac_f32 %[a1], %[w], v125\n\t"
-        "v_fmac_f32 %[a2], %[w], v126\n\t"
-        "v_fmac_f32 %[a3], %[w], v127\n\t"
-        "ds_read_b128 v[124:127], %[o11] offset:%[B]\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v112\n\t"
-        "v_fmac_f32 %[a1], %[w], v113\n\t"
-        "v_fmac_f32 %[a2], %[w], v114\n\t"
-        "v_fmac_f32 %[a3], %[w], v115\n\t"
-        "ds_read_b128 v[112:115], %[o12] offset:%[B]\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v116\n\t"
-        "v_fmac_f32 %[a1], %[w], v117\n\t"
-        "v_fmac_f32 %[a2], %[w], v118\n\t"
-        "v_fmac_f32 %[a3], %[w], v119\n\t"
-        "ds_read_b128 v[116:119], %[o13] offset:%[B]\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v120\n\t"
-        "v_fmac_f32 %[a1], %[w], v121\n\t"
-        "v_fmac_f32 %[a2], %[w], v122\n\t"
-        "v_fmac_f32 %[a3], %[w], v123\n\t"
-        "ds_read_b128 v[120:123], %[o14] offset:%[B]\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v124\n\t"
-        "v_fmac_f32 %[a1], %[w], v125\n\t"
-        "v_fmac_f32 %[a2], %[w], v126\n\t"
-        "v_fmac_f32 %[a3], %[w], v127\n\t"
-        "ds_read_b128 v[124:127], %[o15] offset:%[B]\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v112\n\t"
-        "v_fmac_f32 %[a1], %[w], v113\n\t"
-        "v_fmac_f32 %[a2], %[w], v114\n\t"
-        "v_fmac_f32 %[a3], %[w], v115\n\t"
-        "s_waitcnt lgkmcnt(2)\n\t"
-        "v_fmac_f32 %[a0], %[w], v116\n\t"
-        "v_fmac_f32 %[a1], %[w], v117\n\t"
-        "v_fmac_f32 %[a2], %[w], v118\n\t"
-        "v_fmac_f32 %[a3], %[w], v119\n\t"
-        "s_waitcnt lgkmcnt(1)\n\t"
-        "v_fmac_f32 %[a0], %[w], v120\n\t"
-        "v_fmac_f32 %[a1], %[w], v121\n\t"
-        "v_fmac_f32 %[a2], %[w], v122\n\t"
-        "v_fmac_f32 %[a3], %[w], v123\n\t"
-        "s_waitcnt lgkmcnt(0)\n\t"
-        "v_fmac_f32 %[a0], %[w], v124\n\t"
-        "v_fmac_f32 %[a1], %[w], v125\n\t"
-        "v_fmac_f32 %[a2], %[w], v126\n\t"
-        "v_fmac_f32 %[a3], %[w], v127\n\t"
-        : [a0] "+v"(acc[0]), [a1] "+v"(acc[1]), [a2] "+v"(acc[2]), [a3] "+v"(acc[3])
-        : [o0] "v"(o[0]), [o1] "v"(o[1]), [o2] "v"(o[2]), [o3] "v"(o[3]), [o4] "v"(o[4]), [o5] "v"(o[5]), [o6] "v"(o[6]), [o7] "v"(o[7]), [o8] "v"(o[8]), [o9] "v"(o[9]), [o10] "v"(o[10]), [o11] "v"(o[11]), [o12] "v"(o[12]), [o13] "v"(o[13]), [o14] "v"(o[14]), [o15] "v"(o[15]),
-          [w] "s"(w), [B] "n"(P * kBufSkew)
-        : "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v120", "v121", "v122", "v123",
-          "v124", "v125", "v126", "v127", "memory");
+    if constexpr (FIRST)
+        asm volatile(SPDNN_FMA16S_READ SPDNN_FMA16S_SET SPDNN_FMA16S_REST
+                     : [a0] "=&v"(acc[0]), [a1] "=&v"(acc[1]), [a2] "=&v"(acc[2]), [a3] "=&v"(acc[3])
+                     : SPDNN_FMA16S_IN
+                     : SPDNN_FMA16S_CLOBBER);
+    else
+        asm volatile(SPDNN_FMA16S_READ SPDNN_FMA16S_ADD SPDNN_FMA16S_REST
+                     : [a0] "+v"(acc[0]), [a1] "+v"(acc[1]), [a2] "+v"(acc[2]), [a3] "+v"(acc[3])
+                     : SPDNN_FMA16S_IN
+                     : SPDNN_FMA16S_CLOBBER);
 }
+#undef SPDNN_FMA16S_READ
+#undef SPDNN_FMA16S_ADD
+#undef SPDNN_FMA16S_SET
+#undef SPDNN_FMA16S_REST
+#undef SPDNN_FMA16S_IN
+#undef SPDNN_FMA16S_CLOBBER
 
 // Eight connections, one scalar weight (see fma_block16s).
 template <int P>
@@ -772,9 +799,15 @@ __device__ __forceinline__ unsigned finish_rows(float (&a)[kRows], float bj, flo
                          (__builtin_amdgcn_ballot_w64(y2 > 0.0f) != 0ull ? 4u : 0u) |
                          (__builtin_amdgcn_ballot_w64(y3 > 0.0f) != 0ull ? 8u : 0u);
     transpose_quartet(y0, y1, y2, y3);
+    // A buffer store from the first row on: the lane's place behind it is the same in every step, so that no address is worked
+    // out in vector registers (a 64-bit multiply-add and a 64-bit addition: with them and the accumulators cleared 24 000 rows of
+    // 65536 neurons, 6 layers, took 10.98 ms, 10.95 without; 2000 rows 1032 us, 1013).
     const int r = lane & 3;
-    if (jok && r < nlive)
-        __builtin_nontemporal_store(f32x4{y0, y1, y2, y3}, reinterpret_cast<f32x4*>(Yout + (size_t)(row0 + r) * N + (j & ~3)));
+    if (jok && r < nlive) {
+        const auto rows = __builtin_amdgcn_make_buffer_rsrc((void*)(Yout + (size_t)row0 * N), 0, 0xffffffff, 0x00027000);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{y0, y1, y2, y3}), rows, 4u * (uint32_t)(r * N + (j & ~3)), 0,
+                                               2 /* nt */);
+    }
     return pos;
 }
 
@@ -1141,7 +1174,7 @@ __global__ __launch_bounds__(kBlk) void fused_pair_kernel(
         if (staging) stage_store(st, a + P * kBufSkew, q);
     };
 
-    float accA[kRows] = {0.f, 0.f, 0.f, 0.f}, accB[kRows] = {0.f, 0.f, 0.f, 0.f};
+    float accA[kRows], accB[kRows];
     {
         const int pw = __builtin_amdgcn_readfirstlane(3 - ((threadIdx.x >> 8) & 3));
         if (pw == 1) __builtin_amdgcn_s_setprio(1);
@@ -1154,7 +1187,7 @@ __global__ __launch_bounds__(kBlk) void fused_pair_kernel(
         uint32_t o[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[i] = off[k0 + i];
-        fma_block16s<P>(acc, o, wuni);
+        fma_block16s<P, k0 == 0>(acc, o, wuni);
     };
 
     const int lane = tid & 63;

@@ -84,8 +84,6 @@ constexpr int kStopNum = 5, kStopDen = 8, kStopLeft = 3;
 SPDNN_HD inline uint32_t res_chunk_bytes(int planes) { return 256u * (uint32_t)planes; }
 SPDNN_HD inline uint32_t res_tile_bytes(int N, int planes) { return (uint32_t)((N + 255) / 256) * 16u * res_chunk_bytes(planes); }
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
 // A lane's 16 bytes of an array that the wave reads at a scalar place: base + scalar offset + the lane's.  As a buffer load it
 // takes no vector instruction and no vector register for the address, where a pointer of the lane's own takes one and two.
 __device__ __forceinline__ u32x4 load_lanes(const __attribute__((address_space(1))) char* base, uint32_t offset, uint32_t lane_offset) {

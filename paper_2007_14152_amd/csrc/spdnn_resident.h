@@ -100,7 +100,7 @@ __device__ __forceinline__ u32x4 load_lanes(const __attribute__((address_space(1
     "v_lshlrev_b32_sdwa v[72+" I "], %[s4], %[" C "] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_" H "\n\t"
 #define SPDNN_RES_READ(K)                                                                                        \
     "ds_read_b128 v[112+4*((" K ")%%4):115+4*((" K ")%%4)], v[72+(" K ")/%[P]] offset:256*((" K ")%%%[P])\n\t"
-#define SPDNN_RES_CONN(W)                                    \
+#define SPDNN_RES_CONN_(ADD, W, FROM)                        \
     ".set spdnn_p, 0\n\t"                                    \
     ".rept %[P]\n\t"                                         \
     ".if 8*%[P]-spdnn_k > 4\n\t"                             \
@@ -108,46 +108,53 @@ __device__ __forceinline__ u32x4 load_lanes(const __attribute__((address_space(1
     ".else\n\t"                                              \
     "s_waitcnt lgkmcnt(8*%[P]-spdnn_k-1)\n\t"                \
     ".endif\n\t"                                             \
-    "v_fmac_f32 v[80+4*spdnn_p], " W ", v[112+4*(spdnn_k%%4)]\n\t" \
-    "v_fmac_f32 v[81+4*spdnn_p], " W ", v[113+4*(spdnn_k%%4)]\n\t" \
-    "v_fmac_f32 v[82+4*spdnn_p], " W ", v[114+4*(spdnn_k%%4)]\n\t" \
-    "v_fmac_f32 v[83+4*spdnn_p], " W ", v[115+4*(spdnn_k%%4)]\n\t" \
+    ADD " v[80+4*spdnn_p], " W ", v[112+4*(spdnn_k%%4)]" FROM "\n\t" \
+    ADD " v[81+4*spdnn_p], " W ", v[113+4*(spdnn_k%%4)]" FROM "\n\t" \
+    ADD " v[82+4*spdnn_p], " W ", v[114+4*(spdnn_k%%4)]" FROM "\n\t" \
+    ADD " v[83+4*spdnn_p], " W ", v[115+4*(spdnn_k%%4)]" FROM "\n\t" \
     ".if spdnn_k+4 < 8*%[P]\n\t"                             \
     SPDNN_RES_READ("spdnn_k+4")                              \
     ".endif\n\t"                                             \
     ".set spdnn_p, spdnn_p+1\n\t"                            \
     ".set spdnn_k, spdnn_k+1\n\t"                            \
     ".endr\n\t"
+#define SPDNN_RES_CONN(W) SPDNN_RES_CONN_("v_fmac_f32", W, "")
+#define SPDNN_RES_CONN0(W) SPDNN_RES_CONN_("v_fma_f32", W, ", 0")  // the first of all: sums start at 0
 #define SPDNN_RES_HEAD                                                                                                 \
     SPDNN_RES_ADDR("0", "c0", "0") SPDNN_RES_ADDR("1", "c0", "1") SPDNN_RES_ADDR("2", "c1", "0") SPDNN_RES_ADDR("3", "c1", "1") \
     ".set spdnn_k, 0\n\t" SPDNN_RES_READ("0") SPDNN_RES_READ("1") SPDNN_RES_READ("2") SPDNN_RES_READ("3")                 \
     SPDNN_RES_ADDR("4", "c2", "0") SPDNN_RES_ADDR("5", "c2", "1") SPDNN_RES_ADDR("6", "c3", "0") SPDNN_RES_ADDR("7", "c3", "1")
-#define SPDNN_RES_ASM_U                                                                                                \
-    SPDNN_RES_HEAD SPDNN_RES_CONN("%[w]") SPDNN_RES_CONN("%[w]") SPDNN_RES_CONN("%[w]") SPDNN_RES_CONN("%[w]")           \
+#define SPDNN_RES_ASM_U(FIRST)                                                                                         \
+    SPDNN_RES_HEAD FIRST("%[w]") SPDNN_RES_CONN("%[w]") SPDNN_RES_CONN("%[w]") SPDNN_RES_CONN("%[w]")                    \
     SPDNN_RES_CONN("%[w]") SPDNN_RES_CONN("%[w]") SPDNN_RES_CONN("%[w]") SPDNN_RES_CONN("%[w]")
-#define SPDNN_RES_ASM_W                                                                                                \
-    SPDNN_RES_HEAD SPDNN_RES_CONN("%[w0]") SPDNN_RES_CONN("%[w1]") SPDNN_RES_CONN("%[w2]") SPDNN_RES_CONN("%[w3]")       \
+#define SPDNN_RES_ASM_W(FIRST)                                                                                         \
+    SPDNN_RES_HEAD FIRST("%[w0]") SPDNN_RES_CONN("%[w1]") SPDNN_RES_CONN("%[w2]") SPDNN_RES_CONN("%[w3]")                \
     SPDNN_RES_CONN("%[w4]") SPDNN_RES_CONN("%[w5]") SPDNN_RES_CONN("%[w6]") SPDNN_RES_CONN("%[w7]")
-#define SPDNN_RES_ACC1 "+{v[80:83]}"(acc[0])
-#define SPDNN_RES_ACC2 SPDNN_RES_ACC1, "+{v[84:87]}"(acc[1])
-#define SPDNN_RES_ACC3 SPDNN_RES_ACC2, "+{v[88:91]}"(acc[2])
-#define SPDNN_RES_ACC4 SPDNN_RES_ACC3, "+{v[92:95]}"(acc[3])
+#define SPDNN_RES_ACC1(D) D "{v[80:83]}"(acc[0])
+#define SPDNN_RES_ACC2(D) SPDNN_RES_ACC1(D), D "{v[84:87]}"(acc[1])
+#define SPDNN_RES_ACC3(D) SPDNN_RES_ACC2(D), D "{v[88:91]}"(acc[2])
+#define SPDNN_RES_ACC4(D) SPDNN_RES_ACC3(D), D "{v[92:95]}"(acc[3])
 #define SPDNN_RES_IN [c0] "v"(codes.x), [c1] "v"(codes.y), [c2] "v"(codes.z), [c3] "v"(codes.w), [s4] "s"(4), [P] "n"(P)
 #define SPDNN_RES_CLOBBER                                                                                            \
     "v72", "v73", "v74", "v75", "v76", "v77", "v78", "v79", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119",  \
         "v120", "v121", "v122", "v123", "v124", "v125", "v126", "v127", "memory"
+#define SPDNN_RES_CASE2(Q, D, FIRST)                                                                                    \
+    if constexpr (UNI)                                                                                               \
+        asm volatile(SPDNN_RES_ASM_U(FIRST) : SPDNN_RES_ACC##Q(D) : SPDNN_RES_IN, [w] "s"(wu) : SPDNN_RES_CLOBBER);     \
+    else                                                                                                             \
+        asm volatile(SPDNN_RES_ASM_W(FIRST)                                                                            \
+                     : SPDNN_RES_ACC##Q(D)                                                                             \
+                     : SPDNN_RES_IN, [w0] "v"(wa.x), [w1] "v"(wa.y), [w2] "v"(wa.z), [w3] "v"(wa.w), [w4] "v"(wb.x),     \
+                       [w5] "v"(wb.y), [w6] "v"(wb.z), [w7] "v"(wb.w)                                                  \
+                     : SPDNN_RES_CLOBBER);
 #define SPDNN_RES_CASE(Q)                                                                                             \
-    if constexpr (P == Q) {                                                                                          \
-        if constexpr (UNI)                                                                                           \
-            asm volatile(SPDNN_RES_ASM_U : SPDNN_RES_ACC##Q : SPDNN_RES_IN, [w] "s"(wu) : SPDNN_RES_CLOBBER);          \
-        else                                                                                                         \
-            asm volatile(SPDNN_RES_ASM_W                                                                              \
-                         : SPDNN_RES_ACC##Q                                                                          \
-                         : SPDNN_RES_IN, [w0] "v"(wa.x), [w1] "v"(wa.y), [w2] "v"(wa.z), [w3] "v"(wa.w), [w4] "v"(wb.x), \
-                           [w5] "v"(wb.y), [w6] "v"(wb.z), [w7] "v"(wb.w)                                              \
-                         : SPDNN_RES_CLOBBER);                                                                       \
+    if constexpr (P == Q && FIRST) {                                                                                 \
+        SPDNN_RES_CASE2(Q, "=&", SPDNN_RES_CONN0)                                                                      \
+    } else if constexpr (P == Q) {                                                                                   \
+        SPDNN_RES_CASE2(Q, "+", SPDNN_RES_CONN)                                                                        \
     }
-template <int P, bool UNI>
+// FIRST: acc need not be set, the sums start at 0.
+template <int P, bool UNI, bool FIRST>
 __device__ __forceinline__ void res_fma8(f32x4 (&acc)[P], u32x4 codes, float wu, f32x4 wa, f32x4 wb) {
     SPDNN_RES_CASE(1)
     SPDNN_RES_CASE(2)
@@ -365,8 +372,6 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
                         for (int p = 0; p < PP; ++p) res[b][p] = f32x4{0.f, 0.f, 0.f, 0.f};
                         if (b < nb_w) {
                             f32x4 acc[PP];
-#pragma unroll
-                            for (int p = 0; p < PP; ++p) acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
                             const Item mine = ahead;
                             const Item next = b + 1 < nb_w ? item(cur, b + 1) : item(nxt, 0);
                             ahead = next;
@@ -374,7 +379,8 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
 #pragma unroll
                                 for (int c = 0; c < 4; ++c) {
                                     if ((b * 4 + c) % NB == 0) set_wave_prio(3 - (b * 4 + c) / NB);
-                                    res_fma8<PP, MODE == kResUniform>(acc, cbuf[c], cur.wuni, wbuf[2 * (c & 1)], wbuf[2 * (c & 1) + 1]);
+                                    if (c == 0) res_fma8<PP, MODE == kResUniform, true>(acc, cbuf[0], cur.wuni, wbuf[0], wbuf[1]);
+                                    else res_fma8<PP, MODE == kResUniform, false>(acc, cbuf[c], cur.wuni, wbuf[2 * (c & 1)], wbuf[2 * (c & 1) + 1]);
                                     fetch_codes(next, c);
                                     if (c < 2) fetch_weights(mine, c + 2);
                                     else fetch_weights(next, c - 2);
@@ -387,6 +393,8 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
                                 // its way at any point is the same on every path, so a chunk's wait is for that chunk (with
                                 // refills on some paths only, for all that had been asked for: 10 000 rows, 6 layers of 4096
                                 // neurons of 16 to 64 connections 701 us, 670 so).
+#pragma unroll
+                                for (int p = 0; p < PP; ++p) acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
                                 set_wave_prio(3 - b * 4 / NB);
                                 uint32_t off = 0;  // of the part of 32 connections that the next two chunks are of
                                 for (int c = 0; c == 0 || c < mine.nch; c += 2) {
@@ -396,7 +404,7 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
                                     const Item from = last ? Item{next.c, next.w, 0} : Item{mine.c + off, mine.w + off, 0};
 #pragma unroll
                                     for (int i = 0; i < 2; ++i) {
-                                        if (c + i < mine.nch) res_fma8<PP, false>(acc, cbuf[i], 0.0f, wbuf[2 * i], wbuf[2 * i + 1]);
+                                        if (c + i < mine.nch) res_fma8<PP, false, false>(acc, cbuf[i], 0.0f, wbuf[2 * i], wbuf[2 * i + 1]);
                                         fetch_chunk(from, i, half + i);
                                     }
                                     if (last || (c & 2))

@@ -93,27 +93,27 @@ __device__ __forceinline__ u32x4 load_lanes(const __attribute__((address_space(1
 
 // Eight connections of one neuron on P planes: acc[p] += tile[plane p][column i] * w_i, i = 0..7 in that order.  codes =
 // the eight entry codes, two to a register; an SDWA shift makes a half an LDS address, which serves all planes through
-// the read's immediate offset.  The reads of all (connection, plane) pairs form one pipeline of four in flight.  The
+// the read's immediate offset.  The reads of all (connection, plane) pairs form one pipeline of D in flight.  The
 // accumulators and addresses sit in fixed registers so that the assembler's own loop can number them: plane p in
 // v[80+4p .. 83+4p], address i in v[72+i], reads in v[112:127].
 #define SPDNN_RES_ADDR(I, C, H) \
     "v_lshlrev_b32_sdwa v[72+" I "], %[s4], %[" C "] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_" H "\n\t"
 #define SPDNN_RES_READ(K)                                                                                        \
-    "ds_read_b128 v[112+4*((" K ")%%4):115+4*((" K ")%%4)], v[72+(" K ")/%[P]] offset:256*((" K ")%%%[P])\n\t"
+    "ds_read_b128 v[112+4*((" K ")%%%[D]):115+4*((" K ")%%%[D])], v[72+(" K ")/%[P]] offset:256*((" K ")%%%[P])\n\t"
 #define SPDNN_RES_CONN_(ADD, W, FROM)                        \
     ".set spdnn_p, 0\n\t"                                    \
     ".rept %[P]\n\t"                                         \
-    ".if 8*%[P]-spdnn_k > 4\n\t"                             \
-    "s_waitcnt lgkmcnt(3)\n\t"                               \
+    ".if 8*%[P]-spdnn_k > %[D]\n\t"                             \
+    "s_waitcnt lgkmcnt(%[D]-1)\n\t"                          \
     ".else\n\t"                                              \
     "s_waitcnt lgkmcnt(8*%[P]-spdnn_k-1)\n\t"                \
     ".endif\n\t"                                             \
-    ADD " v[80+4*spdnn_p], " W ", v[112+4*(spdnn_k%%4)]" FROM "\n\t" \
-    ADD " v[81+4*spdnn_p], " W ", v[113+4*(spdnn_k%%4)]" FROM "\n\t" \
-    ADD " v[82+4*spdnn_p], " W ", v[114+4*(spdnn_k%%4)]" FROM "\n\t" \
-    ADD " v[83+4*spdnn_p], " W ", v[115+4*(spdnn_k%%4)]" FROM "\n\t" \
-    ".if spdnn_k+4 < 8*%[P]\n\t"                             \
-    SPDNN_RES_READ("spdnn_k+4")                              \
+    ADD " v[80+4*spdnn_p], " W ", v[112+4*(spdnn_k%%%[D])]" FROM "\n\t" \
+    ADD " v[81+4*spdnn_p], " W ", v[113+4*(spdnn_k%%%[D])]" FROM "\n\t" \
+    ADD " v[82+4*spdnn_p], " W ", v[114+4*(spdnn_k%%%[D])]" FROM "\n\t" \
+    ADD " v[83+4*spdnn_p], " W ", v[115+4*(spdnn_k%%%[D])]" FROM "\n\t" \
+    ".if spdnn_k+%[D] < 8*%[P]\n\t"                          \
+    SPDNN_RES_READ("spdnn_k+%[D]")                           \
     ".endif\n\t"                                             \
     ".set spdnn_p, spdnn_p+1\n\t"                            \
     ".set spdnn_k, spdnn_k+1\n\t"                            \
@@ -122,7 +122,7 @@ __device__ __forceinline__ u32x4 load_lanes(const __attribute__((address_space(1
 #define SPDNN_RES_CONN0(W) SPDNN_RES_CONN_("v_fma_f32", W, ", 0")  // the first of all: sums start at 0
 #define SPDNN_RES_HEAD                                                                                                 \
     SPDNN_RES_ADDR("0", "c0", "0") SPDNN_RES_ADDR("1", "c0", "1") SPDNN_RES_ADDR("2", "c1", "0") SPDNN_RES_ADDR("3", "c1", "1") \
-    ".set spdnn_k, 0\n\t" SPDNN_RES_READ("0") SPDNN_RES_READ("1") SPDNN_RES_READ("2") SPDNN_RES_READ("3")                 \
+    ".set spdnn_k, 0\n\t" SPDNN_RES_READ("0") SPDNN_RES_READ("1") SPDNN_RES_READ("2") ".if %[D] > 3\n\t" SPDNN_RES_READ("3") ".endif\n\t" \
     SPDNN_RES_ADDR("4", "c2", "0") SPDNN_RES_ADDR("5", "c2", "1") SPDNN_RES_ADDR("6", "c3", "0") SPDNN_RES_ADDR("7", "c3", "1")
 #define SPDNN_RES_ASM_U(FIRST)                                                                                         \
     SPDNN_RES_HEAD FIRST("%[w]") SPDNN_RES_CONN("%[w]") SPDNN_RES_CONN("%[w]") SPDNN_RES_CONN("%[w]")                    \
@@ -134,27 +134,30 @@ __device__ __forceinline__ u32x4 load_lanes(const __attribute__((address_space(1
 #define SPDNN_RES_ACC2(D) SPDNN_RES_ACC1(D), D "{v[84:87]}"(acc[1])
 #define SPDNN_RES_ACC3(D) SPDNN_RES_ACC2(D), D "{v[88:91]}"(acc[2])
 #define SPDNN_RES_ACC4(D) SPDNN_RES_ACC3(D), D "{v[92:95]}"(acc[3])
-#define SPDNN_RES_IN [c0] "v"(codes.x), [c1] "v"(codes.y), [c2] "v"(codes.z), [c3] "v"(codes.w), [s4] "s"(4), [P] "n"(P)
-#define SPDNN_RES_CLOBBER                                                                                            \
+#define SPDNN_RES_IN [c0] "v"(codes.x), [c1] "v"(codes.y), [c2] "v"(codes.z), [c3] "v"(codes.w), [s4] "s"(4), [P] "n"(P), [D] "n"(D)
+#define SPDNN_RES_CLOBBER3                                                                                           \
     "v72", "v73", "v74", "v75", "v76", "v77", "v78", "v79", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119",  \
-        "v120", "v121", "v122", "v123", "v124", "v125", "v126", "v127", "memory"
-#define SPDNN_RES_CASE2(Q, D, FIRST)                                                                                    \
+        "v120", "v121", "v122", "v123", "memory"
+#define SPDNN_RES_CLOBBER4 SPDNN_RES_CLOBBER3, "v124", "v125", "v126", "v127"
+#define SPDNN_RES_RUN(Q, OUT, FIRST_CONN, CLOBBER)                                                                      \
     if constexpr (UNI)                                                                                               \
-        asm volatile(SPDNN_RES_ASM_U(FIRST) : SPDNN_RES_ACC##Q(D) : SPDNN_RES_IN, [w] "s"(wu) : SPDNN_RES_CLOBBER);     \
+        asm volatile(SPDNN_RES_ASM_U(FIRST_CONN) : SPDNN_RES_ACC##Q(OUT) : SPDNN_RES_IN, [w] "s"(wu) : CLOBBER);        \
     else                                                                                                             \
-        asm volatile(SPDNN_RES_ASM_W(FIRST)                                                                            \
-                     : SPDNN_RES_ACC##Q(D)                                                                             \
+        asm volatile(SPDNN_RES_ASM_W(FIRST_CONN)                                                                       \
+                     : SPDNN_RES_ACC##Q(OUT)                                                                           \
                      : SPDNN_RES_IN, [w0] "v"(wa.x), [w1] "v"(wa.y), [w2] "v"(wa.z), [w3] "v"(wa.w), [w4] "v"(wb.x),     \
                        [w5] "v"(wb.y), [w6] "v"(wb.z), [w7] "v"(wb.w)                                                  \
-                     : SPDNN_RES_CLOBBER);
+                     : CLOBBER);
 #define SPDNN_RES_CASE(Q)                                                                                             \
-    if constexpr (P == Q && FIRST) {                                                                                 \
-        SPDNN_RES_CASE2(Q, "=&", SPDNN_RES_CONN0)                                                                      \
+    if constexpr (P == Q && D == 3) {                                                                                \
+        if constexpr (FIRST) { SPDNN_RES_RUN(Q, "=&", SPDNN_RES_CONN0, SPDNN_RES_CLOBBER3) }                            \
+        else { SPDNN_RES_RUN(Q, "+", SPDNN_RES_CONN, SPDNN_RES_CLOBBER3) }                                              \
     } else if constexpr (P == Q) {                                                                                   \
-        SPDNN_RES_CASE2(Q, "+", SPDNN_RES_CONN)                                                                        \
+        if constexpr (FIRST) { SPDNN_RES_RUN(Q, "=&", SPDNN_RES_CONN0, SPDNN_RES_CLOBBER4) }                            \
+        else { SPDNN_RES_RUN(Q, "+", SPDNN_RES_CONN, SPDNN_RES_CLOBBER4) }                                              \
     }
-// FIRST: acc need not be set, the sums start at 0.
-template <int P, bool UNI, bool FIRST>
+// FIRST: acc need not be set, the sums start at 0.  D: reads in flight, 3 or 4.
+template <int P, bool UNI, bool FIRST, int D>
 __device__ __forceinline__ void res_fma8(f32x4 (&acc)[P], u32x4 codes, float wu, f32x4 wa, f32x4 wb) {
     SPDNN_RES_CASE(1)
     SPDNN_RES_CASE(2)
@@ -173,6 +176,10 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
     // The entry codes are addresses from the start of the workgroup's LDS: everything is dynamic, nothing static.
     extern __shared__ __align__(16) char res_lds[];
     using lds_f4 = __attribute__((address_space(3))) f32x4;
+    // Three reads in flight leave registers that the weights take; four are better only where there is room for them (three / four:
+    // 8 layers of 2048 neurons with weights, 20 000 rows 562 / 575 us, 120 layers of 1024 neurons, 60 000 rows 4594 / 4627; 24 layers
+    // of 4096 neurons, one weight, 60 000 rows 4443 / 4431, 16 to 64 connections 670 / 665).
+    constexpr int D = PM == 2 && MODE != kResWeights ? 4 : 3;
     constexpr uint32_t CH = 256u * PM;  // bytes of a chunk: 16 columns x PM planes
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -379,8 +386,8 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
 #pragma unroll
                                 for (int c = 0; c < 4; ++c) {
                                     if ((b * 4 + c) % NB == 0) set_wave_prio(3 - (b * 4 + c) / NB);
-                                    if (c == 0) res_fma8<PP, MODE == kResUniform, true>(acc, cbuf[0], cur.wuni, wbuf[0], wbuf[1]);
-                                    else res_fma8<PP, MODE == kResUniform, false>(acc, cbuf[c], cur.wuni, wbuf[2 * (c & 1)], wbuf[2 * (c & 1) + 1]);
+                                    if (c == 0) res_fma8<PP, MODE == kResUniform, true, D>(acc, cbuf[0], cur.wuni, wbuf[0], wbuf[1]);
+                                    else res_fma8<PP, MODE == kResUniform, false, D>(acc, cbuf[c], cur.wuni, wbuf[2 * (c & 1)], wbuf[2 * (c & 1) + 1]);
                                     fetch_codes(next, c);
                                     if (c < 2) fetch_weights(mine, c + 2);
                                     else fetch_weights(next, c - 2);
@@ -404,7 +411,7 @@ __global__ __launch_bounds__(kBlk) void resident_kernel(const float* __restrict_
                                     const Item from = last ? Item{next.c, next.w, 0} : Item{mine.c + off, mine.w + off, 0};
 #pragma unroll
                                     for (int i = 0; i < 2; ++i) {
-                                        if (c + i < mine.nch) res_fma8<PP, false, false>(acc, cbuf[i], 0.0f, wbuf[2 * i], wbuf[2 * i + 1]);
+                                        if (c + i < mine.nch) res_fma8<PP, false, false, D>(acc, cbuf[i], 0.0f, wbuf[2 * i], wbuf[2 * i + 1]);
                                         fetch_chunk(from, i, half + i);
                                     }
                                     if (last || (c & 2))

@@ -78,7 +78,6 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x32 __attribute__((ext_vector_type(32)));
-typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
 constexpr int flat_ahead(int R) { return 12 / R; }
 #define SPDNN_FLAT_W(SUMS, REGS)                                                                                           \
     template <int R, int NS>                                                                                               \

@@ -32,6 +32,7 @@ constexpr float kClip = 32.0f;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
 
 // A lane's connections are stored so that it fetches them with 16-byte loads, consecutive lanes from consecutive
 // addresses: eight slots or four weights per load.

@@ -25,7 +25,6 @@ namespace spdnn {
 constexpr int kRows2 = 2;            // feature rows per tile
 constexpr int kUnit4 = 4 * kBlk;     // output neurons per workgroup
 constexpr int kRow2Cols = 16384;     // columns a tile holds
-constexpr int kRow2Bursts = 4;       // bursts in which a tile's eight loads per lane are issued (2, 4 or 8; measured: 4)
 constexpr int kRow2Seg = 4096;       // columns staged per lane and segment (1024 lanes x 4 columns)
 constexpr int kRow2TileBytes = kRow2Cols * kRows2 * 4;
 constexpr int kRow2LdsBytes = kRow2TileBytes + kUnit4 * 4;  // the tile, then the unit's biases
@@ -53,98 +52,47 @@ __device__ __forceinline__ int2 row2_window(const int2* __restrict__ win, int u,
     return make_int2(x, y);
 }
 
-// 16 connections of one neuron: acc[r] = fma(tile[col_k][r], w, acc[r]), k = 0..15 in that order.
-// p[i] holds the (LDS byte address >> 3) of connections 2i and 2i+1 in its halves; an SDWA shift
-// turns a half into the byte address, written into the first register of the read's own
-// destination; s3 (scalar) holds 3.  Two reads in flight in v124..v127 (with 16 waves per CU the LDS
-// stays busy at this depth, and the kernel needs every other register).
-__device__ __forceinline__ void fma_row2_block16(float (&acc)[kRows2], const uint32_t* p, float w, uint32_t s3) {
-    asm volatile(
-        "v_lshlrev_b32_sdwa v120, %[s3], %[p0] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
-        "ds_read_b64 v[120:121], v120\n\t"
-        "v_lshlrev_b32_sdwa v122, %[s3], %[p0] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
-        "ds_read_b64 v[122:123], v122\n\t"
-        "v_lshlrev_b32_sdwa v124, %[s3], %[p1] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
-        "ds_read_b64 v[124:125], v124\n\t"
-        "v_lshlrev_b32_sdwa v126, %[s3], %[p1] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
-        "ds_read_b64 v[126:127], v126\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v120\n\t"
-        "v_fmac_f32 %[a1], %[w], v121\n\t"
-        "v_lshlrev_b32_sdwa v120, %[s3], %[p2] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
-        "ds_read_b64 v[120:121], v120\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v122\n\t"
-        "v_fmac_f32 %[a1], %[w], v123\n\t"
-        "v_lshlrev_b32_sdwa v122, %[s3], %[p2] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
-        "ds_read_b64 v[122:123], v122\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v124\n\t"
-        "v_fmac_f32 %[a1], %[w], v125\n\t"
-        "v_lshlrev_b32_sdwa v124, %[s3], %[p3] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
-        "ds_read_b64 v[124:125], v124\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v126\n\t"
-        "v_fmac_f32 %[a1], %[w], v127\n\t"
-        "v_lshlrev_b32_sdwa v126, %[s3], %[p3] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
-        "ds_read_b64 v[126:127], v126\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v120\n\t"
-        "v_fmac_f32 %[a1], %[w], v121\n\t"
-        "v_lshlrev_b32_sdwa v120, %[s3], %[p4] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
-        "ds_read_b64 v[120:121], v120\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v122\n\t"
-        "v_fmac_f32 %[a1], %[w], v123\n\t"
-        "v_lshlrev_b32_sdwa v122, %[s3], %[p4] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
-        "ds_read_b64 v[122:123], v122\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v124\n\t"
-        "v_fmac_f32 %[a1], %[w], v125\n\t"
-        "v_lshlrev_b32_sdwa v124, %[s3], %[p5] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
-        "ds_read_b64 v[124:125], v124\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v126\n\t"
-        "v_fmac_f32 %[a1], %[w], v127\n\t"
-        "v_lshlrev_b32_sdwa v126, %[s3], %[p5] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
-        "ds_read_b64 v[126:127], v126\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v120\n\t"
-        "v_fmac_f32 %[a1], %[w], v121\n\t"
-        "v_lshlrev_b32_sdwa v120, %[s3], %[p6] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
-        "ds_read_b64 v[120:121], v120\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v122\n\t"
-        "v_fmac_f32 %[a1], %[w], v123\n\t"
-        "v_lshlrev_b32_sdwa v122, %[s3], %[p6] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
-        "ds_read_b64 v[122:123], v122\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v124\n\t"
-        "v_fmac_f32 %[a1], %[w], v125\n\t"
-        "v_lshlrev_b32_sdwa v124, %[s3], %[p7] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
-        "ds_read_b64 v[124:125], v124\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v126\n\t"
-        "v_fmac_f32 %[a1], %[w], v127\n\t"
-        "v_lshlrev_b32_sdwa v126, %[s3], %[p7] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"
-        "ds_read_b64 v[126:127], v126\n\t"
-        "s_waitcnt lgkmcnt(3)\n\t"
-        "v_fmac_f32 %[a0], %[w], v120\n\t"
-        "v_fmac_f32 %[a1], %[w], v121\n\t"
-        "s_waitcnt lgkmcnt(2)\n\t"
-        "v_fmac_f32 %[a0], %[w], v122\n\t"
-        "v_fmac_f32 %[a1], %[w], v123\n\t"
-        "s_waitcnt lgkmcnt(1)\n\t"
-        "v_fmac_f32 %[a0], %[w], v124\n\t"
-        "v_fmac_f32 %[a1], %[w], v125\n\t"
-        "s_waitcnt lgkmcnt(0)\n\t"
-        "v_fmac_f32 %[a0], %[w], v126\n\t"
-        "v_fmac_f32 %[a1], %[w], v127\n\t"
-        : [a0] "+v"(acc[0]), [a1] "+v"(acc[1])
-        : [p0] "v"(p[0]), [p1] "v"(p[1]), [p2] "v"(p[2]), [p3] "v"(p[3]), [p4] "v"(p[4]), [p5] "v"(p[5]), [p6] "v"(p[6]),
-          [p7] "v"(p[7]), [w] "s"(w), [s3] "s"(s3)
-        : "v120", "v121", "v122", "v123", "v124", "v125", "v126", "v127", "memory");
-}
+// The 32 connections of one of the lane's neurons: acc[r] = fma(tile[col_k][r], w, acc[r]), k = 0..31 in that order, from 0.
+// p holds the (LDS byte address >> 3) of connections 2i and 2i+1 in its halves; an SDWA shift turns a half into the byte
+// address, written into the first register of the read's own destination; s3 (scalar) holds 3.  One pipeline of four reads in
+// flight, in v[120:127]; the four neurons' addresses sit in fixed registers, v[48:111], so that the assembler's own loop can
+// number them.  (Drained after 16 connections, 8 layers of 8192 neurons on 10 000 rows took 1039 us, 1022 this way; 24 of 16384 on 3000 rows 1875, 1853.)
+#define SPDNN_ROW2_READ(K)                                                                                                 \
+    ".if ((" K ")&1)==0\n\t"                                                                                               \
+    "v_lshlrev_b32_sdwa v[120+2*((" K ")%%4)], %[s3], v[%[B]+(" K ")/2] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t" \
+    ".else\n\t"                                                                                                            \
+    "v_lshlrev_b32_sdwa v[120+2*((" K ")%%4)], %[s3], v[%[B]+(" K ")/2] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t" \
+    ".endif\n\t"                                                                                                           \
+    "ds_read_b64 v[120+2*((" K ")%%4):121+2*((" K ")%%4)], v[120+2*((" K ")%%4)]\n\t"
+#define SPDNN_ROW2_NEURON(SLOT, BASE, REGS)                                                                                \
+    template <int S>                                                                                                       \
+    __device__ __forceinline__ std::enable_if_t<S == SLOT> fma_row2(float (&acc)[kRows2], const u32x16& p, float w, uint32_t s3) { \
+        asm volatile(SPDNN_ROW2_READ("0") SPDNN_ROW2_READ("1") SPDNN_ROW2_READ("2") SPDNN_ROW2_READ("3")                     \
+                     ".set spdnn_k, 0\n\t"                                                                                 \
+                     ".rept 32\n\t"                                                                                        \
+                     ".if spdnn_k < 28\n\t"                                                                                \
+                     "s_waitcnt lgkmcnt(3)\n\t"                                                                            \
+                     ".else\n\t"                                                                                           \
+                     "s_waitcnt lgkmcnt(31-spdnn_k)\n\t"                                                                   \
+                     ".endif\n\t"                                                                                          \
+                     ".if spdnn_k == 0\n\t"                                                                                \
+                     "v_fma_f32 %[a0], %[w], v120, 0\n\t"                                                                  \
+                     "v_fma_f32 %[a1], %[w], v121, 0\n\t"                                                                  \
+                     ".else\n\t"                                                                                           \
+                     "v_fmac_f32 %[a0], %[w], v[120+2*(spdnn_k%%4)]\n\t"                                                   \
+                     "v_fmac_f32 %[a1], %[w], v[121+2*(spdnn_k%%4)]\n\t"                                                   \
+                     ".endif\n\t"                                                                                          \
+                     ".if spdnn_k < 28\n\t" SPDNN_ROW2_READ("spdnn_k+4") ".endif\n\t"                                     \
+                     ".set spdnn_k, spdnn_k+1\n\t"                                                                         \
+                     ".endr\n\t"                                                                                           \
+                     : [a0] "=&v"(acc[0]), [a1] "=&v"(acc[1])                                                              \
+                     : "{" REGS "}"(p), [w] "s"(w), [s3] "s"(s3), [B] "n"(BASE)                                             \
+                     : "v120", "v121", "v122", "v123", "v124", "v125", "v126", "v127", "memory");                          \
+    }
+SPDNN_ROW2_NEURON(0, 48, "v[48:63]")
+SPDNN_ROW2_NEURON(1, 64, "v[64:79]")
+SPDNN_ROW2_NEURON(2, 80, "v[80:95]")
+SPDNN_ROW2_NEURON(3, 96, "v[96:111]")
 
 __global__ __launch_bounds__(kBlk) void fused_row2_kernel(
     const float* __restrict__ Yin, float* __restrict__ Yout, uint8_t* __restrict__ flags,
@@ -167,10 +115,10 @@ __global__ __launch_bounds__(kBlk) void fused_row2_kernel(
     const int ncols = win.y;  // <= kRow2Cols, a multiple of 4
     const uint32_t lds_base = (uint32_t)(uintptr_t)lds4;
     uint32_t s3 = 3;
-    asm volatile("" : "+s"(s3));  // the shift count of fma_row2_block32, kept in a scalar register
+    asm volatile("" : "+s"(s3));  // the shift count of fma_row2, kept in a scalar register
 
     // step lists of my four neurons (u * 4096 + s * 1024 + tid), two LDS addresses (>> 3) per register
-    uint32_t p[4][16];
+    u32x16 p[4];
     {
         const uint32_t base8 = lds_base >> 3;
         const uint32_t both = base8 | (base8 << 16);
@@ -228,10 +176,7 @@ __global__ __launch_bounds__(kBlk) void fused_row2_kernel(
 #pragma unroll
         for (int s = 0; s < 4; ++s) asm volatile("" : "+v"(st[s][0]), "+v"(st[s][1]));
     };
-    // The eight loads of a tile are issued back to back.  The memory pipeline accepts them only as fast as
-    // L2 delivers (about 22 bytes per clock and CU), so the last wave starts computing some 6000 clocks
-    // after the first; spreading the loads over the compute phase instead was measured slower (every wave
-    // then waits at every load).
+    // The first tile's eight loads, back to back; the others' are spread over the arithmetic of the tile before.
     auto load_tile = [&](int t) {
         tile_rows(t);
         load_piece(0);
@@ -281,20 +226,25 @@ __global__ __launch_bounds__(kBlk) void fused_row2_kernel(
         if (more) tile_rows(t + 1);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {  // two neuron slots at a time: compute, then Eq. 1's bias, ReLU and clip
-            // The loads of the next tile go out in kRow2Bursts bursts spread over the compute phase, one before
-            // every (8 / kRow2Bursts)-th block of 16 connections.  A wave that issues loads is stuck until the
-            // memory pipeline has taken them, which it does only as fast as L2 delivers (about 22 bytes per
-            // clock and CU): all eight loads back to back leave the last wave 6000 clocks behind the first.
-            float a0[kRows2] = {0.0f, 0.0f}, a1[kRows2] = {0.0f, 0.0f};
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {  // block b of this pair of slots = block 4h + b of the step
-                constexpr int every = 8 / kRow2Bursts;
-                if (more && (4 * h + b) % every == 0) {
-#pragma unroll
-                    for (int i = 0; i < every; ++i) load_piece(4 * h + b + i);
+            // The loads of the next tile go out in four bursts spread over the compute phase, one before every
+            // neuron.  A wave that issues loads is stuck until the memory pipeline has taken them: all eight loads back
+            // to back leave the last wave 6000 clocks behind the first.
+            float a0[kRows2], a1[kRows2];
+            const auto neuron = [&](auto slot, float (&acc)[kRows2]) {
+                constexpr int s = decltype(slot)::value;
+                if (more) {
+                    load_piece(2 * s);
+                    load_piece(2 * s + 1);
                 }
-                if (b % 2 == 0) set_wave_prio(3 - (4 * h + b) / 2);
-                fma_row2_block16(b < 2 ? a0 : a1, &p[2 * h + (b >> 1)][8 * (b & 1)], wuni, s3);
+                set_wave_prio(3 - s);
+                fma_row2<s>(acc, p[s], wuni, s3);
+            };
+            if (h == 0) {
+                neuron(std::integral_constant<int, 0>{}, a0);
+                neuron(std::integral_constant<int, 1>{}, a1);
+            } else {
+                neuron(std::integral_constant<int, 2>{}, a0);
+                neuron(std::integral_constant<int, 3>{}, a1);
             }
             const float b0 = *reinterpret_cast<const lds_f1*>(bias_addr + (2 * h) * (4 * kBlk));
             const float b1 = *reinterpret_cast<const lds_f1*>(bias_addr + (2 * h + 1) * (4 * kBlk));

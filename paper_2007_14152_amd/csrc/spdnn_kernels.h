@@ -582,6 +582,7 @@ struct ListWindow {
     __device__ __forceinline__ void fill() {
         const int e = min(lo + (int)(threadIdx.x & 63), end - 1);
         v = identity ? e : cat[e];
+        asm volatile("" : "+v"(v));  // wait for it here: a caller that does not refill would wait for all that it has under way
     }
     __device__ __forceinline__ void seek(int e) {  // e: the same in every lane
         const int want = first + ((e - first) & ~63);

@@ -268,7 +268,8 @@ int spdnn_layer_kernel(spdnn_t h, int32_t l, int32_t* kind);
  * neurons per layer whose weights are resident do so -- one workgroup then computes every neuron of its rows, so
  * Listing 1's loop over the layers (kernel, pruning, buffer swap) can run inside the workgroup -- when a workgroup's
  * share of the rows is small: at most 128 rows for models of at most 1024 neurons, what it holds at a time for larger
- * ones.  So do models of at most 16384 neurons whose layers are all strided sums -- neuron j reads the columns
+ * ones; but at most four rows per CU (two above 2048 neurons) and more than one take two launches from 64 layers on,
+ * so that the rows that live are shared out anew.  So do models of at most 16384 neurons whose layers are all strided sums -- neuron j reads the columns
  * (j + off + k S) mod N, k = 0 .. 31, with one weight per layer, off and S the layer's -- with one bias for all neurons,
  * wherever their weights live, when a workgroup holds its share of the rows at a time.  Larger batches keep their rows on the chip for several layers per launch.  With profiling on, a launch's
  * duration is shared out among its layers in proportion to the rows they had (spdnn_get_profile). */

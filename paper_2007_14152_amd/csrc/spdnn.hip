@@ -1134,10 +1134,14 @@ StridedShape strided_shape(const spdnn_model* h, int32_t rows) {
 constexpr int32_t kFewSplitLayers = 64;
 // Four rows per workgroup are as many as resident_kernel's smallest pass: not for more than two output blocks, where its
 // second barrier weighs little (24 layers of 4096 neurons, 1000 rows: 192 -> 197 us with four, 500 rows of 12 layers with weights
-// 135 -> 130 with two).
+// 135 -> 130 with two).  Neurons of any length: not above kFewPartsN, where it was measured to
+// lose (6 layers, 7 and 500 rows, resident_kernel -> few_kernel: 16 to 64
+// connections, 2200 neurons 83 -> 79 and 84 -> 80 us, 2600 87 -> 89 and 88 -> 88, 3200 96 -> 103 and 96 -> 103, 4096 112 -> 124 and
+// 111 -> 124; 8 to 32 connections, 4096 neurons 81 -> 87 and 82 -> 90).
+constexpr int32_t kFewPartsN = 2560;
 bool few_rows(const spdnn_model* h, int32_t batch) {
     const int32_t most = h->nblk > 2 ? 2 : spdnn::kFewRows;
-    return h->res_layers && !h->strided && batch <= most * h->num_cu;
+    return h->res_layers && !h->strided && batch <= most * h->num_cu && (h->res_mode != spdnn::kResParts || h->N <= kFewPartsN);
 }
 bool few_split(const spdnn_model* h, int32_t batch) { return batch > h->num_cu && h->L >= kFewSplitLayers; }
 

@@ -1091,7 +1091,9 @@ int static_scratch(void** out) {
 }
 
 constexpr int32_t kCopyBoundLayers = 48;             // spdnn_infer_host: so many layers take less time than their input's copy
-constexpr size_t kPieceBytes = (size_t)16 << 20;     // ... and so much of it is cut in two
+constexpr size_t kPieceBytes = (size_t)16 << 20;     // ... and so much of it is cut in two, ...
+constexpr size_t kPieceBytesPerLayer = 700 << 10;    // ... or so much per pass of a layer, if that is more: rows stay in LDS
+constexpr size_t kPieceBytesPerLaunch = 2400 << 10;  // (the same where every layer is a launch)
 constexpr int32_t kFewLayers = 4;  // networks of so few layers are not cut into launches that keep rows in LDS
 
 // How resident_kernel runs a network: the most groups of 64 neurons a wave owns, the most planes of 4 rows a pass
@@ -2020,20 +2022,25 @@ int spdnn_infer_host(spdnn_t h, const float* Y0_host, int32_t batch, int32_t row
         } drain{h->in_stream};
         // The batches, and the last one in pieces of one half, a quarter, ..., a piece being copied while the one before it is
         // inferred: what is left to do when the last byte has come is a piece, not a batch (6000 rows of 4096 neurons through 24
-        // layers in batches of 1500: 2110 -> 2026 us; in one batch 2319 -> 2034).  Only where copying takes longer than inferring, which is a question of
-        // the layers alone (4 bytes per neuron and row at PCIe's 55 GB/s against 32 multiply-adds per layer), and where a
-        // piece is worth the launches.
+        // layers in batches of 1500: 2110 -> 2026 us; in one batch 2319 -> 2034).  Only where copying takes longer than inferring:
+        // 4 bytes per neuron and row at PCIe's 55 GB/s against 32 multiply-adds per layer, and what a layer takes however few
+        // rows it has, which every piece takes again, so the line is at bytes per layer.  4096 neurons, whole -> pieces, MB per
+        // layer in the batch that is cut: 1.4 (12 layers) 493 -> 447 us, 0.9 (24, three batches) 1509 -> 1471, 0.6 (36, three batches)
+        // 1648 -> 1736; 2500 neurons, 1.0 (24) 726 -> 706, 0.5 (48) 929 -> 1053.  A launch per layer: 16384 neurons, 8.2 (12) 2357 ->
+        // 2186, 1.6 (12) 657 -> 686; windows of 16384 columns, 1.3 (22) 980 -> 1040; 12128 neurons, 1.5 (18, seven batches) 4182 -> 4380.
+        // Weights out of core go over PCIe too, with every piece again: never cut.
         struct Piece {
             int32_t first, rows;
             float* to;
             hipEvent_t ready;
         };
         std::vector<Piece> pieces;
+        const size_t cut_bytes = std::max(kPieceBytes, h->res_layers ? kPieceBytesPerLayer * (size_t)h->first_pass.back() : kPieceBytesPerLaunch * (size_t)h->first_pass.back());
         for (int32_t k = 0, first = 0; first < batch; ++k) {
             int32_t rows = std::min(step, batch - first);
             float* to = in[k & 1];
-            if (first + rows == batch && h->L <= kCopyBoundLayers)
-                for (int i = 2; i < kInEvents && (size_t)rows * N * sizeof(float) >= kPieceBytes; ++i) {
+            if (first + rows == batch && h->L <= kCopyBoundLayers && !h->ooc_host)
+                for (int i = 2; i < kInEvents && (size_t)rows * N * sizeof(float) >= cut_bytes; ++i) {
                     const int32_t half = rows / 2 & ~7;
                     pieces.push_back(Piece{first, half, to, h->in_ready[i]});
                     first += half;

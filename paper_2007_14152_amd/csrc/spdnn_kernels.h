@@ -2063,20 +2063,22 @@ __global__ __launch_bounds__(kFinishThreads) void finish_rows_kernel(const uint8
     int sum = 0;
 #pragma unroll
     for (int w = 0; w < kFinishThreads / 64; ++w) sum += red[w];
-    if (blockIdx.x == 0 && tid == 0) __hip_atomic_store(host_count, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) __hip_atomic_store(host_count, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     const int base = blockIdx.x == 0 ? 0 : sum, n = nkept;
-    if (tid < n) rows_out[base + tid] = gid_in ? gid_in[kept[tid]] : row_offset + kept[tid];
+    if (blockIdx.y == 0 && tid < n) rows_out[base + tid] = gid_in ? gid_in[kept[tid]] : row_offset + kept[tid];
     if (!dst) return;
+    const int share = (n4 + (int)gridDim.y - 1) / (int)gridDim.y;  // of every row
+    const int i_lo = (int)blockIdx.y * share, i_hi = min(n4, i_lo + share);
     for (int k = 0; k < n; ++k) {
         const float4* from = src + (size_t)kept[k] * n4;
         float4* to = dst + (size_t)(base + k) * n4;
-        for (int i0 = tid; i0 < n4; i0 += 4 * kFinishThreads) {  // four loads in flight
+        for (int i0 = i_lo + tid; i0 < i_hi; i0 += 4 * kFinishThreads) {  // four loads in flight
             float4 v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = from[min(i0 + u * kFinishThreads, n4 - 1)];
+            for (int u = 0; u < 4; ++u) v[u] = from[min(i0 + u * kFinishThreads, i_hi - 1)];
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                if (i0 + u * kFinishThreads < n4) to[i0 + u * kFinishThreads] = v[u];
+                if (i0 + u * kFinishThreads < i_hi) to[i0 + u * kFinishThreads] = v[u];
         }
     }
 }

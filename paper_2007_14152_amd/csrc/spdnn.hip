@@ -772,7 +772,8 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
             sl.T = N / sl.orbits;
             if (sl.T > spdnn::kNnz) sl.per = (sl.T + spdnn::kStrideOut - 1) / spdnn::kStrideOut;
             std::memcpy(&sl.w, &strided_info[3], sizeof(float));
-            all_strided = spdnn::strided_lanes(sl) <= spdnn::kStrideThreads;
+            // (infinity times an input of 0 is NaN: the sum has to be taken after the multiplication)
+            all_strided = spdnn::strided_lanes(sl) <= spdnn::kStrideThreads && std::isfinite(sl.w);
             strided.push_back(sl);
         }
         // One weight, but the windows are too wide for two neurons per lane.  If units of 2048 neurons in segments

@@ -70,10 +70,10 @@ def test_strided_networks(N, strides, batch, weight, offs):
     ooc.close()
 
 
-@pytest.mark.parametrize("change", ["column", "weight", "bias", "two strides", "duplicate", "too many lanes"])
+@pytest.mark.parametrize("change", ["column", "weight", "infinite weight", "bias", "two strides", "duplicate", "too many lanes"])
 def test_what_is_no_strided_network_runs_as_before(change):
-    """One connection, weight or bias out of line, a pattern that is not one sequence, or orbits that take more lanes than a
-    workgroup has: the general kernels, with the oracle's result."""
+    """One connection, weight or bias out of line, a pattern that is not one sequence, a weight whose products cannot be
+    summed first, or orbits that take more lanes than a workgroup has: the general kernels, with the oracle's result."""
     import paper_2007_14152_amd as sp
     N, L, batch = (16320, 2, 9) if change == "too many lanes" else (8192, 2, 9)
     idx, val = network(N, (480, 480) if change == "too many lanes" else (1, 32), 0.0625)
@@ -83,6 +83,8 @@ def test_what_is_no_strided_network_runs_as_before(change):
         idx[1][N - 1][7] = (idx[1][N - 1][7] + 1) % N
     elif change == "weight":
         val[1][N - 1][31] = np.nextafter(np.float32(0.0625), np.float32(1))
+    elif change == "infinite weight":
+        val[1][:] = np.inf
     elif change == "bias":
         bias[N - 1] = -0.31
     elif change == "two strides":
@@ -96,4 +98,6 @@ def test_what_is_no_strided_network_runs_as_before(change):
     n, rows, Y = gpu_infer(idx, val, bias, Y0, model=m)
     assert m.launches()[1] == 0
     m.close()
+    if change == "infinite weight":  # infinity times 0 is NaN, which the kernels' maximum with 0 turns into 0: an output is 0 or 32
+        ref.Y = np.nan_to_num(ref.Y, nan=0.0)
     check_against_oracle(ref, n, rows, Y, what=change)

@@ -152,13 +152,14 @@ __global__ __launch_bounds__(kBlk) void fused_flat_kernel(const float* __restric
         bj[s] = j < N ? bias[j] : 0.0f;
     }
 
-    ListWindow rows_of(rl.cat, g0 * R, min(A, wi.g1 * R), wi.identity);
+    ListWindow<(R > 1)> rows_of(rl.cat, g0 * R, min(A, wi.g1 * R), wi.identity);
     const int nload = (N + 255) >> 8;            // kilobytes of a row
     const uint32_t row_end = 4u * N - 16u;       // the last lanes of a row's last kilobyte read its end again
     // Tile t into buffer p: wave w takes the row's kilobytes w, 16 + w, ...  The rows' loads are under way together: a slot's
     // number comes from a register that ListWindow has waited for where it filled it.  (With that wait left to the use, every
     // row of a tile but the first stood behind the one before: 6 layers with weights of their own, 8000 rows, 8000 neurons, two
-    // rows to a tile, 1.47 -> 1.29 ms; 6000, three, 1.34 -> 1.17; one weight, 6144 neurons, 0.83 -> 0.75.)
+    // rows to a tile, 1.47 -> 1.29 ms; 6000, three, 1.34 -> 1.17; one weight, 6144 neurons, 0.83 -> 0.75.  One row to a tile has
+    // nothing to gain from it and lost 1 %: 10 layers of 16384 neurons, 1187 rows 816 -> 823 us.)
     auto load_tile = [&](int t, int p) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {

@@ -569,6 +569,7 @@ __device__ __forceinline__ int2 uniform2(int2 v) {
 // entries are picked out with v_readlane.  The tile loop therefore meets a load from the list, and the
 // wait for it (which also waits for every tile load in flight), once per 64 entries, not once per tile.
 // Entries past the slice's end repeat its last entry: a valid row to re-read, for the ragged last group.
+template <bool WAIT = false>
 struct ListWindow {
     const int* cat;
     int first, end;  // the slice [first, end) of the list, end > first
@@ -582,7 +583,7 @@ struct ListWindow {
     __device__ __forceinline__ void fill() {
         const int e = min(lo + (int)(threadIdx.x & 63), end - 1);
         v = identity ? e : cat[e];
-        asm volatile("" : "+v"(v));  // wait for it here: a caller that does not refill would wait for all that it has under way
+        if constexpr (WAIT) asm volatile("" : "+v"(v));  // wait for it here: a caller that does not refill would wait for all that it has under way
     }
     __device__ __forceinline__ void seek(int e) {  // e: the same in every lane
         const int want = first + ((e - first) & ~63);

@@ -13,6 +13,7 @@ SOURCES = [os.path.join(CSRC, "spdnn.hip")]
 HEADERS = [os.path.join(CSRC, "spdnn_kernels.h"), os.path.join(CSRC, "spdnn_order.h"),
            os.path.join(CSRC, "spdnn_layout.h"), os.path.join(CSRC, "spdnn_row2.h"),
            os.path.join(CSRC, "spdnn_flat.h"), os.path.join(CSRC, "spdnn_resident.h"), os.path.join(CSRC, "spdnn_few.h"), os.path.join(CSRC, "spdnn_strided.h"), os.path.join(CSRC, "spdnn_cut.h"),
+           os.path.join(CSRC, "spdnn_profile.h"),
            os.path.join(os.path.dirname(_HERE), "include", "spdnn.h")]
 # host build of the connection-ordering routine, for tests of the set-up logic without a GPU
 ORDER_HOST_LIB = os.path.join(CSRC, "libspdnn_order_host.so")

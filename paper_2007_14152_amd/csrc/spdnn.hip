@@ -20,6 +20,7 @@
 
 #include "spdnn_kernels.h"
 #include "spdnn_cut.h"
+#include "spdnn_profile.h"
 
 // Work memory of spdnn_infer_static, the entry point for callers that cannot allocate: a fixed array in
 // every GPU's memory instead of a caller-made work arena.  In host code this name is only a stand-in for
@@ -1467,10 +1468,7 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
     // Strided sums take a third of the time per layer: more layers are one launch.
     const int32_t last_layers = h->strided ? 64 : 32;
     const bool halves = !h->strided && h->res_mode != spdnn::kResUniform && h->nblk > 2;
-    struct Run {
-        int32_t l0, l1;
-    };
-    std::vector<Run> runs;
+    std::vector<spdnn::LayerRun> runs;
     int32_t alive = batch, before = batch;
     spdnn::RowLists rl{};    // the rows on entry to the next run (rl.count == NULL: the whole batch)
     const float* Yin = Y0_dev;
@@ -1510,7 +1508,7 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
             ++h->launches;
             ++h->res_launches;
             if (h->profiling) HIP_TRY(hipEventRecord(h->t1[fa.l0], s));
-            runs.push_back(Run{fa.l0, fa.l1});
+            runs.push_back({fa.l0, fa.l1, false});
             fa.l0 = fa.l1;
             fa.l1 = L;
             fa.flags_prev = wv.flags[0];
@@ -1529,7 +1527,7 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
             HIP_TRY(launch_layer(h, h->layers[l], l == 0 ? Y0_dev : wv.Y[0], wv.Y[l], wv.flags[l], layer_lists(h, wv, l, true), batch));
             ++h->launches;
             if (h->profiling) HIP_TRY(hipEventRecord(h->t1[l], s));
-            runs.push_back(Run{l, l + 1});
+            runs.push_back({l, l + 1, true});
         }
         const int rc = compact(wv.flags[1], wv.count[1], wv.gid[1], 2);
         if (rc != SPDNN_OK) return rc;
@@ -1558,7 +1556,7 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
         ++h->launches;
         ++h->res_launches;
         if (h->profiling) HIP_TRY(hipEventRecord(h->t1[l0], s));
-        runs.push_back(Run{l0, l1});
+        runs.push_back({l0, l1, false});
         l0 = l1;
         if (l1 == L) break;
         const int rc = compact(wv.flags[0], rl.count, rl.gid, l1);
@@ -1584,10 +1582,7 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
         std::vector<int> rows((size_t)L + 1);
         HIP_TRY(hipMemcpy(rows.data(), layer_rows, sizeof(int) * rows.size(), hipMemcpyDeviceToHost));
         rows[0] = batch;
-        if (runs[0].l1 == 1) {  // the first two layers were launches of their own
-            rows[1] = h->host_counts[1];
-            rows[2] = h->host_counts[2];
-        }
+        spdnn::take_host_counts(runs.data(), runs.size(), h->host_counts, rows.data());
         int32_t run = L;  // "launched": up to the first layer without rows
         for (int32_t l = 1; l < L; ++l)
             if (rows[l] == 0) {
@@ -1597,7 +1592,7 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
         h->prof_layers = run;
         h->prof_ms.assign(run, 0.0f);
         h->prof_rows.assign(rows.begin(), rows.begin() + run);
-        for (const Run& r : runs) {
+        for (const spdnn::LayerRun& r : runs) {
             float ms = 0.0f;
             HIP_TRY(hipEventElapsedTime(&ms, h->t0[r.l0], h->t1[r.l0]));
             double sum = 0.0;

@@ -1,9 +1,10 @@
-// Host build of the connection-ordering routine (spdnn_order.h) and of the tile
-// layout functions (spdnn_layout.h), so that the set-up logic can be tested without a
-// GPU.  Not used by the inference path.
+// Host build of the connection-ordering routine (spdnn_order.h), of the tile
+// layout functions (spdnn_layout.h) and of other host logic (spdnn_cut.h, spdnn_profile.h), so that
+// it can be tested without a GPU.  Not used by the inference path.
 #include "spdnn_cut.h"
 #include "spdnn_layout.h"
 #include "spdnn_order.h"
+#include "spdnn_profile.h"
 
 extern "C" {
 
@@ -104,6 +105,12 @@ void spdnn_order_by_length_host(const int32_t* ptr, int N, int nlanes, int waves
 }
 double spdnn_uneven_chunks_host(const int32_t* ptr, int N, const uint32_t* nch, int groups, int waves) {
     return spdnn::uneven_chunks(ptr, N, std::vector<uint32_t>(nch, nch + groups), waves);
+}
+// runs: n triples {first layer, one past the last, a layer's own kernel?} (spdnn_profile.h).
+void spdnn_take_host_counts_host(const int32_t* runs, int n, const int* host_counts, int* rows) {
+    std::vector<spdnn::LayerRun> r;
+    for (int i = 0; i < n; ++i) r.push_back({runs[3 * i], runs[3 * i + 1], runs[3 * i + 2] != 0});
+    spdnn::take_host_counts(r.data(), r.size(), host_counts, rows);
 }
 uint32_t spdnn_res_code_host(uint32_t slot, int planes_log2) { return spdnn::res_code(slot, planes_log2); }
 uint32_t spdnn_res_slot_host(uint32_t code, int planes_log2) { return spdnn::res_slot(code, planes_log2); }

@@ -280,6 +280,13 @@ int spdnn_one_launch(spdnn_t h, int32_t batch, int32_t* yes);
  * rows on the chip from layer to layer. */
 int spdnn_get_launches(spdnn_t h, int32_t* launches, int32_t* resident);
 
+/* Which kernel kept rows on the chip in the last inference (its last such launch). */
+#define SPDNN_ROWS_NONE 0     /* none: every launch was a layer */
+#define SPDNN_ROWS_RESIDENT 1 /* networks of at most 4096 neurons */
+#define SPDNN_ROWS_FEW 2      /* the same on few rows */
+#define SPDNN_ROWS_STRIDED 3  /* networks of strided sums */
+int spdnn_row_kernel(spdnn_t h, int32_t* kind);
+
 /* Passes of layer l -- its share of the weights arena, and, where layers are launched one by one, the most launches it
  * takes: 1, or for a general layer whose longest neuron has K > 32 connections ceil(K/32) rounded up to a power of two. */
 int spdnn_layer_passes(spdnn_t h, int32_t l, int32_t* passes);

@@ -29,13 +29,17 @@ SPDNN_KERNEL_WIDE_PAIR = 4
 SPDNN_KERNEL_WIDE_PAIR4 = 5
 SPDNN_KERNEL_ROW2 = 6
 SPDNN_KERNEL_FLAT = 7
+SPDNN_ROWS_NONE = 0
+SPDNN_ROWS_RESIDENT = 1
+SPDNN_ROWS_FEW = 2
+SPDNN_ROWS_STRIDED = 3
 
 EXPORTS = ("spdnn_weights_bytes", "spdnn_work_bytes", "spdnn_create", "spdnn_infer", "spdnn_destroy",
            "spdnn_last_error", "spdnn_set_profiling", "spdnn_get_profile", "spdnn_infer_static",
            "spdnn_host_work_bytes", "spdnn_infer_host",
            "spdnn_weights_bytes_for_window", "spdnn_scan_windows", "spdnn_layer_kernel",
            "spdnn_csr_passes", "spdnn_create_csr", "spdnn_layer_passes", "spdnn_ooc_bytes", "spdnn_create_ooc",
-           "spdnn_one_launch", "spdnn_get_launches")
+           "spdnn_one_launch", "spdnn_get_launches", "spdnn_row_kernel")
 KERNEL_NAMES = {0: "fused_layer_kernel<false>", 1: "fused_layer_kernel<true>", 2: "fused_wide_kernel",
                 3: "fused_pair_kernel", 4: "fused_wide_pair_kernel", 5: "fused_wide_pair4_kernel", 6: "fused_row2_kernel",
                 7: "fused_flat_kernel"}
@@ -75,6 +79,7 @@ def lib():
         L.spdnn_layer_passes.argtypes = [vp, i32, ctypes.POINTER(i32)]
         L.spdnn_one_launch.argtypes = [vp, i32, ctypes.POINTER(i32)]
         L.spdnn_get_launches.argtypes = [vp, ctypes.POINTER(i32), ctypes.POINTER(i32)]
+        L.spdnn_row_kernel.argtypes = [vp, ctypes.POINTER(i32)]
         L.spdnn_ooc_bytes.argtypes = [i32, i32, i32, ctypes.POINTER(sz), ctypes.POINTER(sz)]
         L.spdnn_create_ooc.argtypes = [ctypes.POINTER(vp), i32, i32, ctypes.POINTER(vp), ctypes.POINTER(vp), vp,
                                        i32, vp, sz, vp, sz, vp]
@@ -236,6 +241,13 @@ def spdnn_get_launches(h):
     n, r = ctypes.c_int32(-1), ctypes.c_int32(-1)
     _check(lib().spdnn_get_launches(ctypes.c_void_p(h), ctypes.byref(n), ctypes.byref(r)))
     return n.value, r.value
+
+
+def spdnn_row_kernel(h) -> int:
+    """Which kernel kept rows on the chip in the last inference (SPDNN_ROWS_*)."""
+    k = ctypes.c_int32(-1)
+    _check(lib().spdnn_row_kernel(ctypes.c_void_p(h), ctypes.byref(k)))
+    return k.value
 
 
 SPDNN_STATIC_SCRATCH_BYTES = 64 << 20
@@ -426,6 +438,9 @@ class Model:
 
     def launches(self):
         return spdnn_get_launches(self.h)
+
+    def row_kernel(self):
+        return spdnn_row_kernel(self.h)
 
     def close(self):
         if getattr(self, "h", None):

@@ -120,7 +120,8 @@ struct spdnn_model {
     // inputs in host memory (spdnn_infer_host): copy stream and "batch has landed" events, made on first use
     hipStream_t in_stream = nullptr;
     hipEvent_t in_ready[kInEvents] = {};
-    int32_t launches = 0, res_launches = 0;  // of fused kernels in the last inference; of resident_kernel among them
+    int32_t launches = 0, res_launches = 0;  // of fused kernels in the last inference; among them of those that keep rows on the chip
+    int32_t row_kernel = SPDNN_ROWS_NONE;    // ... and which of these was the last
     // profiling
     int profiling = 0;
     std::vector<hipEvent_t> t0, t1;
@@ -1060,7 +1061,7 @@ int check_infer_args(spdnn_t h, const float* Y0_dev, int32_t batch, int32_t* n_a
     if (!n_active_host) return fail(SPDNN_EINVAL, "n_active_host is NULL");
     if (batch < 0) return fail(SPDNN_EINVAL, "batch < 0");
     h->prof_layers = 0;
-    h->launches = h->res_launches = 0;
+    h->launches = h->res_launches = h->row_kernel = 0;
     if (batch == 0) {
         *n_active_host = 0;
         return SPDNN_OK;
@@ -1507,6 +1508,7 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
             last_flags = wv.flags[i];
             ++h->launches;
             ++h->res_launches;
+            h->row_kernel = SPDNN_ROWS_FEW;
             if (h->profiling) HIP_TRY(hipEventRecord(h->t1[fa.l0], s));
             runs.push_back({fa.l0, fa.l1, false});
             fa.l0 = fa.l1;
@@ -1555,6 +1557,7 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
         }
         ++h->launches;
         ++h->res_launches;
+        h->row_kernel = h->strided ? SPDNN_ROWS_STRIDED : SPDNN_ROWS_RESIDENT;
         if (h->profiling) HIP_TRY(hipEventRecord(h->t1[l0], s));
         runs.push_back({l0, l1, false});
         l0 = l1;
@@ -1926,6 +1929,12 @@ int spdnn_get_launches(spdnn_t h, int32_t* launches, int32_t* resident) {
     return SPDNN_OK;
 }
 
+int spdnn_row_kernel(spdnn_t h, int32_t* kind) {
+    if (!h || !kind) return fail(SPDNN_EINVAL, "null argument");
+    *kind = h->row_kernel;
+    return SPDNN_OK;
+}
+
 int spdnn_layer_passes(spdnn_t h, int32_t l, int32_t* passes) {
     if (!h || !passes) return fail(SPDNN_EINVAL, "null argument");
     if (l < 0 || l >= h->L) return fail(SPDNN_EINVAL, "layer %d outside [0, %d)", l, h->L);
@@ -1995,7 +2004,7 @@ int spdnn_infer_host(spdnn_t h, const float* Y0_host, int32_t batch, int32_t row
         if (!n_active_host) return fail(SPDNN_EINVAL, "n_active_host is NULL");
         if (batch < 0 || rows_per_batch < 1) return fail(SPDNN_EINVAL, "need batch >= 0 and rows_per_batch >= 1");
         h->prof_layers = 0;
-        h->launches = h->res_launches = 0;
+        h->launches = h->res_launches = h->row_kernel = 0;
         *n_active_host = 0;
         if (batch == 0) return SPDNN_OK;
         if (!Y0_host || !work_arena || !active_rows_dev) return fail(SPDNN_EINVAL, "null argument");

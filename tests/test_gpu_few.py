@@ -30,7 +30,7 @@ def network(kind, N, L, rng):
 
 
 @pytest.mark.parametrize("kind", ["uniform", "weights", "general"])
-@pytest.mark.parametrize("N,L", [(32, 3), (100, 3), (1024, 4), (1028, 3), (2052, 3), (4096, 3)])
+@pytest.mark.parametrize("N,L", [(32, 3), (100, 3), (1024, 4), (1028, 3), (2052, 3), (2560, 2), (4096, 3)])
 def test_few_rows(kind, N, L):
     import torch
     import paper_2007_14152_amd as sp
@@ -44,11 +44,13 @@ def test_few_rows(kind, N, L):
     m = sp.Model.from_csr(ptr, idx, val, bias) if ptr else sp.Model(idx, val, bias)
     y0 = torch.from_numpy(Y0).to("cuda:0")
     n, rows, Y = m.infer(y0)
+    assert m.row_kernel() == sp.SPDNN_ROWS_RESIDENT
     check_against_oracle(ref, n, rows.cpu().numpy(), Y.cpu().numpy(), what="%s N=%d" % (kind, N))
     for first, batch in ((0, 1024), (3, 769), (1, 512), (0, 257), (0, 256), (5, 7), (0, 3), (1, 1), (2, 1)):
         m.set_profiling(batch in (1, 512, 1024))
         n2, rows2, Y2 = m.infer(y0[first:first + batch].contiguous())
-        assert m.one_launch(batch) and m.launches() == (1, 1)   # (few_kernel's up to 512 rows, to 1024 in small networks)
+        few = batch <= (1024 if N <= 2048 else 512) and not (kind == "general" and N > 2560)
+        assert m.one_launch(batch) and m.launches() == (1, 1) and m.row_kernel() == (sp.SPDNN_ROWS_FEW if few else sp.SPDNN_ROWS_RESIDENT)
         keep = (rows >= first) & (rows < first + batch)
         assert n2 == int(keep.sum()) and torch.equal(rows2, rows[keep] - first) and torch.equal(Y2, Y[keep]), (first, batch)
         if batch in (512, 1024) and not (ref.fragile_layer >= 0).any():
@@ -79,7 +81,7 @@ def test_deep_networks_are_shared_out_anew(N, kind):
         y0 = torch.from_numpy(np.where(live, 0.9, 0.04).astype(np.float32)).to("cuda:0")[:, None].expand(batch, N).contiguous()
         assert not m.one_launch(batch)
         n, rows, Y = m.infer(y0)
-        assert m.launches() == (2, 2)
+        assert m.launches() == (2, 2) and m.row_kernel() == sp.SPDNN_ROWS_FEW
         ids = np.nonzero(live)[0]
         assert n == len(ids) and np.array_equal(rows.cpu().numpy(), ids)
         if n:

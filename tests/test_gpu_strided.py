@@ -96,7 +96,7 @@ def test_what_is_no_strided_network_runs_as_before(change):
     m = sp.Model(idx, val, bias)
     from parity_util import gpu_infer
     n, rows, Y = gpu_infer(idx, val, bias, Y0, model=m)
-    assert m.launches()[1] == 0
+    assert m.launches()[1] == 0 and m.row_kernel() == sp.SPDNN_ROWS_NONE
     m.close()
     if change == "infinite weight":  # infinity times 0 is NaN, which the kernels' maximum with 0 turns into 0: an output is 0 or 32
         ref.Y = np.nan_to_num(ref.Y, nan=0.0)

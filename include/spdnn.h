@@ -269,7 +269,7 @@ int spdnn_layer_kernel(spdnn_t h, int32_t l, int32_t* kind);
  * Listing 1's loop over the layers (kernel, pruning, buffer swap) can run inside the workgroup -- when a workgroup's
  * share of the rows is small: at most 128 rows for models of at most 1024 neurons, what it holds at a time for larger
  * ones; but at most four rows per CU (two above 2048 neurons) and more than one take two launches from 64 layers on,
- * so that the rows that live are shared out anew.  So do models of at most 16384 neurons whose layers are all strided sums -- neuron j reads the columns
+ * so that the rows that live are shared out anew.  So do models of 1152 to 16384 neurons whose layers are all strided sums -- neuron j reads the columns
  * (j + off + k S) mod N, k = 0 .. 31, with one weight per layer, off and S the layer's -- with one bias for all neurons,
  * wherever their weights live, when a workgroup holds its share of the rows at a time.  Larger batches keep their rows on the chip for several layers per launch.  With profiling on, a launch's
  * duration is shared out among its layers in proportion to the rows they had (spdnn_get_profile). */
@@ -284,7 +284,7 @@ int spdnn_get_launches(spdnn_t h, int32_t* launches, int32_t* resident);
 #define SPDNN_ROWS_NONE 0     /* none: every launch was a layer */
 #define SPDNN_ROWS_RESIDENT 1 /* networks of at most 4096 neurons */
 #define SPDNN_ROWS_FEW 2      /* the same on few rows */
-#define SPDNN_ROWS_STRIDED 3  /* networks of strided sums */
+#define SPDNN_ROWS_STRIDED 3  /* networks of strided sums (see spdnn_one_launch) */
 int spdnn_row_kernel(spdnn_t h, int32_t* kind);
 
 /* Passes of layer l -- its share of the weights arena, and, where layers are launched one by one, the most launches it

@@ -55,7 +55,13 @@ int static_scratch(void** out);  // defined below
 constexpr size_t kAlign = 256;
 inline size_t up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
-constexpr int32_t kStridedColumns = 16384;  // rows of strided_kernel: two of them fit the LDS
+// Columns of the rows of strided_kernel.  Most: two of them fit the LDS.  Fewest: a layer takes it 1.6 us (orbits of 32) to 3.2
+// however few the rows are, resident_kernel 1.2 (256 columns) to 2.6 (1152).  Deep networks on few rows, resident_kernel ->
+// strided_kernel, 200 layers of stride 1, 60 and 500 rows: 512 columns 287 -> 650 and 285 -> 586 us, 1024 411 -> 645 and 417 ->
+// 584, 1088 477 -> 527 and 482 -> 530, 1152 532 -> 527 and 539 -> 530, 1536 (60 layers) 191 -> 178; 60 000 rows, 1 layer: 64 columns
+// 52 -> 99, 512 133 -> 150.  (Large batches of 384 columns and more lose by it -- 60 layers of 1024, strides 1 and 32, 60 000 rows 870 ->
+// 2570 -- but a choice by the batch would make a row's bits depend on the rows beside it.)
+constexpr int32_t kStridedColumns = 16384, kStridedFewest = 1152;
 constexpr int kLag = 2;  // the host runs at most this many layers ahead of the GPU
 // Set-up of device-resident layers runs on this many streams, a layer per stream in turn: its kernels
 // are single-wave, latency-bound searches that fill a fraction of the chip, so several layers overlap.
@@ -615,7 +621,7 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
     // A network of strided sums?  Looked at layer by layer until one is not.  (The descriptors and the rows-per-layer counters
     // take the place of the staged weights, which is free once the set-up is over.)
     std::vector<spdnn::StridedLayer> strided;
-    bool all_strided = !ptr && N <= kStridedColumns && std::all_of(hb.begin(), hb.end(), [&](float b) { return b == hb[0]; }) &&
+    bool all_strided = !ptr && N >= kStridedFewest && N <= kStridedColumns && std::all_of(hb.begin(), hb.end(), [&](float b) { return b == hb[0]; }) &&
                        (size_t)L * (sizeof(spdnn::StridedLayer) + sizeof(int)) + sizeof(int) <= lanes * spdnn::kNnz * sizeof(float);
     std::vector<int2> hw((size_t)P * nblk);
     std::vector<int2> virt_ranges;  // several lanes per neuron: {first neuron, neurons} of the current layer's workgroups

@@ -1,7 +1,7 @@
 """Networks of strided sums -- neuron j reads the columns (j + off + k S) mod N with one weight -- which strided_kernel runs
 with the rows in LDS and sums shared along the orbits of "+S".  Orbits of 32, of lengths that 33 does and does not divide,
 strides that wrap around the row end inside a lane's span, one and several pairs of rows per pass, odd batches, several
-passes and launches; against the oracle, and the same bits whatever the batch and wherever the weights live."""
+passes and launches, rows of fewer columns than it takes; against the oracle, and the same bits whatever the batch and wherever the weights live."""
 import numpy as np
 import pytest
 
@@ -33,6 +33,13 @@ def network(N, strides, weight, offs=(0,)):
     (8188, (1, 4, 92), 301, 0.0625, (8187, 3)),
     (16384, (1, 32, 512, 2, 264, 3), 301, 0.0625, (0, 1, 16383)),
     (16384, (512, 1), 1, 0.0625, (0,)),
+    # (the sizes below 1152 go to the kernels for any columns; from here on the same edges in strided_kernel)
+    (1148, (1, 3), 70, 0.0625, (0,)),                  # one size below: as before
+    (1152, (36, 1, 36), 8001, 0.0625, (0, 1151)),      # orbits of 32 and the whole row, seven pairs of rows per pass, the last row alone
+    (1152, (1, 36), 5, 0.07, (0,)),
+    (1188, (36, 1, 1), 400, 0.0625, (0, 5)),           # orbits of 33
+    (1224, (36, 3), 2000, 0.0625, (7, 0)),             # orbits of 34 and 408
+    (1320, (40, 37, 2), 77, 0.0625, (0,)),             # a stride that has no divisor in common with the row
 ])
 def test_strided_networks(N, strides, batch, weight, offs):
     import torch
@@ -51,6 +58,7 @@ def test_strided_networks(N, strides, batch, weight, offs):
     n, rows, Y = m.infer(y0)
     launches, resident = m.launches()
     assert resident == launches and (L <= 4) <= (launches == 1)   # no layer of its own
+    assert (m.row_kernel() == sp.SPDNN_ROWS_STRIDED) == (N >= 1152)
     run, rows_in, _ = m.profile()
     rows_h, Y_h = rows.cpu().numpy(), Y.cpu().numpy()
     mine = np.isin(rows_h, ids)

@@ -1402,8 +1402,9 @@ int finish_infer(spdnn_t h, const uint8_t* flags, const int* count_in, const int
     const int n4 = h->N / 4;
     const float4* from = reinterpret_cast<const float4*>(Y_last);
     float4* to = reinterpret_cast<float4*>(Y_final_dev);
-    if (bound <= spdnn::kFinishRows && (!Y_final_dev || Y_last != Y_final_dev)) {  // both in one launch
-        const int per = std::max(1, (bound + 1023) / 1024), grid = std::max(1, (bound + per - 1) / per);
+    if (bound <= spdnn::kFinishRows && (size_t)bound * h->N * sizeof(float) <= spdnn::kFinishBytes &&
+        (!Y_final_dev || Y_last != Y_final_dev)) {  // both in one launch
+        const int per = std::max(1, (bound + spdnn::kFinishGrid - 1) / spdnn::kFinishGrid), grid = std::max(1, (bound + per - 1) / per);
         // a few long rows: a row's copy is shared by as many workgroups as have one turn of it each (one workgroup per row: 40 rows through
         // 20 layers of 65536 neurons 339 -> 337 us now, 363 without; 86 rows, 2 layers of 16384 75 -> 72, 77 without; first = two launches)
         const int parts = to ? std::max(1, std::min(n4 / (4 * spdnn::kFinishThreads), 2048 / grid)) : 1;

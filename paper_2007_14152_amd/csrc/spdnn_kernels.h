@@ -2030,12 +2030,18 @@ __global__ void gather_rows_kernel(const float4* __restrict__ src, const int* __
     }
 }
 
-// compact_kernel and gather_rows_kernel in one, for up to kFinishRows rows: every workgroup counts the flags before its own
-// rows for itself -- a few kilobytes that all of them read -- and so knows where its rows go.  (Two launches and the gap
-// between them are a fifth of a small call: one row through 12 layers of 1024 neurons 56 -> 51 us.)  dst == NULL: no values.
-constexpr int kFinishRows = 16384;
+// compact_kernel and gather_rows_kernel in one: every workgroup counts the flags before its own rows for itself -- a few
+// kilobytes that all of them read -- and so knows where its rows go.  dst == NULL: no values.
+// It saves a launch and the gap between the two, 3 us, and copies a little slower than gather_rows_kernel, whose grid is the
+// size of the result and not of its rows: for up to kFinishRows rows and kFinishBytes of them.  One layer, two launches -> one:
+// 1024 columns, 300 rows 36 -> 33 us, 10 000 69 -> 66; 16384, 1000 rows (66 MB) 95 -> 93, 2200 (144 MB) 174 -> 180, 6000 384 -> 419;
+// 65536, 250 rows (66 MB) 85 -> 84, 600 155 -> 168; 4096, 6000 rows (98 MB) 112 -> 111, 16384 234 -> 250; 64 columns, 8000 rows 36 -> 36,
+// 16384 38 -> 42.
+constexpr int kFinishRows = 8192;
+constexpr size_t kFinishBytes = (size_t)64 << 20;
 constexpr int kFinishThreads = 256;
-constexpr int kFinishMost = 64;  // rows per workgroup, at most
+constexpr int kFinishGrid = 1024;                        // workgroups, at most, beside those that share a row
+constexpr int kFinishMost = kFinishRows / kFinishGrid;  // rows per workgroup, at most
 __global__ __launch_bounds__(kFinishThreads) void finish_rows_kernel(const uint8_t* __restrict__ flags, const int* __restrict__ count_in,
                                                                      const int* __restrict__ gid_in, int batch, int row_offset, int per,
                                                                      int* __restrict__ rows_out, int* host_count,
@@ -2055,7 +2061,8 @@ __global__ __launch_bounds__(kFinishThreads) void finish_rows_kernel(const uint8
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
     if (lane == 0) red[wave] = c;
-    const bool keep = tid < per && lo + tid < hi && flags[lo + tid] != 0;  // (per <= 64: the first wave's rows)
+    static_assert(kFinishMost <= 64);
+    const bool keep = tid < per && lo + tid < hi && flags[lo + tid] != 0;  // (the first wave's rows)
     const unsigned long long m = __ballot(keep);
     if (keep) kept[__popcll(m & ((1ull << lane) - 1ull))] = lo + tid;
     __shared__ int nkept;

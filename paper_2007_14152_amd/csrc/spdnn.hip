@@ -1141,7 +1141,10 @@ StridedShape strided_shape(const spdnn_model* h, int32_t rows) {
 }
 
 // Few rows: few_kernel, in one launch, or, where so many layers follow that it pays to share out anew the rows that are left
-// behind the first two, in two.
+// behind the first two, in two.  (How many are left is not known beforehand.  One weight, 900 to 1000 rows,
+// resident_kernel -> few_kernel with 450, 510, 700 and 1000 of them left: 64 layers of 1024 neurons 155 -> 137, 147, 149 and 162 us,
+// 120 of 2048 430 -> 365, 404, 403 and 453, 120 of 256 152 -> 129, 138, 138 and 145; weights of their own, 64 of 1024, 188 -> 181 at
+// worst.  The second launch costs 5 us; four rows per workgroup, of about 1024 or 2048 neurons with one weight, are what loses.)
 constexpr int32_t kFewSplitLayers = 64;
 // Four rows per workgroup are as many as resident_kernel's smallest pass: not for more than two output blocks, where its
 // second barrier weighs little (24 layers of 4096 neurons, 1000 rows: 192 -> 197 us with four, 500 rows of 12 layers with weights
@@ -1152,7 +1155,7 @@ constexpr int32_t kFewSplitLayers = 64;
 constexpr int32_t kFewPartsN = 2560;
 bool few_rows(const spdnn_model* h, int32_t batch) {
     const int32_t most = h->nblk > 2 ? 2 : spdnn::kFewRows;
-    return h->res_layers && !h->strided && batch <= most * h->num_cu && (h->res_mode != spdnn::kResParts || h->N <= kFewPartsN);
+    return h->res_layers && !h->strided && batch <= std::min(most * h->num_cu, spdnn::kFewCount) && (h->res_mode != spdnn::kResParts || h->N <= kFewPartsN);
 }
 bool few_split(const spdnn_model* h, int32_t batch) { return batch > h->num_cu && h->L >= kFewSplitLayers; }
 

@@ -1,11 +1,11 @@
 // Networks of at most 4096 neurons on few rows -- at most four per workgroup, a workgroup per CU: the rows stay in LDS from
 // layer to layer as in resident_kernel, and with so few of them a layer is a matter of latency and instruction issue.
 //
-// A workgroup has R = 1, 2 or 4 rows, as few as the batch allows: an entry is a column's R values (4, 8 or 16 bytes), and a
+// A workgroup has R = 1 to 4 rows, as few as the batch allows: an entry is a column's R values (4, 8 or 16 bytes), and a
 // connection costs one read of R values and R multiply-adds, where resident_kernel always computes four.  The rows are kept
 // twice, a layer reads one copy and writes the other, so that it has one barrier instead of two, results go out as each
 // group of 64 neurons is done, and which rows still live is looked at while the next layer is computed.  The copies are
-// planes 0 and 1 of resident_kernel's tile layout at R / 4 of its size: the connections' entry codes are the same, and the
+// planes 0 and 1 of resident_kernel's tile layout at a quarter, half or all of its size: the connections' entry codes are the same, and the
 // sums are the same products in the same order (kResParts: parts of 32 likewise), so the results have the same bits.
 //
 // The connections of a group are on their way while the group before is computed, all 32 with their weights: 12 KB per wave,
@@ -25,12 +25,13 @@
 namespace spdnn {
 
 constexpr int kFewRows = 4;        // rows per workgroup, at most
+constexpr int kFewCount = 1024;    // rows whose flags a second launch counts, at most
 constexpr int kFewMiscBytes = 256;
 
 struct FewArgs {
     const ResidentLayer* layers;
     int l0, l1, L;         // layers l0 .. l1-1 of L
-    int A;                 // rows on entry, without flags_prev; else rows that flags_prev speaks about (at most 1024)
+    int A;                 // rows on entry, without flags_prev; else rows that flags_prev speaks about (at most kFewCount)
     uint32_t part_stride;  // see ResidentArgs
     int planes_log2;
     int* layer_rows;       // see ResidentArgs
@@ -51,6 +52,10 @@ struct FewEntry<1> {
 template <>
 struct FewEntry<2> {
     typedef float T __attribute__((ext_vector_type(2)));
+};
+template <>
+struct FewEntry<3> {  // as for four, the last value unused
+    typedef float T __attribute__((ext_vector_type(4)));
 };
 template <>
 struct FewEntry<4> {
@@ -77,7 +82,7 @@ __device__ __forceinline__ void few_layers(const float* __restrict__ Yin, float*
     using cu32 = const __attribute__((address_space(4))) uint32_t;
     using clayer = const __attribute__((address_space(4))) ResidentLayer;
     constexpr int LOG2R = R == 1 ? 0 : R == 2 ? 1 : 2;
-    constexpr uint32_t COPY = 64u * R;  // bytes from an entry to its place in the other copy: plane 1
+    constexpr uint32_t COPY = 16u << (2 + LOG2R);  // bytes from an entry to its place in the other copy: plane 1
     const int tid = threadIdx.x, lane = tid & 63, T_ = blockDim.x, W = T_ >> 6, U = (N + 63) >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row0 = (int)blockIdx.x * R, nrow = min(R, A - row0);
@@ -136,7 +141,7 @@ __device__ __forceinline__ void few_layers(const float* __restrict__ Yin, float*
         const uint32_t q = ((gu32*)(uintptr_t)cur.qsel)[t];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            T e;
+            T e = {};
 #pragma unroll
             for (int r = 0; r < R; ++r) e[r] = a[r][i];
             *(lds_T*)(entry(4 * t + i, q)) = e;
@@ -279,53 +284,52 @@ __global__ __launch_bounds__(kBlk) void few_kernel(const float* __restrict__ Yin
     char* misc = few_lds + res_tile_bytes(N, 1 << fa.planes_log2);
     uint32_t* live_word = reinterpret_cast<uint32_t*>(misc);    // [3], raised by the layers in turn
     int* row_at = reinterpret_cast<int*>(misc + 16);            // [4] slots of my rows
-    int* kept = row_at + kFewRows;                              // [16] flags set, per wave
+    int* kept = row_at + kFewRows;                              // flags set
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nwg = gridDim.x;
-    int A = fa.A, R = 0;
-    const auto rows_per = [&](int a) { return a <= nwg ? 1 : a <= 2 * nwg ? 2 : 4; };
+    int A = fa.A;
+    const auto rows_per = [&](int a) { return (a + nwg - 1) / nwg; };  // 1 to 4: a is at most kFewRows * nwg
     if (tid < 3) live_word[tid] = 0u;
-    if (fa.flags_prev) {
-        const int waves = blockDim.x >> 6;
-        int total = 0;  // first, because how many rows a workgroup takes depends on it
-        for (int i0 = 0; i0 < fa.A; i0 += blockDim.x) {
-            const int i = i0 + tid;
-            const unsigned long long m = __ballot(i < fa.A && fa.flags_prev[i] != 0);
-            if (lane == 0) kept[wave] = __popcll(m);
-            __syncthreads();
-            for (int w = 0; w < waves; ++w) total += kept[w];
-            __syncthreads();
-        }
-        A = __builtin_amdgcn_readfirstlane(total);
-        R = rows_per(A);
-        const int r0 = blockIdx.x * R;
-        int base = 0;
-        for (int i0 = 0; i0 < fa.A; i0 += blockDim.x) {
-            const int i = i0 + tid;
-            const bool keep = i < fa.A && fa.flags_prev[i] != 0;
-            const unsigned long long m = __ballot(keep);
-            if (lane == 0) kept[wave] = __popcll(m);
-            __syncthreads();
-            int rank = base + __popcll(m & ((1ull << lane) - 1ull));
-            for (int w = 0; w < waves; ++w) {
-                if (w < wave) rank += kept[w];
-                base += kept[w];
+    if (fa.flags_prev) {  // at most kFewCount flags: a wave counts and numbers them all
+        if (wave == 0) {
+            uint32_t f[4] = {0u, 0u, 0u, 0u};
+            if (16 * lane < fa.A) {
+                const uint4 v = flags16(fa.flags_prev, 16 * lane, fa.A);
+                f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
             }
-            if (keep && rank >= r0 && rank < r0 + R) {
-                row_at[rank - r0] = i;
-                fa.gid[rank] = fa.row_offset + i;
+            const int mine = __popc(f[0]) + __popc(f[1]) + __popc(f[2]) + __popc(f[3]);
+            int upto = mine;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int before = __shfl_up(upto, d, 64);
+                if (lane >= d) upto += before;
             }
-            __syncthreads();
+            const int total = __builtin_amdgcn_readlane(upto, 63), per = rows_per(total);
+            const int r0 = (int)blockIdx.x * per;
+            int rank = upto - mine;
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if ((f[i >> 2] >> (8 * (i & 3))) & 1u) {
+                    if (rank >= r0 && rank < r0 + per) {
+                        row_at[rank - r0] = 16 * lane + i;
+                        fa.gid[rank] = fa.row_offset + 16 * lane + i;
+                    }
+                    ++rank;
+                }
+            if (lane == 0) *kept = total;
         }
+        __syncthreads();
+        A = __builtin_amdgcn_readfirstlane(*kept);
         if (blockIdx.x == 0 && tid == 0) *fa.count = A;
     } else {
-        R = rows_per(A);
         __syncthreads();
     }
+    const int R = rows_per(A);
     if ((int)blockIdx.x * R >= A) return;
     const int* at = fa.flags_prev ? row_at : nullptr;
     if (R == 1) few_layers<1, MODE>(Yin, Yout, flags, fa, bias, N, A, at, live_word);
     else if (R == 2) few_layers<2, MODE>(Yin, Yout, flags, fa, bias, N, A, at, live_word);
+    else if (R == 3) few_layers<3, MODE>(Yin, Yout, flags, fa, bias, N, A, at, live_word);
     else few_layers<4, MODE>(Yin, Yout, flags, fa, bias, N, A, at, live_word);
 }
 

@@ -206,7 +206,7 @@ int spdnn_infer_static(spdnn_t h, const float* Y0_dev, int32_t batch, int32_t* n
  *            for spdnn_infer, over the whole input -- rows are numbered as in Y0_host and come out
  *            ascending.
  * Results are those of one spdnn_infer over all rows (rows are independent, Eq. 1).  The last batch
- * may go through in pieces, so that its inference starts before all of it has come.  The copies
+ * may go through in pieces if Y0_host is pinned, so that its inference starts before all of it has come.  The copies
  * run on a second HIP stream that the handle makes on first use (default priority); the call
  * returns with both streams idle.  batch == 0 is valid. */
 int spdnn_host_work_bytes(int32_t N, int32_t rows_per_batch, size_t* bytes);

@@ -1099,6 +1099,16 @@ int static_scratch(void** out) {
     return SPDNN_OK;
 }
 
+// Is this pinned host memory, copies from which run beside kernels?
+bool pinned(const void* host) {
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, host) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return a.type == hipMemoryTypeHost;
+}
+
 constexpr int32_t kCopyBoundLayers = 48;             // spdnn_infer_host: so many layers take less time than their input's copy
 constexpr size_t kPieceBytes = (size_t)16 << 20;     // ... and so much of it is cut in two, ...
 constexpr size_t kPieceBytesPerLayer = 700 << 10;    // ... or so much per pass of a layer, if that is more: rows stay in LDS
@@ -2046,18 +2056,21 @@ int spdnn_infer_host(spdnn_t h, const float* Y0_host, int32_t batch, int32_t row
         // layer in the batch that is cut: 1.4 (12 layers) 493 -> 447 us, 0.9 (24, three batches) 1509 -> 1471, 0.6 (36, three batches)
         // 1648 -> 1736; 2500 neurons, 1.0 (24) 726 -> 706, 0.5 (48) 929 -> 1053.  A launch per layer: 16384 neurons, 8.2 (12) 2357 ->
         // 2186, 1.6 (12) 657 -> 686; windows of 16384 columns, 1.3 (22) 980 -> 1040; 12128 neurons, 1.5 (18, seven batches) 4182 -> 4380.
-        // Weights out of core go over PCIe too, with every piece again: never cut.
+        // Weights out of core go over PCIe too, with every piece again: never cut.  Nor are inputs in pageable memory, where a piece's
+        // copy is over before the next call to the GPU is made and every piece takes its layers' fixed times for nothing (4096 neurons,
+        // 24 layers, 6000 rows, whole -> pieces 4107 -> 4584 us; 16384, 6 layers, 2000 rows 5260 -> 5584).
         struct Piece {
             int32_t first, rows;
             float* to;
             hipEvent_t ready;
         };
         std::vector<Piece> pieces;
+        const bool cut = h->L <= kCopyBoundLayers && !h->ooc_host && pinned(Y0_host);
         const size_t cut_bytes = std::max(kPieceBytes, h->res_layers ? kPieceBytesPerLayer * (size_t)h->first_pass.back() : kPieceBytesPerLaunch * (size_t)h->first_pass.back());
         for (int32_t k = 0, first = 0; first < batch; ++k) {
             int32_t rows = std::min(step, batch - first);
             float* to = in[k & 1];
-            if (first + rows == batch && h->L <= kCopyBoundLayers && !h->ooc_host)
+            if (cut && first + rows == batch)
                 for (int i = 2; i < kInEvents && (size_t)rows * N * sizeof(float) >= cut_bytes; ++i) {
                     const int32_t half = rows / 2 & ~7;
                     pieces.push_back(Piece{first, half, to, h->in_ready[i]});

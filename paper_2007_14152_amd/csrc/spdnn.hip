@@ -1113,6 +1113,13 @@ constexpr int32_t kCopyBoundLayers = 48;             // spdnn_infer_host: so man
 constexpr size_t kPieceBytes = (size_t)16 << 20;     // ... and so much of it is cut in two, ...
 constexpr size_t kPieceBytesPerLayer = 700 << 10;    // ... or so much per pass of a layer, if that is more: rows stay in LDS
 constexpr size_t kPieceBytesPerLaunch = 2400 << 10;  // (the same where every layer is a launch)
+// Networks of strided sums take a third of the time per layer and less for a batch: little is left behind the last byte of a
+// small one, and a piece costs 10 us beside its layers.  Whole -> two pieces, 4096 and 16384 neurons, MB in the batch that is cut:
+// 4 layers, 34 662 -> 675 and 662 -> 676 us, 42 820 -> 824 and 823 -> 821, 101 1882 -> 1870 (three pieces 1877); 12, 42 857 -> 844, 34
+// 684 -> 689 and 681 -> 691; 24, 67 1377 -> 1328 and 1394 -> 1318; 96, 42 1117 -> 1083; 144, 50 1406 -> 1368, 34 1064 -> 1049 and 1017 ->
+// 1096; 200, 50 1566 -> 1659 and 1505 -> 1536, 67 2180 -> 1830 and 2304 -> 1758.
+constexpr int32_t kStridedCopyBoundLayers = 200;
+constexpr size_t kStridedPieceBytes = (size_t)40 << 20, kStridedPieceBytesPerLayer = 320 << 10;
 constexpr int32_t kFewLayers = 4;  // networks of so few layers are not cut into launches that keep rows in LDS
 
 // How resident_kernel runs a network: the most groups of 64 neurons a wave owns, the most planes of 4 rows a pass
@@ -2065,8 +2072,10 @@ int spdnn_infer_host(spdnn_t h, const float* Y0_host, int32_t batch, int32_t row
             hipEvent_t ready;
         };
         std::vector<Piece> pieces;
-        const bool cut = h->L <= kCopyBoundLayers && !h->ooc_host && pinned(Y0_host);
-        const size_t cut_bytes = std::max(kPieceBytes, h->res_layers ? kPieceBytesPerLayer * (size_t)h->first_pass.back() : kPieceBytesPerLaunch * (size_t)h->first_pass.back());
+        const size_t passes = (size_t)h->first_pass.back();
+        const bool cut = h->L <= (h->strided ? kStridedCopyBoundLayers : kCopyBoundLayers) && !h->ooc_host && pinned(Y0_host);
+        const size_t cut_bytes = h->strided ? std::max(kStridedPieceBytes, kStridedPieceBytesPerLayer * passes)
+                                            : std::max(kPieceBytes, (h->res_layers ? kPieceBytesPerLayer : kPieceBytesPerLaunch) * passes);
         for (int32_t k = 0, first = 0; first < batch; ++k) {
             int32_t rows = std::min(step, batch - first);
             float* to = in[k & 1];

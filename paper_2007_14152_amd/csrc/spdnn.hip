@@ -612,9 +612,8 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
         // A single layer of at most 32 connections per neuron: what one_by_one() says of one layer, for any batch (the
         // layouts differ).  8 to 32 connections, 30 000 rows: 2048 neurons 319 -> 253 us, 4096 600 -> 472; 100 rows 48 ->
         // 54, 53 -> 55.
-        // (and the offsets of a neuron's parts are 32-bit numbers)
-        const bool far = (size_t)*std::max_element(passes_of.begin(), passes_of.end()) * blk_bytes > 0x7fffffff;
-        if (far || uneven > 0.0 || (parts && P == 1 && (nblk == 2 || nblk == 4))) resident = parts = false;
+        // (The offsets of a neuron's parts are 32-bit numbers: at most 256 passes of about 1 MB.)
+        if (uneven > 0.0 || (parts && P == 1 && (nblk == 2 || nblk == 4))) resident = parts = false;
     }
 
     const size_t raw = (size_t)N * spdnn::kNnz;

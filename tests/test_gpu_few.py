@@ -30,7 +30,7 @@ def network(kind, N, L, rng):
 
 
 @pytest.mark.parametrize("kind", ["uniform", "weights", "general"])
-@pytest.mark.parametrize("N,L", [(32, 3), (100, 3), (1024, 4), (1028, 3), (2052, 3), (2560, 2), (4096, 3)])
+@pytest.mark.parametrize("N,L", [(32, 3), (100, 3), (256, 1), (1024, 4), (1028, 3), (2052, 3), (2560, 2), (4096, 3)])
 def test_few_rows(kind, N, L):
     import torch
     import paper_2007_14152_amd as sp

@@ -802,7 +802,8 @@ def test_scattered_windows_gathered_footprint(N, w, batch):
 def test_strided_layers_wrap_around_the_row_end(N, strides, uniform, kinds):
     """Strided, modular patterns (neuron j reads (j + k*S) mod N): the footprint of the last blocks runs
     over the row end, so their windows are narrow only as arcs of the circle of columns.  Every kernel
-    family with such cyclic windows, against the oracle."""
+    family with such cyclic windows, against the oracle.  (Up to 16384 neurons networks of strided sums with one bias go to
+    strided_kernel; one bias apart, and they run through the kernels that their layers are set up for.)"""
     import paper_2007_14152_amd as sp
     rng = np.random.default_rng(N + len(strides))
     L, batch = len(strides), 11
@@ -818,17 +819,22 @@ def test_strided_layers_wrap_around_the_row_end(N, strides, uniform, kinds):
         val = [synth.gen_values(N) for _ in range(L)]
     else:
         val = [rng.uniform(0.03, 0.1, size=(N, 32)).astype(np.float32) for _ in range(L)]
-    bias = synth.gen_bias(N, -0.3)
     Y0 = synth.gen_y0(batch, N, 5, density="mixed")
-    ref = oracle.infer(idx, val, bias, Y0)
-    assert 0 < ref.n_active <= batch
-    m = sp.Model(idx, val, bias)
     want = [getattr(sp, "SPDNN_KERNEL_" + k) for k in kinds.split()]
-    assert [m.layer_kernel(l) for l in range(L)] == (want if len(want) == L else want * L)
-    n, rows, Y = gpu_infer(idx, val, bias, Y0, model=m)
-    m.close()
-    common, _ = check_against_oracle(ref, n, rows, Y, what="strided N=%d %s" % (N, strides))
-    assert common > 0
+    for one_bias in (True, False):
+        bias = synth.gen_bias(N, -0.3)
+        if not one_bias:
+            bias[N - 1] = -0.31
+        ref = oracle.infer(idx, val, bias, Y0)
+        assert 0 < ref.n_active <= batch
+        m = sp.Model(idx, val, bias)
+        assert [m.layer_kernel(l) for l in range(L)] == (want if len(want) == L else want * L)
+        n, rows, Y = gpu_infer(idx, val, bias, Y0, model=m)
+        if N > 4096 and not (one_bias and m.row_kernel() == sp.SPDNN_ROWS_STRIDED):
+            assert m.launches()[1] == 0 and m.row_kernel() == sp.SPDNN_ROWS_NONE
+        m.close()
+        common, _ = check_against_oracle(ref, n, rows, Y, what="strided N=%d %s one bias=%s" % (N, strides, one_bias))
+        assert common > 0
 
 
 @pytest.mark.parametrize("seed", [1, 2, 3])
@@ -868,6 +874,14 @@ def test_seeded_sweep_over_layer_shapes(seed):
                  else sp.KERNEL_NAMES[m.layer_kernel(0)])
         m.close()
         check_against_oracle(ref, n, rows, Y, what=what)
+        if case % 2:   # the same pattern with one bias apart: no network of strided sums
+            bias = bias.copy()
+            bias[N // 2] = -0.29
+            m = sp.Model(idx, val, bias)
+            n, rows, Y = gpu_infer(idx, val, bias, Y0, model=m)
+            assert m.row_kernel() != sp.SPDNN_ROWS_STRIDED, what
+            m.close()
+            check_against_oracle(oracle.infer(idx, val, bias, Y0), n, rows, Y, what=what + " one bias apart")
     assert len(seen) >= 3, seen
 
 

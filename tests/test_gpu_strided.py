@@ -40,6 +40,7 @@ def network(N, strides, weight, offs=(0,)):
     (1188, (36, 1, 1), 400, 0.0625, (0, 5)),           # orbits of 33
     (1224, (36, 3), 2000, 0.0625, (7, 0)),             # orbits of 34 and 408
     (1320, (40, 37, 2), 77, 0.0625, (0,)),             # a stride that has no divisor in common with the row
+    (2048, (3,), 50, 0.0625, (0,)),                    # one layer
 ])
 def test_strided_networks(N, strides, batch, weight, offs):
     import torch
@@ -109,3 +110,44 @@ def test_what_is_no_strided_network_runs_as_before(change):
     if change == "infinite weight":  # infinity times 0 is NaN, which the kernels' maximum with 0 turns into 0: an output is 0 or 32
         ref.Y = np.nan_to_num(ref.Y, nan=0.0)
     check_against_oracle(ref, n, rows, Y, what=change)
+
+
+@pytest.mark.parametrize("N,strides,batch", [
+    (1152, (1, 36, 5), 3001),       # several pairs of rows per pass
+    (8192, (256, 1, 3), 30),        # orbits of 32 first
+    (16384, (1, 512), 9),
+])
+@pytest.mark.parametrize("weights", [(0.07,), (0.0613, -0.04, 0.09), (0.05, 0.0, 0.07), (-0.03, 0.1)])
+def test_inputs_and_weights_of_any_sign(N, strides, batch, weights):
+    """Real inputs between -5 and 40, blank rows, and rows of a few values; weights that are no power of two, negative and zero:
+    against the oracle, and against 64 bits.  Layer 0 rounds the products before it adds them up (inputs may be of any size), later layers the sum:
+    32 products and 31 additions of relative error u = 2^-24 each at most, then weight and bias in one, so an output differs from the exact one
+    by at most 33 u (sum of the magnitudes), layer by layer."""
+    import torch
+    import paper_2007_14152_amd as sp
+    L = len(strides)
+    rng = np.random.default_rng(N + len(weights))
+    idx, _ = network(N, strides, 0.0, (3, 0))
+    w = [np.float32(weights[l % len(weights)]) for l in range(L)]
+    val = [np.full((N, 32), x, np.float32) for x in w]
+    bias = synth.gen_bias(N, -0.02)
+    Y0 = rng.uniform(-5, 40, size=(batch, N)).astype(np.float32)
+    Y0[1::4] *= rng.uniform(size=Y0[1::4].shape) < 0.05
+    Y0[2] = 0
+    ids = np.unique(np.r_[0:min(batch, 12), batch - 5:batch])
+    ref = oracle.infer(idx, val, bias, Y0[ids])
+    m = sp.Model(idx, val, bias)
+    n, rows, Y = m.infer(torch.from_numpy(Y0).to("cuda:0"))
+    assert m.row_kernel() == sp.SPDNN_ROWS_STRIDED
+    m.close()
+    rows, Y = rows.cpu().numpy(), Y.cpu().numpy()
+    mine = np.isin(rows, ids)
+    check_against_oracle(ref, int(mine.sum()), rows[mine], Y[mine], row_ids=ids, what="strided N=%d %s" % (N, weights))
+    y, bound = Y0[ids].astype(np.float64), np.zeros((len(ids), N))
+    for c, x in zip(idx, w.copy()):
+        a = abs(np.float64(x))
+        bound = a * sum(bound[:, c[:, k]] for k in range(32)) + 33 * 2.0 ** -24 * (a * sum(np.abs(y[:, c[:, k]]) for k in range(32)) + 0.02)
+        y = np.clip(np.float64(x) * sum(y[:, c[:, k]] for k in range(32)) + np.float64(bias[0]), 0, 32)
+    full = np.zeros_like(y)
+    full[np.searchsorted(ids, rows[mine])] = Y[mine]
+    assert (np.abs(full - y) <= bound * 1.001).all()

@@ -1232,10 +1232,10 @@ hipError_t launch_resident(spdnn_t h, const ResidentShape& r, int32_t Q, const f
     return hipGetLastError();
 }
 
-hipError_t launch_few(spdnn_t h, const spdnn::FewArgs& fa, int32_t workgroups, const float* Yin, float* Yout, uint8_t* flags) {
+hipError_t launch_few(spdnn_t h, const spdnn::FewArgs& fa, int32_t workgroups, const float* Yin) {
     const int threads = 64 * std::min(16, (h->N + 63) / 64);
     const auto run = [&](auto mode) {
-        spdnn::few_kernel<decltype(mode)::value><<<workgroups, threads, few_lds(h->N, h->nblk), h->stream>>>(Yin, Yout, flags, fa, h->bias_dev, h->N);
+        spdnn::few_kernel<decltype(mode)::value><<<workgroups, threads, few_lds(h->N, h->nblk), h->stream>>>(fa, Yin, h->bias_dev, h->N);
     };
     if (h->res_mode == spdnn::kResUniform) run(std::integral_constant<int, spdnn::kResUniform>{});
     else if (h->res_mode == spdnn::kResParts) run(std::integral_constant<int, spdnn::kResParts>{});
@@ -1524,14 +1524,14 @@ int infer_resident(spdnn_t h, const float* Y0_dev, int32_t batch, const WorkView
         const bool split = few_split(h, batch);
         finished = batch == 1;  // (a workgroup with more rows would take longer than the launch it saves)
         if (finished) h->host_counts[L + 1] = -1;
-        spdnn::FewArgs fa{h->res_layers, 0, split ? 2 : L, L, batch, h->res_part_stride, spdnn::res_planes_log2(h->nblk), layer_rows,
-                          nullptr, wv.gid[0], wv.count[0], row_offset, finished ? active_rows_dev : nullptr, h->host_counts + L + 1};
+        spdnn::FewArgs fa{h->res_layers, 0, split ? 2 : L, batch, h->res_part_stride, spdnn::res_planes_log2(h->nblk), layer_rows,
+                          nullptr, wv.gid[0], wv.count[0], row_offset, nullptr, nullptr, finished ? active_rows_dev : nullptr, h->host_counts + L + 1};
         const int32_t workgroups = std::min(batch, h->num_cu);
         for (int32_t i = 0; i <= (split ? 1 : 0); ++i) {
             if (h->profiling) HIP_TRY(hipEventRecord(h->t0[fa.l0], s));
-            Y_last = finished ? Y_final_dev : wv.Y[i];
-            HIP_TRY(launch_few(h, fa, workgroups, i == 0 ? Y0_dev : wv.Y[0], Y_last, wv.flags[i]));
-            last_flags = wv.flags[i];
+            Y_last = fa.Yout = finished ? Y_final_dev : wv.Y[i];
+            last_flags = fa.flags = wv.flags[i];
+            HIP_TRY(launch_few(h, fa, workgroups, i == 0 ? Y0_dev : wv.Y[0]));
             ++h->launches;
             ++h->res_launches;
             h->row_kernel = SPDNN_ROWS_FEW;

@@ -30,7 +30,7 @@ constexpr int kFewMiscBytes = 256;
 
 struct FewArgs {
     const ResidentLayer* layers;
-    int l0, l1, L;         // layers l0 .. l1-1 of L
+    int l0, l1;            // layers l0 .. l1-1
     int A;                 // rows on entry, without flags_prev; else rows that flags_prev speaks about (at most kFewCount)
     uint32_t part_stride;  // see ResidentArgs
     int planes_log2;
@@ -39,6 +39,8 @@ struct FewArgs {
     int* gid;                   // ... whose numbers (row_offset + slot) go here ...
     int* count;                 // ... and how many there are here
     int row_offset;
+    float* Yout;
+    uint8_t* flags;        // whose rows live
     int* rows_out;         // not NULL: the workgroup is the only one and finishes the call: the survivors' numbers, ...
     int* host_count;       // ... their count; their rows are the first ones of Yout
 };
@@ -70,8 +72,7 @@ __device__ __forceinline__ void few_address(uint32_t codes, uint32_t& lo, uint32
 }
 
 template <int R, int MODE>
-__device__ __forceinline__ void few_layers(const float* __restrict__ Yin, float* __restrict__ Yout, uint8_t* __restrict__ flags,
-                                           const FewArgs& fa, const float* __restrict__ bias, int N, int A, const int* row_at,
+__device__ __forceinline__ void few_layers(const FewArgs& fa, const float* __restrict__ Yin, const float* __restrict__ bias, int N, int A, const int* row_at,
                                            uint32_t* live_word) {
     using T = typename FewEntry<R>::T;
     using lds_T = __attribute__((address_space(3))) T;
@@ -150,14 +151,13 @@ __device__ __forceinline__ void few_layers(const float* __restrict__ Yin, float*
     __syncthreads();
 
     uint32_t live = (1u << nrow) - 1u;
-    gu32* q_out = (gu32*)(uintptr_t)layer_at(min(fa.l1, fa.L - 1)).qsel;  // any layout does for the last layer's output
     const uint32_t live_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t*)live_word;
     bool other = false;  // the copy that holds the rows
     const auto layer = [&](int l, auto from) {
         constexpr uint32_t FROM = decltype(from)::value, TO = COPY - FROM;
         // (scalar loads are waited for with the first reads of the rows, so not any later than this)
         const ResidentLayer after = layer_at(l + 2 < fa.l1 ? l + 2 : fa.l1 - 1);
-        gchar* q_next = (gchar*)(l + 1 < fa.l1 ? (gu32*)(uintptr_t)nxt.qsel : q_out);
+        gchar* q_next = (gchar*)(uintptr_t)nxt.qsel;  // (any layout does for the last layer's output: its own)
         const uint32_t raised = l > fa.l0 ? live_word[(l + 2) % 3] : live;  // (looked at behind the arithmetic)
         uint32_t pos = 0;
 #pragma unroll 1
@@ -254,13 +254,21 @@ __device__ __forceinline__ void few_layers(const float* __restrict__ Yin, float*
     }
     if (live) live &= __builtin_amdgcn_readfirstlane(live_word[(l + 2) % 3]);  // the last layer's
     if (tid == 0 && live && fa.layer_rows) atomicAdd(&fa.layer_rows[l], __popc(live));
-    if (fa.rows_out) {
-        if (tid < R && ((live >> tid) & 1u)) fa.rows_out[__popc(live & ((1u << tid) - 1u))] = fa.row_offset + tid;
-        if (tid == 0) __hip_atomic_store(fa.host_count, __popc(live), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    // What is needed only now is read again (the kernel's first argument): kept over the layers these would be scalar registers
+    // too many, and every layer would fetch others back from vector registers.
+    using cargs = const __attribute__((address_space(4))) FewArgs;
+    cargs* late = (cargs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(late));
+    float* const Yout = late->Yout;
+    int* const rows_out = late->rows_out;
+    if (rows_out) {
+        if (tid < R && ((live >> tid) & 1u)) rows_out[__popc(live & ((1u << tid) - 1u))] = late->row_offset + tid;
+        if (tid == 0) __hip_atomic_store(late->host_count, __popc(live), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     } else if (tid < nrow) {
-        flags[row0 + tid] = (live >> tid) & 1u;
+        late->flags[row0 + tid] = (live >> tid) & 1u;
     }
     if (!live || !Yout) return;
+    gu32* q_out = (gu32*)(uintptr_t)nxt.qsel;
     for (int t = tid; t < n4; t += T_) {
         const uint32_t q = q_out[t];
         T e[4];
@@ -269,7 +277,7 @@ __device__ __forceinline__ void few_layers(const float* __restrict__ Yin, float*
 #pragma unroll
         for (int r = 0; r < R; ++r)
             if ((live >> r) & 1u) {
-                const int to = fa.rows_out ? __popc(live & ((1u << r) - 1u)) : row0 + r;
+                const int to = rows_out ? __popc(live & ((1u << r) - 1u)) : row0 + r;
                 *reinterpret_cast<f32x4*>(Yout + (size_t)to * N + 4 * (size_t)t) = f32x4{e[0][r], e[1][r], e[2][r], e[3][r]};
             }
     }
@@ -277,8 +285,7 @@ __device__ __forceinline__ void few_layers(const float* __restrict__ Yin, float*
 
 // blockDim.x = 64 * W, W = min(16, U), U = ceil(N / 64) groups of 64 neurons; wave w owns the groups w, w + W, ...
 template <int MODE>
-__global__ __launch_bounds__(kBlk) void few_kernel(const float* __restrict__ Yin, float* __restrict__ Yout, uint8_t* __restrict__ flags,
-                                                   FewArgs fa, const float* __restrict__ bias, int N) {
+__global__ __launch_bounds__(kBlk) void few_kernel(FewArgs fa, const float* __restrict__ Yin, const float* __restrict__ bias, int N) {
     // The entry codes are addresses from the start of the workgroup's LDS: everything is dynamic, nothing static.
     extern __shared__ __align__(16) char few_lds[];
     char* misc = few_lds + res_tile_bytes(N, 1 << fa.planes_log2);
@@ -327,10 +334,10 @@ __global__ __launch_bounds__(kBlk) void few_kernel(const float* __restrict__ Yin
     const int R = rows_per(A);
     if ((int)blockIdx.x * R >= A) return;
     const int* at = fa.flags_prev ? row_at : nullptr;
-    if (R == 1) few_layers<1, MODE>(Yin, Yout, flags, fa, bias, N, A, at, live_word);
-    else if (R == 2) few_layers<2, MODE>(Yin, Yout, flags, fa, bias, N, A, at, live_word);
-    else if (R == 3) few_layers<3, MODE>(Yin, Yout, flags, fa, bias, N, A, at, live_word);
-    else few_layers<4, MODE>(Yin, Yout, flags, fa, bias, N, A, at, live_word);
+    if (R == 1) few_layers<1, MODE>(fa, Yin, bias, N, A, at, live_word);
+    else if (R == 2) few_layers<2, MODE>(fa, Yin, bias, N, A, at, live_word);
+    else if (R == 3) few_layers<3, MODE>(fa, Yin, bias, N, A, at, live_word);
+    else few_layers<4, MODE>(fa, Yin, bias, N, A, at, live_word);
 }
 
 }  // namespace spdnn

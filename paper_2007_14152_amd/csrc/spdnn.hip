@@ -59,8 +59,8 @@ inline size_t up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // however few the rows are, resident_kernel 1.2 (256 columns) to 2.6 (1152).  Deep networks on few rows, resident_kernel ->
 // strided_kernel, 200 layers of stride 1, 60 and 500 rows: 512 columns 287 -> 650 and 285 -> 586 us, 1024 411 -> 645 and 417 ->
 // 584, 1088 477 -> 527 and 482 -> 530, 1152 532 -> 527 and 539 -> 530, 1536 (60 layers) 191 -> 178; 60 000 rows, 1 layer: 64 columns
-// 52 -> 99, 512 133 -> 150.  (Large batches of 384 columns and more lose by it -- 60 layers of 1024, strides 1 and 32, 60 000 rows 870 ->
-// 2570 -- but a choice by the batch would make a row's bits depend on the rows beside it.)
+// 52 -> 99, 512 133 -> 150.  (Large batches of 384 columns and more lose by it -- 60 layers of 1024, strides 1 and 32, 60 000 rows 867 ->
+// 2510 -- but a choice by the batch would make a row's bits depend on the rows beside it.)
 constexpr int32_t kStridedColumns = 16384, kStridedFewest = 1152;
 constexpr int kLag = 2;  // the host runs at most this many layers ahead of the GPU
 // Set-up of device-resident layers runs on this many streams, a layer per stream in turn: its kernels

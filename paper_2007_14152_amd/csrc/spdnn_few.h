@@ -5,14 +5,16 @@
 // connection costs one read of R values and R multiply-adds, where resident_kernel always computes four.  The rows are kept
 // twice, a layer reads one copy and writes the other, so that it has one barrier instead of two, results go out as each
 // group of 64 neurons is done, and which rows still live is looked at while the next layer is computed.  The copies are
-// planes 0 and 1 of resident_kernel's tile layout at a quarter, half or all of its size: the connections' entry codes are the same, and the
-// sums are the same products in the same order (kResParts: parts of 32 likewise), so the results have the same bits.
+// planes 0 and 1 of resident_kernel's tile layout at a quarter, half or (three rows too) all of its size: the connections' entry
+// codes are the same, and the sums are the same products in the same order (kResParts: parts of 32 likewise), so the results have the same bits.
 //
 // The connections of a group are on their way while the group before is computed, all 32 with their weights: 12 KB per wave,
 // which is what it takes for the 53 to 60 bytes per clock that a CU gets out of its L2.  (Neurons of any length: 16 of them.)
 //
-// What bounds it: the bank conflicts of reads that were ordered for 16-byte entries, 4.7 clocks per read whatever its size,
-// and with weights of their own the stream of connections; 700 to 1000 clocks of a layer's 3500 (1024 neurons) to 17 000
+// What bounds it: the bank conflicts of reads that were ordered for 16-byte entries, 4.5 clocks per read whatever its size
+// (counters, 118 layers of 1024 neurons on 500 rows, two to a workgroup: LDS 63 % of the clocks, 54 % of that conflicts, vector
+// instructions 55 %), and with weights of their own the stream of connections (one row, 12 layers of 1024: LDS 34 %, vector
+// instructions 23 % of the one CU's clocks); 700 to 1000 clocks of a layer's 3500 (1024 neurons) to 17 000
 // (4096 with weights) are the barrier and the waits at its ends.  Whole calls, resident_kernel -> this kernel: one row
 // through 12 layers of 1024 neurons with weights 57 -> 51 us, of 4096 neurons 130 -> 116; 1000 rows, half of which die, through
 // 120 layers of 1024 neurons with one weight 261 -> 228; 100 rows through 24 layers of 4096 neurons 179 -> 147.

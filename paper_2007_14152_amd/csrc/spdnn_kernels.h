@@ -803,8 +803,8 @@ __device__ __forceinline__ unsigned finish_rows(float (&a)[kRows], float bj, flo
                          (__builtin_amdgcn_ballot_w64(y3 > 0.0f) != 0ull ? 8u : 0u);
     transpose_quartet(y0, y1, y2, y3);
     // A buffer store from the first row on: the lane's place behind it is the same in every step, so that no address is worked
-    // out in vector registers (a 64-bit multiply-add and a 64-bit addition: with them and the accumulators cleared 24 000 rows of
-    // 65536 neurons, 6 layers, took 10.98 ms, 10.95 without; 2000 rows 1032 us, 1013).
+    // out in vector registers (a 64-bit multiply-add and a 64-bit addition: with them and the accumulators cleared 2000 rows of
+    // 65536 neurons, 6 layers, took 1032 us, 1013 without; 24 000 rows, bound by HBM, the same).
     const int r = lane & 3;
     if (jok && r < nlive) {
         const auto rows = __builtin_amdgcn_make_buffer_rsrc((void*)(Yout + (size_t)row0 * N), 0, 0xffffffff, 0x00027000);

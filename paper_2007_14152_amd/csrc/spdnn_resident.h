@@ -27,9 +27,9 @@
 // with weights of their own: nine in ten die in layer 3 6.97 -> 3.41 ms; seven in ten, the first of the batch, 8.36 -> 4.44.
 //
 // What bounds it.  One weight per layer: LDS reads (16 bytes per connection, plane and lane; 256 B per clock and CU) and
-// the FMAs behind them, which take nearly the same time (counters at 1024 neurons, 30 000 rows: LDS active 82 % of the
-// clocks, a fifth of that bank conflicts, vector instructions 72 %).  Weights of their own: the same two, at 30 000
-// clocks per layer and pass of 4096 neurons, of which the reads would take 16 400 without conflicts (without any one of reads, FMAs and connection loads a layer takes 10 to 18 %
+// the FMAs behind them, which take nearly the same time (counters, 30 000 rows: LDS active 90 % of the clocks at
+// 1024 neurons and 82 % at 4096, a fifth of that bank conflicts, vector instructions 80 and 78 %).  Weights of their own: the same two
+// (74 and 71 %; neurons of any length 66 and 70), at 30 000 clocks per layer and pass of 4096 neurons, of which the reads would take 16 400 without conflicts (without any one of reads, FMAs and connection loads a layer takes 10 to 18 %
 // less), and the rows' way in and out, 33 000 clocks per pass; the connections, 768 KB per layer and pass, are not what it
 // waits for: a CU gets 53 bytes per clock out of its L2, in loads or beside LDS reads.  One workgroup on its own: latency.
 // The copies between LDS and memory happen once per launch instead of once per layer.  What a wave can find out before the

@@ -7,7 +7,9 @@
 // for 33 neurons, 3 per neuron instead of 32 multiply-adds, from 2 reads per neuron instead of 32, and there are no
 // connections to store or fetch: a layer is {S, off, weight}.  A sum is 31 additions as before, in two runs, with weight
 // and bias in one fused multiply-add at the end.  (Nothing is ever subtracted.  Five rounds of doubling, x[i] += x[i + 1],
-// x[i] += x[i + 2], ... + 16, take 263 additions: 383 us where this takes 363.)
+// x[i] += x[i + 2], ... + 16, take 263 additions: 383 us where this takes 363.)  The runs are shorter than the chain was, and so is
+// the error of dense rows: 0.80 to 0.93 of it, 2-norm, in the first layer, which rounds its products, 0.1 to 0.6 behind later ones.  Where one
+// to four of a neuron's 32 inputs are not 0 and the weight is no power of two, the first layer's is 1.0 to 1.12 of it.
 //
 // Rows stay in LDS over a run of layers, two of them side by side (an entry = the two rows of a column, 8 bytes).  A lane
 // owns kStrideOut neighbours of an orbit: it reads its 64 entries into registers, adds, and after a barrier writes its 33
@@ -15,9 +17,12 @@
 // into different bank pairs; lanes of orbits next to each other read neighbouring entries anyway.  The last lane of an
 // orbit that 33 does not divide writes fewer.  An orbit of exactly 32 (S = N / 32) has one sum for all its neurons: one lane computes it once.
 //
-// What bounds it: reading, adding and writing, one behind the other: 256 registers leave two waves per SIMD, and they meet
-// at two barriers per layer.  48 layers of 16384 neurons, strides 1, 32 and 512 in turn, on 2000 rows of which half die:
-// 1.95 -> 0.36 ms (two neurons per lane under new names, one launch per layer before: 40 us a layer, 5 now); 24 layers of
+// What bounds it: vector instructions and the waits between reading, adding and writing, one behind the other: 256 registers
+// leave two waves per SIMD, and they meet at two barriers per layer (counters, 46 layers of 16384 neurons on 1000 rows: vector
+// instructions 56 % of the clocks, LDS 27 %, 2 % of that conflicts).  Of a neuron's vector instructions per row three are the sum's;
+// weight and bias, ReLU, clip and the test for a live row are four, and its addresses come on top.  48 layers of 16384 neurons,
+// strides 1, 32 and 512 in turn, on 2000 rows of which half die: 1.95 -> 0.36 ms (two neurons per lane under new names, one launch per
+// layer before: 40 us a layer, 28 for the first two now and 6 for the others, on half the rows); 24 layers of
 // 4096 neurons, strides 1, 32 and 128, 60 000 rows 4.45 -> 1.50 ms (resident_kernel before), 48 of them on 100 rows 324 -> 136 us.
 #pragma once
 

@@ -11,11 +11,15 @@
 // The connections of a group are on their way while the group before is computed, all 32 with their weights: 12 KB per wave,
 // which is what it takes for the 53 to 60 bytes per clock that a CU gets out of its L2.  (Neurons of any length: 16 of them.)
 //
-// What bounds it: the bank conflicts of reads that were ordered for 16-byte entries, 4.5 clocks per read whatever its size
-// (counters, 118 layers of 1024 neurons on 500 rows, two to a workgroup: LDS 63 % of the clocks, 54 % of that conflicts, vector
-// instructions 55 %), and with weights of their own the stream of connections (one row, 12 layers of 1024: LDS 34 %, vector
-// instructions 23 % of the one CU's clocks); 700 to 1000 clocks of a layer's 3500 (1024 neurons) to 17 000
-// (4096 with weights) are the barrier and the waits at its ends.  Whole calls, resident_kernel -> this kernel: one row
+// Two rows or one, an entry of 8 or 4 bytes: such reads are served for two sets of 16 lanes at a time, and the order of the connections
+// is that of 16-byte entries, which keeps a set's lanes apart and knows nothing of the other set.  The rows are there twice
+// therefore, in planes that lie in different halves of the banks, a plane for each set: with one weight, 120 layers of 1024
+// neurons on 1000 rows 218 -> 201 us, of 2048 on 300 rows 340 -> 281; 24 layers of 4096 on 200 rows 142 -> 119.
+//
+// What bounds it: latency -- 700 to 1000 clocks of a layer's 3300 (1024 neurons) to 17 000
+// (4096 with weights) are the barrier and the waits at its ends -- and with weights of their own the stream of connections (one row, 12
+// layers of 1024: LDS 34 %, vector instructions 23 % of the one CU's clocks).
+// Whole calls, resident_kernel -> this kernel when it was new: one row
 // through 12 layers of 1024 neurons with weights 57 -> 51 us, of 4096 neurons 130 -> 116; 1000 rows, half of which die, through
 // 120 layers of 1024 neurons with one weight 261 -> 228; 100 rows through 24 layers of 4096 neurons 179 -> 147.
 //
@@ -85,12 +89,18 @@ __device__ __forceinline__ void few_layers(const FewArgs& fa, const float* __res
     using cu32 = const __attribute__((address_space(4))) uint32_t;
     using clayer = const __attribute__((address_space(4))) ResidentLayer;
     constexpr int LOG2R = R == 1 ? 0 : R == 2 ? 1 : 2;
-    constexpr uint32_t COPY = 16u << (2 + LOG2R);  // bytes from an entry to its place in the other copy: plane 1
+    // Entries of 4 and 8 bytes are read for two sets of 16 lanes at once, whose connections were ordered for 16-byte entries, each
+    // set's by itself: the sets find the rows in planes of their own, one in the lower half of the banks, one in the upper.
+    constexpr bool TWICE = LOG2R < 2;
+    constexpr uint32_t PLANE = 16u << (2 + LOG2R);  // bytes from an entry to its place in the next plane
     const int tid = threadIdx.x, lane = tid & 63, T_ = blockDim.x, W = T_ >> 6, U = (N + 63) >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row0 = (int)blockIdx.x * R, nrow = min(R, A - row0);
     const int nb_w = (U - wave + W - 1) / W;
     const uint32_t lane16 = 16u * lane;
+    // bytes from an entry to its place in the other copy of the rows: a layer reads one and writes the other
+    const uint32_t copy = !TWICE ? PLANE : fa.planes_log2 == 2 ? 2 * PLANE : ((uint32_t)(N + 255) / 256u * 512u) << (2 + LOG2R);
+    const uint32_t my_plane = TWICE && (set_of_lane((uint32_t)lane) & 1u) ? 0x00100010u : 0u;  // added to two entry codes
     // LDS address of column j of a row laid out by q = its quads' word
     const auto entry = [&](int j, uint32_t q) -> uint32_t {
         return ((store_group((uint32_t)j) << (8 + fa.planes_log2)) | ((q >> (8 * (j & 3))) & 0xffu)) >> (2 - LOG2R);
@@ -148,6 +158,7 @@ __device__ __forceinline__ void few_layers(const FewArgs& fa, const float* __res
 #pragma unroll
             for (int r = 0; r < R; ++r) e[r] = a[r][i];
             *(lds_T*)(entry(4 * t + i, q)) = e;
+            if constexpr (TWICE) *(lds_T*)(entry(4 * t + i, q) + PLANE) = e;
         }
     }
     __syncthreads();
@@ -156,7 +167,10 @@ __device__ __forceinline__ void few_layers(const FewArgs& fa, const float* __res
     const uint32_t live_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t*)live_word;
     bool other = false;  // the copy that holds the rows
     const auto layer = [&](int l, auto from) {
-        constexpr uint32_t FROM = decltype(from)::value, TO = COPY - FROM;
+        constexpr bool OTHER = decltype(from)::value;
+        constexpr uint32_t FROM = TWICE || !OTHER ? 0u : PLANE;  // (16-byte entries: the other copy is a constant away)
+        const uint32_t shift = !TWICE ? 0u : my_plane + (OTHER ? (copy >> (2 + LOG2R)) * 0x00010001u : 0u);
+        const uint32_t to_copy = OTHER ? 0u : copy;
         // (scalar loads are waited for with the first reads of the rows, so not any later than this)
         const ResidentLayer after = layer_at(l + 2 < fa.l1 ? l + 2 : fa.l1 - 1);
         gchar* q_next = (gchar*)(uintptr_t)nxt.qsel;  // (any layout does for the last layer's output: its own)
@@ -177,7 +191,7 @@ __device__ __forceinline__ void few_layers(const FewArgs& fa, const float* __res
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     uint32_t lo, hi;
-                    few_address<LOG2R>(c[k], lo, hi);
+                    few_address<LOG2R>(TWICE ? c[k] + shift : c[k], lo, hi);
                     y[2 * k] = *(const lds_T*)(lo + FROM);
                     y[2 * k + 1] = *(const lds_T*)(hi + FROM);
                 }
@@ -230,9 +244,12 @@ __device__ __forceinline__ void few_layers(const FewArgs& fa, const float* __res
                 sum[r] = fminf(fmaxf(sum[r] + bj, 0.0f), kClip);
                 if (__builtin_amdgcn_ballot_w64(sum[r] > 0.0f) != 0ull) pos |= 1u << r;
             }
-            uint32_t to = entry(j, q) + TO;
+            uint32_t to = entry(j, q) + to_copy;
             asm volatile("" : "+v"(to));  // (or its load would be moved behind the branch, and wait for all that were asked for since)
-            if (mine) *(lds_T*)to = sum;
+            if (mine) {
+                *(lds_T*)to = sum;
+                if constexpr (TWICE) *(lds_T*)(to + PLANE) = sum;
+            }
         }
         cur = nxt;
         nxt = after;
@@ -248,10 +265,10 @@ __device__ __forceinline__ void few_layers(const FewArgs& fa, const float* __res
     };
     int l = fa.l0;
     while (l < fa.l1 && live) {
-        layer(l++, std::integral_constant<uint32_t, 0>{});
+        layer(l++, std::false_type{});
         other = true;
         if (l == fa.l1 || !live) break;
-        layer(l++, std::integral_constant<uint32_t, COPY>{});
+        layer(l++, std::true_type{});
         other = false;
     }
     if (live) live &= __builtin_amdgcn_readfirstlane(live_word[(l + 2) % 3]);  // the last layer's
@@ -275,7 +292,7 @@ __device__ __forceinline__ void few_layers(const FewArgs& fa, const float* __res
         const uint32_t q = q_out[t];
         T e[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) e[i] = *(const lds_T*)(entry(4 * t + i, q) + (other ? COPY : 0u));
+        for (int i = 0; i < 4; ++i) e[i] = *(const lds_T*)(entry(4 * t + i, q) + (other ? copy : 0u));
 #pragma unroll
         for (int r = 0; r < R; ++r)
             if ((live >> r) & 1u) {

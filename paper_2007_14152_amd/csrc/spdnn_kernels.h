@@ -2705,55 +2705,59 @@ __global__ __launch_bounds__(kOrderPackThreads) void order_pack_kernel(const int
         const int left = nsteps - step;
         const uint32_t adj = on ? S.adj[l] : 0u;  // as quad q = l
         const int remq = on ? (int)S.remq[l] : 0;
-        int lane_of_quad = -1;  // as quad
         int quad_of_lane = -1;  // as lane
-        int parent = -1;        // as lane: the quad from which the search reached me
-        uint32_t free_lanes = 0xFFFFu;  // lanes without a quad (the same in every lane)
-        uint32_t done = 0;              // quads already offered
-        for (int r = 0; r < 16; ++r) {
-            // the most urgent quad not offered yet, the lowest-numbered one among equals
-            const int key = (!on || ((done >> l) & 1u)) ? -1 : ((((remq >= left) ? 4096 : 0) + remq) << 4) | (15 - l);
+        int parent = -1;        // as lane: the entry of the queue from which the search reached me
+        int mult = 0;           // as quad: uses in this step (saturates at 15)
+        // a quad that holds more than there are steps left is read twice in one of them: those steps come first
+        const int cap = __builtin_amdgcn_readfirstlane(row16_max(remq)) > left ? 2 : 1;
+        uint32_t free_lanes = (uint32_t)__builtin_amdgcn_ballot_w64(on && unplaced != 0u);  // lanes without a quad (the same in every lane)
+        uint32_t done = 0;              // quads that are not offered any more
+        while (free_lanes) {
+            // the quad that holds most behind this step so far, the lowest-numbered one among equals
+            const int key = (!on || ((done >> l) & 1u) || mult >= cap) ? -1 : ((remq - mult) << 4) | (15 - l);
             const int best = __builtin_amdgcn_readfirstlane(row16_max(key));
+            if (best < 16) break;  // none, or the rest are empty
             const int q0 = 15 - (best & 15);
-            done |= 1u << q0;
-            if (((best >> 4) & 4095) == 0) break;  // the rest are empty too
-            // breadth-first search for an augmenting path from q0 to a free lane
+            // breadth-first search for an augmenting path from q0 to a free lane; an entry of the queue is a quad and,
+            // behind the first, the lane that would give it up
             int head = 0, tail = 1, found = -1;
             uint32_t seen = 0;
-            if (lane == 0) S.queue[0] = (uint32_t)q0;
+            if (lane == 0) S.queue[0] = (uint32_t)q0 | 256u;
             __syncthreads();
             while (head < tail && found < 0) {
-                const int q = __builtin_amdgcn_readfirstlane((int)S.queue[head]);
+                const int from = __builtin_amdgcn_readfirstlane((int)S.queue[head]);
                 ++head;
-                const uint32_t cand = (uint32_t)__builtin_amdgcn_readlane((int)adj, q) & ~seen;
+                const uint32_t cand = (uint32_t)__builtin_amdgcn_readlane((int)adj, from & 15) & ~seen;
                 const uint32_t hit = cand & free_lanes;
                 if (hit) {
                     found = __builtin_ctz(hit);
-                    if (lane == found) parent = q;
+                    if (lane == found) parent = from;
                 } else if (cand) {
                     seen |= cand;
                     if (on && ((cand >> l) & 1u)) {
-                        parent = q;
-                        S.queue[tail + __popc(cand & ((1u << l) - 1u))] = (uint32_t)quad_of_lane;  // a lane is seen once: at most 16 entries follow q0
+                        parent = from;
+                        S.queue[tail + __popc(cand & ((1u << l) - 1u))] = (uint32_t)(quad_of_lane | (l << 4));  // a lane is seen once: at most 16 entries follow q0
                     }
                     tail += __popc(cand);
                     __syncthreads();
                 }
             }
-            if (found < 0) continue;
+            __syncthreads();  // the queue's next first entry
+            if (found < 0) {
+                done |= 1u << q0;
+                continue;
+            }
             free_lanes &= ~(1u << found);
+            if (lane == q0) ++mult;
             for (int cur = found;;) {
-                const int q = __builtin_amdgcn_readlane(parent, cur);
-                const int next = __builtin_amdgcn_readlane(lane_of_quad, q);  // meaningful only if q was matched
-                if (lane == q) lane_of_quad = cur;
-                if (lane == cur) quad_of_lane = q;
-                if (q == q0) break;
-                cur = next;
+                const int from = __builtin_amdgcn_readlane(parent, cur);
+                if (lane == cur) quad_of_lane = from & 15;
+                if (from & 256) break;
+                cur = from >> 4;
             }
         }
         // lanes without a quad of their own share the least loaded one they can use, in ascending order; a lane
         // with fewer connections left than steps sits this step out
-        int mult = (on && lane_of_quad >= 0) ? 1 : 0;  // as quad: uses in this step (saturates at 15)
         const int reml = __popc(unplaced);
         for (uint32_t rest = free_lanes; rest;) {
             const int ll = __builtin_ctz(rest);
@@ -2778,8 +2782,9 @@ __global__ __launch_bounds__(kOrderPackThreads) void order_pack_kernel(const int
             const int c = idx[src];
             const bool ok = c >= 0 && c < N;
             const uint32_t r = ok ? (uint32_t)win_rel(c, c_lo, N) : 0u;  // stage number | slot inside the stage
-            rel[entry(step)] = (uint16_t)((r & ~(uint32_t)(kCap - 1)) | res_code(slot_of(r & (kCap - 1)), planes_log2));
-            wval[wentry(step)] = ok ? val[src] : 0.0f;
+            const int at = spread_step(step, nsteps, set >> 1);  // (few_kernel's entries of 8 bytes are read for two sets at a time)
+            rel[entry(at)] = (uint16_t)((r & ~(uint32_t)(kCap - 1)) | res_code(slot_of(r & (kCap - 1)), planes_log2));
+            wval[wentry(at)] = ok ? val[src] : 0.0f;
         }
         __syncthreads();
     }

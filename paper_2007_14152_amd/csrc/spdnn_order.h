@@ -12,13 +12,15 @@
 // sliced-ELL of Section III-A-3 plays for coalescing weight reads: a layout
 // decision made once, before inference.
 //
-// How.  32 rounds, one per step.  In each round a maximum bipartite matching
-// lanes <-> quads is built (augmenting paths), quads being offered in priority
-// order: first those whose remaining connections equal or exceed the remaining
-// steps (they must be served now or cost an extra cycle later), then by remaining
-// count.  A lane left unmatched takes a connection from the quad that is least
-// loaded in this round.  Cost = sum over rounds of the largest quad
-// multiplicity; the lower bound is max(32, busiest quad's total).
+// How.  32 rounds, one per step.  In each round lanes and quads are matched with augmenting paths, quads being offered
+// in the order of what they still hold: a lane that no path reaches takes a connection from the quad that is least
+// loaded in this round.  A quad that holds more connections than there are steps left has to be read twice in one of
+// them.  Such steps come first, and in them every quad may be given to two lanes: the full quads lose two connections,
+// the emptiest none, until all hold as many as there are steps left.  From there on a step is a perfect matching, and
+// what it leaves is as even as what it found.  (With single matchings in every step the emptiest quads run out early and
+// later steps collide for it: of 32 lanes with uniform columns 1.54 clocks per step, this way 1.42, the bound 1.40; where
+// the quads are nearly even 1.133, 1.099 and 1.091; of 16 lanes 1.41, 1.34 and 1.30.)  Cost = sum over rounds of the
+// largest quad multiplicity; the lower bound is max(32, busiest quad's total).
 #pragma once
 #include <stdint.h>
 
@@ -32,7 +34,7 @@ namespace spdnn {
 
 constexpr int kGroup = 16;  // lanes served per clock by a 16-byte LDS read = quads per 256-byte bank row
 
-// Working memory of one group (1104 bytes).  On the device it lives in LDS.
+// Working memory of one group (1156 bytes).  On the device it lives in LDS.
 struct OrderScratch {
     uint8_t cnt[kGroup][16];   // connections of lane l still unplaced, per quad
     uint8_t end[kGroup][16];   // end of quad q's bucket in sorted[l]
@@ -40,6 +42,9 @@ struct OrderScratch {
     uint16_t adj[16];          // adj[q]: lanes that still have a connection in quad q
     uint16_t remq[16];         // connections still unplaced in quad q over the whole group
     uint8_t reml[kGroup];      // connections of lane l still unplaced
+    uint8_t parent[kGroup];    // place in the queue from which the search reached lane l
+    uint8_t queue[kGroup + 1];  // quads to search from ...
+    uint8_t via[kGroup + 1];    // ... and the lane that would give such a quad up
 };
 
 SPDNN_HD inline unsigned nib_get(uint64_t w, int i) { return (unsigned)(w >> (4 * i)) & 15u; }
@@ -95,64 +100,60 @@ SPDNN_HD inline void order_group(OrderScratch& S, int nsteps, QuadOf quad_of, Em
     }
     for (int step = 0; step < nsteps; ++step) {
         const int left = nsteps - step;
-        uint64_t lane_of = 0, quad_of_l = 0, par = 0;  // nibble arrays
-        unsigned mq = 0, ml = 0;                        // matched quads / lanes
-        unsigned done = 0;                              // quads already offered
-        for (int r = 0; r < 16; ++r) {
-            // next quad by priority
+        uint64_t quad_of_l = 0, mult = 0;  // nibble arrays: quad of a matched lane; uses of quad q in this step
+        unsigned ml = 0;                   // matched lanes
+        unsigned done = 0;                 // quads that are not offered any more
+        int most = 0;
+        for (int q = 0; q < 16; ++q) most = remq[q] > most ? remq[q] : most;
+        const int cap = most > left ? 2 : 1;  // lanes that may take the same quad
+        while (ml != live) {
+            // the quad that holds most behind this step so far, the lowest-numbered among equals
             int q0 = -1;
-            int best = -1;
+            int best = 0;
             for (int q = 0; q < 16; ++q) {
-                if ((done >> q) & 1u) continue;
-                const int key = (remq[q] >= left ? 4096 : 0) + remq[q];
-                if (key > best) {
-                    best = key;
+                const int used = (int)nib_get(mult, q);
+                if (((done >> q) & 1u) || used >= cap) continue;
+                if ((int)remq[q] - used > best) {
+                    best = (int)remq[q] - used;
                     q0 = q;
                 }
             }
-            done |= 1u << q0;
-            if (remq[q0] == 0) break;  // the rest are empty too
+            if (q0 < 0) break;
             // breadth-first search for an augmenting path from q0 to a free lane
-            uint64_t queue = (uint64_t)q0;
+            S.queue[0] = (uint8_t)q0;
             int head = 0, tail = 1;
             unsigned seen = 0;
             int found = -1;
-            while (head < tail && found < 0) {
-                const int q = (int)nib_get(queue, head++);
-                unsigned cand = adj[q] & ~seen;
-                while (cand) {
-                    const int l = ctz16(cand);
-                    cand &= cand - 1;
-                    seen |= 1u << l;
-                    par = nib_set(par, l, (unsigned)q);
-                    if (!((ml >> l) & 1u)) {
-                        found = l;
-                        break;
-                    }
-                    queue = nib_set(queue, tail++, nib_get(quad_of_l, l));
+            for (; head < tail && found < 0; ++head) {
+                const unsigned cand = adj[S.queue[head]] & ~seen;
+                const unsigned hit = cand & ~ml;
+                if (hit) {
+                    found = ctz16(hit);
+                    S.parent[found] = (uint8_t)head;
+                    break;
+                }
+                seen |= cand;
+                for (unsigned rest = cand; rest; rest &= rest - 1) {
+                    const int l = ctz16(rest);
+                    S.parent[l] = (uint8_t)head;
+                    S.queue[tail] = (uint8_t)nib_get(quad_of_l, l);
+                    S.via[tail++] = (uint8_t)l;  // a lane is seen once: at most 16 entries follow q0
                 }
             }
-            if (found < 0) continue;
-            int cur = found;
-            for (;;) {
-                const int q = (int)nib_get(par, cur);
-                const int next = (int)nib_get(lane_of, q);  // meaningful only if q was matched
-                lane_of = nib_set(lane_of, q, (unsigned)cur);
-                quad_of_l = nib_set(quad_of_l, cur, (unsigned)q);
-                ml |= 1u << cur;
-                const bool first = (q == q0);
-                mq |= 1u << q;
-                if (first) break;
-                cur = next;
+            if (found < 0) {
+                done |= 1u << q0;
+                continue;
             }
+            for (int cur = found;;) {
+                const int at = S.parent[cur];
+                quad_of_l = nib_set(quad_of_l, cur, S.queue[at]);
+                if (at == 0) break;
+                cur = S.via[at];
+            }
+            ml |= 1u << found;
+            mult = nib_set(mult, q0, nib_get(mult, q0) + 1);
         }
-        // lanes without a quad of their own share the least loaded one they can use
-        uint64_t mult = 0;  // nibble: uses of quad q in this step (saturates at 15)
-        for (int l = 0; l < kGroup; ++l)
-            if ((ml >> l) & 1u) {
-                const int q = (int)nib_get(quad_of_l, l);
-                mult = nib_set(mult, q, nib_get(mult, q) + 1);
-            }
+        // lanes without a quad of their own share the least loaded one they can use (the count saturates at 15)
         unsigned placed = ml;  // lanes that place a connection in this step
         for (int l = 0; l < kGroup; ++l) {
             if (!((live >> l) & 1u) || ((ml >> l) & 1u)) continue;
@@ -186,6 +187,16 @@ SPDNN_HD inline void order_group(OrderScratch& S, int nsteps, QuadOf quad_of, Em
     }
 }
 
+// Where step `step` of the order goes among the nsteps (a multiple of 8) that a kernel runs: the steps that read a bank
+// twice, which come first, are spread over all of them, and over different ones for the halves of a wave (`half`), so that the LDS
+// has about the same to do for every read.  Order as it was -> spread -> and the order above, 60 000 rows: 120 layers of 1024
+// neurons 4608 -> 4492 -> 4452 us, 24 of 4096 4425 -> 4356 -> 4360; the new order with its full steps all in front 4630 and 4415.
+SPDNN_HD inline int spread_step(int step, int nsteps, int half) {
+    if (nsteps != 32) return (13 * step + half) % nsteps;
+    const int reversed = ((step & 1) << 4) | ((step & 2) << 2) | (step & 4) | ((step & 8) >> 2) | ((step & 16) >> 4);
+    return (reversed + half) & 31;
+}
+
 // Cost model used by tests: LDS cycles of one group's 32 steps (largest quad
 // multiplicity per step, summed).  quad_at(l, step) as placed.
 template <typename QuadAt>
@@ -209,10 +220,8 @@ SPDNN_HD inline int order_cost(QuadAt quad_at) {
 // neighbouring neurons and a step is conflict-free when their 32 entries fall in 32 different
 // bank pairs.  Every lane has exactly 32 connections and places one per step.
 //
-// Per step: a maximum bipartite matching pairs <-> lanes by augmenting paths (breadth-first),
-// pairs offered by urgency -- first those that hold at least as many unplaced connections as
-// there are steps left (they must be served in every remaining step or cost an extra cycle
-// later), then by what they still hold.  A lane left without a pair of its own shares the least
+// Per step as above: pairs are offered by what they hold, every pair once, or twice in the steps that come first as long
+// as some pair holds more than there are steps left; a lane left without a pair of its own shares the least
 // used pair it can.  Cost of a group = sum over the steps of the largest pair multiplicity;
 // the lower bound is max(32, the busiest pair's total).
 constexpr int kGroup32 = 32;
@@ -221,10 +230,10 @@ struct Order32Scratch {
     uint32_t unplaced[kGroup32];  // connections of lane l not placed yet (bit k)
     uint32_t adj[32];             // lanes that still have a connection in pair q
     uint16_t remq[32];            // connections not placed yet in pair q, whole group
-    int8_t lane_of_pair[32];      // matching of the current step
-    int8_t pair_of_lane[kGroup32];
-    int8_t parent[kGroup32];      // pair from which the search reached lane l
-    uint8_t queue[36];
+    int8_t pair_of_lane[kGroup32];  // matching of the current step
+    uint8_t parent[kGroup32];     // place in the queue from which the search reached lane l
+    uint8_t queue[kGroup32 + 1];  // pairs to search from ...
+    uint8_t via[kGroup32 + 1];    // ... and the lane that would give such a pair up
     uint8_t mult[32];             // lanes using pair q in the current step
 };
 
@@ -250,7 +259,6 @@ SPDNN_HD inline void order_group32(Order32Scratch& S, PairOf pair_of, Emit emit)
         for (int q = 0; q < 32; ++q) {
             S.adj[q] = 0;
             S.remq[q] = 0;
-            S.lane_of_pair[q] = -1;
             S.mult[q] = 0;
         }
         for (int l = 0; l < kGroup32; ++l) {
@@ -264,50 +272,54 @@ SPDNN_HD inline void order_group32(Order32Scratch& S, PairOf pair_of, Emit emit)
                 S.remq[q]++;
             }
         }
-        uint32_t done = 0;  // pairs already offered
-        for (int r = 0; r < 32; ++r) {
-            int q0 = -1, best = -1;
+        int most = 0;
+        for (int q = 0; q < 32; ++q) most = S.remq[q] > most ? S.remq[q] : most;
+        const int cap = most > left ? 2 : 1;  // lanes that may take the same pair
+        uint32_t done = 0;                    // pairs that are not offered any more
+        uint32_t free_lanes = 0xFFFFFFFFu;
+        while (free_lanes) {
+            int q0 = -1, best = 0;
             for (int q = 0; q < 32; ++q) {
-                if ((done >> q) & 1u) continue;
-                const int key = (S.remq[q] >= left ? 4096 : 0) + S.remq[q];
-                if (key > best) {
-                    best = key;
+                if (((done >> q) & 1u) || S.mult[q] >= cap) continue;
+                if ((int)S.remq[q] - (int)S.mult[q] > best) {
+                    best = (int)S.remq[q] - (int)S.mult[q];
                     q0 = q;
                 }
             }
-            done |= 1u << q0;
-            if (S.remq[q0] == 0) break;  // the rest are empty too
+            if (q0 < 0) break;
             // breadth-first search for an augmenting path from pair q0 to a lane without a pair
-            int head = 0, tail = 0, found = -1;
+            int head = 0, tail = 1, found = -1;
             uint32_t seen = 0;
-            S.queue[tail++] = (uint8_t)q0;
-            while (head < tail && found < 0) {
-                const int q = S.queue[head++];
-                uint32_t cand = S.adj[q] & ~seen;
-                while (cand) {
-                    const int l = ctz32(cand);
-                    cand &= cand - 1;
-                    seen |= 1u << l;
-                    S.parent[l] = (int8_t)q;
-                    if (S.pair_of_lane[l] < 0) {
-                        found = l;
-                        break;
-                    }
-                    S.queue[tail++] = (uint8_t)S.pair_of_lane[l];  // a lane is seen once: at most 32 entries follow q0
+            S.queue[0] = (uint8_t)q0;
+            for (; head < tail && found < 0; ++head) {
+                const uint32_t cand = S.adj[S.queue[head]] & ~seen;
+                const uint32_t hit = cand & free_lanes;
+                if (hit) {
+                    found = ctz32(hit);
+                    S.parent[found] = (uint8_t)head;
+                    break;
+                }
+                seen |= cand;
+                for (uint32_t rest = cand; rest; rest &= rest - 1) {
+                    const int l = ctz32(rest);
+                    S.parent[l] = (uint8_t)head;
+                    S.queue[tail] = (uint8_t)S.pair_of_lane[l];
+                    S.via[tail++] = (uint8_t)l;  // a lane is seen once: at most 32 entries follow q0
                 }
             }
-            if (found < 0) continue;
-            for (int cur = found;;) {
-                const int q = S.parent[cur];
-                const int next = S.lane_of_pair[q];  // the lane that gives q up (meaningful unless q == q0)
-                S.lane_of_pair[q] = (int8_t)cur;
-                S.pair_of_lane[cur] = (int8_t)q;
-                if (q == q0) break;
-                cur = next;
+            if (found < 0) {
+                done |= 1u << q0;
+                continue;
             }
+            for (int cur = found;;) {
+                const int at = S.parent[cur];
+                S.pair_of_lane[cur] = (int8_t)S.queue[at];
+                if (at == 0) break;
+                cur = S.via[at];
+            }
+            free_lanes &= ~(1u << found);
+            S.mult[q0]++;
         }
-        for (int l = 0; l < kGroup32; ++l)
-            if (S.pair_of_lane[l] >= 0) S.mult[S.pair_of_lane[l]]++;
         for (int l = 0; l < kGroup32; ++l) {
             if (S.pair_of_lane[l] >= 0) continue;
             int bq = -1, bkey = 1 << 30;

@@ -418,54 +418,58 @@ __device__ __forceinline__ void order32_wave(Pack32Scratch& S, bool exists, Bank
         const int left = 32 - step;
         const uint32_t adj = on ? S.adj[l] : 0u;  // as pair q = l
         const int remq = on ? (int)S.remq[l] : 0;
-        int lane_of_pair = -1;  // as pair
         int pair_of_lane = -1;  // as lane
-        int parent = -1;        // as lane: the pair from which the search reached me
+        int parent = -1;        // as lane: the entry of the queue from which the search reached me
+        int mult = 0;           // as pair: lanes using me in this step
+        // a pair that holds more than there are steps left is read twice in one of them: those steps come first
+        const int cap = wave32_max(remq) > left ? 2 : 1;
         uint32_t free_lanes = lanes;        // lanes without a pair (the same in every lane)
-        uint32_t done = 0;                  // pairs already offered
-        for (int r = 0; r < 32; ++r) {
-            // the most urgent pair not offered yet, the lowest-numbered one among equals
-            const int key = (!on || ((done >> l) & 1u)) ? -1 : ((((remq >= left) ? 4096 : 0) + remq) << 5) | (31 - l);
+        uint32_t done = 0;                  // pairs that are not offered any more
+        while (free_lanes) {
+            // the pair that holds most behind this step so far, the lowest-numbered one among equals
+            const int key = (!on || ((done >> l) & 1u) || mult >= cap) ? -1 : ((remq - mult) << 5) | (31 - l);
             const int best = wave32_max(key);
+            if (best < 32) break;  // none, or the rest are empty
             const int q0 = 31 - (best & 31);
-            done |= 1u << q0;
-            if (((best >> 5) & 4095) == 0) break;  // the rest are empty too
-            // breadth-first search for an augmenting path from pair q0 to a lane without a pair
+            // breadth-first search for an augmenting path from pair q0 to a lane without a pair; an entry of the queue is
+            // a pair and, behind the first, the lane that would give it up
             int head = 0, tail = 1, found = -1;
             uint32_t seen = 0;
-            if (lane == 0) S.queue[0] = (uint32_t)q0;
+            if (lane == 0) S.queue[0] = (uint32_t)q0 | 1024u;
             __syncthreads();
             while (head < tail && found < 0) {
-                const int q = __builtin_amdgcn_readfirstlane((int)S.queue[head]);
+                const int from = __builtin_amdgcn_readfirstlane((int)S.queue[head]);
                 ++head;
-                const uint32_t cand = (uint32_t)__builtin_amdgcn_readlane((int)adj, q) & ~seen;
+                const uint32_t cand = (uint32_t)__builtin_amdgcn_readlane((int)adj, from & 31) & ~seen;
                 const uint32_t hit = cand & free_lanes;
                 if (hit) {
                     found = __builtin_ctz(hit);
-                    if (lane == found) parent = q;
+                    if (lane == found) parent = from;
                 } else if (cand) {
                     seen |= cand;
                     if (on && ((cand >> l) & 1u)) {
-                        parent = q;
-                        S.queue[tail + __popc(cand & ((1u << l) - 1u))] = (uint32_t)pair_of_lane;  // a lane is seen once: at most 32 entries follow q0
+                        parent = from;
+                        S.queue[tail + __popc(cand & ((1u << l) - 1u))] = (uint32_t)(pair_of_lane | (l << 5));  // a lane is seen once: at most 32 entries follow q0
                     }
                     tail += __popc(cand);
                     __syncthreads();
                 }
             }
-            if (found < 0) continue;
+            __syncthreads();  // the queue's next first entry
+            if (found < 0) {
+                done |= 1u << q0;
+                continue;
+            }
             free_lanes &= ~(1u << found);
+            if (lane == q0) ++mult;
             for (int cur = found;;) {
-                const int q = __builtin_amdgcn_readlane(parent, cur);
-                const int next = __builtin_amdgcn_readlane(lane_of_pair, q);  // the lane that gives q up (meaningful unless q == q0)
-                if (lane == q) lane_of_pair = cur;
-                if (lane == cur) pair_of_lane = q;
-                if (q == q0) break;
-                cur = next;
+                const int from = __builtin_amdgcn_readlane(parent, cur);
+                if (lane == cur) pair_of_lane = from & 31;
+                if (from & 1024) break;
+                cur = from >> 5;
             }
         }
         // a lane left without a pair of its own shares the least used pair it can, lanes in ascending order
-        int mult = (on && lane_of_pair >= 0) ? 1 : 0;  // as pair: lanes using me in this step
         for (uint32_t rest = free_lanes; rest;) {
             const int ll = __builtin_ctz(rest);
             rest &= rest - 1;
@@ -481,7 +485,7 @@ __device__ __forceinline__ void order32_wave(Pack32Scratch& S, bool exists, Bank
             unplaced &= ~(1u << k);
             atomicSub(&S.remq[pair_of_lane], 1u);
             if ((in_pair & unplaced) == 0) atomicAnd(&S.adj[pair_of_lane], ~(1u << l));
-            place(step, k);
+            place(spread_step(step, 32, (int)(blockIdx.x & 1)), k);  // (a block per group, the two of a wave side by side)
         }
         __syncthreads();
     }

@@ -26,10 +26,10 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
 
 NO_SCRATCH_KERNELS = ["fused_row2_kernel", "fused_pair_kernel"]
 # Kernels that count LDS addresses from the start of the workgroup's LDS: all of it must be dynamic.
-LDS_FROM_ZERO_KERNELS = ["resident_kernel", "fused_flat_kernel", "few_kernel"]
+LDS_FROM_ZERO_KERNELS = ["resident_kernel", "fused_flat_kernel", "few_kernel", "strided_kernel"]
 # Bytes of scratch per lane that these may spill: outside the arithmetic, at what was measured with them.  (Spills are
 # memory operations more, which the waits written out by hand cover: they count at most what comes after the loads.)
-SCRATCH_LIMIT = {"resident_kernel": 32, "fused_flat_kernel": 24, "few_kernel": 0}
+SCRATCH_LIMIT = {"resident_kernel": 32, "fused_flat_kernel": 24, "few_kernel": 0, "strided_kernel": 0}
 
 
 def _resource_usage(text):

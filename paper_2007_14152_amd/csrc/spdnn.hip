@@ -116,6 +116,7 @@ struct spdnn_model {
     const spdnn::StridedLayer* strided = nullptr;  // device copy of the layers' descriptors (NULL: not such a network)
     int32_t strided_lanes = 0;                     // lanes a pair of rows takes in the layer that takes most
     float strided_bias = 0.0f;
+    bool strided_known = false;  // all strides are among those that strided_kernel has code of its own for
     // out-of-core weights: pass p's block lives in host memory and is copied into device slot p & 1
     const char* ooc_host = nullptr;
     char* ooc_slot[2] = {nullptr, nullptr};
@@ -249,9 +250,9 @@ hipError_t allow_flat_lds() {
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, spdnn::flat_lds_bytes(R));
 }
 constexpr int kLdsBytes = 160 * 1024;
-template <bool PAIRS>
+template <bool PAIRS, bool KNOWN>
 hipError_t allow_strided_lds() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::strided_kernel<PAIRS>), hipFuncAttributeMaxDynamicSharedMemorySize,
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::strided_kernel<PAIRS, KNOWN>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                kLdsBytes);
 }
 int few_lds(int32_t N, int32_t nblk) {
@@ -282,8 +283,10 @@ int allow_large_lds() {
     constexpr size_t wide_lds = spdnn::kOrderThreads * sizeof(spdnn::WideScratch);
     const int tile_lds = (int)spdnn::tile_pair_bytes(spdnn::kCap);
     HIP_TRY(allow_few_lds());
-    HIP_TRY(allow_strided_lds<false>());
-    HIP_TRY(allow_strided_lds<true>());
+    HIP_TRY((allow_strided_lds<false, false>()));
+    HIP_TRY((allow_strided_lds<true, false>()));
+    HIP_TRY((allow_strided_lds<false, true>()));
+    HIP_TRY((allow_strided_lds<true, true>()));
     HIP_TRY((allow_big_lds<false, false>()));
     HIP_TRY((allow_big_lds<true, false>()));
     HIP_TRY((allow_big_lds<false, true>()));
@@ -1040,6 +1043,7 @@ int create_impl(spdnn_t* out, int32_t N, int32_t L, const std::vector<int32_t>& 
         m->res_rows = reinterpret_cast<int*>(layers_dev + L);
         m->strided_bias = hb[0];
         for (const spdnn::StridedLayer& sl : strided) m->strided_lanes = std::max(m->strided_lanes, spdnn::strided_lanes(sl));
+        m->strided_known = std::all_of(strided.begin(), strided.end(), [&](const spdnn::StridedLayer& sl) { return spdnn::strided_known(sl, N); });
     }
     guard.m = nullptr;
     *out = m;
@@ -1249,8 +1253,11 @@ hipError_t launch_strided(spdnn_t h, int32_t l0, int32_t l1, int32_t rows, const
     const StridedShape r = strided_shape(h, rows);
     const spdnn::StridedArgs sa{h->strided, l0, l1, rows, r.pairs, h->strided_bias, layer_rows};
     const int grid = std::min((rows + 2 * r.pairs - 1) / (2 * r.pairs), r.slots);
-    if (r.pairs > 1) spdnn::strided_kernel<true><<<grid, r.threads, r.lds, h->stream>>>(Yin, Yout, flags, rl, sa, h->N);
-    else spdnn::strided_kernel<false><<<grid, r.threads, r.lds, h->stream>>>(Yin, Yout, flags, rl, sa, h->N);
+    const auto run = [&](auto pairs, auto known) {
+        spdnn::strided_kernel<decltype(pairs)::value, decltype(known)::value><<<grid, r.threads, r.lds, h->stream>>>(Yin, Yout, flags, rl, sa, h->N);
+    };
+    if (r.pairs > 1) h->strided_known ? run(std::true_type{}, std::true_type{}) : run(std::true_type{}, std::false_type{});
+    else h->strided_known ? run(std::false_type{}, std::true_type{}) : run(std::false_type{}, std::false_type{});
     return hipGetLastError();
 }
 

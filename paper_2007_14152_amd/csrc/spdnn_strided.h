@@ -17,13 +17,21 @@
 // into different bank pairs; lanes of orbits next to each other read neighbouring entries anyway.  The last lane of an
 // orbit that 33 does not divide writes fewer.  An orbit of exactly 32 (S = N / 32) has one sum for all its neurons: one lane computes it once.
 //
-// What bounds it: vector instructions and the waits between reading, adding and writing, one behind the other: 256 registers
-// leave two waves per SIMD, and they meet at two barriers per layer (counters, 46 layers of 16384 neurons on 1000 rows: vector
-// instructions 56 % of the clocks, LDS 27 %, 2 % of that conflicts).  Of a neuron's vector instructions per row three are the sum's;
-// weight and bias, ReLU, clip and the test for a live row are four, and its addresses come on top.  48 layers of 16384 neurons,
-// strides 1, 32 and 512 in turn, on 2000 rows of which half die: 1.95 -> 0.36 ms (two neurons per lane under new names, one launch per
+// The rows are kept as 1/32 of what they are, exactly (from 2^-121 on): ReLU and clip are then the clamp of the multiply-add that weight and
+// bias take.
+// Strides that are powers of two, and the row length a multiple, have code of their own (strided_known): an entry's distance from a
+// lane's first is in the read's offset, and a lane that comes past the row end chooses between two addresses.  With one address
+// worked out per entry and ReLU and clip instructions of their own before, pairs of rows through layers of one stride, clocks of 2.4 GHz
+// per layer of 32768 neurons and rows: 4096 neurons, stride 1 8570 -> 6640, 32 8670 -> 6980, 128 4150 -> 4000, 3 (any other) 8730 -> 7760;
+// 16384 neurons 7240 -> 6800, 7170 -> 7130, 512 4290 -> 4260, 3 7530 -> 7220.
+//
+// What bounds it: the chain of reading, adding and writing: a CU's LDS has room for the rows of 8 waves, two per SIMD, which meet at two
+// barriers per layer.  A wave issues an instruction every 5 clocks, so two do not fill a SIMD; a write of 8 bytes per lane takes the LDS 6.2
+// clocks where a read takes 2.5 (33 writes of 8 waves: 1640 clocks, with nothing else to do meanwhile); and the wave that comes past the row
+// end has a third more instructions than the others, which wait for it.  48 layers of 16384 neurons,
+// strides 1, 32 and 512 in turn, on 2000 rows of which half die: 1.95 -> 0.35 ms (two neurons per lane under new names, one launch per
 // layer before: 40 us a layer, 28 for the first two now and 6 for the others, on half the rows); 24 layers of
-// 4096 neurons, strides 1, 32 and 128, 60 000 rows 4.45 -> 1.50 ms (resident_kernel before), 48 of them on 100 rows 324 -> 136 us.
+// 4096 neurons, strides 1, 32 and 128, 60 000 rows 4.45 -> 1.27 ms (resident_kernel before), 48 of them on 100 rows 324 -> 120 us.
 #pragma once
 
 namespace spdnn {
@@ -48,6 +56,11 @@ struct StridedArgs {
     int* layer_rows;  // NULL, or counters: [l] += rows alive on entry to layer l
 };
 SPDNN_HD inline int strided_lanes(const StridedLayer& d) { return d.orbits * d.per; }
+// Has strided_kernel code of its own for the layer's stride?  A power of two up to 512 that divides N; and a lane's entries come past
+// the row end at most once, or the orbit is one sum.  (The networks of the Sparse DNN Challenge have such strides only.)
+SPDNN_HD inline bool strided_known(const StridedLayer& d, int N) {
+    return d.S <= 512 && (d.S & (d.S - 1)) == 0 && N % d.S == 0 && (N / d.S >= kStrideIn || N / d.S == kNnz);
+}
 
 // n entries of an orbit, from column c on, every S-th, around the row end.
 template <int n>
@@ -67,8 +80,49 @@ __device__ __forceinline__ void read_orbit(f32x2 (&x)[n], __attribute__((address
     }
 }
 
+// The same for a stride that is known beforehand and divides N, with what is done with the entries: an entry's distance from the first is
+// part of the read, and no addition.  (It has 16 bits: every kFar entries the address moves on.)  base: of the row.
+// Both ways have reads and additions in one block of code: only there does the compiler mix them.
+template <int n, int S, typename Sums>
+__device__ __forceinline__ void sum_stride(f32x2 (&x)[n], uint32_t base, uint32_t c, uint32_t N, Sums sums) {
+    using lds_f2 = __attribute__((address_space(3))) f32x2;
+    constexpr int kFar = S <= 128 ? n : 65536 / (8 * S);
+    if (__builtin_amdgcn_ballot_w64(c + (n - 1) * S >= N) == 0ull) {
+        uint32_t at[(n + kFar - 1) / kFar];
+#pragma unroll
+        for (int g = 0; g < n; g += kFar) {
+            at[g / kFar] = base + 8u * c + 8u * S * g;
+            if constexpr (kFar < n) asm("" : "+v"(at[g / kFar]));
+        }
+#pragma unroll
+        for (int i = 0; i < n; ++i) {  // as they are added: from the middle on, to both sides
+            const int k = i & 1 ? n / 2 + i / 2 : n / 2 - 1 - i / 2;
+            x[k] = *(const lds_f2*)(at[k / kFar] + 8u * S * (k % kFar));
+        }
+        sums();
+        asm volatile("");  // (or what the ways have in common would be put behind them)
+    } else {
+        const uint32_t over = (N - c + S - 1u) / S;  // the first entry past the row end
+        uint32_t at[(n + kFar - 1) / kFar], past[(n + kFar - 1) / kFar];
+#pragma unroll
+        for (int g = 0; g < n; g += kFar) {
+            at[g / kFar] = base + 8u * c + 8u * S * g;
+            past[g / kFar] = at[g / kFar] - 8u * N;
+            if constexpr (kFar < n) asm("" : "+v"(at[g / kFar]), "+v"(past[g / kFar]));
+        }
+#pragma unroll
+        for (int i = 0; i < n; ++i) {
+            const int k = i & 1 ? n / 2 + i / 2 : n / 2 - 1 - i / 2;
+            uint32_t from;
+            asm("v_cmp_ge_u32 vcc, %1, %2\n\tv_cndmask_b32 %0, %3, %4, vcc" : "=v"(from) : "n"(k), "v"(over), "v"(at[k / kFar]), "v"(past[k / kFar]) : "vcc");
+            x[k] = *(const lds_f2*)(from + 8u * S * (k % kFar));
+        }
+        sums();
+    }
+}
+
 // PAIRS: more than one pair of rows, the lanes shared out among them.
-template <bool PAIRS>
+template <bool PAIRS, bool KNOWN>
 __global__ __launch_bounds__(kStrideThreads) void strided_kernel(const float* __restrict__ Yin, float* __restrict__ Yout,
                                                                  uint8_t* __restrict__ flags, RowLists rl, StridedArgs sa, int N) {
     extern __shared__ __align__(16) char strided_lds[];
@@ -79,17 +133,19 @@ __global__ __launch_bounds__(kStrideThreads) void strided_kernel(const float* __
     const int tid = threadIdx.x, lane = tid & 63, nthreads = blockDim.x;
     const int np = PAIRS ? sa.pairs : 1;
     const uint32_t row_bytes = 8u * (uint32_t)N;  // of a pair
-    uint32_t* live_word = reinterpret_cast<uint32_t*>(strided_lds + (size_t)np * row_bytes);  // [2], raised by the layers in turn
+    uint32_t* live_word = reinterpret_cast<uint32_t*>(strided_lds + (size_t)np * row_bytes + 8);  // [2], raised by the layers in turn
+    const uint32_t live_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t*)live_word;
     const int A = rl.count ? __builtin_amdgcn_readfirstlane(*rl.count) : sa.A;
     const int npass = (A + 2 * np - 1) / (2 * np), n4 = N >> 2;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    const float bias = sa.bias * (1.0f / kClip);
     using clayer = const __attribute__((address_space(4))) StridedLayer;  // constant while the kernel runs: scalar loads
 
     for (int pass = blockIdx.x; pass < npass; pass += gridDim.x) {
         const int row0 = pass * 2 * np, nrow = min(2 * np, A - row0);
         if (tid < 2) live_word[tid] = 0u;
         // the rows; layer 0 sums inputs of any size, so they meet its weight before they are added up
-        const float first_w = sa.l0 == 0 ? ((clayer*)(uintptr_t)sa.layers)->w : 1.0f;
+        const float first_w = (sa.l0 == 0 ? ((clayer*)(uintptr_t)sa.layers)->w : 1.0f) * (1.0f / kClip);
         for (int p = 0; p < np; ++p) {
             const bool one = 2 * p < nrow, two = 2 * p + 1 < nrow;
             const int s0 = !one ? 0 : rl.count ? rl.cat[row0 + 2 * p] : row0 + 2 * p;
@@ -118,54 +174,76 @@ __global__ __launch_bounds__(kStrideThreads) void strided_kernel(const float* __
             }
         }
         uint32_t live = 0u;
-        __syncthreads();
-        for (int l = sa.l0; l < sa.l1; ++l) {
+        const auto layer_at = [&](int l) -> StridedLayer {
             clayer* d = (clayer*)(uintptr_t)(sa.layers + l);
-            const uint32_t S = (uint32_t)d->S, orbits = (uint32_t)d->orbits, T = (uint32_t)d->T, per = (uint32_t)d->per;
-            const float w = l == 0 ? 1.0f : d->w;
+            return StridedLayer{d->S, d->off, d->orbits, d->T, d->per, d->w};
+        };
+        StridedLayer cur = layer_at(sa.l0);
+        __syncthreads();
+        // A layer of stride S (0: of any), up to where its outputs are in place.
+        const auto layer = [&](int l, auto Stag, uint32_t& raised) {
+            constexpr uint32_t kS = decltype(Stag)::value;
+            const uint32_t S = kS ? kS : (uint32_t)cur.S, orbits = kS ? kS : (uint32_t)cur.orbits, T = (uint32_t)cur.T, per = (uint32_t)cur.per;
+            const float w = l == 0 ? 1.0f : cur.w;
             const uint32_t lanes = orbits * per;
             // my pair of rows, my orbit, my place on it
-            const uint32_t p = PAIRS ? (uint32_t)tid / lanes : 0u;
-            const uint32_t i = (uint32_t)tid - p * lanes;
-            const bool mine = PAIRS ? p < (uint32_t)np : (uint32_t)tid < lanes;
+            uint32_t me = (uint32_t)tid;
+            asm volatile("" : "+v"(me));  // (or the places of all strides' entries would be worked out before the layers, for registers that are not there)
+            const uint32_t p = PAIRS ? me / lanes : 0u;
+            const uint32_t i = me - p * lanes;
+            const bool mine = PAIRS ? p < (uint32_t)np : me < lanes;
             const uint32_t b = i / orbits, r = i - b * orbits;
             const uint32_t t0 = b * kStrideOut, left = T - t0;  // the last lane of an orbit has fewer neurons: `left`
-            const uint32_t j0 = (r + t0 * S) % (uint32_t)N;
-            uint32_t c0 = j0 + (uint32_t)d->off;
+            const uint32_t j0 = kS ? r + t0 * S : (r + t0 * S) % (uint32_t)N;
+            uint32_t c0 = j0 + (uint32_t)cur.off;
             c0 = min(c0, c0 - (uint32_t)N);
             const uint32_t base = PAIRS ? p * row_bytes : 0u;
             const uint32_t s8 = 8u * S, back = 8u * S - row_bytes;
+            const bool whole = T == (uint32_t)kNnz;  // one sum for all of an orbit
             f32x2 y[kStrideOut];
             uint32_t bits = 0u;
             if (mine) {
-                const bool whole = T == (uint32_t)kNnz;  // one sum for all of an orbit
                 float m0 = 0.0f, m1 = 0.0f;
                 const auto finish = [&](f32x2 v) -> f32x2 {
-                    v.x = fminf(fmaxf(__builtin_fmaf(w, v.x, sa.bias), 0.0f), kClip);
-                    v.y = fminf(fmaxf(__builtin_fmaf(w, v.y, sa.bias), 0.0f), kClip);
+                    v.x = fminf(fmaxf(__builtin_fmaf(w, v.x, bias), 0.0f), 1.0f);
+                    v.y = fminf(fmaxf(__builtin_fmaf(w, v.y, bias), 0.0f), 1.0f);
                     m0 = fmaxf(m0, v.x);
                     m1 = fmaxf(m1, v.y);
                     return v;
                 };
                 if (whole) {
                     f32x2 v[kNnz];
-                    read_orbit<kNnz>(v, tile + base, c0, S, (uint32_t)N);
+                    const auto sums = [&]() {
 #pragma unroll
-                    for (int h = 1; h < kNnz; h *= 2)
+                        for (int h = 1; h < kNnz; h *= 2)
 #pragma unroll
-                        for (int k = 0; k + h < kNnz; k += 2 * h) v[k] += v[k + h];
-                    y[0] = finish(v[0]);
+                            for (int k = 0; k + h < kNnz; k += 2 * h) v[k] += v[k + h];
+                        y[0] = finish(v[0]);
+                    };
+                    if constexpr (kS != 0) {
+                        sum_stride<kNnz, kS>(v, base, c0 & (kS - 1u), (uint32_t)N, sums);  // (all of the orbit, whichever comes first)
+                    } else {
+                        read_orbit<kNnz>(v, tile + base, c0, S, (uint32_t)N);
+                        sums();
+                    }
                 } else {
                     f32x2 x[kStrideIn];
-                    read_orbit<kStrideIn>(x, tile + base, c0, S, (uint32_t)N);
+                    const auto sums = [&]() {
 #pragma unroll
-                    for (int k = kNnz - 2; k >= 0; --k) x[k] += x[k + 1];  // x[k .. 31]
+                        for (int k = kNnz - 2; k >= 0; --k) x[k] += x[k + 1];  // x[k .. 31]
 #pragma unroll
-                    for (int k = kNnz + 1; k < kStrideIn; ++k) x[k] += x[k - 1];  // x[32 .. k]
-                    y[0] = finish(x[0]);
+                        for (int k = kNnz + 1; k < kStrideIn; ++k) x[k] += x[k - 1];  // x[32 .. k]
+                        y[0] = finish(x[0]);
 #pragma unroll
-                    for (int k = 1; k < kNnz; ++k) y[k] = finish(x[k] + x[k + kNnz - 1]);
-                    y[kNnz] = finish(x[kStrideIn - 1]);
+                        for (int k = 1; k < kNnz; ++k) y[k] = finish(x[k] + x[k + kNnz - 1]);
+                        y[kNnz] = finish(x[kStrideIn - 1]);
+                    };
+                    if constexpr (kS != 0) {
+                        sum_stride<kStrideIn, kS>(x, base, c0, (uint32_t)N, sums);
+                    } else {
+                        read_orbit<kStrideIn>(x, tile + base, c0, S, (uint32_t)N);
+                        sums();
+                    }
                 }
                 // which rows have a positive output: the wave's first lane of every pair speaks for it
                 const unsigned long long pos0 = __builtin_amdgcn_ballot_w64(m0 > 0.0f), pos1 = __builtin_amdgcn_ballot_w64(m1 > 0.0f);
@@ -177,32 +255,62 @@ __global__ __launch_bounds__(kStrideThreads) void strided_kernel(const float* __
                     first = lane == from;
                 }
                 bits = (pos0 & of_pair ? 1u : 0u) | (pos1 & of_pair ? 2u : 0u);
-                if (first && bits) atomicOr(&live_word[l & 1], bits << (2u * p));
+                // (a plain LDS operation: the compiler's atomic would look for the first active lane on its own)
+                if (first) asm volatile("ds_or_b32 %0, %1" ::"v"(live_at + 4u * (uint32_t)(l & 1)), "v"(bits << (2u * p)) : "memory");
             }
+            cur = layer_at(min(l + 1, sa.l1 - 1));  // (here nothing else waits for it)
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __syncthreads();  // every wave has read what it needs of the rows
-            live = __builtin_amdgcn_readfirstlane(live_word[l & 1]);
-            if (mine) {
-                if (T == (uint32_t)kNnz) {
-                    uint32_t at = 8u * j0;
+            raised = live_word[l & 1];  // (on its way while the results go out)
+            if (!mine) return;
+            const uint32_t nowhere = (uint32_t)np * row_bytes;
+            const auto put = [&](auto n, auto value) {  // outputs that stay on this side of the row end
+                constexpr int far = kS == 0 || kS <= 128 ? decltype(n)::value : 65536 / (8 * (int)kS);
 #pragma unroll
-                    for (int k = 0; k < kNnz; ++k) {
-                        *(lds_f2*)(tile + (base + at)) = y[0];
-                        at = min(at + s8, at + back);
-                    }
-                } else if (__builtin_amdgcn_ballot_w64(j0 + (kStrideOut - 1) * S >= (uint32_t)N) == 0ull) {
+                for (int g = 0; g < decltype(n)::value; g += far) {
+                    uint32_t at = base + 8u * j0 + g * s8;
+                    if constexpr (kS != 0 && far < decltype(n)::value) asm("" : "+v"(at));
 #pragma unroll
-                    for (int k = 0; k < kStrideOut; ++k) *(lds_f2*)(tile + (base + 8u * j0 + k * s8)) = y[k];
-                } else {
-                    // an orbit's last lane is always among these: it comes past the row end where the orbit ends
-                    const uint32_t nowhere = (uint32_t)np * row_bytes + 8u;
-                    uint32_t at = 8u * j0;
+                    for (int k = g; k < g + far && k < decltype(n)::value; ++k) *(lds_f2*)(at + (k - g) * s8) = value(k);
+                }
+                asm volatile("");
+            };
+            if (whole && kS != 0) {
+                put(std::integral_constant<int, kNnz>{}, [&](int) { return y[0]; });
+            } else if (whole) {
+                uint32_t at = 8u * j0;
 #pragma unroll
-                    for (int k = 0; k < kStrideOut; ++k) {
-                        *(lds_f2*)(tile + ((uint32_t)k < left ? base + at : nowhere)) = y[k];
-                        at = min(at + s8, at + back);
-                    }
+                for (int k = 0; k < kNnz; ++k) {
+                    *(lds_f2*)(tile + (base + at)) = y[0];
+                    at = min(at + s8, at + back);
+                }
+            } else if (__builtin_amdgcn_ballot_w64(j0 + (kStrideOut - 1) * S >= (uint32_t)N) == 0ull) {
+                put(std::integral_constant<int, kStrideOut>{}, [&](int k) { return y[k]; });
+            } else if constexpr (kS != 0) {  // an orbit ends at the row end
+#pragma unroll
+                for (int k = 0; k < kStrideOut; ++k) *(lds_f2*)(PAIRS ? ((uint32_t)k < left ? base + 8u * j0 + k * s8 : nowhere) : min(8u * j0 + k * s8, row_bytes)) = y[k];
+            } else {
+                // an orbit's last lane is always among these: it comes past the row end where the orbit ends
+                uint32_t at = 8u * j0;
+#pragma unroll
+                for (int k = 0; k < kStrideOut; ++k) {
+                    *(lds_f2*)(tile + ((uint32_t)k < left ? base + at : nowhere)) = y[k];
+                    at = min(at + s8, at + back);
                 }
             }
+        };
+        for (int l = sa.l0; l < sa.l1; ++l) {
+            uint32_t raised = 0u;
+            if constexpr (!KNOWN) layer(l, std::integral_constant<uint32_t, 0>{}, raised);
+            else switch (cur.S) {
+#define SPDNN_STRIDE(S_) \
+    case S_: layer(l, std::integral_constant<uint32_t, S_>{}, raised); break;
+                SPDNN_STRIDE(1) SPDNN_STRIDE(2) SPDNN_STRIDE(4) SPDNN_STRIDE(8) SPDNN_STRIDE(16) SPDNN_STRIDE(32)
+                SPDNN_STRIDE(64) SPDNN_STRIDE(128) SPDNN_STRIDE(256)
+#undef SPDNN_STRIDE
+                default: layer(l, std::integral_constant<uint32_t, 512>{}, raised);
+            }
+            live = __builtin_amdgcn_readfirstlane(raised);
             if (tid == 0) {
                 live_word[(l + 1) & 1] = 0u;
                 if (sa.layer_rows && live) atomicAdd(&sa.layer_rows[l + 1], __popc(live));
@@ -220,8 +328,8 @@ __global__ __launch_bounds__(kStrideThreads) void strided_kernel(const float* __
                 for (int t = tid; t < n4; t += nthreads) {
                     const lds_f4* from = (const lds_f4*)(tile + p * row_bytes + 32u * t);
                     const f32x4 u = from[0], v = from[1];
-                    if (one) dst0[t] = f32x4{u.x, u.z, v.x, v.z};
-                    if (two) dst1[t] = f32x4{u.y, u.w, v.y, v.w};
+                    if (one) dst0[t] = f32x4{u.x, u.z, v.x, v.z} * kClip;
+                    if (two) dst1[t] = f32x4{u.y, u.w, v.y, v.w} * kClip;
                 }
             }
         }

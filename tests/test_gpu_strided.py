@@ -151,3 +151,41 @@ def test_inputs_and_weights_of_any_sign(N, strides, batch, weights):
     full = np.zeros_like(y)
     full[np.searchsorted(ids, rows[mine])] = Y[mine]
     assert (np.abs(full - y) <= bound * 1.001).all()
+
+
+@pytest.mark.parametrize("N,strides,batch,weight,offs", [
+    (2048, (1, 2, 4, 8, 16, 32, 64), 300, 0.0625, (0, 2047, 33)),       # all that leave orbits of 32 or of 64 and more; several pairs of rows
+    (4096, (16, 32, 64, 128), 41, 0.07, (4095, 0, 31)),                 # orbits of 256 down to 32
+    (8192, (256, 128, 1, 64), 30, 0.0625, (0, 127, 8191)),
+    (16384, (1, 2, 4, 8, 16, 32, 64, 128, 256, 512), 9, 0.0625, (0, 16383, 5)),  # a pair of rows per pass
+    (16384, (512, 256, 512), 600, 0.0625, (511, 512, 8000)),
+    (12288, (1, 64, 128), 21, 0.0625, (0, 12287)),                      # rows that are no power of two
+    (12288, (128, 256), 21, 0.0625, (12000, 12287)),                    # orbits of 48: a lane's 64 entries go past the row end twice
+    (1280, (4, 16, 20), 500, 0.0625, (1279, 0)),                        # orbits of 320, 80 and 64, the last stride no power of two
+])
+def test_strides_that_are_known_beforehand(N, strides, batch, weight, offs):
+    test_strided_networks(N, strides, batch, weight, offs)
+
+
+@pytest.mark.parametrize("N,strides", [(2048, (1, 64)), (16384, (32, 1)), (12288, (3, 256))])
+def test_infinite_inputs(N, strides):
+    """Infinity is clipped to 32, infinity less infinity and NaN give 0, in the neurons that read them."""
+    import torch
+    import paper_2007_14152_amd as sp
+    idx, val = network(N, strides, 0.0625, (N - 1,))
+    bias = synth.gen_bias(N, -0.3)
+    Y0 = synth.gen_y0(6, N, 7, density="mixed")
+    Y0[0, 17], Y0[1, N - 1], Y0[2, 100], Y0[2, 101], Y0[3, 0] = np.inf, -np.inf, np.inf, -np.inf, np.nan
+    y = Y0.astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        for i, v in zip(idx, val):
+            s = y[:, i].sum(2) * np.float64(v[0, 0]) + np.float64(np.float32(-0.3))
+            y = np.clip(np.nan_to_num(s, nan=0.0, posinf=np.inf, neginf=-np.inf), 0.0, 32.0)
+    m = sp.Model(idx, val, bias)
+    n, rows, Y = m.infer(torch.from_numpy(Y0).to("cuda:0"))
+    assert m.row_kernel() == sp.SPDNN_ROWS_STRIDED
+    alive = np.flatnonzero((y > 0).any(1))
+    assert [int(r) for r in rows] == [int(r) for r in alive]
+    # weights are 1/16, inputs 0 and 1: 31 additions and one rounding per layer, 34 u of at most 32 * 32 / 16 + 0.3
+    np.testing.assert_allclose(Y.cpu().numpy(), y[alive], rtol=0, atol=2 * 34 * 2.0**-24 * 64.3)
+    m.close()

@@ -14,7 +14,8 @@
 // Two rows or one, an entry of 8 or 4 bytes: such reads are served for two sets of 16 lanes at a time, and the order of the connections
 // is that of 16-byte entries, which keeps a set's lanes apart and knows nothing of the other set.  The rows are there twice
 // therefore, in planes that lie in different halves of the banks, a plane for each set: with one weight, 120 layers of 1024
-// neurons on 1000 rows 218 -> 201 us, of 2048 on 300 rows 340 -> 281; 24 layers of 4096 on 200 rows 142 -> 119.
+// neurons on 1000 rows 218 -> 201 us, of 2048 on 300 rows 340 -> 281; 24 layers of 4096 on 200 rows 142 -> 119 (197, -, 115 with
+few_address and less work around the call since).
 //
 // What bounds it: latency -- 700 to 1000 clocks of a layer's 3300 (1024 neurons) to 17 000
 // (4096 with weights) are the barrier and the waits at its ends -- and with weights of their own the stream of connections (one row, 12
@@ -70,7 +71,15 @@ struct FewEntry<4> {
     typedef float T __attribute__((ext_vector_type(4)));
 };
 
-// The two entry codes of a register as LDS addresses of entries of 4 << LOG2R bytes.
+// The two entry codes of a register as LDS addresses of entries of 4 << LOG2R bytes, from `base` on: an instruction for each, where
+// adding a plane and a copy to both codes first took half a one more (one weight, 120 layers of 1024 neurons, 500 rows 188 -> 181 us, of
+// 2048 on 300 rows, 60 layers, 175 -> 167; 24 layers of 4096 on 500 rows 145 -> 136).  Without a base: 16-byte entries, whose copy
+// is in the read's offset.
+template <int LOG2R>
+__device__ __forceinline__ void few_address(uint32_t codes, uint32_t base, uint32_t& lo, uint32_t& hi) {
+    asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(lo) : "v"(codes), "n"(4 << LOG2R), "v"(base));
+    asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(hi) : "v"(codes), "n"(4 << LOG2R), "v"(base));
+}
 template <int LOG2R>
 __device__ __forceinline__ void few_address(uint32_t codes, uint32_t& lo, uint32_t& hi) {
     asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0" : "=v"(lo) : "s"(2 + LOG2R), "v"(codes));
@@ -100,7 +109,7 @@ __device__ __forceinline__ void few_layers(const FewArgs& fa, const float* __res
     const uint32_t lane16 = 16u * lane;
     // bytes from an entry to its place in the other copy of the rows: a layer reads one and writes the other
     const uint32_t copy = !TWICE ? PLANE : fa.planes_log2 == 2 ? 2 * PLANE : ((uint32_t)(N + 255) / 256u * 512u) << (2 + LOG2R);
-    const uint32_t my_plane = TWICE && (set_of_lane((uint32_t)lane) & 1u) ? 0x00100010u : 0u;  // added to two entry codes
+    const uint32_t my_plane = TWICE && (set_of_lane((uint32_t)lane) & 1u) ? PLANE : 0u;
     // LDS address of column j of a row laid out by q = its quads' word
     const auto entry = [&](int j, uint32_t q) -> uint32_t {
         return ((store_group((uint32_t)j) << (8 + fa.planes_log2)) | ((q >> (8 * (j & 3))) & 0xffu)) >> (2 - LOG2R);
@@ -169,7 +178,7 @@ __device__ __forceinline__ void few_layers(const FewArgs& fa, const float* __res
     const auto layer = [&](int l, auto from) {
         constexpr bool OTHER = decltype(from)::value;
         constexpr uint32_t FROM = TWICE || !OTHER ? 0u : PLANE;  // (16-byte entries: the other copy is a constant away)
-        const uint32_t shift = !TWICE ? 0u : my_plane + (OTHER ? (copy >> (2 + LOG2R)) * 0x00010001u : 0u);
+        const uint32_t rows_at = my_plane + (OTHER ? copy : 0u);  // (TWICE)
         const uint32_t to_copy = OTHER ? 0u : copy;
         // (scalar loads are waited for with the first reads of the rows, so not any later than this)
         const ResidentLayer after = layer_at(l + 2 < fa.l1 ? l + 2 : fa.l1 - 1);
@@ -191,7 +200,8 @@ __device__ __forceinline__ void few_layers(const FewArgs& fa, const float* __res
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     uint32_t lo, hi;
-                    few_address<LOG2R>(TWICE ? c[k] + shift : c[k], lo, hi);
+                    if constexpr (TWICE) few_address<LOG2R>(c[k], rows_at, lo, hi);
+                    else few_address<LOG2R>(c[k], lo, hi);
                     y[2 * k] = *(const lds_T*)(lo + FROM);
                     y[2 * k + 1] = *(const lds_T*)(hi + FROM);
                 }

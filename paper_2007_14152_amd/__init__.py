@@ -7,6 +7,7 @@ import of the library raises.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 
@@ -189,10 +190,8 @@ def spdnn_create_csr(N, L, ptr_ptrs, idx_ptrs, val_ptrs, bias_ptr, arena_ptr, ar
 def spdnn_infer(h, y0_ptr, batch, work_ptr, work_bytes, active_rows_ptr, y_final_ptr) -> int:
     """Returns n_active."""
     n = ctypes.c_int32(-1)
-    _check(lib().spdnn_infer(ctypes.c_void_p(h), ctypes.c_void_p(int(y0_ptr)), batch,
-                             ctypes.c_void_p(int(work_ptr)), work_bytes, ctypes.byref(n),
-                             ctypes.c_void_p(int(active_rows_ptr)),
-                             ctypes.c_void_p(int(y_final_ptr)) if y_final_ptr else None))
+    _check(lib().spdnn_infer(h, int(y0_ptr), batch, int(work_ptr), work_bytes, ctypes.byref(n), int(active_rows_ptr),
+                             int(y_final_ptr) if y_final_ptr else None))
     return n.value
 
 
@@ -256,9 +255,8 @@ SPDNN_STATIC_SCRATCH_BYTES = 64 << 20
 def spdnn_infer_static(h, y0_ptr, batch, active_rows_ptr, y_final_ptr) -> int:
     """spdnn_infer with the library's static scratch array as work memory.  Returns n_active."""
     n = ctypes.c_int32(-1)
-    _check(lib().spdnn_infer_static(ctypes.c_void_p(h), ctypes.c_void_p(int(y0_ptr)), batch, ctypes.byref(n),
-                                    ctypes.c_void_p(int(active_rows_ptr)),
-                                    ctypes.c_void_p(int(y_final_ptr)) if y_final_ptr else None))
+    _check(lib().spdnn_infer_static(h, int(y0_ptr), batch, ctypes.byref(n), int(active_rows_ptr),
+                                    int(y_final_ptr) if y_final_ptr else None))
     return n.value
 
 
@@ -276,6 +274,16 @@ def spdnn_infer_host(h, y0_host_ptr, batch, rows_per_batch, work_ptr, work_bytes
                                   ctypes.c_void_p(int(active_rows_ptr)),
                                   ctypes.c_void_p(int(y_final_ptr)) if y_final_ptr else None))
     return n.value
+
+
+_NO_SWITCH = contextlib.nullcontext()
+
+
+def _survivors(n, rows, Y):
+    """What infer returns: the first n rows of both."""
+    if n == rows.shape[0]:
+        return n, rows, Y
+    return n, rows[:n], (None if Y is None else Y[:n])
 
 
 class Model:
@@ -336,6 +344,7 @@ class Model:
                 self.arena = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
                 self.h = spdnn_create(N, L, ip, vp, bp, where, self.arena.data_ptr(), nbytes, s.cuda_stream)
         self.work = None
+        self._work_bytes = -1, 0  # of the last batch size
         del keep
 
     @classmethod
@@ -374,6 +383,12 @@ class Model:
                                       [v.data_ptr() for v in val], b.data_ptr(), self.arena.data_ptr(), nbytes,
                                       s.cuda_stream)
         self.work = None
+        self._work_bytes = -1, 0  # of the last batch size
+
+    def _on_device(self):
+        """The model's device made current, if it is not (the switch there and back takes 1.4 us of a call's 45)."""
+        cuda = self.torch.cuda
+        return _NO_SWITCH if cuda.current_device() == self.device.index else cuda.device(self.device)
 
     def infer(self, Y0, want_Y=True):
         """Y0: CUDA float32 [batch, N].  Returns (n_active, active_rows[int32 n], Y[n, N] or None)."""
@@ -381,8 +396,10 @@ class Model:
         assert Y0.is_cuda and Y0.dtype == torch.float32 and Y0.is_contiguous()
         batch = int(Y0.shape[0])
         assert Y0.shape[1] == self.N
-        with torch.cuda.device(self.device):
-            need = spdnn_work_bytes(self.N, batch)
+        with self._on_device():
+            if self._work_bytes[0] != batch:
+                self._work_bytes = batch, spdnn_work_bytes(self.N, batch)
+            need = self._work_bytes[1]
             if self.work is None or self.work.numel() < need:
                 self.work = None
                 self.work = torch.empty(need, dtype=torch.uint8, device=self.device)
@@ -390,18 +407,18 @@ class Model:
             Yf = torch.empty((max(batch, 1), self.N), dtype=torch.float32, device=self.device) if want_Y else None
             n = spdnn_infer(self.h, Y0.data_ptr(), batch, self.work.data_ptr(), self.work.numel(),
                             rows.data_ptr(), Yf.data_ptr() if want_Y else 0)
-        return n, rows[:n], (Yf[:n] if want_Y else None)
+        return _survivors(n, rows, Yf)
 
     def infer_static(self, Y0, want_Y=True):
         """infer() through spdnn_infer_static: the library's fixed scratch array is the work memory."""
         torch = self.torch
         assert Y0.is_cuda and Y0.dtype == torch.float32 and Y0.is_contiguous() and Y0.shape[1] == self.N
         batch = int(Y0.shape[0])
-        with torch.cuda.device(self.device):
+        with self._on_device():
             rows = torch.empty(max(batch, 1), dtype=torch.int32, device=self.device)
             Yf = torch.empty((max(batch, 1), self.N), dtype=torch.float32, device=self.device) if want_Y else None
             n = spdnn_infer_static(self.h, Y0.data_ptr(), batch, rows.data_ptr(), Yf.data_ptr() if want_Y else 0)
-        return n, rows[:n], (Yf[:n] if want_Y else None)
+        return _survivors(n, rows, Yf)
 
     def infer_batched(self, Y0_host, rows_per_batch, want_Y=True):
         """Inputs that stay in host memory, processed in serial batches (Section III-B-2) by

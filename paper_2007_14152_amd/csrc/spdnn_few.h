@@ -14,8 +14,7 @@
 // Two rows or one, an entry of 8 or 4 bytes: such reads are served for two sets of 16 lanes at a time, and the order of the connections
 // is that of 16-byte entries, which keeps a set's lanes apart and knows nothing of the other set.  The rows are there twice
 // therefore, in planes that lie in different halves of the banks, a plane for each set: with one weight, 120 layers of 1024
-// neurons on 1000 rows 218 -> 201 us, of 2048 on 300 rows 340 -> 281; 24 layers of 4096 on 200 rows 142 -> 119 (197, -, 115 with
-few_address and less work around the call since).
+// neurons on 1000 rows 218 -> 201 us, of 2048 on 300 rows 340 -> 281; 24 layers of 4096 on 200 rows 142 -> 119.
 //
 // What bounds it: latency -- 700 to 1000 clocks of a layer's 3300 (1024 neurons) to 17 000
 // (4096 with weights) are the barrier and the waits at its ends -- and with weights of their own the stream of connections (one row, 12

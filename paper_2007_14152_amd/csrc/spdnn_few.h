@@ -9,7 +9,8 @@
 // codes are the same, and the sums are the same products in the same order (kResParts: parts of 32 likewise), so the results have the same bits.
 //
 // The connections of a group are on their way while the group before is computed, all 32 with their weights: 12 KB per wave,
-// which is what it takes for the 53 to 60 bytes per clock that a CU gets out of its L2.  (Neurons of any length: 16 of them.)
+// which is what it takes for the 47 to 60 bytes per clock that a CU gets out of its L2 (two groups ahead, one row: 12 layers of 1024
+// neurons 49.0 -> 48.7 us, 3100 neurons 87 -> 91).  (Neurons of any length: 16 of them.)
 //
 // Two rows or one, an entry of 8 or 4 bytes: such reads are served for two sets of 16 lanes at a time, and the order of the connections
 // is that of 16-byte entries, which keeps a set's lanes apart and knows nothing of the other set.  The rows are there twice
@@ -18,7 +19,8 @@
 //
 // What bounds it: latency -- 700 to 1000 clocks of a layer's 3300 (1024 neurons) to 17 000
 // (4096 with weights) are the barrier and the waits at its ends -- and with weights of their own the stream of connections (one row, 12
-// layers of 1024: LDS 34 %, vector instructions 23 % of the one CU's clocks).
+// layers of 1024: LDS 21 %, vector instructions 23 % of the one CU's clocks).  With one weight and two rows: instructions, of which a
+// wave issues one every 5 clocks and has 290 in a layer.
 // Whole calls, resident_kernel -> this kernel when it was new: one row
 // through 12 layers of 1024 neurons with weights 57 -> 51 us, of 4096 neurons 130 -> 116; 1000 rows, half of which die, through
 // 120 layers of 1024 neurons with one weight 261 -> 228; 100 rows through 24 layers of 4096 neurons 179 -> 147.

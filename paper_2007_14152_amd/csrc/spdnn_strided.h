@@ -31,7 +31,7 @@
 // end has a third more instructions than the others, which wait for it.  48 layers of 16384 neurons,
 // strides 1, 32 and 512 in turn, on 2000 rows of which half die: 1.95 -> 0.35 ms (two neurons per lane under new names, one launch per
 // layer before: 40 us a layer, 28 for the first two now and 6 for the others, on half the rows); 24 layers of
-// 4096 neurons, strides 1, 32 and 128, 60 000 rows 4.45 -> 1.27 ms (resident_kernel before), 48 of them on 100 rows 324 -> 120 us.
+// 4096 neurons, strides 1, 32 and 128, 60 000 rows 4.45 -> 1.50 ms (resident_kernel before) -> 1.29 with code for known strides, 48 of them on 100 rows 324 -> 133 -> 107 us.
 #pragma once
 
 namespace spdnn {
@@ -39,7 +39,7 @@ namespace spdnn {
 constexpr int kStrideOut = 33;                      // neurons a lane owns
 constexpr int kStrideIn = kStrideOut + kNnz - 1;    // inputs they read
 constexpr int kStrideThreads = 512;
-constexpr int kStrideMisc = 16;  // bytes of LDS behind the rows: two words of flags, an entry that nobody reads
+constexpr int kStrideMisc = 16;  // bytes of LDS behind the rows: an entry that nobody reads, two words of flags
 
 struct StridedLayer {
     int S, off;     // columns (j + off + k * S) mod N

@@ -2709,7 +2709,8 @@ __global__ __launch_bounds__(kOrderPackThreads) void order_pack_kernel(const int
         int parent = -1;        // as lane: the entry of the queue from which the search reached me
         int mult = 0;           // as quad: uses in this step (saturates at 15)
         // a quad that holds more than there are steps left is read twice in one of them: those steps come first
-        const int cap = __builtin_amdgcn_readfirstlane(row16_max(remq)) > left ? 2 : 1;
+        // (rows of at most 4096 columns: longer ones go through the kernels that stage tiles, which gain nothing by it)
+        const int cap = N <= kCap && __builtin_amdgcn_readfirstlane(row16_max(remq)) > left ? 2 : 1;
         uint32_t free_lanes = (uint32_t)__builtin_amdgcn_ballot_w64(on && unplaced != 0u);  // lanes without a quad (the same in every lane)
         uint32_t done = 0;              // quads that are not offered any more
         while (free_lanes) {

@@ -103,18 +103,22 @@ __device__ __forceinline__ void sum_stride(f32x2 (&x)[n], uint32_t base, uint32_
         asm volatile("");  // (or what the ways have in common would be put behind them)
     } else {
         const uint32_t over = (N - c + S - 1u) / S;  // the first entry past the row end
+        const uint32_t gone[2] = {over < 32u ? ~0u << over : 0u, over < 32u ? ~0u : over < 64u ? ~0u << (over - 32u) : 0u};  // bit k: entry k is
         uint32_t at[(n + kFar - 1) / kFar], past[(n + kFar - 1) / kFar];
 #pragma unroll
         for (int g = 0; g < n; g += kFar) {
             at[g / kFar] = base + 8u * c + 8u * S * g;
             past[g / kFar] = at[g / kFar] - 8u * N;
-            if constexpr (kFar < n) asm("" : "+v"(at[g / kFar]), "+v"(past[g / kFar]));
+            asm("" : "+v"(at[g / kFar]), "+v"(past[g / kFar]));  // (or the choice would be moved in front of the sums that make an address)
         }
 #pragma unroll
         for (int i = 0; i < n; ++i) {
             const int k = i & 1 ? n / 2 + i / 2 : n / 2 - 1 - i / 2;
-            uint32_t from;
-            asm("v_cmp_ge_u32 vcc, %1, %2\n\tv_cndmask_b32 %0, %3, %4, vcc" : "=v"(from) : "n"(k), "v"(over), "v"(at[k / kFar]), "v"(past[k / kFar]) : "vcc");
+            // A choice by bits: one by a comparison has to wait for VCC, an instruction more per entry where a wave has nothing else to do
+            // (24 layers of 4096 neurons, strides 1, 32 and 128, 60 000 rows 1357 us, this way 1287).
+            uint32_t mask = (uint32_t)__builtin_amdgcn_sbfe((int)gone[k / 32], k % 32, 1);
+            asm("" : "+v"(mask));  // (or it would become a comparison)
+            const uint32_t from = (mask & past[k / kFar]) | (~mask & at[k / kFar]);
             x[k] = *(const lds_f2*)(from + 8u * S * (k % kFar));
         }
         sums();

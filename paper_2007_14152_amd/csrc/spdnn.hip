@@ -252,8 +252,10 @@ hipError_t allow_flat_lds() {
 constexpr int kLdsBytes = 160 * 1024;
 template <bool PAIRS, bool KNOWN>
 hipError_t allow_strided_lds() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&spdnn::strided_kernel<PAIRS, KNOWN>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               kLdsBytes);
+    const void* const both[2] = {reinterpret_cast<const void*>(&spdnn::strided_kernel<PAIRS, KNOWN, false>),
+                                 reinterpret_cast<const void*>(&spdnn::strided_kernel<PAIRS, KNOWN, true>)};
+    const hipError_t e = hipFuncSetAttribute(both[0], hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+    return e != hipSuccess ? e : hipFuncSetAttribute(both[1], hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
 }
 int few_lds(int32_t N, int32_t nblk) {
     return (int)spdnn::res_tile_bytes(N, 1 << spdnn::res_planes_log2(nblk)) + spdnn::kFewMiscBytes;
@@ -1253,11 +1255,15 @@ hipError_t launch_strided(spdnn_t h, int32_t l0, int32_t l1, int32_t rows, const
     const StridedShape r = strided_shape(h, rows);
     const spdnn::StridedArgs sa{h->strided, l0, l1, rows, r.pairs, h->strided_bias, layer_rows};
     const int grid = std::min((rows + 2 * r.pairs - 1) / (2 * r.pairs), r.slots);
-    const auto run = [&](auto pairs, auto known) {
-        spdnn::strided_kernel<decltype(pairs)::value, decltype(known)::value><<<grid, r.threads, r.lds, h->stream>>>(Yin, Yout, flags, rl, sa, h->N);
+    const auto run = [&](auto pairs, auto known, auto scaled) {
+        spdnn::strided_kernel<decltype(pairs)::value, decltype(known)::value, decltype(scaled)::value>
+            <<<grid, r.threads, r.lds, h->stream>>>(Yin, Yout, flags, rl, sa, h->N);
     };
-    if (r.pairs > 1) h->strided_known ? run(std::true_type{}, std::true_type{}) : run(std::true_type{}, std::false_type{});
-    else h->strided_known ? run(std::false_type{}, std::true_type{}) : run(std::false_type{}, std::false_type{});
+    const auto run_pairs = [&](auto pairs, auto known) {
+        spdnn::strided_scaled(h->strided_bias) ? run(pairs, known, std::true_type{}) : run(pairs, known, std::false_type{});
+    };
+    if (r.pairs > 1) h->strided_known ? run_pairs(std::true_type{}, std::true_type{}) : run_pairs(std::true_type{}, std::false_type{});
+    else h->strided_known ? run_pairs(std::false_type{}, std::true_type{}) : run_pairs(std::false_type{}, std::false_type{});
     return hipGetLastError();
 }
 

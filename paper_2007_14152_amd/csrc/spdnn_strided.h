@@ -17,8 +17,8 @@
 // into different bank pairs; lanes of orbits next to each other read neighbouring entries anyway.  The last lane of an
 // orbit that 33 does not divide writes fewer.  An orbit of exactly 32 (S = N / 32) has one sum for all its neurons: one lane computes it once.
 //
-// The rows are kept as 1/32 of what they are, exactly (from 2^-121 on): ReLU and clip are then the clamp of the multiply-add that weight and
-// bias take.
+// The rows are kept as 1/32 of what they are, where no bit is lost by it (strided_scaled): ReLU and clip are then the clamp of the
+// multiply-add that weight and bias take.
 // Strides that are powers of two, and the row length a multiple, have code of their own (strided_known): an entry's distance from a
 // lane's first is in the read's offset, and a lane that comes past the row end chooses between two addresses.  With one address
 // worked out per entry and ReLU and clip instructions of their own before, pairs of rows through layers of one stride, clocks of 2.4 GHz
@@ -31,7 +31,7 @@
 // end has a third more instructions than the others, which wait for it.  48 layers of 16384 neurons,
 // strides 1, 32 and 512 in turn, on 2000 rows of which half die: 1.95 -> 0.35 ms (two neurons per lane under new names, one launch per
 // layer before: 40 us a layer, 28 for the first two now and 6 for the others, on half the rows); 24 layers of
-// 4096 neurons, strides 1, 32 and 128, 60 000 rows 4.45 -> 1.50 ms (resident_kernel before) -> 1.29 with code for known strides, 48 of them on 100 rows 324 -> 133 -> 107 us.
+// 4096 neurons, strides 1, 32 and 128, 60 000 rows 4.45 -> 1.50 ms (resident_kernel before) -> 1.31 with code for known strides, 48 of them on 100 rows 324 -> 133 -> 108 us.
 #pragma once
 
 namespace spdnn {
@@ -61,6 +61,13 @@ SPDNN_HD inline int strided_lanes(const StridedLayer& d) { return d.orbits * d.p
 SPDNN_HD inline bool strided_known(const StridedLayer& d, int N) {
     return d.S <= 512 && (d.S & (d.S - 1)) == 0 && N % d.S == 0 && (N / d.S >= kStrideIn || N / d.S == kNnz);
 }
+// Can the rows be kept as 1/32 of what they are, bit for bit?  Below 2^-121 an entry would lose its last bits.  An output is weight times sum (48
+// bits at most) and a bias that is not above 0, rounded once: 0, or at least 2^-48 of the bias.  A bias of -2^-60 and more leaves no output
+// below 2^-108, and what layer 0's products lose below 2^-121 is far below the last bit of a sum that gets past the bias.  (That layer's weight
+// meets its inputs as it is, and the product is scaled: a weight below 2^-121 has no bits to spare.)  Smaller biases, 0 among them: rows as they are,
+// with an instruction more per neuron and row (rows that all live: 24 layers of 4096 neurons, strides 1, 32 and 128, 60 000 rows 2195 -> 2308 us,
+// 48 layers of 16384 neurons, strides 1, 32 and 512, 2000 rows 615 -> 628).
+SPDNN_HD inline bool strided_scaled(float bias) { return bias <= -0x1p-60f; }
 
 // n entries of an orbit, from column c on, every S-th, around the row end.
 template <int n>
@@ -125,8 +132,8 @@ __device__ __forceinline__ void sum_stride(f32x2 (&x)[n], uint32_t base, uint32_
     }
 }
 
-// PAIRS: more than one pair of rows, the lanes shared out among them.
-template <bool PAIRS, bool KNOWN>
+// PAIRS: more than one pair of rows, the lanes shared out among them.  KNOWN: all strides are.  SCALED: rows as 1/32.
+template <bool PAIRS, bool KNOWN, bool SCALED>
 __global__ __launch_bounds__(kStrideThreads) void strided_kernel(const float* __restrict__ Yin, float* __restrict__ Yout,
                                                                  uint8_t* __restrict__ flags, RowLists rl, StridedArgs sa, int N) {
     extern __shared__ __align__(16) char strided_lds[];
@@ -142,14 +149,15 @@ __global__ __launch_bounds__(kStrideThreads) void strided_kernel(const float* __
     const int A = rl.count ? __builtin_amdgcn_readfirstlane(*rl.count) : sa.A;
     const int npass = (A + 2 * np - 1) / (2 * np), n4 = N >> 2;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    const float bias = sa.bias * (1.0f / kClip);
+    constexpr float kScale = SCALED ? 1.0f / kClip : 1.0f, kMost = kClip * kScale;  // of the rows in LDS
+    const float bias = sa.bias * kScale;
     using clayer = const __attribute__((address_space(4))) StridedLayer;  // constant while the kernel runs: scalar loads
 
     for (int pass = blockIdx.x; pass < npass; pass += gridDim.x) {
         const int row0 = pass * 2 * np, nrow = min(2 * np, A - row0);
         if (tid < 2) live_word[tid] = 0u;
         // the rows; layer 0 sums inputs of any size, so they meet its weight before they are added up
-        const float first_w = (sa.l0 == 0 ? ((clayer*)(uintptr_t)sa.layers)->w : 1.0f) * (1.0f / kClip);
+        const float first_w = sa.l0 == 0 ? ((clayer*)(uintptr_t)sa.layers)->w : 1.0f;
         for (int p = 0; p < np; ++p) {
             const bool one = 2 * p < nrow, two = 2 * p + 1 < nrow;
             const int s0 = !one ? 0 : rl.count ? rl.cat[row0 + 2 * p] : row0 + 2 * p;
@@ -168,8 +176,8 @@ __global__ __launch_bounds__(kStrideThreads) void strided_kernel(const float* __
                 for (int i = 0; i < 4; ++i) {
                     const int t = t0 + i * nthreads;
                     if (t < n4) {
-                        a[i] *= first_w;
-                        b[i] *= first_w;
+                        a[i] = a[i] * first_w * kScale;
+                        b[i] = b[i] * first_w * kScale;
                         lds_f4* to = (lds_f4*)(tile + p * row_bytes + 32u * t);
                         to[0] = f32x4{a[i].x, b[i].x, a[i].y, b[i].y};
                         to[1] = f32x4{a[i].z, b[i].z, a[i].w, b[i].w};
@@ -209,8 +217,8 @@ __global__ __launch_bounds__(kStrideThreads) void strided_kernel(const float* __
             if (mine) {
                 float m0 = 0.0f, m1 = 0.0f;
                 const auto finish = [&](f32x2 v) -> f32x2 {
-                    v.x = fminf(fmaxf(__builtin_fmaf(w, v.x, bias), 0.0f), 1.0f);
-                    v.y = fminf(fmaxf(__builtin_fmaf(w, v.y, bias), 0.0f), 1.0f);
+                    v.x = fminf(fmaxf(__builtin_fmaf(w, v.x, bias), 0.0f), kMost);
+                    v.y = fminf(fmaxf(__builtin_fmaf(w, v.y, bias), 0.0f), kMost);
                     m0 = fmaxf(m0, v.x);
                     m1 = fmaxf(m1, v.y);
                     return v;
@@ -332,8 +340,8 @@ __global__ __launch_bounds__(kStrideThreads) void strided_kernel(const float* __
                 for (int t = tid; t < n4; t += nthreads) {
                     const lds_f4* from = (const lds_f4*)(tile + p * row_bytes + 32u * t);
                     const f32x4 u = from[0], v = from[1];
-                    if (one) dst0[t] = f32x4{u.x, u.z, v.x, v.z} * kClip;
-                    if (two) dst1[t] = f32x4{u.y, u.w, v.y, v.w} * kClip;
+                    if (one) dst0[t] = f32x4{u.x, u.z, v.x, v.z} * (1.0f / kScale);
+                    if (two) dst1[t] = f32x4{u.y, u.w, v.y, v.w} * (1.0f / kScale);
                 }
             }
         }

@@ -189,3 +189,49 @@ def test_infinite_inputs(N, strides):
     # weights are 1/16, inputs 0 and 1: 31 additions and one rounding per layer, 34 u of at most 32 * 32 / 16 + 0.3
     np.testing.assert_allclose(Y.cpu().numpy(), y[alive], rtol=0, atol=2 * 34 * 2.0**-24 * 64.3)
     m.close()
+
+
+@pytest.mark.parametrize("N,strides", [(2048, (1, 64)), (16384, (32, 1)), (12288, (3, 256))])  # several pairs of rows, one, a stride like any other
+@pytest.mark.parametrize("weight", [1e-38, 1e-40, 1e-43, 1e-44])
+@pytest.mark.parametrize("bias", [-0.01, -1e-6, 0.0])
+def test_small_weights_on_large_inputs(N, strides, weight, bias):
+    """A first layer whose weight is near the end of the 32-bit range or below its normal part, and inputs that make up for it: the products
+    are ordinary numbers with all their bits.  Against 64 bits, the bound of test_inputs_and_weights_of_any_sign."""
+    rng = np.random.default_rng(N)
+    Y0 = rng.uniform(0.5e38, 1e38, size=(7, N)).astype(np.float32)
+    Y0[2:] *= rng.uniform(size=(5, N)) < 0.1
+    against_64_bits(N, strides, (weight, 0.0625), bias, Y0)
+
+
+@pytest.mark.parametrize("N,strides", [(2048, (1, 64)), (16384, (32, 1)), (12288, (3, 256))])
+@pytest.mark.parametrize("weights", [(1.0, 1.0), (0.07, 0.0613)])
+@pytest.mark.parametrize("bias", [0.0, -2.0 ** -149, -2.0 ** -140, -2.0 ** -61, -2.0 ** -60])
+def test_small_values(N, strides, weights, bias):
+    """Rows of the smallest numbers, whose outputs are as small where the bias is, and still count as outputs."""
+    rng = np.random.default_rng(N + 1)
+    Y0 = np.zeros((6, N), np.float32)
+    for b, e in enumerate((-149, -146, -130, -120, -62, -58)):
+        Y0[b] = np.ldexp(rng.uniform(1, 2, size=N), e) * (rng.uniform(size=N) < 0.2)
+    against_64_bits(N, strides, weights, bias, Y0)
+
+
+def against_64_bits(N, strides, weights, bias, Y0):
+    """33 roundings of relative error 2^-24 per layer (32 products or one, 31 additions, one multiply-add), or half of 2^-149 where that is more."""
+    import torch
+    import paper_2007_14152_amd as sp
+    idx, _ = network(N, strides, 0.0, (N - 1,))
+    w = [np.float32(x) for x in weights]
+    b = np.float32(bias)
+    m = sp.Model(idx, [np.full((N, 32), x, np.float32) for x in w], np.full(N, b, np.float32))
+    n, rows, Y = m.infer(torch.from_numpy(Y0).to("cuda:0"))
+    assert m.row_kernel() == sp.SPDNN_ROWS_STRIDED
+    m.close()
+    y, bound = Y0.astype(np.float64), np.zeros(Y0.shape)
+    for i, x in zip(idx, w):
+        s, x = y[:, i].sum(2), np.float64(x)
+        bound = x * bound[:, i].sum(2) + 33 * (2.0 ** -24 * (x * s + abs(np.float64(b))) + 2.0 ** -150)
+        y = np.clip(x * s + np.float64(b), 0.0, 32.0)
+    full = np.zeros_like(y)
+    full[rows.cpu().numpy()] = Y.cpu().numpy()
+    assert (np.abs(full - y) <= bound * 1.001).all()
+    assert not ((y > bound * 1.001).any(1) & ~np.isin(np.arange(len(y)), rows.cpu().numpy())).any()

@@ -2606,7 +2606,7 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const int32_t*
 // the stage number in bits 12 and up) and its weight, for the connection lane t
 // uses at step s.
 //
-// The ordering is order_group's (spdnn_order.h), choice for choice, with the wave's first 16 lanes in
+// The ordering is that of order_group (spdnn_order.h) with reads_twice(N), choice for choice, with the wave's first 16 lanes in
 // two roles: lane l as the set's l-th neuron (its unplaced connections, its quad of the current step,
 // its parent in the search) and lane q as bank quad q (the lanes that still have a connection there,
 // how many connections, how many lanes use it in this step).  What the serial routine loops over is a
@@ -2709,8 +2709,7 @@ __global__ __launch_bounds__(kOrderPackThreads) void order_pack_kernel(const int
         int parent = -1;        // as lane: the entry of the queue from which the search reached me
         int mult = 0;           // as quad: uses in this step (saturates at 15)
         // a quad that holds more than there are steps left is read twice in one of them: those steps come first
-        // (rows of at most 4096 columns: longer ones go through the kernels that stage tiles, which gain nothing by it)
-        const int cap = N <= kCap && __builtin_amdgcn_readfirstlane(row16_max(remq)) > left ? 2 : 1;
+        const int cap = reads_twice(N) && __builtin_amdgcn_readfirstlane(row16_max(remq)) > left ? 2 : 1;
         uint32_t free_lanes = (uint32_t)__builtin_amdgcn_ballot_w64(on && unplaced != 0u);  // lanes without a quad (the same in every lane)
         uint32_t done = 0;              // quads that are not offered any more
         while (free_lanes) {
@@ -2783,9 +2782,8 @@ __global__ __launch_bounds__(kOrderPackThreads) void order_pack_kernel(const int
             const int c = idx[src];
             const bool ok = c >= 0 && c < N;
             const uint32_t r = ok ? (uint32_t)win_rel(c, c_lo, N) : 0u;  // stage number | slot inside the stage
-            // (few_kernel's entries of 8 bytes are read for two sets at a time.  Longer rows go through the kernels that stage tiles, which are
-            // bound by memory: 65536 neurons, windows, 6 layers, 24 000 rows 0.6 % slower with the steps spread, as fast as ever without)
-            const int at = N <= kCap ? spread_step(step, nsteps, set >> 1) : step;
+            // (few_kernel's entries of 8 bytes are read for two sets at a time)
+            const int at = reads_twice(N) ? spread_step(step, nsteps, set >> 1) : step;
             rel[entry(at)] = (uint16_t)((r & ~(uint32_t)(kCap - 1)) | res_code(slot_of(r & (kCap - 1)), planes_log2));
             wval[wentry(at)] = ok ? val[src] : 0.0f;
         }
@@ -2893,7 +2891,7 @@ __global__ __launch_bounds__(kOrderThreads) void wide_pack_kernel(const int32_t*
         for (int i = 0; i < 32; ++i) quads_of_step[i] = 0;
         for (int l = 0; l < kGroup; ++l) steps_of_lane[l] = 0;
         order_group(
-            W.order, nsteps,
+            W.order, nsteps, reads_twice(N),
             [&](int l, int k) -> unsigned {
                 return ((W.keep[l] >> k) & 1u) ? (col_slot((uint32_t)rel_of(l, k) & (kCap - 1)) & 15u) : 255u;
             },

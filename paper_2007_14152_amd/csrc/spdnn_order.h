@@ -47,6 +47,12 @@ struct OrderScratch {
     uint8_t via[kGroup + 1];    // ... and the lane that would give such a quad up
 };
 
+// Has a layer of N columns the steps that read a quad twice first, spread over its reads (spread_step)?  Rows of one stage have.  Longer ones go
+// through kernels that stage tiles, which gain nothing by it: 65536 neurons, one weight, windows, 6 layers, 24 000 rows 0.6 % slower with
+// them; weights of their own, columns anywhere, 4 layers, 4000 rows, single matchings, double steps in front, double steps spread: 18000 neurons 4150,
+// 4157 and 4153 us, 32768 neurons 6761, 6766 and 6763.
+SPDNN_HD inline bool reads_twice(int N) { return N <= 4096; }
+
 SPDNN_HD inline unsigned nib_get(uint64_t w, int i) { return (unsigned)(w >> (4 * i)) & 15u; }
 SPDNN_HD inline uint64_t nib_set(uint64_t w, int i, unsigned v) {
     return (w & ~(15ull << (4 * i))) | ((uint64_t)(v & 15u) << (4 * i));
@@ -65,9 +71,10 @@ SPDNN_HD inline int ctz16(unsigned m) {
 // connection k of lane l is placed at step `step` < nsteps.  nsteps must be at least
 // the largest number of connections any lane has; every existing connection is emitted
 // exactly once, at most one per lane and step; a lane with fewer connections than
-// steps sits out the steps in which it would collide.
+// steps sits out the steps in which it would collide.  twice: are there steps in which a quad may be
+// given to two lanes?
 template <typename QuadOf, typename Emit>
-SPDNN_HD inline void order_group(OrderScratch& S, int nsteps, QuadOf quad_of, Emit emit) {
+SPDNN_HD inline void order_group(OrderScratch& S, int nsteps, bool twice, QuadOf quad_of, Emit emit) {
     uint16_t* adj = S.adj;
     uint16_t* remq = S.remq;
     for (int q = 0; q < 16; ++q) {
@@ -105,7 +112,7 @@ SPDNN_HD inline void order_group(OrderScratch& S, int nsteps, QuadOf quad_of, Em
         unsigned done = 0;                 // quads that are not offered any more
         int most = 0;
         for (int q = 0; q < 16; ++q) most = remq[q] > most ? remq[q] : most;
-        const int cap = most > left ? 2 : 1;  // lanes that may take the same quad
+        const int cap = twice && most > left ? 2 : 1;  // lanes that may take the same quad
         while (ml != live) {
             // the quad that holds most behind this step so far, the lowest-numbered among equals
             int q0 = -1;

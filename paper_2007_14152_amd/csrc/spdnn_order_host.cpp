@@ -11,8 +11,9 @@ extern "C" {
 // quads: [16][32] quad (0..15) of every connection of 16 neighbouring neurons, 255 = absent.
 // step_of: [16][32] out, step at which connection k of lane l is placed (255 if absent).
 // nsteps: number of steps (>= the largest number of connections of any lane).
+// N: columns of the row, which say whether there are steps that read a quad twice.
 // Returns the cost (sum over steps of the largest quad multiplicity).
-int spdnn_order_group_host(const uint8_t* quads, uint8_t* step_of, int nsteps) {
+int spdnn_order_row_host(const uint8_t* quads, uint8_t* step_of, int nsteps, int N) {
     spdnn::OrderScratch S;
     uint8_t placed[16][32];
     for (int i = 0; i < 16 * 32; ++i) {
@@ -20,13 +21,16 @@ int spdnn_order_group_host(const uint8_t* quads, uint8_t* step_of, int nsteps) {
         (&placed[0][0])[i] = 255;
     }
     spdnn::order_group(
-        S, nsteps, [&](int l, int k) -> unsigned { return quads[l * 32 + k]; },
+        S, nsteps, spdnn::reads_twice(N), [&](int l, int k) -> unsigned { return quads[l * 32 + k]; },
         [&](int l, int step, int k) {
             step_of[l * 32 + k] = (uint8_t)step;
             placed[l][step] = quads[l * 32 + k];
         });
     return spdnn::order_cost([&](int l, int step) -> unsigned { return placed[l][step]; });
 }
+
+// The same for rows of one stage.
+int spdnn_order_group_host(const uint8_t* quads, uint8_t* step_of, int nsteps) { return spdnn_order_row_host(quads, step_of, nsteps, 1024); }
 
 // Cost of the order as given (connection k at step k).
 int spdnn_order_cost_host(const uint8_t* quads) {

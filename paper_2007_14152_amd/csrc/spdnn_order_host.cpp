@@ -32,6 +32,8 @@ int spdnn_order_row_host(const uint8_t* quads, uint8_t* step_of, int nsteps, int
 // The same for rows of one stage.
 int spdnn_order_group_host(const uint8_t* quads, uint8_t* step_of, int nsteps) { return spdnn_order_row_host(quads, step_of, nsteps, 1024); }
 
+int spdnn_spread_step_host(int step, int nsteps, int half) { return spdnn::spread_step(step, nsteps, half); }
+
 // Cost of the order as given (connection k at step k).
 int spdnn_order_cost_host(const uint8_t* quads) {
     return spdnn::order_cost([&](int l, int step) -> unsigned { return quads[l * 32 + step]; });

@@ -102,7 +102,7 @@ def test_benchmark_patterns_get_close_to_the_bound(lib):
         nat.append(lib.spdnn_order_cost_host(np.ascontiguousarray(g).ctypes.data))
         lb.append(max(32, np.bincount(g.ravel(), minlength=16).max()))
     assert np.mean(nat) > 90            # random order: about three lanes per quad in the worst quad
-    assert np.mean(cost) < 1.12 * np.mean(lb)
+    assert np.mean(cost) < 1.05 * np.mean(lb)  # (1.08 with single matchings)
     assert np.mean(cost) < 0.5 * np.mean(nat)
 
 
@@ -148,7 +148,7 @@ def test_group32_latin_square_and_worst_case(lib):
 
 def test_group32_uniform_patterns_close_to_the_bound(lib):
     """Uniform columns at N = 16384 (the benchmark's 16384-neuron configuration): the cost stays within
-    15 % of the lower bound max(32, busiest pair)."""
+    5 % of the lower bound max(32, busiest pair) (10 % with single matchings)."""
     c = synth.config(3)
     cols = synth.gen_layer(c["N"], 0, c["seed"])[:32 * 24]
     tot = lb = 0
@@ -157,4 +157,4 @@ def test_group32_uniform_patterns_close_to_the_bound(lib):
         cost, _ = order32(lib, pairs)
         tot += cost
         lb += max(32, int(np.bincount(pairs.ravel(), minlength=32).max()))
-    assert tot <= 1.15 * lb, (tot, lb)
+    assert tot <= 1.05 * lb, (tot, lb)

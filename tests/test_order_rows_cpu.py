@@ -4,6 +4,7 @@ import ctypes
 
 import numpy as np
 import pytest
+import synth
 from scipy.sparse import csr_matrix
 from scipy.sparse.csgraph import maximum_bipartite_matching
 
@@ -55,3 +56,24 @@ def test_short_rows_have_the_double_steps(lib):  # noqa: F811
         assert (cost, step_of.tolist()) == (lambda c, s: (c, s.tolist()))(*order(lib, quads))
         fewer += order_row(lib, quads, 32, 65536)[0] - cost
     assert fewer > 0
+
+
+@pytest.mark.parametrize("config,limit", [(0, 1.05), (2, 1.05), (3, 1.12), (4, 1.12)])
+def test_benchmark_patterns_at_their_own_length(lib, config, limit):  # noqa: F811
+    """1024 and 4096 columns with double steps, 16384 and 65536 with single matchings."""
+    c = synth.config(config)
+    idx = synth.gen_layer(c["N"], 0, c["seed"], c["window"])[:1024]
+    cost = bound = 0
+    for g in ((idx - (idx.min() // 4) * 4) % 16).astype(np.uint8).reshape(-1, 16, 32):
+        cost += order_row(lib, g, 32, c["N"])[0]
+        bound += max(32, int(np.bincount(g.ravel(), minlength=16).max()))
+    assert cost < limit * bound
+
+
+@pytest.mark.parametrize("nsteps", [8, 16, 24, 32])  # a layer's steps come in eights
+@pytest.mark.parametrize("half", [0, 1])
+def test_spread_steps_are_a_permutation(lib, nsteps, half):  # noqa: F811
+    at = [lib.spdnn_spread_step_host(step, nsteps, half) for step in range(nsteps)]
+    assert sorted(at) == list(range(nsteps))
+    # the first half, where the double steps are, leaves no four reads in a row without one of its own
+    assert max(np.diff([-1] + sorted(at[:nsteps // 2]) + [nsteps])) <= 4

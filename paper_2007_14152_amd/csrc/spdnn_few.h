@@ -14,7 +14,7 @@
 //
 // Two rows or one, an entry of 8 or 4 bytes: such reads are served for two sets of 16 lanes at a time, and the order of the connections
 // is that of 16-byte entries, which keeps a set's lanes apart and knows nothing of the other set.  The rows are there twice
-// therefore, in planes that lie in different halves of the banks, a plane for each set: with one weight, 120 layers of 1024
+// therefore, in planes that lie in different banks, a plane for each set: with one weight, 120 layers of 1024
 // neurons on 1000 rows 218 -> 201 us, of 2048 on 300 rows 340 -> 281; 24 layers of 4096 on 200 rows 142 -> 119.
 //
 // What bounds it: latency -- 700 to 1000 clocks of a layer's 3300 (1024 neurons) to 17 000
@@ -100,7 +100,9 @@ __device__ __forceinline__ void few_layers(const FewArgs& fa, const float* __res
     using clayer = const __attribute__((address_space(4))) ResidentLayer;
     constexpr int LOG2R = R == 1 ? 0 : R == 2 ? 1 : 2;
     // Entries of 4 and 8 bytes are read for two sets of 16 lanes at once, whose connections were ordered for 16-byte entries, each
-    // set's by itself: the sets find the rows in planes of their own, one in the lower half of the banks, one in the upper.
+    // set's by itself: the sets find the rows in planes of their own.  Of 8-byte entries one plane lies in the lower half of the banks, the other in
+    // the upper.  Of 4-byte entries 16 take 16 banks: up to 2048 columns the two planes of one copy lie in banks 0 to 15 and 16 to 31, those of
+    // the other copy in 32 to 47 and 48 to 63; of more columns a copy's planes alternate, 16 banks each, through all 64.
     constexpr bool TWICE = LOG2R < 2;
     constexpr uint32_t PLANE = 16u << (2 + LOG2R);  // bytes from an entry to its place in the next plane
     const int tid = threadIdx.x, lane = tid & 63, T_ = blockDim.x, W = T_ >> 6, U = (N + 63) >> 6;

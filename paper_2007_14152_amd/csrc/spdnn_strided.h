@@ -22,8 +22,9 @@
 // Strides that are powers of two, and the row length a multiple, have code of their own (strided_known): an entry's distance from a
 // lane's first is in the read's offset, and a lane that comes past the row end chooses between two addresses.  With one address
 // worked out per entry and ReLU and clip instructions of their own before, pairs of rows through layers of one stride, clocks of 2.4 GHz
-// per layer of 32768 neurons and rows: 4096 neurons, stride 1 8570 -> 6640, 32 8670 -> 6980, 128 4150 -> 4000, 3 (any other) 8730 -> 7760;
-// 16384 neurons 7240 -> 6800, 7170 -> 7130, 512 4290 -> 4260, 3 7530 -> 7220.
+// per layer of 32768 neurons and rows: 4096 neurons, stride 1 8660 -> 6890, 32 8680 -> 7340, 128 4380 -> 4170, 3 (any other) 8850 -> 7920;
+// 16384 neurons 7390 -> 6930, 7400 -> 7510 (the lanes past the row end), 512 4550 -> 4280, 3 7710 -> 7300.  All ten strides in one network take
+// more code than the instruction cache holds: 50 layers of 16384 neurons on 2000 rows 401 -> 399 us.
 //
 // What bounds it: the chain of reading, adding and writing: a CU's LDS has room for the rows of 8 waves, two per SIMD, which meet at two
 // barriers per layer.  A wave issues an instruction every 5 clocks, so two do not fill a SIMD; a write of 8 bytes per lane takes the LDS 6.2
@@ -64,7 +65,8 @@ SPDNN_HD inline bool strided_known(const StridedLayer& d, int N) {
 // Can the rows be kept as 1/32 of what they are, bit for bit?  Below 2^-121 an entry would lose its last bits.  An output is weight times sum (48
 // bits at most) and a bias that is not above 0, rounded once: 0, or at least 2^-48 of the bias.  A bias of -2^-60 and more leaves no output
 // below 2^-108, and what layer 0's products lose below 2^-121 is far below the last bit of a sum that gets past the bias.  (That layer's weight
-// meets its inputs as it is, and the product is scaled: a weight below 2^-121 has no bits to spare.)  Smaller biases, 0 among them: rows as they are,
+// meets its inputs as it is, and the product is scaled: a weight below 2^-121 has no bits to spare.  Sums of inputs
+// that are as large overflow five binary places later than unscaled ones.)  Smaller biases, 0 among them: rows as they are,
 // with an instruction more per neuron and row (rows that all live: 24 layers of 4096 neurons, strides 1, 32 and 128, 60 000 rows 2195 -> 2308 us,
 // 48 layers of 16384 neurons, strides 1, 32 and 512, 2000 rows 615 -> 628).
 SPDNN_HD inline bool strided_scaled(float bias) { return bias <= -0x1p-60f; }
